@@ -54,10 +54,12 @@
  *  - Activation scales are group-major: s_x[j * M + m] for group j, token m.
  *  - The GEMM calls pick one of several schedules of the same arithmetic from the problem
  *    size (few tokens: K split over the waves of a workgroup; medium: 128 x 128 tiles;
- *    large: persistent wave-specialised workgroups; asymmetric layers use the last two).  The fp32 additions of an output are
- *    ordered differently in each, so a token's result is deterministic for a given
+ *    large: persistent workgroups, whose waves all stage and multiply or are specialised for
+ *    one of the two; asymmetric layers use the 128 x 128 tiles and the specialised waves).
+ *    The fp32 additions of an output are ordered differently in each, so a token's result
+ *    is deterministic for a given
  *    (M, N, K, r, g) but not bit-identical across different M.  For testing, the
- *    environment variables DIROTQ_W4A4_KERNEL (ws | tile | skinny) and
+ *    environment variables DIROTQ_W4A4_KERNEL (pipe | large | small | ws | tile | skinny) and
  *    DIROTQ_W4A16_KERNEL (tile) are read at every launch and force a schedule wherever
  *    it applies; they are not needed in normal use.
  */

@@ -108,6 +108,13 @@ int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, 
 // activation codes, or NULL for symmetric ones
 int launch_w4a4_gemm_ws(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx, const void* blob,
                         const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype, hipStream_t s);
+// symmetric activation codes, large: persistent workgroups whose waves all stage and multiply
+int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
+                          const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
+                          long big_tokens, hipStream_t s);
+// how many of the first tokens go to its 256 x 256 tiles (the others to 256 x 128 ones); returns its time in units of a
+// 256 x 256 tile per CU
+double w4a4_pipe_plan(int M, int N, int cus, long& big_tokens);
 // symmetric activation codes, few tokens: the K axis split over the waves of a workgroup (64 x 64 outputs each)
 int launch_w4a4_gemm_skinny(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                             const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,

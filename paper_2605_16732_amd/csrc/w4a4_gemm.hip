@@ -435,27 +435,52 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
-// Which of the three schedules runs a symmetric layer.  The wave-specialised kernel (persistent workgroups, one
-// per CU, 256 x 128 tiles) is the fastest per tile; the kernel in this file (128 x 128 tiles, two workgroups per
-// CU) spreads a medium problem over more CUs; with few tokens both leave most of the chip idle and the split-K
-// kernel (64 x 64 outputs per workgroup, the K axis over its 8 waves) is the one with the shortest latency.
-// Measured crossovers: about 128 of the 256 x 128 tiles; about 288 of the 64 x 64 ones (512 from K = 2048 on,
-// 768 from K = 8192 on: the longer K is, the longer each workgroup of the tiled kernel walks alone).
-// DIROTQ_W4A4_KERNEL=ws / tile / skinny in the environment forces one of them wherever it applies (the tests use
-// it to run all of them on the same inputs).
-enum class W4A4Schedule { kTile, kWs, kSkinny };
-static W4A4Schedule w4a4_schedule(int M, int N, int K, int r) {
-  if (K - r <= 0) return W4A4Schedule::kTile;
+// Which of the schedules runs a layer.  Large symmetric layers: the pipelined kernel (persistent workgroups, 256 x 256
+// and 256 x 128 tiles).  While its plan has less than a round of large tiles the wave-specialised kernel (256 x 128) is
+// the faster one on the same half-size tiles: a round of them takes 0.61 of a round of 256 x 256 tiles (M = 2048,
+// K = N = 3072: 42 against 46 us; M = 4096, K = 1152, N = 4608: 57 against 54 us); it also runs the asymmetric layers.
+// Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).  The kernel
+// in this file (128 x 128 tiles, two workgroups per CU) spreads a medium problem over more CUs; with few tokens all
+// leave most of the chip idle and the split-K kernel (64 x 64 outputs per workgroup, the K axis over its 8 waves) is
+// the one with the shortest latency.  Measured crossovers: about 128 of the 256 x 128 tiles; about 288 of the 64 x 64
+// ones (512 from K = 2048 on, 768 from K = 8192 on: the longer K is, the longer each workgroup of the tiled kernel
+// walks alone).
+// DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny in the environment forces one of them wherever it
+// applies (the tests use it to run all of them on the same inputs; large and small: the pipelined kernel with one kind
+// of tile).
+enum class W4A4Schedule { kTile, kWs, kSkinny, kPipe };
+static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens) {
+  sch = W4A4Schedule::kTile;
+  big_tokens = 0;
+  if (K - r <= 0) return DIROTQ_OK;
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_failed(e);
   if (const char* f = getenv("DIROTQ_W4A4_KERNEL")) {
-    if (!strcmp(f, "ws")) return W4A4Schedule::kWs;
-    if (!strcmp(f, "tile")) return W4A4Schedule::kTile;
-    if (!strcmp(f, "skinny")) return W4A4Schedule::kSkinny;
+    const bool large = !strcmp(f, "large"), small = !strcmp(f, "small"), ws = !strcmp(f, "ws");
+    if (!strcmp(f, "tile")) return DIROTQ_OK;
+    if (!strcmp(f, "skinny")) return sch = W4A4Schedule::kSkinny, DIROTQ_OK;
+    if (ws || large || small || !strcmp(f, "pipe")) {
+      // (symmetric groups of 32 have no wave-specialised form, asymmetric layers no pipelined one)
+      sch = asym || (ws && g != 32) ? W4A4Schedule::kWs : W4A4Schedule::kPipe;
+      w4a4_pipe_plan(M, N, cus, big_tokens);
+      if (large || small) big_tokens = large ? M : 0;
+      return DIROTQ_OK;
+    }
   }
-  const long big = (long)((M + 127) / 128) * ((N + 255) / 256);
-  if (big >= 128) return W4A4Schedule::kWs;
+  const long half_tiles = (long)((M + 127) / 128) * ((N + 255) / 256);
+  if (half_tiles >= 128) {
+    sch = W4A4Schedule::kWs;
+    if (asym) return DIROTQ_OK;
+    const long slots = cus < 8 ? 8 : cus / 8 * 8;
+    const double rounds = w4a4_pipe_plan(M, N, cus, big_tokens);
+    if (g == 32 || rounds <= 0.61 * (double)((half_tiles + slots - 1) / slots)) sch = W4A4Schedule::kPipe;
+    return DIROTQ_OK;
+  }
   const long small = (long)((M + 63) / 64) * ((N + 63) / 64);
-  return (small <= 288 || (small <= 512 && K >= 2048) || (small <= 768 && K >= 8192)) ? W4A4Schedule::kSkinny
-                                                                                        : W4A4Schedule::kTile;
+  if (small <= 288 || (small <= 512 && K >= 2048) || (small <= 768 && K >= 8192)) sch = W4A4Schedule::kSkinny;
+  return DIROTQ_OK;
 }
 
 int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
@@ -469,9 +494,13 @@ int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, 
     return y_dtype ? launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)        \
                    : launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
   {
-    // (asymmetric layers: the wave-specialised schedule or this file's kernel; the few-token one has no
-    // zero-point term)
-    const W4A4Schedule sch = w4a4_schedule(M, N, K, r);
+    // (asymmetric layers: the wave-specialised schedule or this file's kernel; the others have no zero-point term)
+    W4A4Schedule sch;
+    long big_tokens;
+    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens);
+    if (st) return st;
+    if (sch == W4A4Schedule::kPipe)
+      return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, big_tokens, s);
     if (sch == W4A4Schedule::kWs)
       return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
     if (sch == W4A4Schedule::kSkinny && !zx)

@@ -565,17 +565,20 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 
 int launch_w4a4_gemm_ws(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx, const void* blob,
                         const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype, hipStream_t s) {
-#define DIROTQ_WS_CASE(GS)                                                                                 \
+  // (symmetric groups of 32 run in the pipelined kernel at every size)
+#define DIROTQ_WS_CASE(GS, SYM)                                                                            \
   case GS:                                                                                                 \
     if (zx)                                                                                                \
       return y_dtype ? ws::launch_one<GS, true, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)        \
                      : ws::launch_one<GS, false, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);      \
-    return y_dtype ? ws::launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)         \
-                   : ws::launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
+    if constexpr (SYM)                                                                                     \
+      return y_dtype ? ws::launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)       \
+                     : ws::launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);     \
+    break;
   switch (g) {
-    DIROTQ_WS_CASE(32)
-    DIROTQ_WS_CASE(64)
-    DIROTQ_WS_CASE(128)
+    DIROTQ_WS_CASE(32, false)
+    DIROTQ_WS_CASE(64, true)
+    DIROTQ_WS_CASE(128, true)
   }
 #undef DIROTQ_WS_CASE
   return DIROTQ_ERR_SHAPE;
