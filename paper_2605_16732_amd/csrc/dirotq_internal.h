@@ -93,6 +93,10 @@ struct RqOut {
 };
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
                            hipStream_t s);
+// few tokens: tiles of `channels` (64: not for xf or groups of 128; or 128) x `tokens` (32 or 64), K split over the
+// waves of a workgroup; virtual channels as in rotate_quantize.hip
+int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
+                               int r_pad, int Kv, int channels, int tokens, hipStream_t s);
 // per-token INT8 quantization of xf [M][KL] given pmax [ceil(KL/128)][M] -> x8 [M][KL], sx [M]
 int launch_quantize_tokens(const float* xf, const float* pmax, int M, int KL, uint8_t* x8, uint16_t* sx,
                            hipStream_t s);

@@ -651,8 +651,8 @@ static int launch_cfg(const RqOut& o, const uint16_t* x, const uint16_t* Qt, int
 
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o,
                            hipStream_t s) {
-  // Large problems: 256 x 256 workgroup tiles (8 waves); medium: 256 channels x 128 tokens
-  // (4 waves); small: 128 x 128 as 4 waves of 128 channels x 32 tokens, or 128 x 64 with K split over two
+  // Few tokens: rotate_quantize_few.hip.  Large problems: 256 x 256 workgroup tiles (8 waves); medium: 256 channels x
+  // 128 tokens (4 waves); small: 128 x 128 as 4 waves of 128 channels x 32 tokens, or 128 x 64 with K split over two
   // sets of such waves (below).  A small launch is a chain of latencies (a few dozen workgroups, each alone
   // on its CU, walk K stage by stage), so its waves carry half the arithmetic per stage: 13 instead of 20 us
   // at M = 256, K = 1152.
@@ -665,6 +665,26 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
   const long n_tc256 = (Kv + 255) / 256;
   const long big_tiles = n_tc256 * ((M + 255) / 256);    // 256 channels x 256 tokens
   const long mid_tiles = n_tc256 * ((M + 127) / 128);    // 256 channels x 128 tokens
+  int cus = 0;
+  {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return hip_failed(e);
+    if (cus < 1) cus = 1;
+  }
+  // Few tokens: the split-K kernel, as long as all its workgroups are resident at once (its LDS admits one per CU); in
+  // a second round it loses (K = 3072: 11.0 / 13.7 / 16.9 us at M = 77 / 256 / 384 against 20.1 / 20.0 / 20.9 here, 30
+  // against 20 us at M = 512; K = 1152: 6.7-10 against 11 us up to M = 1280; K = 12288: 52 / 78 against 86 / 90 us at
+  // M = 1 / 77).  The smallest token tile that fits: more workgroups, each with fewer bytes to pull.
+  if (o.xf || g == 128) {
+    if ((long)((Kv + 127) / 128) * ((M + 31) / 32) <= cus)
+      return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, 128, 32, s);
+  } else {
+    for (int tokens = 32; tokens <= 96; tokens += 32)
+      if ((long)((Kv + 63) / 64) * ((M + tokens - 1) / tokens) <= cus)
+        return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, 64, tokens, s);
+  }
   if (K % 64 != 0) {
     if (mid_tiles >= 100) return launch_cfg<2, 2, 32, 32>(o, x, Qt, M, K, r, g, s);
     return launch_cfg<1, 4, 32, 32, 32>(o, x, Qt, M, K, r, g, s);
@@ -684,14 +704,6 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
   // Beyond that: rounds of 256 workgroups.  A round of 256 x 128 tiles takes about 0.62 of a round of 256 x 256
   // ones (K = 3072: 53 against 81 us, K = 12288: 186 against 300-320), so the plans compared are: all big, all
   // half-size, or k full rounds of big tiles and the remaining tokens in a second launch of half-size ones.
-  int cus = 0;
-  {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return hip_failed(e);
-    if (cus < 1) cus = 1;
-  }
   auto rounds = [&](long tiles) { return (double)((tiles + cus - 1) / cus); };
   constexpr double MID = 0.62, SECOND_LAUNCH = 0.03;
   double best = rounds(big_tiles);                          // plan: one launch of big tiles

@@ -1,0 +1,283 @@
+// Kernel A for few tokens: x_hat = x Q with the split / per-group quantize / pack fused behind it (rotation/split
+// equation of Section 4.2 and the quantizer of Section 3 of the paper); the same results as rotate_quantize.hip up to
+// the order of the fp32 sums.
+//
+// Bound.  With few tokens the launch is a stream over the K x K basis: what counts is how many workgroups pull at it
+// and how many bytes each has in flight (64 B per clock and CU from the L2, ~2000 clocks of latency from memory: 128
+// KB per CU).  The tiled kernel walks K stage by stage with a barrier each and one stage of loads in flight.
+//
+// Measured (graph replay, us, tiled kernel -> this one): K = 1152: 11.0 -> 6.7 at M = 77, 7.0 at 256; K = 3072: 20.1 ->
+// 11.0 at M = 77, 13.7 at 256; K = 12288 (302 MB of basis): 86 -> 52 at one token.  About 4.5 us are launch, first
+// load and epilogue; the rest is 45-50 B per clock and CU.
+//
+// Here a workgroup owns C channels x T tokens (64 x 32, 64 x 64 or 128 x 32) and its four waves split K: wave w takes the
+// 64-channel chunks w, w + 4, ... of the rows.  Nothing is shared between the waves, so there is no barrier in the
+// loop: each wave copies its chunks (C + T rows of 128 bytes) straight from global memory into its own ring of LDS
+// slots (global_load_lds, no registers and no LDS store instructions on the way), one to three chunks ahead, waits for
+// its own copies only, and multiplies.  The four partial sums meet in LDS, where a thread then owns 8 channels of a
+// token: the absolute maximum of a group is an exchange over 4, 8 or 16 neighbouring lanes, 8 codes are one dword.
+#include <algorithm>
+#include <atomic>
+
+#include "dirotq_internal.h"
+
+namespace dirotq {
+
+namespace few {
+
+constexpr int NW = 4, NT = NW * 64;
+constexpr int KC = 64, KS = KC / 16;                         // channels of a chunk, its MFMA steps
+constexpr int ROWB = KC * 2, CPR = KC / 8;                  // bytes and 16-byte pieces of a row and chunk (32 channels,
+constexpr int RPI = 1024 / ROWB;                            // 64-byte rows: slower on every shape); rows per 1-KB copy
+
+// 16-byte piece c of row `row` goes to slot c ^ swz(row) of the row: 16 consecutive rows then fall into 16 different
+// 16-byte slots of a 256-byte bank line
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
+
+template <int C, int T>                                     // channels x tokens of a workgroup
+struct Tile {
+  static constexpr int R = C + T;                           // rows of a chunk: channels, then tokens
+  static constexpr int SLOT = R * ROWB;
+  static constexpr int D = std::min(4, 160 * 1024 / (NW * SLOT));    // slots per wave
+  static constexpr int NI = R / RPI;                        // 1-KB copies per chunk
+  static constexpr int PROW = (C + 4) * 4;                  // bytes per token of a partial sum (padded: no bank conflicts)
+  static constexpr int SMEM = std::max(NW * D * SLOT, NW * T * PROW);
+  static_assert(D >= 2 && SMEM <= 160 * 1024, "LDS");
+};
+
+// One 1-KB copy, global -> LDS: lane l's 16 bytes go to lds + 16 l.  (Written as asm because the compiler lets every
+// later LDS read wait for all such copies in flight; here a wave waits for those of the chunk that it reads.)
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t voff, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_copies() {             // until at most N copies are in flight
+  static_assert(N < 64, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// QM as in rotate_quantize.hip: 0 symmetric, 1 asymmetric, 2 fp32 values and the maxima of 128-channel tiles.
+template <int C, int T, int QM>
+__global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ Qt, int M, int K, int r, int g,
+    uint16_t* __restrict__ xh, uint8_t* __restrict__ xl, uint16_t* __restrict__ sx, uint16_t* __restrict__ zx,
+    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int n_ct, int n_tt, int per_xcd) {
+  using F = Tile<C, T>;
+  constexpr int CI = C / 32, TI = T / 32;
+  extern __shared__ __align__(16) unsigned char smem[];
+  // consecutive workgroup ids go to different XCDs: each XCD gets a run of channel tiles with all their token tiles, so
+  // that a basis row is read from memory by one XCD only
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= n_ct * n_tt) return;
+  const int v0 = logical / n_tt * C, m0 = logical % n_tt * T;         // first virtual channel, first token
+  const int t = threadIdx.x, l = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+
+  // virtual channel -> channel: the 16-bit part [0, r), then the 4-bit part from r_pad on; past the edges a valid row is
+  // read again (its results are not stored)
+  auto channel = [&](int v) { return max(v < r_pad ? min(v, r - 1) : min(r + (v - r_pad), K - 1), 0); };
+  const int c0 = channel(v0);
+  // copy i of a chunk fills rows RPI i .. RPI (i + 1) - 1
+  uint32_t voff[F::NI];
+#pragma unroll
+  for (int i = 0; i < F::NI; i++) {
+    const int row = i * RPI + l / CPR, piece = (l % CPR) ^ swz(row);
+    const int gr = row < C ? channel(v0 + row) - c0 : min(m0 + row - C, M - 1) - m0;
+    voff[i] = (uint32_t)gr * (uint32_t)(2 * K) + piece * 16;
+  }
+  const unsigned char* qbase = (const unsigned char*)(Qt + (size_t)c0 * K);
+  const unsigned char* xbase = (const unsigned char*)(x + (size_t)m0 * K);
+  const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + w * (F::D * F::SLOT);
+  const int n_chunks = (K + KC - 1) / KC;
+  const int mine = (n_chunks - w + NW - 1) / NW;                      // chunks of this wave
+  // (a last chunk of 32 channels: its upper half would lie past the row's end; it is read from the lower one, unused)
+  const bool half_last = (K & 63) != 0;
+  auto issue = [&](int n, int slot) {                                 // this wave's n-th chunk
+    const int k = (w + n * NW);
+    const size_t off = (size_t)k * ROWB;
+    const bool cut = half_last && k == n_chunks - 1;
+    const uint32_t lds = ring + slot * F::SLOT;
+#pragma unroll
+    for (int i = 0; i < F::NI; i++) {
+      const int row = i * RPI + l / CPR, piece = (l % CPR) ^ swz(row);
+      const uint32_t o = voff[i] - (cut && piece >= 4 ? 64u : 0u);
+      copy_to_lds(lds + i * 1024, o, (i * RPI < C ? qbase : xbase) + off);
+    }
+  };
+
+  f32x16 acc[CI][TI];
+#pragma unroll
+  for (int i = 0; i < CI; i++)
+#pragma unroll
+    for (int j = 0; j < TI; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+
+#pragma unroll
+  for (int n = 0; n < F::D; n++)
+    if (n < mine) issue(n, n);
+  const int lrow = l & 31, h = l >> 5, sw = swz(lrow);         // (tile bases are multiples of 32 rows)
+  int slot = 0;
+  for (int n = 0; n < mine; n++) {
+    // chunk n has landed when only the copies of the chunks behind it are in flight
+    const int behind = min(F::D - 1, mine - 1 - n);
+    if (behind == 0) wait_copies<0>();
+    else if (behind == 1) wait_copies<F::NI>();
+    else if (behind == 2) wait_copies<(F::D > 2 ? 2 * F::NI : 0)>();
+    else wait_copies<(F::D > 3 ? 3 * F::NI : 0)>();
+    const unsigned char* sp = smem + (size_t)w * (F::D * F::SLOT) + slot * F::SLOT;
+    const int steps = half_last && w + n * NW == n_chunks - 1 ? 2 : KS;  // 16-channel MFMA steps of the chunk
+    bf16x8 a[KS][CI], b[KS][TI];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      const int at = ((2 * ks + h) ^ sw) << 4;
+#pragma unroll
+      for (int i = 0; i < CI; i++) a[ks][i] = *(const bf16x8*)(sp + (i * 32 + lrow) * ROWB + at);
+#pragma unroll
+      for (int j = 0; j < TI; j++) b[ks][j] = *(const bf16x8*)(sp + (C + j * 32 + lrow) * ROWB + at);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // the slot has been read: it may be filled again
+    if (n + F::D < mine) issue(n + F::D, slot);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++)
+      if (ks < steps)
+#pragma unroll
+        for (int i = 0; i < CI; i++)
+#pragma unroll
+          for (int j = 0; j < TI; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+    slot = slot + 1 == F::D ? 0 : slot + 1;
+  }
+
+  // ---- the partial sums meet in LDS: [wave][token][channel] ----
+  __syncthreads();                                                    // every wave is done with its ring
+#pragma unroll
+  for (int i = 0; i < CI; i++)
+#pragma unroll
+    for (int j = 0; j < TI; j++)
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        *(float4*)(smem + (w * T + j * 32 + lrow) * F::PROW + (i * 32 + 8 * q + 4 * h) * 4) =
+            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+  __syncthreads();
+  // thread: 8 channels of a token; C / 8 neighbouring lanes hold a token's C channels
+  constexpr int LPT = C / 8, PASSES = T * LPT / NT;
+  const int part = t % LPT, KL = K - r;
+  const int v = v0 + part * 8;                                        // first virtual channel of the thread
+  const int cl = v - r_pad;                                           // first 4-bit channel (negative: 16-bit part)
+#pragma unroll
+  for (int p = 0; p < PASSES; p++) {
+    const int tok = p * (NT / LPT) + t / LPT, m = m0 + tok;
+    float f[8];
+#pragma unroll
+    for (int ww = 0; ww < NW; ww++) {
+      const float4* src = (const float4*)(smem + (ww * T + tok) * F::PROW + part * 32);
+      const float4 lo = src[0], hi = src[1];
+      const float u[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int e = 0; e < 8; e++) f[e] = ww ? f[e] + u[e] : u[e];
+    }
+    if (cl < 0) {                                                     // 16-bit part (channels [r, r_pad) do not exist)
+      if (v < r && m < M) {
+        uint4 o;
+        o.x = f32_to_bf16_bits(f[0]) | (uint32_t)f32_to_bf16_bits(f[1]) << 16;
+        o.y = f32_to_bf16_bits(f[2]) | (uint32_t)f32_to_bf16_bits(f[3]) << 16;
+        o.z = f32_to_bf16_bits(f[4]) | (uint32_t)f32_to_bf16_bits(f[5]) << 16;
+        o.w = f32_to_bf16_bits(f[6]) | (uint32_t)f32_to_bf16_bits(f[7]) << 16;
+        *(uint4*)(xh + (size_t)m * r + v) = o;
+      }
+    }
+    const bool valid = cl >= 0 && cl < KL && m < M;
+    if constexpr (QM == 2) {
+      // (the 4-bit part begins at a multiple of 128 virtual channels here, so C = 128 channels are one tile of maxima)
+      float a = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; e++) a = fmaxf(a, cl < KL ? fabsf(f[e]) : 0.0f);
+#pragma unroll
+      for (int o = 1; o < LPT; o <<= 1) a = fmaxf(a, __shfl_xor(a, o));
+      if (valid) {
+        float4* d = (float4*)(xf + (size_t)m * KL + cl);
+        d[0] = make_float4(f[0], f[1], f[2], f[3]);
+        d[1] = make_float4(f[4], f[5], f[6], f[7]);
+        if (part == 0) pmax[(size_t)(cl >> 7) * M + m] = a;
+      }
+    } else {
+      // maximum (and minimum) over the group's 4, 8 or 16 lanes
+      float hi = QM == 1 ? f[0] : fabsf(f[0]), lo = f[0];
+#pragma unroll
+      for (int e = 1; e < 8; e++) {
+        hi = fmaxf(hi, QM == 1 ? f[e] : fabsf(f[e]));
+        lo = fminf(lo, f[e]);
+      }
+#pragma unroll
+      for (int o = 1; o < LPT; o <<= 1)
+        if (o < g / 8) {
+          hi = fmaxf(hi, __shfl_xor(hi, o));
+          if constexpr (QM == 1) lo = fminf(lo, __shfl_xor(lo, o));
+        }
+      uint16_t sbits, zbits = 0;
+      float sf, zf = 0.0f;
+      if constexpr (QM == 1) {
+        zf = group_zero(lo, zbits);
+        sf = group_scale_asym(lo, hi, sbits);
+      } else {
+        sf = group_scale(hi, sbits);
+      }
+      const float inv = group_inv(sf);
+      uint32_t o = 0;
+#pragma unroll
+      for (int e = 0; e < 8; e++)
+        o |= (QM == 1 ? quant_nibble_asym(f[e], zf, inv) : quant_nibble(f[e], inv)) << (4 * e);
+      if (valid) {
+        *(uint32_t*)(xl + (size_t)m * (KL / 2) + cl / 2) = o;
+        if (cl % g == 0) {
+          sx[(size_t)(cl / g) * M + m] = sbits;
+          if constexpr (QM == 1) zx[(size_t)(cl / g) * M + m] = zbits;
+        }
+      }
+    }
+  }
+}
+
+template <int C, int T, int QM>
+static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o, int r_pad,
+                      int Kv, hipStream_t s) {
+  const int n_ct = (Kv + C - 1) / C, n_tt = (M + T - 1) / T;
+  const int per_xcd = (n_ct * n_tt + 7) / 8;
+  // (idempotent: two threads racing here would both set the same attribute)
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)rotate_quantize_few_kernel<C, T, QM>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, Tile<C, T>::SMEM);
+    if (e != hipSuccess) return hip_failed(e);
+    attr_done.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((rotate_quantize_few_kernel<C, T, QM>), dim3(per_xcd * 8), dim3(NT), (Tile<C, T>::SMEM), s, x, Qt, M,
+                     K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, r_pad, n_ct, n_tt, per_xcd);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+template <int C, int T>
+static int launch_tile(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o, int r_pad,
+                       int Kv, hipStream_t s) {
+  if (o.xf) {
+    if constexpr (C == 128) return launch_one<C, T, 2>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+    return DIROTQ_ERR_UNSUPPORTED;
+  }
+  if (o.zx) return launch_one<C, T, 1>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+  return launch_one<C, T, 0>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+}
+
+}  // namespace few
+
+int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o,
+                               int r_pad, int Kv, int channels, int tokens, hipStream_t s) {
+  if (channels == 64)
+    return tokens == 32   ? few::launch_tile<64, 32>(x, Qt, M, K, r, g, o, r_pad, Kv, s)
+           : tokens == 64 ? few::launch_tile<64, 64>(x, Qt, M, K, r, g, o, r_pad, Kv, s)
+                          : few::launch_tile<64, 96>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+  return few::launch_tile<128, 32>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+}
+
+}  // namespace dirotq
