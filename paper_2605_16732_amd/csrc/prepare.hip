@@ -24,113 +24,152 @@ int launch_prepare_rotation(const float* Q, int K, uint16_t* Qt, hipStream_t s) 
 }
 
 // ---- Wp[n][c] = fp32( sum_k W[n][k] Q[k][c] ) with fp64 accumulation ------------
-// 64 x 64 output tile per workgroup, 4 x 4 outputs per thread, 16 k per LDS stage.
+// Bound: the fp64 matrix pipe (78.6 TFLOP/s, as much as the fp64 VALU, but a 16x16x4 MFMA takes two operand registers
+// for 64 cycles of work where the VALU form needed an LDS read per two fma).  64 (n) x 32 (c) outputs per workgroup, four
+// waves of 32 x 16, 32 k per LDS stage; operands stay fp32 in LDS and become fp64 in registers (exact).  The small tile
+// spreads N = K = 1536 over 4.5 workgroups per CU (64 x 64: 2.25, a quarter of the chip idle in the last third).
+// N = K = 1536: 268 -> 158 us (46 TFLOP/s); N = 3072, K = 12288: 24.9 -> 16.9 ms (55 TFLOP/s).  What is left beside the
+// MFMAs are the conversions (24 per 16 MFMAs and wave).
+// Within a run of 16 k lane group q = l / 16 takes k = 4 q .. 4 q + 3, one per MFMA, on both operands.
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+constexpr int FN = 64, FC = 32, FK = 32, FROW = FK + 4;   // (rows of 144 bytes: 16 rows start in 16 different bank groups)
 __global__ __launch_bounds__(256) void fuse_rotation_fp64_kernel(const float* __restrict__ W,
                                                                  const float* __restrict__ Q, int N, int K,
-                                                                 float* __restrict__ Wp) {
-  __shared__ double Ws[16][64 + 2];
-  __shared__ double Qs[16][64 + 2];
-  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  // one workgroup per 64 x 64 tile, tiles numbered row-major over (n tile, c tile) on a 1-D grid
-  const int n_ct = (K + 63) / 64;
-  const int n0 = (int)(blockIdx.x / n_ct) * 64, c0 = (int)(blockIdx.x % n_ct) * 64;
-  double acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int j = 0; j < 4; j++) acc[i][j] = 0.0;
-  const int wrow = t >> 2, wk = (t & 3) * 4;    // W tile: 64 rows x 16 k
-  const int qk = t >> 4, qc = (t & 15) * 4;     // Q tile: 16 k x 64 c
-  const int wn = min(n0 + wrow, N - 1);
-  const bool qok = c0 + qc < K;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const float4 wv = *(const float4*)(W + (size_t)wn * K + k0 + wk);
-    const float4 qv = qok ? *(const float4*)(Q + (size_t)(k0 + qk) * K + c0 + qc) : make_float4(0, 0, 0, 0);
+                                                                 float* __restrict__ Wp, long n_tiles, long per_xcd) {
+  __shared__ __align__(16) float Ws[2][FN][FROW];
+  __shared__ __align__(16) float Qs[2][FC][FROW];         // [c][k]
+  const int t = threadIdx.x, l = t & 63, w = t >> 6;
+  const int n_ct = K / FC;
+  // consecutive workgroup ids go to different XCDs: each XCD gets a run of tiles, c fastest (its rows of W stay in its L2)
+  for (long b = blockIdx.x; b < 8 * per_xcd; b += gridDim.x) {
+    const long tile = (b & 7) * per_xcd + (b >> 3);
+    if (tile >= n_tiles) continue;
+    const int n0 = (int)(tile / n_ct) * FN, c0 = (int)(tile % n_ct) * FC;
+    const int lr = t >> 3, lk = (t & 7) * 4;              // W: rows lr, lr + 32, k lk .. lk + 3; Q: k lr, c lk .. lk + 3
+    const float* w0 = W + (size_t)min(n0 + lr, N - 1) * K + lk;
+    const float* w1 = W + (size_t)min(n0 + lr + 32, N - 1) * K + lk;
+    const float* q0 = Q + (size_t)lr * K + c0 + lk;
+    float4 rw0, rw1, rq;
+    auto load = [&](int k0) {
+      rw0 = *(const float4*)(w0 + k0);
+      rw1 = *(const float4*)(w1 + k0);
+      rq = *(const float4*)(q0 + (size_t)k0 * K);
+    };
+    auto store = [&](int buf) {
+      *(float4*)&Ws[buf][lr][lk] = rw0;
+      *(float4*)&Ws[buf][lr + 32][lk] = rw1;
+      Qs[buf][lk][lr] = rq.x;
+      Qs[buf][lk + 1][lr] = rq.y;
+      Qs[buf][lk + 2][lr] = rq.z;
+      Qs[buf][lk + 3][lr] = rq.w;
+    };
+    const int rn = (w & 1) * 32 + (l & 15), rc = (w >> 1) * 16 + (l & 15), q4 = (l >> 4) * 4;
+    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+    load(0);
+    store(0);
     __syncthreads();
-    Ws[wk + 0][wrow] = wv.x;
-    Ws[wk + 1][wrow] = wv.y;
-    Ws[wk + 2][wrow] = wv.z;
-    Ws[wk + 3][wrow] = wv.w;
-    Qs[qk][qc + 0] = qv.x;
-    Qs[qk][qc + 1] = qv.y;
-    Qs[qk][qc + 2] = qv.z;
-    Qs[qk][qc + 3] = qv.w;
-    __syncthreads();
+    for (int k0 = 0, buf = 0; k0 < K; k0 += FK, buf ^= 1) {
+      if (k0 + FK < K) load(k0 + FK);
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-      double a[4], b[4];
+      for (int kk = 0; kk < FK; kk += 16) {
+        const float4 a0 = *(const float4*)&Ws[buf][rn][kk + q4], a1 = *(const float4*)&Ws[buf][rn + 16][kk + q4];
+        const float4 bq = *(const float4*)&Qs[buf][rc][kk + q4];
+        const float av[2][4] = {{a0.x, a0.y, a0.z, a0.w}, {a1.x, a1.y, a1.z, a1.w}}, bv[4] = {bq.x, bq.y, bq.z, bq.w};
 #pragma unroll
-      for (int i = 0; i < 4; i++) a[i] = Ws[k][ty * 4 + i];
+        for (int s = 0; s < 4; s++)
 #pragma unroll
-      for (int j = 0; j < 4; j++) b[j] = Qs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+          for (int i = 0; i < 2; i++)
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[i][s], (double)bv[s], acc[i], 0, 0, 0);
+      }
+      if (k0 + FK < K) store(buf ^ 1);
+      __syncthreads();                                    // the next stage is complete; this one may be overwritten
     }
-  }
+    // accumulator e of lane l: row 4 e + l / 16, column l % 16 of its 16 x 16 tile
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int n = n0 + ty * 4 + i, c = c0 + tx * 4;
-    if (n < N && c < K)
-      *(float4*)(Wp + (size_t)n * K + c) =
-          make_float4((float)acc[i][0], (float)acc[i][1], (float)acc[i][2], (float)acc[i][3]);
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int n = n0 + (w & 1) * 32 + i * 16 + 4 * e + (l >> 4);
+        if (n < N) Wp[(size_t)n * K + c0 + rc] = (float)acc[i][e];
+      }
   }
 }
 
 // ---- split + quantize rows of an fp32 matrix -------------------------------------
-// unit u < rows * (r/32): (row, 32-channel chunk of the bf16 part)
-// else: (row, group).  Consecutive threads take consecutive rows.
+// Bound: one read of the matrix.  A thread takes 8 consecutive channels of a row, the channels of the 16-bit part first
+// (unit u: row u / (r/8)), then those of the 4-bit part from unit n_hi_pad on; a group is 4, 8 or 16 neighbouring lanes.
+// (One thread per group, consecutive threads on consecutive rows, read 4 of every 64 bytes: 24 -> 5 us at N = K = 1536, 910 -> 35 us at N = 3072,
+// K = 12288.)
 __global__ __launch_bounds__(256) void split_quantize_rows_kernel(const float* __restrict__ src, int rows,
-                                                                  int K, int r, int g,
+                                                                  int K, int r, int g, long n_hi_pad,
                                                                   uint16_t* __restrict__ hi,
                                                                   uint8_t* __restrict__ codes,
                                                                   uint16_t* __restrict__ scales,
                                                                   int16_t* __restrict__ wsum) {
   const long u = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n_hi = (long)rows * (r / 32);
-  const int G = (K - r) / g;
-  if (u < n_hi) {
-    const int row = (int)(u % rows), chk = (int)(u / rows);
-    const float* s = src + (size_t)row * K + chk * 32;
-    uint16_t* d = hi + (size_t)row * r + chk * 32;
-    for (int p = 0; p < 32; p++) d[p] = f32_to_bf16_bits(s[p]);
+  const int KL = K - r;
+  if (u < n_hi_pad) {
+    if (u >= (long)rows * (r / 8)) return;
+    const long row = u / (r / 8);
+    const int c = (int)(u % (r / 8)) * 8;
+    const float4 a = *(const float4*)(src + row * K + c), b = *(const float4*)(src + row * K + c + 4);
+    uint4 o;
+    o.x = f32_to_bf16_bits(a.x) | (uint32_t)f32_to_bf16_bits(a.y) << 16;
+    o.y = f32_to_bf16_bits(a.z) | (uint32_t)f32_to_bf16_bits(a.w) << 16;
+    o.z = f32_to_bf16_bits(b.x) | (uint32_t)f32_to_bf16_bits(b.y) << 16;
+    o.w = f32_to_bf16_bits(b.z) | (uint32_t)f32_to_bf16_bits(b.w) << 16;
+    *(uint4*)(hi + row * r + c) = o;
     return;
   }
-  const long v = u - n_hi;
-  if (v >= (long)rows * G) return;
-  const int row = (int)(v % rows), j = (int)(v / rows);
-  const float* s = src + (size_t)row * K + r + j * g;
+  const long v = u - n_hi_pad;                       // (a multiple of 256 ahead: groups do not straddle waves)
+  const bool live = KL > 0 && v < (long)rows * (KL / 8);   // (whole groups are live or not)
+  const long row = live ? v / (KL / 8) : 0;
+  const int c = live ? (int)(v % (KL / 8)) * 8 : 0;
+  float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (live) {
+    const float4 a = *(const float4*)(src + row * K + r + c), b = *(const float4*)(src + row * K + r + c + 4);
+    f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
+  }
   float amax = 0.0f;
-  for (int p = 0; p < g; p++) amax = fmaxf(amax, fabsf(s[p]));
+#pragma unroll
+  for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf(f[e]));
+  for (int o = 1; o < g / 8; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
   uint16_t sbits;
   const float sf = group_scale(amax, sbits);
   const float inv = group_inv(sf);
-  scales[(size_t)j * rows + row] = sbits;
-  uint8_t* d = codes + (size_t)row * ((K - r) / 2) + j * (g / 2);
+  uint32_t p = 0;
   int sum = 0;
-  for (int p = 0; p < g; p += 2) {
-    const int q0 = quant_code(s[p], inv), q1 = quant_code(s[p + 1], inv);
-    d[p / 2] = (uint8_t)(code_nibble(q0) | (code_nibble(q1) << 4));
-    sum += q0 + q1;
+#pragma unroll
+  for (int e = 0; e < 8; e++) {
+    const int q = quant_code(f[e], inv);
+    p |= code_nibble(q) << (4 * e);
+    sum += q;
   }
-  wsum[(size_t)j * rows + row] = (int16_t)sum;     // |sum| <= 7 * 128
+  for (int o = 1; o < g / 8; o <<= 1) sum += __shfl_xor(sum, o);   // |sum| <= 7 * 128
+  if (!live) return;
+  *(uint32_t*)(codes + row * (KL / 2) + c / 2) = p;
+  if (c % g == 0) {
+    scales[(size_t)(c / g) * rows + row] = sbits;
+    wsum[(size_t)(c / g) * rows + row] = (int16_t)sum;
+  }
 }
 
 int launch_prepare_weights(const float* W, const float* Q, int N, int K, int r, int g, void* blob,
                            float* scratch, hipStream_t s) {
   const BlobLayout L = blob_layout(N, K, r, g);
   char* bp = (char*)blob;
-  // 1-D grids: both launches must stay within 2^31 - 1 workgroups (only shapes whose fp32 scratch alone
-  // would exceed 2^44 bytes get there)
-  const long n_tiles = (long)((K + 63) / 64) * (long)((N + 63) / 64);
-  const long n_units = (long)N * (r / 32) + (long)N * ((K - r) / g);
-  if (n_tiles > 0x7FFFFFFFL || (n_units + 255) / 256 > 0x7FFFFFFFL) return DIROTQ_ERR_SHAPE;
-  hipLaunchKernelGGL(fuse_rotation_fp64_kernel, dim3((unsigned)n_tiles), dim3(256), 0, s, W, Q, N, K, scratch);
+  // 1-D grids (only shapes whose fp32 scratch alone would exceed 2^44 bytes are refused)
+  const long n_tiles64 = (long)((K + 63) / 64) * (long)((N + 63) / 64);
+  const long n_hi_pad = ((long)N * (r / 8) + 255) / 256 * 256;
+  const long n_blocks = (n_hi_pad + (long)N * ((K - r) / 8) + 255) / 256;
+  if (n_tiles64 > 0x7FFFFFFFL || n_blocks > 0x7FFFFFFFL) return DIROTQ_ERR_SHAPE;
+  const long n_tiles = (long)(K / FC) * (long)((N + FN - 1) / FN), per_xcd = (n_tiles + 7) / 8;
+  const unsigned grid = (unsigned)(8 * (per_xcd < (1 << 18) ? per_xcd : (1 << 18)));   // (beyond: several tiles each)
+  hipLaunchKernelGGL(fuse_rotation_fp64_kernel, dim3(grid), dim3(256), 0, s, W, Q, N, K, scratch, n_tiles, per_xcd);
   hipError_t e0 = hipGetLastError();
   if (e0 != hipSuccess) return hip_failed(e0);      // nothing else is enqueued on an unwritten scratch
-  hipLaunchKernelGGL(split_quantize_rows_kernel, dim3((unsigned)((n_units + 255) / 256)), dim3(256), 0, s,
-                     scratch, N, K, r, g, (uint16_t*)(bp + L.off_wh), (uint8_t*)(bp + L.off_codes),
+  hipLaunchKernelGGL(split_quantize_rows_kernel, dim3((unsigned)n_blocks), dim3(256), 0, s, scratch, N, K, r, g,
+                     n_hi_pad, (uint16_t*)(bp + L.off_wh), (uint8_t*)(bp + L.off_codes),
                      (uint16_t*)(bp + L.off_sw), (int16_t*)(bp + L.off_wsum));
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
