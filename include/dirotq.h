@@ -55,7 +55,7 @@
  *  - The GEMM calls pick one of several schedules of the same arithmetic from the problem
  *    size (few tokens: K split over the waves of a workgroup; medium: 128 x 128 tiles;
  *    large: persistent workgroups, whose waves all stage and multiply or are specialised for
- *    one of the two; asymmetric layers use the 128 x 128 tiles and the specialised waves).
+ *    one of the two: asymmetric layers use the specialised ones).
  *    The fp32 additions of an output are ordered differently in each, so a token's result
  *    is deterministic for a given
  *    (M, N, K, r, g) but not bit-identical across different M.  For testing, the

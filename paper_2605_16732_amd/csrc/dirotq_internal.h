@@ -119,10 +119,10 @@ int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t*
 // how many of the first tokens go to its 256 x 256 tiles (the others to 256 x 128 ones); returns its time in units of a
 // 256 x 256 tile per CU
 double w4a4_pipe_plan(int M, int N, int cus, long& big_tokens);
-// symmetric activation codes, few tokens: the K axis split over the waves of a workgroup (64 x 64 outputs each)
-int launch_w4a4_gemm_skinny(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
-                            const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
-                            hipStream_t s);
+// few tokens: the K axis split over the waves of a workgroup (64 x 64 outputs each, or `small`: 32 x 32); zx as above
+int launch_w4a4_gemm_skinny(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
+                            const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,
+                            int y_dtype, bool small, hipStream_t s);
 int launch_prepare_rotation(const float* Q, int K, uint16_t* Qt, hipStream_t s);
 int launch_prepare_weights(const float* W, const float* Q, int N, int K, int r, int g, void* blob,
                            float* scratch, hipStream_t s);

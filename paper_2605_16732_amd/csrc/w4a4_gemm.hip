@@ -441,22 +441,31 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 // K = N = 3072: 42 against 46 us; M = 4096, K = 1152, N = 4608: 57 against 54 us); it also runs the asymmetric layers.
 // Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).  The kernel
 // in this file (128 x 128 tiles, two workgroups per CU) spreads a medium problem over more CUs; with few tokens all
-// leave most of the chip idle and the split-K kernel (64 x 64 outputs per workgroup, the K axis over its 8 waves) is
-// the one with the shortest latency.  Measured crossovers: about 128 of the 256 x 128 tiles; about 288 of the 64 x 64
-// ones (512 from K = 2048 on, 768 from K = 8192 on: the longer K is, the longer each workgroup of the tiled kernel
-// walks alone).
+// leave most of the chip idle and the split-K kernels (64 x 64 or 32 x 32 outputs per workgroup, the K axis over its 8
+// waves) have the shortest latency.  From about 128 tiles of 256 x 128 on the persistent kernels are the faster ones;
+// below, costs in microseconds fitted to measurements at K = 1152 ... 12288 and N = 640 ... 9216 (within 15%) decide:
+// a round of 64 x 64 workgroups (one per CU) 6.3 + 2.1 K/1000; 32 x 32 ones, several per CU, 2.5 + 0.6 K/1000 and
+// 0.0087 (longer K: 0.0037 K/1000) each; 128 x 128 tiles 6 + 8 K/1000 while there is one per CU.
 // DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny in the environment forces one of them wherever it
 // applies (the tests use it to run all of them on the same inputs; large and small: the pipelined kernel with one kind
 // of tile).
 enum class W4A4Schedule { kTile, kWs, kSkinny, kPipe };
-static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens) {
+static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens,
+                         bool& small_tiles) {
   sch = W4A4Schedule::kTile;
   big_tokens = 0;
+  small_tiles = false;
   if (K - r <= 0) return DIROTQ_OK;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_failed(e);
+  const auto tiles = [&](long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); };
+  const double k = K / 1000.0;
+  const double cost64 = (double)((tiles(64, 64) + cus - 1) / cus) * (6.3 + 2.1 * k);
+  const double cost32 = 2.5 + 0.6 * k + (double)tiles(32, 32) * (k > 2.35 ? 0.0037 * k : 0.0087);
+  const double cost128 = (6.0 + 8.0 * k) * (tiles(128, 128) <= cus ? 1.0 : 1.5);
+  small_tiles = cost32 <= cost64;
   if (const char* f = getenv("DIROTQ_W4A4_KERNEL")) {
     const bool large = !strcmp(f, "large"), small = !strcmp(f, "small"), ws = !strcmp(f, "ws");
     if (!strcmp(f, "tile")) return DIROTQ_OK;
@@ -469,7 +478,7 @@ static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Sched
       return DIROTQ_OK;
     }
   }
-  const long half_tiles = (long)((M + 127) / 128) * ((N + 255) / 256);
+  const long half_tiles = tiles(128, 256);
   if (half_tiles >= 128) {
     sch = W4A4Schedule::kWs;
     if (asym) return DIROTQ_OK;
@@ -478,8 +487,7 @@ static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Sched
     if (g == 32 || rounds <= 0.61 * (double)((half_tiles + slots - 1) / slots)) sch = W4A4Schedule::kPipe;
     return DIROTQ_OK;
   }
-  const long small = (long)((M + 63) / 64) * ((N + 63) / 64);
-  if (small <= 288 || (small <= 512 && K >= 2048) || (small <= 768 && K >= 8192)) sch = W4A4Schedule::kSkinny;
+  if ((small_tiles ? cost32 : cost64) < cost128) sch = W4A4Schedule::kSkinny;
   return DIROTQ_OK;
 }
 
@@ -494,17 +502,18 @@ int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, 
     return y_dtype ? launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)        \
                    : launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
   {
-    // (asymmetric layers: the wave-specialised schedule or this file's kernel; the others have no zero-point term)
+    // (asymmetric layers: the wave-specialised schedule, the split-K ones or this file's kernel)
     W4A4Schedule sch;
     long big_tokens;
-    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens);
+    bool small_tiles;
+    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens, small_tiles);
     if (st) return st;
     if (sch == W4A4Schedule::kPipe)
       return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, big_tokens, s);
     if (sch == W4A4Schedule::kWs)
       return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
-    if (sch == W4A4Schedule::kSkinny && !zx)
-      return launch_w4a4_gemm_skinny(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, s);
+    if (sch == W4A4Schedule::kSkinny)
+      return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, small_tiles, s);
   }
   switch (g) {
     DIROTQ_CASE(32)
