@@ -20,6 +20,7 @@
 //
 // Stage = 64 channels: weights [128 rows][64 B], activations [128 rows][64 B a-plane | 64 B
 // b-plane]; two stages in LDS; global loads run one stage ahead through registers.
+#include <algorithm>
 #include <atomic>
 
 #include "gemm_tail.h"
@@ -374,15 +375,191 @@ static int launch_one8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
+// ---- GEMM, few tokens: K split over the waves of a workgroup -------------------------------------
+// The 128 x 128 tiling walks all of K stage by stage on a few workgroups (M = 77, N = K = 3072: 24 of them, 48 stages).
+// Here a workgroup owns 32 output channels x 32 NJ tokens and its eight waves split the K axis: wave w takes the work
+// items w, w + 8, ... (an item = 64 8-bit channels, a 32-channel group when g = 32, or 16 channels of the 16-bit branch),
+// operands straight from global memory in the MFMA operand layout, two items' loads in flight; the eight partial sums
+// meet in LDS.  D[token][n] orientation: a lane owns an output channel, so the group's weight scale is a per-lane number
+// and one fma per accumulator applies it (no scale-product MFMA); the token's scale multiplies a wave's sum once.
+// us, graph replay, 128 x 128 tiles -> this: N = K = 3072: M = 1 39.3 -> 7.9, M = 77 40.6 -> 13.8, M = 256 41.8 -> 22.3;
+// N = 3072, K = 12288, M = 77 154 -> 37.
+constexpr int FEW_NT = 512;
+
+// 4 sign-magnitude bytes -> the two planes [s 0000 aaa], [s 000 bbbb]
+__device__ __forceinline__ void a8_planes(uint32_t x, uint32_t& a, uint32_t& b) {
+  a = (x & 0x80808080u) | ((x >> 4) & 0x07070707u);
+  b = x & 0x8F8F8F8Fu;
+}
+
+template <int GS, int NJ>
+struct FewItem {
+  uint4 w[GS == 32 ? 1 : 2], x[NJ][GS == 32 ? 1 : 2];
+  uint16_t s;
+};
+
+template <int GS, bool OUT_F32, int NJ>
+__global__ __launch_bounds__(FEW_NT, 2) void w4a8_few_kernel(
+    const uint16_t* __restrict__ xh, const uint8_t* __restrict__ x8, const uint16_t* __restrict__ sx,
+    const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
+    const uint16_t* __restrict__ bias, int M, int N, int K, int r, void* __restrict__ y, int n_nt) {
+  constexpr int NW = 8, NP = GS == 32 ? 1 : 2;           // 32-channel blocks per item
+  __shared__ __align__(16) float part[NW][NJ * 16][64];
+  const int n0 = (blockIdx.x % n_nt) * 32, m0 = (blockIdx.x / n_nt) * (32 * NJ);
+  const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int KL = K - r;
+  const int nb = r / 16, nq = KL / (32 * NP), items = nb + nq;
+  const size_t rowN = (size_t)min(n0 + c, N - 1);
+  size_t rowM[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++) rowM[j] = (size_t)min(m0 + j * 32 + c, M - 1);
+  auto load = [&](FewItem<GS, NJ>& it, int idx) {
+    if (idx < nb) {                                      // this lane's 8 of the 16 bf16 channels
+      it.w[0] = *(const uint4*)(wh + rowN * r + idx * 16 + h * 8);
+#pragma unroll
+      for (int j = 0; j < NJ; j++) it.x[j][0] = *(const uint4*)(xh + rowM[j] * r + idx * 16 + h * 8);
+      return;
+    }
+    const int q = idx - nb;
+#pragma unroll
+    for (int p = 0; p < NP; p++) {
+      it.w[p] = *(const uint4*)(wq + rowN * (KL / 2) + (size_t)(q * NP + p) * 16);
+#pragma unroll
+      for (int j = 0; j < NJ; j++) it.x[j][p] = *(const uint4*)(x8 + rowM[j] * KL + (size_t)(q * NP + p) * 32 + h * 16);
+    }
+    it.s = sw[(size_t)(GS == 128 ? q >> 1 : q) * N + rowN];
+  };
+  f32x16 acc[NJ], acc16[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[j][v] = acc16[j][v] = 0.0f;
+  const int sc_x = h ? 127 + 9 : 127 + 13, sc_w = 127 + 9;
+  auto compute = [&](const FewItem<GS, NJ>& it, int idx) {
+    if (idx < nb) {
+#pragma unroll
+      for (int j = 0; j < NJ; j++)
+        acc16[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, it.x[j][0]),
+                                                           __builtin_bit_cast(bf16x8, it.w[0]), acc16[j], 0, 0, 0);
+      return;
+    }
+    i32x8_t wv[NP];
+#pragma unroll
+    for (int p = 0; p < NP; p++) {                       // lane half 0: even channels, 1: odd ones
+      const uint32_t d[4] = {it.w[p].x, it.w[p].y, it.w[p].z, it.w[p].w};
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const uint32_t u = d[e] >> (4 * h);
+        wv[p][e] = wv[p][e + 4] = (int)((u & 0x07070707u) | ((u & 0x08080808u) << 4));
+      }
+    }
+    const float s = f16_bits_to_f32(it.s);
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+      f32x16 z;
+#pragma unroll
+      for (int v = 0; v < 16; v++) z[v] = 0.0f;
+#pragma unroll
+      for (int p = 0; p < NP; p++) {
+        const uint32_t d[4] = {it.x[j][p].x, it.x[j][p].y, it.x[j][p].z, it.x[j][p].w};
+        i32x8_t xv;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          uint32_t a, b;
+          a8_planes(d[e], a, b);
+          xv[e] = (int)a;
+          xv[e + 4] = (int)b;
+        }
+        z = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(xv, wv[p], z, 0, 0, 0, sc_x, 0, sc_w);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[j][v] = fmaf(z[v], s, acc[j][v]);
+    }
+  };
+  FewItem<GS, NJ> set[2];
+#pragma unroll
+  for (int d = 0; d < 2; d++)
+    if (w + d * NW < items) load(set[d], w + d * NW);
+  for (int idx = w; idx < items; idx += 2 * NW) {
+#pragma unroll
+    for (int d = 0; d < 2; d++) {
+      if (idx + d * NW < items) compute(set[d], idx + d * NW);
+      if (idx + (d + 2) * NW < items) load(set[d], idx + (d + 2) * NW);
+    }
+  }
+  // accumulator v of a lane: token 8 (v / 4) + 4 h + v % 4 of its tile, channel c
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int m = min(m0 + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3), M - 1);
+      part[w][j * 16 + v][l] = fmaf(acc[j][v], KL ? f16_bits_to_f32(sx[m]) : 0.0f, acc16[j][v]);
+    }
+  __syncthreads();
+  for (int slot = t; slot < NJ * 16 * 64; slot += FEW_NT) {
+    const int jv = slot >> 6, lane = slot & 63, v = jv & 15;
+    const int m = m0 + (jv >> 4) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), n = n0 + (lane & 31);
+    float o = part[0][jv][lane];
+#pragma unroll
+    for (int ww = 1; ww < NW; ww++) o += part[ww][jv][lane];
+    if (m >= M || n >= N) continue;
+    if (bias) o += bf16_bits_to_f32(bias[n]);
+    if (OUT_F32) ((float*)y)[(size_t)m * N + n] = o;
+    else ((uint16_t*)y)[(size_t)m * N + n] = f32_to_bf16_bits(o);
+  }
+}
+
+template <int GS, bool OUT_F32, int NJ>
+static int launch_few8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias,
+                       int M, int N, int K, int r, void* y, hipStream_t s) {
+  const BlobLayout L = blob_layout(N, K, r, GS);
+  const char* bp = (const char*)blob;
+  const int n_nt = (N + 31) / 32;
+  const long n_blocks = (long)n_nt * ((M + 32 * NJ - 1) / (32 * NJ));
+  hipLaunchKernelGGL((w4a8_few_kernel<GS, OUT_F32, NJ>), dim3((unsigned)n_blocks), dim3(FEW_NT), 0, s, xh, x8, sx,
+                     (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes),
+                     (const uint16_t*)(bp + L.off_sw), bias, M, N, K, r, y, n_nt);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+// Which kernel: costs in microseconds fitted to measurements at K = 1152 ... 12288, N = 1152 ... 12288 (r = 128, g = 64).
+// The split-K kernel: 3.4 + K/2500 and, per 32 x 32 outputs, 0.017 (K = 1152) or 0.0075 K/1000 (longer K); two token
+// tiles per workgroup once that many workgroups walk a long K (K = 12288, M = 128: 38.6 against 46.9 us).  The 128 x 128
+// tiles: 4 + 13 K/1000 while there is at most one per CU, half as much again up to two.
+template <int GS, bool OUT_F32>
+static int launch_case8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias,
+                        int M, int N, int K, int r, int g, void* y, hipStream_t s) {
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_failed(e);
+  const double k = K / 1000.0;
+  const long t32 = (long)((M + 31) / 32) * ((N + 31) / 32), t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+  const double few = 3.4 + 0.4 * k + (double)t32 * std::max(0.017, 0.0075 * k);
+  const double tiled = (4.0 + 13.0 * k) * (t128 <= cus ? 1.0 : 1.5);
+  if (t128 <= 2L * cus && few < tiled) {
+    return K >= 8192 && M > 32 && t32 >= 256 ? launch_few8<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s)
+                                             : launch_few8<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
+  }
+  constexpr int TS = GS == 32 ? 32 : 64;                 // (the tiled kernel runs groups of 128 as two halves)
+  return launch_one8<TS, OUT_F32>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s);
+}
+
 int launch_w4a8_gemm(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob,
                      const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
                      hipStream_t s) {
-  if (g == 32)
-    return y_dtype ? launch_one8<32, true>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s)
-                   : launch_one8<32, false>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s);
-  if (g == 64 || g == 128)
-    return y_dtype ? launch_one8<64, true>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s)
-                   : launch_one8<64, false>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s);
+#define DIROTQ_A8_CASE(GS)                                                                                   \
+  case GS:                                                                                                   \
+    return y_dtype ? launch_case8<GS, true>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s)                     \
+                   : launch_case8<GS, false>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s);
+  switch (g) {
+    DIROTQ_A8_CASE(32)
+    DIROTQ_A8_CASE(64)
+    DIROTQ_A8_CASE(128)
+  }
+#undef DIROTQ_A8_CASE
   return DIROTQ_ERR_UNSUPPORTED;
 }
 

@@ -1,0 +1,46 @@
+"""Both schedules of the W4A8 GEMM (K split over the waves of a workgroup for few tokens, 128 x 128 tiles beyond) against
+the CPU oracle on identical inputs: one output, one item of the K axis, fewer items than waves, no 8-bit part, groups of
+two 64-channel pieces, cut tiles, two token tiles per workgroup (long K)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dirotq_oracle as O
+from paper_2605_16732_amd import binding as B
+
+from gpu_util import dev, dev_bf16, host_bf16_bits, import_blob
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,r,g", [
+    (1, 1, 64, 0, 64), (1, 33, 32, 0, 32), (31, 70, 96, 32, 32), (33, 32, 192, 64, 128), (40, 50, 64, 64, 64),
+    (65, 129, 1152, 64, 64), (64, 4200, 8224, 32, 128), (400, 300, 96, 32, 32), (500, 700, 352, 96, 128),
+    (900, 650, 320, 64, 64),
+])
+def test_schedules_match_oracle(M, N, K, r, g):
+    """fp32 sums of at most G + r/16 partial terms per wave, 8 waves and one product with the token scale against a
+    float64 sum: 1e-5 of the largest output; the bf16 output is the rounded fp32 one."""
+    print(f"[case] w4a8 M={M} N={N} K={K} r={r} g={g}", flush=True)
+    rng = np.random.default_rng([M, N, K])
+    G = (K - r) // g
+    xh = O.round_to_bf16(rng.standard_normal((M, r)).astype(np.float32) * 20)
+    Wh = O.round_to_bf16(rng.standard_normal((N, r)).astype(np.float32) * 0.05)
+    qx = rng.integers(-127, 128, size=(M, K - r)).astype(np.int32)
+    qw = rng.integers(-7, 8, size=(N, K - r)).astype(np.int8)
+    sx = rng.lognormal(-3, 1, size=M).astype(np.float16)
+    sw = rng.lognormal(-5, 1, size=(N, G)).astype(np.float16)
+    bias = O.round_to_bf16(rng.standard_normal(N).astype(np.float32))
+    want, _ = O.combine_a8(xh, qx, sx, Wh, qw, sw, g, bias)
+    sm = np.where(qx < 0, 0x80 - qx, qx).astype(np.uint8).reshape(M, (K - r) // 32, 16, 2)
+    x8 = np.ascontiguousarray(sm.transpose(0, 1, 3, 2)).reshape(M, K - r)      # blocks of 32: even channels, odd ones
+    low = r < K
+    args = (dev_bf16(O.bf16_bits(xh)) if r else None, dev(x8) if low else None, dev(sx) if low else None,
+            import_blob(Wh, qw, sw, N, K, r, g), M, N, K, r, g)
+    bias_d = dev_bf16(O.bf16_bits(bias))
+    yf = B.w4a8_gemm(*args, bias=bias_d, out_dtype=torch.float32).cpu().numpy()
+    yb = B.w4a8_gemm(*args, bias=bias_d, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert np.abs(yf - want).max() <= 1e-5 * np.abs(want).max()
+    np.testing.assert_array_equal(host_bf16_bits(yb).astype(np.int32),
+                                  O.bf16_bits(O.round_to_bf16(yf)).astype(np.int32))
