@@ -134,6 +134,24 @@ int launch_export_weights(const void* blob, int N, int K, int r, int g, uint16_t
 #if defined(__HIPCC__)
 // ---- device helpers ---------------------------------------------------------
 
+// One copy global -> LDS without registers on the way: lane l's 16 (4) bytes at base + voff go to lds + 16 l (4 l).
+// (Written as asm because the compiler lets every later LDS read wait for all such copies in flight; a wave that reads
+// its ring of slots waits for the copies of the slot it reads, with wait_copies.)
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t voff, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+__device__ __forceinline__ void copy4_to_lds(uint32_t lds, uint32_t voff, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_copies() {             // until at most N copies (and other loads) are in flight
+  static_assert(N < 64, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
+}
+
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   // round to nearest even; inputs are finite in this library
   uint32_t u = __builtin_bit_cast(uint32_t, f);

@@ -45,17 +45,6 @@ struct Tile {
   static_assert(D >= 2 && SMEM <= 160 * 1024, "LDS");
 };
 
-// One 1-KB copy, global -> LDS: lane l's 16 bytes go to lds + 16 l.  (Written as asm because the compiler lets every
-// later LDS read wait for all such copies in flight; here a wave waits for those of the chunk that it reads.)
-__device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t voff, const void* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_copies() {             // until at most N copies are in flight
-  static_assert(N < 64, "vmcnt");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // QM as in rotate_quantize.hip: 0 symmetric, 1 asymmetric, 2 fp32 values and the maxima of 128-channel tiles.
 template <int C, int T, int QM>
 __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
@@ -87,7 +76,7 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
   }
   const unsigned char* qbase = (const unsigned char*)(Qt + (size_t)c0 * K);
   const unsigned char* xbase = (const unsigned char*)(x + (size_t)m0 * K);
-  const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + w * (F::D * F::SLOT);
+  const uint32_t ring = lds_address(smem) + w * (F::D * F::SLOT);
   const int n_chunks = (K + KC - 1) / KC;
   const int mine = (n_chunks - w + NW - 1) / NW;                      // chunks of this wave
   // (a last chunk of 32 channels: its upper half would lie past the row's end; it is read from the lower one, unused)

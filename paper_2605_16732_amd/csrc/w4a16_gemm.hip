@@ -4,228 +4,276 @@
 //
 // A 4-bit code is a small integer and therefore an exact bf16 number, so the group sums run on
 // the bf16 matrix pipe with nothing rounded before the fp32 accumulator; the per-group weight
-// scale is applied afterwards, as in the W4A4 kernel: one fp16 MFMA spreads s_w[n,j] over the
-// accumulator layout (token operand = 1), one fma per accumulator and group applies it.
+// scale is applied afterwards, by one fma per accumulator and group.
 //
-// Codes become bf16 on their way into LDS (once per workgroup): the sign-magnitude nibble
-// [s mmm] indexes an 8-entry byte table through v_perm_b32 (high and low byte of bf16(m)), the
-// sign moves to bit 15, and two more rounds of byte permutes restore the channel order.
-//
-// Tile 128 n x 128 tokens, 4 waves as 2 x 2, stage = 64 channels as a [256 rows][128 B] tile
-// (weights rows 0..127, tokens 128..255), two stages in LDS, global loads one stage ahead
-// through registers.
+// Two schedules: up to 32 tokens a stream over the packed weights, beyond that MFMA tiles (launch_w4a16_gemm).
 #include <atomic>
 
 #include <cstdlib>
 #include <cstring>
 
-#include "gemm_tail.h"
+#include "dirotq_internal.h"
 
 namespace dirotq {
 
-constexpr int BK16 = 64;                               // channels per LDS stage
-constexpr int STAGE16 = (TN + TM) * 128;               // 32 KB
-constexpr int SCALE16_OFF = 2 * STAGE16;               // u64 [2 bufs][groups per stage][128 rows]: {fp16 s_w, 0, 0, 0}
-constexpr int scale16_buf_bytes(int gs) { return (BK16 / gs) * TN * 8; }
-constexpr int zero16_off(int gs) { return SCALE16_OFF + 2 * scale16_buf_bytes(gs); }
-constexpr int smem16_bytes(int gs) { return zero16_off(gs) + 256; }
+// ---- large: 128 n x 32 NJ tokens per workgroup, eight waves: four of 32 n, twice, for the even and the odd stages of
+// 64 channels (so that two waves per SIMD hide each other's latencies without decoding a weight twice; their sums meet in
+// LDS at the end) ------------------------------------------------------------------------------------------------------
+// All staging is copies global -> LDS (activations, packed codes, scales; a ring of three stages for each half, two in
+// flight, one barrier per stage), so the waves issue nothing but operand reads, the decode, MFMAs and the scale sweep.
+// A wave decodes the codes of its own 32 rows in registers, for its NJ token tiles: nibble -> fp8 subnormal byte -> bf16
+// by the scaled conversion instruction (scale 2^9, exact), 12 instructions per 8 codes.
+// D[token][n] orientation: a lane owns an output channel, so the group's scale is a per-lane number and one fma per
+// accumulator and group applies it (no scale-product MFMA).
+// Bound: not the matrix pipe alone (32 cycles x 4 per 32 x 32 tile and stage, 43 % of the time at NJ = 5) but with it the
+// sweep and decode on the VALU and 28 KB of LDS traffic per 128 x 32 tile and stage (operand reads 16 KB, copies).  The
+// kernel it replaces (128 x 128 tiles, two workgroups per CU) decoded into LDS, whose writes run at a quarter of the rate
+// of reads, and had one stage of loads in flight.  Before -> now, us: 4096 x 4608 -> 1152 (M x K -> N) 111 -> 55 (788
+// TFLOP/s), 512 tokens 88 -> 23; 4096 x 3072 -> 12288 444 -> 370; 256 x 3072 -> 3072 52 -> 17.
+namespace w16 {
 
-// 8 sign-magnitude nibbles (channels c0..c7, c0 lowest) -> 8 bf16 numbers in channel order
-__device__ __forceinline__ uint4 nibbles_to_bf16(uint32_t p) {
-  const uint32_t sel_e = p & 0x07070707u, sel_o = (p >> 4) & 0x07070707u;   // magnitudes of c0 c2 c4 c6 / c1 c3 c5 c7
-  // bf16(m), m = 0..7: 0000 3F80 4000 4040 4080 40A0 40C0 40E0 (selectors 0..3 read the second operand)
-  const uint32_t lo_e = __builtin_amdgcn_perm(0xE0C0A080u, 0x40008000u, sel_e);
-  const uint32_t lo_o = __builtin_amdgcn_perm(0xE0C0A080u, 0x40008000u, sel_o);
-  uint32_t hi_e = __builtin_amdgcn_perm(0x40404040u, 0x40403F00u, sel_e);
-  uint32_t hi_o = __builtin_amdgcn_perm(0x40404040u, 0x40403F00u, sel_o);
-  hi_e |= (p & 0x08080808u) << 4;                                            // sign -> bit 7 of the high byte
-  hi_o |= p & 0x80808080u;
-  const uint32_t e01 = __builtin_amdgcn_perm(hi_e, lo_e, 0x05010400u);        // bf16(c0), bf16(c2)
-  const uint32_t e23 = __builtin_amdgcn_perm(hi_e, lo_e, 0x07030602u);        // c4, c6
-  const uint32_t o01 = __builtin_amdgcn_perm(hi_o, lo_o, 0x05010400u);        // c1, c3
-  const uint32_t o23 = __builtin_amdgcn_perm(hi_o, lo_o, 0x07030602u);        // c5, c7
-  uint4 r;
-  r.x = __builtin_amdgcn_perm(o01, e01, 0x05040100u);                         // c0, c1
-  r.y = __builtin_amdgcn_perm(o01, e01, 0x07060302u);                         // c2, c3
-  r.z = __builtin_amdgcn_perm(o23, e23, 0x05040100u);                         // c4, c5
-  r.w = __builtin_amdgcn_perm(o23, e23, 0x07060302u);                         // c6, c7
-  return r;
+constexpr int TN_ = 128, NT = 512, NBUF = 3;
+constexpr int W_BYTES = TN_ * 32, S_BYTES = 4 * 256;     // of a stage: rows of 64 channels; scales per wave
+
+// 8 sign-magnitude nibbles of a dword -> 8 bf16 numbers in channel order
+__device__ __forceinline__ bf16x8 decode(uint32_t p) {
+  const uint32_t e = (p & 0x07070707u) | ((p & 0x08080808u) << 4), o = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
+  const uint32_t lo = __builtin_amdgcn_perm(o, e, 0x05010400u), hi = __builtin_amdgcn_perm(o, e, 0x07030602u);
+  uint4 r;                                               // bytes [s 0000 mmm] = m 2^-9 as fp8, times 2^9
+  r.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, false));
+  r.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, true));
+  r.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, false));
+  r.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, true));
+  return __builtin_bit_cast(bf16x8, r);
+}
+
+template <int GS, bool OUT_F32, int NJ>
+__global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
+    const uint16_t* __restrict__ x, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
+    const uint16_t* __restrict__ bias, int M, int N, int K, void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int GPS = GS == 32 ? 2 : 1;                  // groups per stage
+  constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 128, SLOT = X_BYTES + W_BYTES + S_BYTES;
+  constexpr int COPIES = NJ + 2;                         // per wave and stage: activations, codes, scales
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= n_mt * n_nt) return;
+  constexpr int GN = 4;                                  // output tiles swept per token tile (operands stay in the L2)
+  const int grp = logical / (GN * n_mt), in_grp = logical % (GN * n_mt);
+  const int gn = min(n_nt - grp * GN, GN);
+  const int n0 = (grp * GN + in_grp % gn) * TN_, m0 = in_grp / gn * TM_;
+  const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), w = wave & 3, kh = wave >> 2;
+  const int G = K / GS, nst = (K + 63) / 64, steps = (nst + 1) / 2;
+  const bool short_last = GS == 32 && (K & 63) != 0;     // the last stage holds one 32-channel group
+
+  // ---- copies of a stage by this wave: token rows 8 NJ w .. 8 NJ w + 8 NJ - 1 (8 rows per copy; 16-byte piece p of row `row` at
+  // slot p ^ ((row >> 1) & 7)), the packed codes of its 32 weight rows (half p of row `row` at p ^ ((row >> 3) & 1)), and
+  // their scales (a window of dwords that begins at the dword of the first one)
+  uint32_t vo_x[NJ];
+#pragma unroll
+  for (int i = 0; i < NJ; i++) {
+    const int row = 8 * NJ * w + 8 * i + (l >> 3), piece = (l & 7) ^ ((row >> 1) & 7);
+    vo_x[i] = (uint32_t)(min(m0 + row, M - 1) - m0) * (uint32_t)(2 * K) + piece * 16;
+  }
+  const int w_row = l >> 1, w_half = (l & 1) ^ ((w_row >> 3) & 1);
+  const uint32_t vo_w = (uint32_t)(min(n0 + 32 * w + w_row, N - 1) - n0) * (uint32_t)(K / 2) + w_half * 16;
+  const int nw = min(n0 + 32 * w, N - 1);                // first channel of the wave (past the edge: nothing is stored)
+  const unsigned char *xb = (const unsigned char*)(x + (size_t)m0 * K), *wb = wq + (size_t)n0 * (K / 2);
+  const uint32_t ring = lds_address(smem) + kh * (NBUF * SLOT);
+  const size_t last_sw = ((size_t)G * N * 2 - 1) & ~(size_t)3;
+  auto group = [&](int s, int jj) { return min(GS == 32 ? 2 * s + jj : GS == 128 ? s >> 1 : s, G - 1); };
+  auto issue = [&](int s, int slot) {                    // (past the last stage: that one again, unused)
+    s = min(s, nst - 1);
+    const uint32_t at = ring + slot;
+    const bool cut = short_last && s == nst - 1;         // (the missing upper half: the lower one again)
+#pragma unroll
+    for (int i = 0; i < NJ; i++) {
+      const int row = 8 * NJ * w + 8 * i + (l >> 3), piece = (l & 7) ^ ((row >> 1) & 7);
+      copy_to_lds(at + (8 * NJ * w + 8 * i) * 128, vo_x[i] - (cut && piece >= 4 ? 64u : 0u), xb + (size_t)s * 128);
+    }
+    copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
+    const size_t e0 = ((size_t)group(s, 0) * N + nw) * 2 & ~(size_t)3;
+    uint32_t vs = min(GS == 32 ? c : l, 19) * 4;
+    if (GS == 32 && h) vs += (uint32_t)((((size_t)group(s, 1) * N + nw) * 2 & ~(size_t)3) - e0);
+    vs = min(vs, (uint32_t)min(last_sw - e0, (size_t)0x7ffffffc));   // (nothing past the dword of the last scale)
+    copy4_to_lds(at + X_BYTES + W_BYTES + w * 256, vs, (const unsigned char*)sw + e0);
+  };
+
+  f32x16 acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[j][v] = 0.0f;
+  // operand reads: k-step ks of lane half h is 16-byte piece 4 h + ks (8 channels) of a token row, dword ks of its half of
+  // a weight row; groups of 32, which must not mix the halves: piece 2 ks + h, dword 2 ks + h of the whole row
+  const int swx = (c >> 1) & 7, swz = (c >> 3) & 1;      // (tile bases are multiples of 32 rows)
+  int ln_x[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ks++) ln_x[ks] = c * 128 + (((GS == 32 ? 2 * ks + h : 4 * h + ks) ^ swx) << 4);
+  issue(kh, 0);
+  issue(2 + kh, SLOT);
+  int cur = 0;
+  for (int step = 0; step < steps; step++) {
+    const int s = 2 * step + kh;
+    wait_copies<COPIES>();                               // this wave's copies of stage s have landed, and (barrier) all
+    __builtin_amdgcn_s_barrier();                        // waves'; stage s - 2 has been read by all of them
+    asm volatile("" ::: "memory");
+    int fill = cur + 2 * SLOT;
+    if (fill >= 3 * SLOT) fill -= 3 * SLOT;
+    issue(s + 4, fill);
+    if (s >= nst) break;                                 // (an odd number of stages: the other half has the last one)
+    const bool half_stage = short_last && s == nst - 1;
+    const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
+    const unsigned char* sc_p = sp + X_BYTES + W_BYTES + w * 256;
+    float sc[GPS];
+#pragma unroll
+    for (int jj = 0; jj < GPS; jj++) {
+      const int odd = (int)(((size_t)group(s, jj) * N + nw) & 1);
+      const uint16_t b = *(const uint16_t*)(sc_p + jj * 128 + (odd + c) * 2);
+      sc[jj] = f16_bits_to_f32(b);
+    }
+    const unsigned char* wp = sp + X_BYTES + w * 1024 + c * 32;
+    bf16x8 b[4];
+    if constexpr (GS == 32) {
+      const uint4 lo = *(const uint4*)(wp + (swz << 4)), hi = *(const uint4*)(wp + ((1 ^ swz) << 4));
+      b[0] = decode(h ? lo.y : lo.x);
+      b[1] = decode(h ? lo.w : lo.z);
+      b[2] = decode(h ? hi.y : hi.x);
+      b[3] = decode(h ? hi.w : hi.z);
+    } else {
+      const uint4 p = *(const uint4*)(wp + ((h ^ swz) << 4));
+      b[0] = decode(p.x);
+      b[1] = decode(p.y);
+      b[2] = decode(p.z);
+      b[3] = decode(p.w);
+    }
+    bf16x8 a[2][4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) a[0][ks] = *(const bf16x8*)(sp + ln_x[ks]);
+    f32x16 I[2][GPS];
+#pragma unroll
+    for (int j = 0; j <= NJ; j++) {
+      if (j < NJ - 1)
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) a[(j + 1) & 1][ks] = *(const bf16x8*)(sp + ln_x[ks] + (j + 1) * (32 * 128));
+      if (j < NJ) {
+#pragma unroll
+        for (int jj = 0; jj < GPS; jj++) {
+          f32x16 z;
+#pragma unroll
+          for (int v = 0; v < 16; v++) z[v] = 0.0f;
+#pragma unroll
+          for (int ks = jj * (4 / GPS); ks < (jj + 1) * (4 / GPS); ks++)
+            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ks], b[ks], z, 0, 0, 0);
+          I[j & 1][jj] = z;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (j > 0) {
+#pragma unroll
+        for (int jj = 0; jj < GPS; jj++)
+          if (jj == 0 || !half_stage)                    // (not 0 x: an infinity would become a NaN)
+#pragma unroll
+          for (int v = 0; v < 16; v++) acc[j - 1][v] = fmaf(I[(j - 1) & 1][jj][v], sc[jj], acc[j - 1][v]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    cur = cur + SLOT >= 3 * SLOT ? 0 : cur + SLOT;
+  }
+  wait_copies<0>();                                      // (nothing may land in LDS after the workgroup has ended)
+
+  // ---- the two halves exchange: token tile j is finished by half j & 1
+  __syncthreads();
+  float4* xch = (float4*)smem;
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+    if ((j & 1) != kh)
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        xch[((j * 4 + w) * 4 + q) * 64 + l] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+  __syncthreads();
+  // two channels of a token in one dword: neighbouring lanes exchange, the even one stores token v, the odd one v + 1
+  const int n = n0 + 32 * w + c;
+  const float bn = bias && n < N ? bf16_bits_to_f32(bias[n]) : 0.0f;
+  const bool pairs = !OUT_F32 && (N & 1) == 0, odd = l & 1;
+#pragma unroll
+  for (int j = 0; j < NJ; j++) {
+    if ((j & 1) != kh) continue;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const float4 o = xch[((j * 4 + w) * 4 + q) * 64 + l];
+      acc[j][4 * q] += o.x;
+      acc[j][4 * q + 1] += o.y;
+      acc[j][4 * q + 2] += o.z;
+      acc[j][4 * q + 3] += o.w;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      const int m = m0 + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+      const float y0 = bias ? acc[j][v] + bn : acc[j][v], y1 = bias ? acc[j][v + 1] + bn : acc[j][v + 1];
+      if (pairs) {
+        const float got = __shfl_xor(odd ? y0 : y1, 1);
+        const uint32_t d = f32x2_to_bf16x2_bits(odd ? got : y0, odd ? y1 : got);
+        if (n < N && m + odd < M) *(uint32_t*)((uint16_t*)y + (size_t)(m + odd) * N + (n - odd)) = d;
+      } else if (n < N) {
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+          if (m + e < M) {
+            const float o = e ? y1 : y0;
+            if (OUT_F32) ((float*)y)[(size_t)(m + e) * N + n] = o;
+            else ((uint16_t*)y)[(size_t)(m + e) * N + n] = f32_to_bf16_bits(o);
+          }
+      }
+    }
+  }
+}
+
+template <int GS, bool OUT_F32, int NJ>
+static int launch_large_one(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, void* y,
+                        hipStream_t s) {
+  const BlobLayout L = blob_layout(N, K, 0, GS);
+  const char* bp = (const char*)blob;
+  constexpr int TM_ = 32 * NJ, SMEM = 2 * NBUF * (TM_ * 128 + W_BYTES + S_BYTES);
+  const int n_mt = (M + TM_ - 1) / TM_, n_nt = (N + TN_ - 1) / TN_;
+  const long n_blocks = (long)n_mt * n_nt;
+  const int per_xcd = (int)((n_blocks + 7) / 8);
+  // (idempotent: two threads racing here would both set the same attribute)
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)w4a16_large_kernel<GS, OUT_F32, NJ>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return hip_failed(e);
+    attr_done.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((w4a16_large_kernel<GS, OUT_F32, NJ>), dim3(per_xcd * 8), dim3(NT), SMEM, s, x,
+                     (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw), bias, M, N, K, y, n_mt, n_nt,
+                     per_xcd);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+// Token tiles per workgroup: the cheapest of 1, 2, 4 and 5, by rounds of workgroups over the CUs times a round's time
+// per step of 128 channels (0.45, 0.63, 1.15 and 1.40 us: a larger tile costs less per output, 0.45 against 0.28 per 32 x
+// 128, a smaller one leaves less of the last round empty).  N = 1152, K = 4608, us with 1 | 2 | 4 | 5 token tiles:
+// 512 tokens 23.1 | 27.3 | 41.5 | 50.3, 2048: 50.3 | 44.6 | 42.8 | 50.2, 4096: 78.6 | 68.2 | 84.3 | 55.4.
+static double tile_us(long M, long N, long K, int nj, int cus) {
+  const double step_us[6] = {0, 0.45, 0.63, 0, 1.15, 1.40};
+  const long wgs = ((M + 32 * nj - 1) / (32 * nj)) * ((N + TN_ - 1) / TN_);
+  return 4.0 + step_us[nj] * (double)((K + 127) / 128) * (double)((wgs + cus - 1) / cus);
 }
 
 template <int GS, bool OUT_F32>
-__global__ __launch_bounds__(NTHREADS, 2) void w4a16_gemm_kernel(
-    const uint16_t* __restrict__ x, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
-    const uint16_t* __restrict__ bias, int M, int N, int K, void* __restrict__ y, int n_mt, int n_nt, int per_xcd,
-    int sw_shift) {
-  // GS = channels per scale application; the stored weight groups hold GS << sw_shift channels
-  // (128-channel groups run as two 64-channel halves with the same scale: the same sum)
-  extern __shared__ __align__(16) unsigned char smem[];
-  static_assert(GS == 32 || GS == 64, "scale granularity");
-
-  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (logical >= n_mt * n_nt) return;
-  constexpr int GN = 4;
-  const int grp = logical / (GN * n_mt), in_grp = logical % (GN * n_mt);
-  const int gn = min(n_nt - grp * GN, GN);
-  const int nt = grp * GN + in_grp % gn, mt = in_grp / gn;
-  const int m0 = mt * TM, n0 = nt * TN;
-
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
-  const int wn = w & 1, wt = w >> 1;
-  const int h = l >> 5;
-  const int G = K / GS;
-  constexpr int GPS = BK16 / GS;   // groups per stage: 1 or 2
-  constexpr int KPG = GS / 16;     // 16-channel MFMA steps per group: 4 or 2
-  constexpr int SBUF = scale16_buf_bytes(GS), ZERO_OFF = zero16_off(GS);
-
-  if (t < 64) ((uint32_t*)(smem + ZERO_OFF))[t] = 0u;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
-
-  int rowA[2], rowB[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++) rowA[i] = wn * 64 + i * 32 + (l & 31);
-#pragma unroll
-  for (int j = 0; j < 2; j++) rowB[j] = TN + wt * 64 + j * 32 + (l & 31);
-  const int swz = ((l & 31) >> 1) & 7;
-
-  // ---- staging: thread t owns one 16-B packed weight chunk (row t/2, 32-channel half t%2) and four
-  // 16-B activation chunks (token rows t/8 + 32 i, chunk t%8) of every stage.
-  // Loads are unconditional: a chunk past the end of a row (K an odd multiple of 32) is re-read from
-  // inside the row and belongs to a group >= G, whose weight scale is forced to zero.
-  const int wrow = t >> 1, whalf = t & 1;
-  const int xrow = t >> 3, xchk = t & 7;
-  const int wbase = min(whalf * 16, K / 2 - 16), wlast = K / 2 - 16 - wbase;        // bytes
-  const int xbase = min(xchk * 8, K - 8), xlast = K - 8 - xbase;                    // bf16 elements
-  const uint8_t* gw = wq + (size_t)min(n0 + wrow, N - 1) * (K / 2) + wbase;
-  const uint16_t* gx[4];
-#pragma unroll
-  for (int i = 0; i < 4; i++) gx[i] = x + (size_t)min(m0 + xrow + 32 * i, M - 1) * K + xbase;
-  const uint16_t* gs = sw + min(n0 + (t & 127), N - 1);        // threads 0..127 stage the weight scales
-  const int nst = (K + BK16 - 1) / BK16;
-  uint4 rw;
-  i32x4 rx[4];                        // (a native vector type: an array of it stays in registers)
-  uint16_t rs[GPS];
-  auto gload = [&](int st) {
-    rw = *(const uint4*)(gw + min(st * (BK16 / 2), wlast));
-#pragma unroll
-    for (int i = 0; i < 4; i++) rx[i] = *(const i32x4*)(gx[i] + min(st * BK16, xlast));
-#pragma unroll
-    for (int jj = 0; jj < GPS; jj++) {
-      const int j = st * GPS + jj;
-      const uint16_t v = gs[(size_t)(min(j, G - 1) >> sw_shift) * N];
-      rs[jj] = (uint16_t)(v & (j < G ? 0xFFFFu : 0u));
-    }
-  };
-  auto sstore = [&](int buf) {
-    unsigned char* sb = smem + buf * STAGE16;
-    *(uint4*)(sb + tile_off_bytes(wrow, 4 * whalf + 0)) = nibbles_to_bf16(rw.x);
-    *(uint4*)(sb + tile_off_bytes(wrow, 4 * whalf + 1)) = nibbles_to_bf16(rw.y);
-    *(uint4*)(sb + tile_off_bytes(wrow, 4 * whalf + 2)) = nibbles_to_bf16(rw.z);
-    *(uint4*)(sb + tile_off_bytes(wrow, 4 * whalf + 3)) = nibbles_to_bf16(rw.w);
-#pragma unroll
-    for (int i = 0; i < 4; i++) *(i32x4*)(sb + tile_off_bytes(TN + xrow + 32 * i, xchk)) = rx[i];
-    if (t < TN) {
-      uint2* sdst = (uint2*)(smem + SCALE16_OFF + buf * SBUF);
-#pragma unroll
-      for (int jj = 0; jj < GPS; jj++) sdst[jj * TN + t] = make_uint2(rs[jj], 0u);
-    }
-  };
-
-  // per-lane LDS addresses: 16-channel step k (0..3) of a stage reads chunk 2k + h of the row
-  int adA[2][4], adB[2][4];
-#pragma unroll
-  for (int k = 0; k < 4; k++) {
-    const int off = ((2 * k + h) ^ swz) << 4;
-#pragma unroll
-    for (int i = 0; i < 2; i++) adA[i][k] = rowA[i] * 128 + off;
-#pragma unroll
-    for (int j = 0; j < 2; j++) adB[j][k] = rowB[j] * 128 + off;
+static int launch_large(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, void* y, int nj,
+                        hipStream_t s) {
+  switch (nj) {
+    case 1: return launch_large_one<GS, OUT_F32, 1>(x, blob, bias, M, N, K, y, s);
+    case 2: return launch_large_one<GS, OUT_F32, 2>(x, blob, bias, M, N, K, y, s);
+    case 4: return launch_large_one<GS, OUT_F32, 4>(x, blob, bias, M, N, K, y, s);
+    default: return launch_large_one<GS, OUT_F32, 5>(x, blob, bias, M, N, K, y, s);
   }
-  int soffA[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++) soffA[i] = h ? ZERO_OFF : SCALE16_OFF + rowA[i] * 8;
-  const int sstep = h ? 0 : TN * 8, sbufstep = h ? 0 : SBUF;
-  // token operand of the scale MFMA: 1 in k-slot 0 (lanes 0..31), zeros elsewhere
-  const f16x4 ones = f16x4{h ? (_Float16)0 : (_Float16)1, (_Float16)0, (_Float16)0, (_Float16)0};
-
-  gload(0);
-  sstore(0);
-  gload(min(1, nst - 1));
-  __syncthreads();
-  for (int st = 0; st < nst; st++) {
-    const int buf = st & 1;
-    const unsigned char* sb = smem + buf * STAGE16;
-    const unsigned char* ssb = smem + buf * sbufstep;
-    f32x16 I[2], P[2];
-    bf16x8 a[2][KPG], b[2][KPG];
-    f16x4 sa[2];
-    auto load_ops = [&](int jj) {
-#pragma unroll
-      for (int kk = 0; kk < KPG; kk++) {
-#pragma unroll
-        for (int i = 0; i < 2; i++) a[i][kk] = *(const bf16x8*)(sb + adA[i][jj * KPG + kk]);
-#pragma unroll
-        for (int j = 0; j < 2; j++) b[j][kk] = *(const bf16x8*)(sb + adB[j][jj * KPG + kk]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; i++) sa[i] = *(const f16x4*)(ssb + soffA[i] + jj * sstep);
-    };
-    auto issue = [&](int i, int j, int slot) {
-      f32x16 z, p;
-#pragma unroll
-      for (int v = 0; v < 16; v++) z[v] = p[v] = 0.0f;
-#pragma unroll
-      for (int kk = 0; kk < KPG; kk++) {
-        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][kk], b[j][kk], z, 0, 0, 0);
-        if (kk == 0) P[slot] = __builtin_amdgcn_mfma_f32_32x32x8f16(sa[i], ones, p, 0, 0, 0);
-      }
-      I[slot] = z;
-    };
-    auto sweep = [&](int i, int j, int slot) {
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = fmaf(I[slot][v], P[slot][v], acc[i][j][v]);
-      asm volatile("" : "+v"(acc[i][j]));
-    };
-    load_ops(0);
-    issue(0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int jj = 0; jj < GPS; jj++) {
-      issue(0, 1, 1);
-      sweep(0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      issue(1, 0, 0);
-      sweep(0, 1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      issue(1, 1, 1);
-      sweep(1, 0, 0);
-      if (jj == GPS - 1) {                      // the next stage: registers -> LDS, then reload for stage st + 2
-        sstore(buf ^ 1);
-        gload(min(st + 2, nst - 1));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("" ::: "memory");
-      if (jj + 1 < GPS) {
-        load_ops(jj + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        issue(0, 0, 0);
-      }
-      sweep(1, 1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
-  }
-
-  gemm_tail<OUT_F32>(acc, smem, nullptr, nullptr, bias, y, M, N, 0, m0, n0, rowA, rowB);
 }
 
+}  // namespace w16
 
 // ---- few tokens (M <= 32): every weight is used once, so the kernel is a stream over the packed weights
 // (HBM-bound).  One workgroup (8 waves) = 32 output channels.  K is walked in chunks of KC channels (1024
@@ -421,29 +469,6 @@ static int launch_few16(const uint16_t* x, const void* blob, const uint16_t* bia
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
-template <int GS, bool OUT_F32>
-static int launch_one16(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
-                        hipStream_t s) {
-  const BlobLayout L = blob_layout(N, K, 0, g);
-  const int sw_shift = g == 2 * GS ? 1 : 0;
-  const char* bp = (const char*)blob;
-  const int n_mt = (M + TM - 1) / TM, n_nt = (N + TN - 1) / TN;
-  const long n_blocks = (long)n_mt * n_nt;
-  const int per_xcd = (int)((n_blocks + 7) / 8);
-  static std::atomic<bool> attr_done{false};
-  if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)w4a16_gemm_kernel<GS, OUT_F32>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem16_bytes(GS));
-    if (e != hipSuccess) return hip_failed(e);
-    attr_done.store(true, std::memory_order_release);
-  }
-  hipLaunchKernelGGL((w4a16_gemm_kernel<GS, OUT_F32>), dim3(per_xcd * 8), dim3(NTHREADS), smem16_bytes(GS), s, x,
-                     (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw), bias, M, N, K, y, n_mt, n_nt,
-                     per_xcd, sw_shift);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
-}
-
 int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
                       int y_dtype, hipStream_t s) {
   const int gs = g == 32 ? 32 : 64;
@@ -467,30 +492,32 @@ int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias,
   const bool force_tile = force && !strcmp(force, "tile");
   // few tokens: the weight stream, not the matrix pipe, is the bound
   if (M <= 32) return few(x, y, M);
-  // A few hundred tokens leave the 128 x 128 tiling with less than one round of workgroups, each walking
-  // all of K: there it is faster to stream the weights once per slice of 32 tokens.  Rough costs in
-  // microseconds from measurements on the FLUX-shaped layers: a slice streams N K / 2 bytes at about
-  // 1.2 TB/s plus 5 us; a round of tiles takes 1.23 us per 64-channel stage.
-  {
-    const int slices = (M + 31) / 32;
-    const long tiles = (long)((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-    const double t_few = slices * ((double)N * K / 2 / 1.2e6 + 5.0);
-    const double t_tiles = (K / 64.0) * 1.23 * (double)((tiles + 511) / 512);
-    if (!force_tile && slices <= 16 && t_few < t_tiles) {
-      const size_t ybytes = y_dtype ? 4 : 2;
-      for (int i = 0; i < slices; i++) {
-        const int st = few(x + (size_t)i * 32 * K, (char*)y + (size_t)i * 32 * N * ybytes, min(32, M - 32 * i));
-        if (st) return st;
-      }
-      return DIROTQ_OK;
-    }
+  int dev = 0, cus = 256;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_failed(e);
+  int nj = 1;
+  for (int c : {2, 4, 5})
+    if (w16::tile_us(M, N, K, c, cus) < w16::tile_us(M, N, K, nj, cus)) nj = c;
+  // 33 to 64 tokens: two launches of the few-token kernel are faster where K is long (the tiles walk it with one workgroup
+  // per 128 channels, the stream with one per 32) or the second one is small.  A launch takes about 3.2 us plus 0.21 us per
+  // 128 channels and round of workgroups, up to 8 tokens 0.14; the second one starts 0.7 us earlier.  Two launches | tiles,
+  // us: 1152 x 1152, 48 tokens 9.8 | 8.8; 1152 x 4608, 33 tokens 18.0 | 21.3, 48: 20.7 | 21.4; 3072 x 12288 49.7 | 51.0;
+  // 12288 x 3072 29.4 | 16.1.
+  const double rounds = (double)(((long)(N + 31) / 32 + cus - 1) / cus), steps = (K + 127) / 128;
+  const double t_few = 5.7 + (0.21 + (M <= 40 ? 0.14 : 0.21)) * steps * rounds;
+  if (!force_tile && M <= 64 && t_few < w16::tile_us(M, N, K, nj, cus)) {
+    const int st = few(x, y, 32);
+    return st ? st : few(x + (size_t)32 * K, (char*)y + (size_t)32 * N * (y_dtype ? 4 : 2), M - 32);
   }
-  if (g == 32)
-    return y_dtype ? launch_one16<32, true>(x, blob, bias, M, N, K, g, y, s)
-                   : launch_one16<32, false>(x, blob, bias, M, N, K, g, y, s);
-  if (g == 64 || g == 128)
-    return y_dtype ? launch_one16<64, true>(x, blob, bias, M, N, K, g, y, s)
-                   : launch_one16<64, false>(x, blob, bias, M, N, K, g, y, s);
+  switch (g) {
+    case 32: return y_dtype ? w16::launch_large<32, true>(x, blob, bias, M, N, K, y, nj, s)
+                            : w16::launch_large<32, false>(x, blob, bias, M, N, K, y, nj, s);
+    case 64: return y_dtype ? w16::launch_large<64, true>(x, blob, bias, M, N, K, y, nj, s)
+                            : w16::launch_large<64, false>(x, blob, bias, M, N, K, y, nj, s);
+    case 128: return y_dtype ? w16::launch_large<128, true>(x, blob, bias, M, N, K, y, nj, s)
+                             : w16::launch_large<128, false>(x, blob, bias, M, N, K, y, nj, s);
+  }
   return DIROTQ_ERR_UNSUPPORTED;
 }
 

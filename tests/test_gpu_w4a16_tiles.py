@@ -1,0 +1,44 @@
+"""The tile schedules of the W4A16 GEMM (1, 2, 4 and 5 token tiles per workgroup, chosen by size) against a float64 product
+of the same numbers: cut tiles, an odd number of output channels, one stage, odd numbers of stages, a last stage of half
+the channels, groups of half a stage and of two, an infinite activation in the last group."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_16732_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,g", [
+    (33, 1, 32, 32), (65, 130, 96, 32), (40, 33, 64, 64), (70, 257, 128, 128),                     # 1 token tile
+    (1030, 1153, 160, 32), (1030, 1160, 192, 64), (1030, 1153, 384, 128),                          # 2
+    (2050, 1153, 160, 32), (2050, 1160, 320, 64), (2050, 1153, 128, 128),                          # 4
+    (4100, 1025, 96, 32), (4100, 1032, 192, 64), (4100, 1025, 256, 128),                           # 5
+])
+def test_tiles_match_float64(M, N, K, g, monkeypatch):
+    """Each output is a sum of K fp32 products and G scaled ones: K + G roundings of at most 2^-24 of the sum of the
+    magnitudes; the bf16 output is the rounded fp32 one."""
+    print(f"[case] w4a16 tiles M={M} N={N} K={K} g={g}", flush=True)
+    monkeypatch.setenv("DIROTQ_W4A16_KERNEL", "tile")
+    rng = np.random.default_rng([M, N, K, g])
+    G = K // g
+    x = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).bfloat16()
+    x[1, K - 1] = float("inf")
+    qw = rng.integers(-7, 8, size=(N, K)).astype(np.int8)
+    sw = rng.lognormal(-4, 0.7, size=(N, G)).astype(np.float16)
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).bfloat16()
+    blob = B.import_weights(None, torch.from_numpy(qw).cuda(), torch.from_numpy(sw).cuda(), N, K, 0, g)
+    w = torch.from_numpy(qw.astype(np.float64) * np.repeat(sw.astype(np.float64), g, axis=1))
+    want = x.double() @ w.T + bias.double()
+    fin = torch.arange(M) != 1
+    bound = (K + G + 1) * 2.0 ** -24 * (x[fin].double().abs() @ w.T.abs() + bias.double().abs())
+    args = (x.cuda(), blob, N, g)
+    yf = B.w4a16_gemm(*args, bias=bias.cuda(), out_dtype=torch.float32)
+    yb = B.w4a16_gemm(*args, bias=bias.cuda(), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    yf, yb = yf.cpu(), yb.cpu()
+    assert bool(((yf[fin].double() - want[fin]).abs() <= bound).all())
+    inf_row = torch.from_numpy(qw[:, K - 1].astype(np.float32)) * float("inf")
+    assert torch.equal(yf[1].nan_to_num(7.0), inf_row.nan_to_num(7.0))
+    assert torch.equal(yb.nan_to_num(7.0), yf.bfloat16().nan_to_num(7.0))
