@@ -12,13 +12,11 @@
 #include <cstdlib>
 #include <cstring>
 
-#include "dirotq_internal.h"
+#include "gemm_halves.h"
 
 namespace dirotq {
 
-// ---- large: 128 n x 32 NJ tokens per workgroup, eight waves: four of 32 n, twice, for the even and the odd stages of
-// 64 channels (so that two waves per SIMD hide each other's latencies without decoding a weight twice; their sums meet in
-// LDS at the end) ------------------------------------------------------------------------------------------------------
+// ---- tiles (the layout of gemm_halves.h) ------------------------------------------------------------------------------
 // All staging is copies global -> LDS (activations, packed codes, scales; a ring of three stages for each half, two in
 // flight, one barrier per stage), so the waves issue nothing but operand reads, the decode, MFMAs and the scale sweep.
 // A wave decodes the codes of its own 32 rows in registers, for its NJ token tiles: nibble -> fp8 subnormal byte -> bf16
@@ -32,8 +30,7 @@ namespace dirotq {
 // TFLOP/s), 512 tokens 88 -> 23; 4096 x 3072 -> 12288 444 -> 370; 256 x 3072 -> 3072 52 -> 17.
 namespace w16 {
 
-constexpr int TN_ = 128, NT = 512, NBUF = 3;
-constexpr int W_BYTES = TN_ * 32, S_BYTES = 4 * 256;     // of a stage: rows of 64 channels; scales per wave
+using namespace halves;
 
 // 8 sign-magnitude nibbles of a dword -> 8 bf16 numbers in channel order
 __device__ __forceinline__ bf16x8 decode(uint32_t p) {
@@ -53,14 +50,10 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
     const uint16_t* __restrict__ bias, int M, int N, int K, void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int GPS = GS == 32 ? 2 : 1;                  // groups per stage
-  constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 128, SLOT = X_BYTES + W_BYTES + S_BYTES;
+  constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 128, SLOT = slot_bytes(128, NJ);
   constexpr int COPIES = NJ + 2;                         // per wave and stage: activations, codes, scales
-  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (logical >= n_mt * n_nt) return;
-  constexpr int GN = 4;                                  // output tiles swept per token tile (operands stay in the L2)
-  const int grp = logical / (GN * n_mt), in_grp = logical % (GN * n_mt);
-  const int gn = min(n_nt - grp * GN, GN);
-  const int n0 = (grp * GN + in_grp % gn) * TN_, m0 = in_grp / gn * TM_;
+  int m0, n0;
+  if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
   const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), w = wave & 3, kh = wave >> 2;
   const int G = K / GS, nst = (K + 63) / 64, steps = (nst + 1) / 2;
@@ -68,7 +61,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
 
   // ---- copies of a stage by this wave: token rows 8 NJ w .. 8 NJ w + 8 NJ - 1 (8 rows per copy; 16-byte piece p of row `row` at
   // slot p ^ ((row >> 1) & 7)), the packed codes of its 32 weight rows (half p of row `row` at p ^ ((row >> 3) & 1)), and
-  // their scales (a window of dwords that begins at the dword of the first one)
+  // their scales
   uint32_t vo_x[NJ];
 #pragma unroll
   for (int i = 0; i < NJ; i++) {
@@ -80,7 +73,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   const int nw = min(n0 + 32 * w, N - 1);                // first channel of the wave (past the edge: nothing is stored)
   const unsigned char *xb = (const unsigned char*)(x + (size_t)m0 * K), *wb = wq + (size_t)n0 * (K / 2);
   const uint32_t ring = lds_address(smem) + kh * (NBUF * SLOT);
-  const size_t last_sw = ((size_t)G * N * 2 - 1) & ~(size_t)3;
+  const ScaleRows scales = {(const unsigned char*)sw, ((size_t)G * N * 2 - 1) & ~(size_t)3, N, nw};
   auto group = [&](int s, int jj) { return min(GS == 32 ? 2 * s + jj : GS == 128 ? s >> 1 : s, G - 1); };
   auto issue = [&](int s, int slot) {                    // (past the last stage: that one again, unused)
     s = min(s, nst - 1);
@@ -92,11 +85,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
       copy_to_lds(at + (8 * NJ * w + 8 * i) * 128, vo_x[i] - (cut && piece >= 4 ? 64u : 0u), xb + (size_t)s * 128);
     }
     copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
-    const size_t e0 = ((size_t)group(s, 0) * N + nw) * 2 & ~(size_t)3;
-    uint32_t vs = min(GS == 32 ? c : l, 19) * 4;
-    if (GS == 32 && h) vs += (uint32_t)((((size_t)group(s, 1) * N + nw) * 2 & ~(size_t)3) - e0);
-    vs = min(vs, (uint32_t)min(last_sw - e0, (size_t)0x7ffffffc));   // (nothing past the dword of the last scale)
-    copy4_to_lds(at + X_BYTES + W_BYTES + w * 256, vs, (const unsigned char*)sw + e0);
+    scales.copy<GS == 32>(at + X_BYTES + W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
   };
 
   f32x16 acc[NJ];
@@ -127,11 +116,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
     const unsigned char* sc_p = sp + X_BYTES + W_BYTES + w * 256;
     float sc[GPS];
 #pragma unroll
-    for (int jj = 0; jj < GPS; jj++) {
-      const int odd = (int)(((size_t)group(s, jj) * N + nw) & 1);
-      const uint16_t b = *(const uint16_t*)(sc_p + jj * 128 + (odd + c) * 2);
-      sc[jj] = f16_bits_to_f32(b);
-    }
+    for (int jj = 0; jj < GPS; jj++) sc[jj] = scales.read(sc_p + jj * 128, group(s, jj), c);
     const unsigned char* wp = sp + X_BYTES + w * 1024 + c * 32;
     bf16x8 b[4];
     if constexpr (GS == 32) {
@@ -182,50 +167,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   }
   wait_copies<0>();                                      // (nothing may land in LDS after the workgroup has ended)
 
-  // ---- the two halves exchange: token tile j is finished by half j & 1
-  __syncthreads();
-  float4* xch = (float4*)smem;
-#pragma unroll
-  for (int j = 0; j < NJ; j++)
-    if ((j & 1) != kh)
-#pragma unroll
-      for (int q = 0; q < 4; q++)
-        xch[((j * 4 + w) * 4 + q) * 64 + l] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
-  __syncthreads();
-  // two channels of a token in one dword: neighbouring lanes exchange, the even one stores token v, the odd one v + 1
-  const int n = n0 + 32 * w + c;
-  const float bn = bias && n < N ? bf16_bits_to_f32(bias[n]) : 0.0f;
-  const bool pairs = !OUT_F32 && (N & 1) == 0, odd = l & 1;
-#pragma unroll
-  for (int j = 0; j < NJ; j++) {
-    if ((j & 1) != kh) continue;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const float4 o = xch[((j * 4 + w) * 4 + q) * 64 + l];
-      acc[j][4 * q] += o.x;
-      acc[j][4 * q + 1] += o.y;
-      acc[j][4 * q + 2] += o.z;
-      acc[j][4 * q + 3] += o.w;
-    }
-#pragma unroll
-    for (int v = 0; v < 16; v += 2) {
-      const int m = m0 + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-      const float y0 = bias ? acc[j][v] + bn : acc[j][v], y1 = bias ? acc[j][v + 1] + bn : acc[j][v + 1];
-      if (pairs) {
-        const float got = __shfl_xor(odd ? y0 : y1, 1);
-        const uint32_t d = f32x2_to_bf16x2_bits(odd ? got : y0, odd ? y1 : got);
-        if (n < N && m + odd < M) *(uint32_t*)((uint16_t*)y + (size_t)(m + odd) * N + (n - odd)) = d;
-      } else if (n < N) {
-#pragma unroll
-        for (int e = 0; e < 2; e++)
-          if (m + e < M) {
-            const float o = e ? y1 : y0;
-            if (OUT_F32) ((float*)y)[(size_t)(m + e) * N + n] = o;
-            else ((uint16_t*)y)[(size_t)(m + e) * N + n] = f32_to_bf16_bits(o);
-          }
-      }
-    }
-  }
+  finish<OUT_F32, NJ>(acc, smem, kh, w, m0, n0, bias, M, N, y);
 }
 
 template <int GS, bool OUT_F32, int NJ>
@@ -233,7 +175,7 @@ static int launch_large_one(const uint16_t* x, const void* blob, const uint16_t*
                         hipStream_t s) {
   const BlobLayout L = blob_layout(N, K, 0, GS);
   const char* bp = (const char*)blob;
-  constexpr int TM_ = 32 * NJ, SMEM = 2 * NBUF * (TM_ * 128 + W_BYTES + S_BYTES);
+  constexpr int TM_ = 32 * NJ, SMEM = smem_bytes(128, NJ);
   const int n_mt = (M + TM_ - 1) / TM_, n_nt = (N + TN_ - 1) / TN_;
   const long n_blocks = (long)n_mt * n_nt;
   const int per_xcd = (int)((n_blocks + 7) / 8);

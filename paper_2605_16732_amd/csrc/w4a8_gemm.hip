@@ -18,12 +18,13 @@
 // same 16 bytes in both blocks.  Everything downstream is the W4A4 kernel: scale product by an
 // fp16 MFMA (s_w[n,j] x s_x[m]), one fma per accumulator and group, 16-bit branch, store.
 //
-// Stage = 64 channels: weights [128 rows][64 B], activations [128 rows][64 B a-plane | 64 B
+// Its stage = 64 channels: weights [128 rows][64 B], activations [128 rows][64 B a-plane | 64 B
 // b-plane]; two stages in LDS; global loads run one stage ahead through registers.
 #include <algorithm>
 #include <atomic>
 
 #include "gemm_tail.h"
+#include "gemm_halves.h"
 
 namespace dirotq {
 
@@ -524,10 +525,239 @@ static int launch_few8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
+// ---- GEMM, medium (the layout of gemm_halves.h) ------------------------------------------------------
+// Between the few-token kernel and several rounds of the 128 x 128 tiles, whose workgroups keep one stage of loads in
+// flight and leave a SIMD one wave: 128 channels x 32, 64 or 128 tokens, everything staged by copies global -> LDS, two
+// stages ahead, a barrier per 128 channels of K.  Each wave splits the activation codes into their planes in registers (32
+// operations per token tile and stage, next to 128 cycles of MFMA and the scale sweep's 16 fma: 240 cycles, plus 700 per
+// step for the weight decode, the copies and the barrier): four waves repeat that split, which is why the 128 x 128 tiles,
+// which do it once in LDS, stay ahead where they fill whole rounds.
+// us, before -> this (r = 128, g = 64): N = K = 3072: 512 tokens 39.5 -> 23.7, 1024 49.6 -> 37.6, 2048 65.0 -> 56.4;
+// N = 12288: 128 tokens 39.8 -> 23.4; K = 12288, N = 3072: 512 tokens 112 -> 74, 1024 173 -> 120; N = 3456, K = 1152: 512
+// tokens 20.1 -> 12.6.
+namespace w8 {
+using namespace halves;
+
+template <int GS, bool OUT_F32, int NJ>
+__global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
+    const uint16_t* __restrict__ xh, const uint8_t* __restrict__ x8, const uint16_t* __restrict__ sx,
+    const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
+    const uint16_t* __restrict__ bias, int M, int N, int K, int r, void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int GPS = GS == 32 ? 2 : 1;                  // groups per stage
+  constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 64, SLOT = slot_bytes(64, NJ);
+  constexpr int XC = (NJ + 1) / 2, COPIES = XC + 2;      // per wave and stage: activations; codes, scales
+  int m0, n0;
+  if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
+  const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), w = wave & 3, kh = wave >> 2;
+  const int KL = K - r, G = KL / GS, nst = (KL + 63) / 64, steps = (nst + 1) / 2;
+  const bool short_last = GS == 32 && (KL & 63) != 0;    // the last stage holds one 32-channel group
+
+  // ---- copies of a stage by this wave: 16 token rows each (copy w + 4 i; past the last one that one again; 16-byte piece
+  // p of row `row` at slot p ^ ((row >> 2) & 3)), the packed codes of its 32 weight rows (half p of row `row` at
+  // p ^ ((row >> 3) & 1)), their scales
+  uint32_t vo_x[XC], at_x[XC];
+#pragma unroll
+  for (int i = 0; i < XC; i++) {
+    const int k = min(w + 4 * i, 2 * NJ - 1), row = 16 * k + (l >> 2), piece = (l & 3) ^ ((row >> 2) & 3);
+    at_x[i] = k * 1024;
+    vo_x[i] = (uint32_t)(min(m0 + row, M - 1) - m0) * (uint32_t)KL + piece * 16;
+  }
+  const int x_piece = (l & 3) ^ ((l >> 4) & 3);          // ((row >> 2) & 3 of any copy's row)
+  const int w_row = l >> 1, w_half = (l & 1) ^ ((w_row >> 3) & 1);
+  const uint32_t vo_w = (uint32_t)(min(n0 + 32 * w + w_row, N - 1) - n0) * (uint32_t)(KL / 2) + w_half * 16;
+  const int nw = min(n0 + 32 * w, N - 1);                // first channel of the wave (past the edge: nothing is stored)
+  const unsigned char *xb = x8 + (size_t)m0 * KL, *wb = wq + (size_t)n0 * (KL / 2);
+  const uint32_t ring = lds_address(smem) + kh * (NBUF * SLOT);
+  const ScaleRows scales = {(const unsigned char*)sw, ((size_t)G * N * 2 - 1) & ~(size_t)3, N, nw};
+  auto group = [&](int s, int jj) { return min(GS == 32 ? 2 * s + jj : GS == 128 ? s >> 1 : s, G - 1); };
+  auto issue = [&](int s, int slot) {                    // (past the last stage: that one again, unused)
+    s = min(s, nst - 1);
+    const uint32_t at = ring + slot;
+    const bool cut = short_last && s == nst - 1;         // (the missing upper half: the lower one again)
+#pragma unroll
+    for (int i = 0; i < XC; i++)
+      copy_to_lds(at + at_x[i], vo_x[i] - (cut && x_piece >= 2 ? 32u : 0u), xb + (size_t)s * 64);
+    copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
+    scales.copy<GS == 32>(at + X_BYTES + halves::W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
+  };
+
+  f32x16 acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[j][v] = 0.0f;
+  if (nst) {
+    const int swz = (c >> 3) & 1;                        // (tile bases are multiples of 32 rows)
+    int ln_x[2];                                         // 32-channel block p: even channels (h = 0), odd ones (h = 1)
+#pragma unroll
+    for (int p = 0; p < 2; p++) ln_x[p] = c * 64 + (((2 * p + h) ^ ((c >> 2) & 3)) << 4);
+    const int sc_x = h ? 127 + 9 : 127 + 13, sc_w = 127 + 9;
+    issue(kh, 0);
+    issue(2 + kh, SLOT);
+    int cur = 0;
+    for (int step = 0; step < steps; step++) {
+      const int s = 2 * step + kh;
+      wait_copies<COPIES>();                             // this wave's copies of stage s have landed, and (barrier) all
+      __builtin_amdgcn_s_barrier();                      // waves'; stage s - 2 has been read by all of them
+      asm volatile("" ::: "memory");
+      int fill = cur + 2 * SLOT;
+      if (fill >= 3 * SLOT) fill -= 3 * SLOT;
+      issue(s + 4, fill);
+      if (s >= nst) break;                               // (an odd number of stages: the other half has the last one)
+      const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
+      const unsigned char* sc_p = sp + X_BYTES + halves::W_BYTES + w * 256;
+      float sc[GPS];
+#pragma unroll
+      for (int jj = 0; jj < GPS; jj++) {
+        sc[jj] = scales.read(sc_p + jj * 128, group(s, jj), c);
+        if (GS == 32 && 2 * s + jj >= G) sc[jj] = 0.0f;  // (codes are whole numbers: 0 x their sum is 0)
+      }
+      const unsigned char* wp = sp + X_BYTES + w * 1024 + c * 32;
+      i32x8_t b[2];
+#pragma unroll
+      for (int p = 0; p < 2; p++) {                      // lane half 0: even channels, 1: odd ones
+        const uint4 u = *(const uint4*)(wp + ((p ^ swz) << 4));
+        const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const uint32_t v = d[e] >> (4 * h);
+          b[p][e] = b[p][e + 4] = (int)((v & 0x07070707u) | ((v & 0x08080808u) << 4));
+        }
+      }
+      uint4 a[2][2];
+#pragma unroll
+      for (int p = 0; p < 2; p++) a[0][p] = *(const uint4*)(sp + ln_x[p]);
+      f32x16 I[2][GPS];
+#pragma unroll
+      for (int j = 0; j <= NJ; j++) {
+        if (j < NJ - 1)
+#pragma unroll
+          for (int p = 0; p < 2; p++) a[(j + 1) & 1][p] = *(const uint4*)(sp + ln_x[p] + (j + 1) * (32 * 64));
+        if (j < NJ) {
+          f32x16 z;
+#pragma unroll
+          for (int p = 0; p < 2; p++) {
+            if (p == 0 || GPS == 2)
+#pragma unroll
+              for (int v = 0; v < 16; v++) z[v] = 0.0f;
+            const uint32_t d[4] = {a[j & 1][p].x, a[j & 1][p].y, a[j & 1][p].z, a[j & 1][p].w};
+            i32x8_t xv;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              uint32_t pa, pb;
+              a8_planes(d[e], pa, pb);
+              xv[e] = (int)pa;
+              xv[e + 4] = (int)pb;
+            }
+            z = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(xv, b[p], z, 0, 0, 0, sc_x, 0, sc_w);
+            I[j & 1][GPS == 2 ? p : 0] = z;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (j > 0) {
+#pragma unroll
+          for (int jj = 0; jj < GPS; jj++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[j - 1][v] = fmaf(I[(j - 1) & 1][jj][v], sc[jj], acc[j - 1][v]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      cur = cur + SLOT >= 3 * SLOT ? 0 : cur + SLOT;
+    }
+    wait_copies<0>();                                    // (nothing may land in LDS after it has another use)
+  }
+  // ---- 16-bit branch: pieces of 64 channels through LDS ([tokens | channels][128 B], 16-byte piece p of row `row` at slot
+  // p ^ ((row >> 1) & 7); two buffers in the ring's place), 32 channels for each half of the waves
+  constexpr int ROWS = TM_ + TN_, PIECE = ROWS * 128;
+  static_assert(2 * PIECE <= smem_bytes(64, NJ), "LDS");
+  const int pieces = (r + 63) / 64;
+  auto issue16 = [&](int i) {
+    const int k0 = i * 64;
+    for (int k = wave; k < ROWS / 8; k += 8) {
+      const int row = 8 * k + (l >> 3), piece = (l & 7) ^ ((row >> 1) & 7);
+      const bool tok = 8 * k < TM_;                      // (wave-uniform: TM_ is a multiple of 8)
+      const int row_g = tok ? min(m0 + row, M - 1) - m0 : min(n0 + row - TM_, N - 1) - n0;
+      const uint32_t vo = (uint32_t)row_g * (uint32_t)(2 * r) + (piece - (piece >= 4 && k0 + 32 >= r ? 4 : 0)) * 16;
+      copy_to_lds(lds_address(smem) + (i & 1) * PIECE + k * 1024, vo, (tok ? xh + (size_t)m0 * r : wh + (size_t)n0 * r) + k0);
+    }
+  };
+  __syncthreads();
+  if (pieces > 0) issue16(0);
+  if (pieces > 1) issue16(1);
+  if (nst) {                                             // (meanwhile) the token's scale
+#pragma unroll
+    for (int j = 0; j < NJ; j++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const int m = m0 + j * 32 + 8 * q + 4 * h;
+        ushort4 u;
+        if (m + 3 < M) u = *(const ushort4*)(sx + m);
+        else u = make_ushort4(sx[min(m, M - 1)], sx[min(m + 1, M - 1)], sx[min(m + 2, M - 1)], sx[M - 1]);
+        acc[j][4 * q] *= f16_bits_to_f32(u.x);
+        acc[j][4 * q + 1] *= f16_bits_to_f32(u.y);
+        acc[j][4 * q + 2] *= f16_bits_to_f32(u.z);
+        acc[j][4 * q + 3] *= f16_bits_to_f32(u.w);
+      }
+  }
+  for (int i = 0; i < pieces; i++) {
+    wait_copies<0>();
+    __syncthreads();
+    if (i > 0 && i + 1 < pieces) issue16(i + 1);         // (into the buffer of piece i - 1, which all waves have read)
+    if (i * 64 + 32 * kh >= r) continue;
+    const unsigned char* sp = smem + (i & 1) * PIECE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) {
+      const int at = c * 128 + (((4 * kh + 2 * ks + h) ^ ((c >> 1) & 7)) << 4);
+      const bf16x8 bw = *(const bf16x8*)(sp + at + (TM_ + 32 * w) * 128);
+#pragma unroll
+      for (int j = 0; j < NJ; j++)
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(sp + at + j * 32 * 128), bw, acc[j], 0, 0, 0);
+    }
+  }
+  finish<OUT_F32, NJ>(acc, smem, kh, w, m0, n0, bias, M, N, y);
+}
+
+template <int GS, bool OUT_F32, int NJ>
+static int launch_medium(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias,
+                       int M, int N, int K, int r, void* y, hipStream_t s) {
+  const BlobLayout L = blob_layout(N, K, r, GS);
+  const char* bp = (const char*)blob;
+  constexpr int TM_ = 32 * NJ, SMEM = smem_bytes(64, NJ);
+  const int n_mt = (M + TM_ - 1) / TM_, n_nt = (N + TN_ - 1) / TN_;
+  const int per_xcd = (int)(((long)n_mt * n_nt + 7) / 8);
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)w4a8_medium_kernel<GS, OUT_F32, NJ>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return hip_failed(e);
+    attr_done.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((w4a8_medium_kernel<GS, OUT_F32, NJ>), dim3(per_xcd * 8), dim3(NT), SMEM, s, xh, x8, sx,
+                     (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes),
+                     (const uint16_t*)(bp + L.off_sw), bias, M, N, K, r, y, n_mt, n_nt, per_xcd);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+}  // namespace w8
+
 // Which kernel: costs in microseconds fitted to measurements at K = 1152 ... 12288, N = 1152 ... 12288 (r = 128, g = 64).
 // The split-K kernel: 3.4 + K/2500 and, per 32 x 32 outputs, 0.017 (K = 1152) or 0.0075 K/1000 (longer K); two token
-// tiles per workgroup once that many workgroups walk a long K (K = 12288, M = 128: 38.6 against 46.9 us).  The 128 x 128
-// tiles: 4 + 13 K/1000 while there is at most one per CU, half as much again up to two.
+// tiles per workgroup once that many workgroups walk a long K (K = 12288, M = 128: 38.6 against 46.9 us).
+// The medium kernel with nj token tiles: a first round of one workgroup per CU, further ones that overlap it (nj = 1, 2:
+// two workgroups fit a CU), per step of 128 channels.  N = K = 3072, us with 1 | 2 | 4: 512 tokens 28.3 | 23.7 | 35.2,
+// 1024: 39.7 | 38.6 | 37.6, 2048: 74.3 | 56.4 | 71.2, 4096: 136 | 109 | 107 (128 x 128 tiles: 39.5, 49.6, 65.0, 109).
+// The 128 x 128 tiles: two workgroups per CU in a round, 4 + 13.6 K/1000 if it has at most one each, 7.2 + 18 K/1000 beyond.
+static double medium_us(long M, long N, long steps, int nj, int cus) {
+  const long wgs = ((M + 32 * nj - 1) / (32 * nj)) * ((N + 127) / 128);
+  const double more = (double)((wgs + cus - 1) / cus - 1), st = (double)steps;
+  if (nj == 1) return 5.4 + 0.55 * st + more * (1.0 + 0.44 * st);
+  if (nj == 2) return 6.2 + 0.70 * st + more * (2.5 + 0.63 * st);
+  return (1.0 + more) * (8.0 + 1.17 * st);
+}
+
 template <int GS, bool OUT_F32>
 static int launch_case8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias,
                         int M, int N, int K, int r, int g, void* y, hipStream_t s) {
@@ -538,11 +768,26 @@ static int launch_case8(const uint16_t* xh, const uint8_t* x8, const uint16_t* s
   const double k = K / 1000.0;
   const long t32 = (long)((M + 31) / 32) * ((N + 31) / 32), t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
   const double few = 3.4 + 0.4 * k + (double)t32 * std::max(0.017, 0.0075 * k);
-  const double tiled = (4.0 + 13.0 * k) * (t128 <= cus ? 1.0 : 1.5);
+  const double half = 4.0 + 13.6 * k, full = 7.2 + 18.0 * k;
+  const long rest = t128 % (2L * cus);
+  double tiled = (double)(t128 / (2L * cus)) * full + (rest == 0 ? 0.0 : rest <= cus ? half : full);
+  // (the medium kernel's 16-bit branch has two pieces of 64 channels in flight at most: beyond that a piece counts as a step)
+  const long steps = (K - r + 127) / 128 + (r > 128 ? (r - 65) / 64 : 0);
+  int nj = 0;                                            // 0: the 128 x 128 tiles
+  for (int c : {1, 2, 4}) {
+    const double t = medium_us(M, N, steps, c, cus);
+    if (t < tiled) {
+      tiled = t;
+      nj = c;
+    }
+  }
   if (t128 <= 2L * cus && few < tiled) {
     return K >= 8192 && M > 32 && t32 >= 256 ? launch_few8<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s)
                                              : launch_few8<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   }
+  if (nj == 1) return w8::launch_medium<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
+  if (nj == 2) return w8::launch_medium<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
+  if (nj == 4) return w8::launch_medium<GS, OUT_F32, 4>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   constexpr int TS = GS == 32 ? 32 : 64;                 // (the tiled kernel runs groups of 128 as two halves)
   return launch_one8<TS, OUT_F32>(xh, x8, sx, blob, bias, M, N, K, r, g, y, s);
 }
