@@ -121,7 +121,7 @@ __device__ __forceinline__ void rq_epilogue32(const f32x16 (&acc)[4][WT], int vb
     return;
   }
   const size_t xl_ld = (size_t)KL / 2;
-  const int gi_tiles = g >> 5;                              // 32-channel MFMA tiles per group: 1, 2, 4
+  const int gi_tiles = g >> 5, g_log2 = 31 - __builtin_clz(g);   // 32-channel MFMA tiles per group: 1, 2, 4
 #pragma unroll
   for (int j = 0; j < WT; j++) {
     const int m = tok_base + j * 32 + (l & 31);
@@ -169,19 +169,18 @@ __device__ __forceinline__ void rq_epilogue32(const f32x16 (&acc)[4][WT], int vb
         sf = group_scale(tmax[i], sbits);
       }
       const float inv = group_inv(sf);
-      if (valid && h == 0 && (i % gi_tiles) == 0) {
-        sx[(size_t)(cl / g) * sx_ld + m] = sbits;
-        if constexpr (ASYM) zx[(size_t)(cl / g) * sx_ld + m] = zbits;
+      if (valid && h == 0 && (i & (gi_tiles - 1)) == 0) {
+        sx[(size_t)(cl >> g_log2) * sx_ld + m] = sbits;
+        if constexpr (ASYM) zx[(size_t)(cl >> g_log2) * sx_ld + m] = zbits;
       }
-      auto nib = [&](float v) { return ASYM ? quant_nibble_asym(v, zf, inv) : quant_nibble(v, inv); };
-      // this lane's 16 codes: quad q covers channels cl + 8q + 4h .. +3 -> one 16-bit piece
-      uint32_t piece[4];
+      // this lane's 16 codes: quad q covers channels cl + 8q + 4h .. +3 -> one 16-bit piece, two pieces a dword
+      float v0[8], v1[8];
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        piece[q] = nib(acc[i][j][4 * q]) | nib(acc[i][j][4 * q + 1]) << 4 | nib(acc[i][j][4 * q + 2]) << 8 |
-                   nib(acc[i][j][4 * q + 3]) << 12;
+      for (int v = 0; v < 8; v++) {
+        v0[v] = acc[i][j][v];
+        v1[v] = acc[i][j][8 + v];
       }
-      const uint32_t P0 = piece[0] | (piece[1] << 16), P1 = piece[2] | (piece[3] << 16);
+      const uint32_t P0 = quant_pack8<ASYM>(v0, zf, inv), P1 = quant_pack8<ASYM>(v1, zf, inv);
       // lane h=0 keeps dwords 0,1 of the tile's 16 bytes, lane h=1 dwords 2,3
       const uint32_t recv = __shfl_xor(h ? P0 : P1, 32);
       const uint32_t lo = h ? recv : P0, hi = h ? P1 : recv;
@@ -470,7 +469,7 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WA
       return;
     }
     const size_t xl_ld = (size_t)KL / 2;
-    const int gu = g >> 5;                                    // 32-channel units per group: 1, 2, 4
+    const int gu = g >> 5, g_log2 = 31 - __builtin_clz(g);    // 32-channel units per group: 1, 2, 4
     // The four lanes of a token are the four 16-lane rows of the wave; data moves between them with
     // the row-swap instructions of gfx950 (4 swaps transpose a 4x4 block of dwords over rows x registers).
     auto swap16 = [](uint32_t& x, uint32_t& y) {              // rows (x1 <-> y0), (x3 <-> y2)
@@ -501,15 +500,15 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WA
           float lo = acc[2 * u][j][0], hi = acc[2 * u][j][0];
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            lo = fminf(lo, fminf(acc[2 * u][j][e], acc[2 * u + 1][j][e]));
-            hi = fmaxf(hi, fmaxf(acc[2 * u][j][e], acc[2 * u + 1][j][e]));
+            lo = fminf(fminf(lo, acc[2 * u][j][e]), acc[2 * u + 1][j][e]);
+            hi = fmaxf(fmaxf(hi, acc[2 * u][j][e]), acc[2 * u + 1][j][e]);
           }
           um[u] = __builtin_bit_cast(uint32_t, hi);
           un[u] = __builtin_bit_cast(uint32_t, lo);
         } else {
           float v = 0.0f;
 #pragma unroll
-          for (int e = 0; e < 4; e++) v = fmaxf(v, fmaxf(fabsf(acc[2 * u][j][e]), fabsf(acc[2 * u + 1][j][e])));
+          for (int e = 0; e < 4; e++) v = fmaxf(fmaxf(v, fabsf(acc[2 * u][j][e])), fabsf(acc[2 * u + 1][j][e]));
           um[u] = __builtin_bit_cast(uint32_t, v);
         }
       }
@@ -553,9 +552,9 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WA
       const float inv_q = group_inv(sf);
       const int clu = cl0 + 32 * hq;                          // first channel of unit hq
       const bool valid = clu >= 0 && clu < KL && m < M;
-      if (valid && (hq % gu) == 0) {
-        sx[(size_t)(clu / g) * sx_ld + m] = sbits;
-        if constexpr (ASYM) zx[(size_t)(clu / g) * sx_ld + m] = zbits;
+      if (valid && (hq & (gu - 1)) == 0) {
+        sx[(size_t)(clu >> g_log2) * sx_ld + m] = sbits;
+        if constexpr (ASYM) zx[(size_t)(clu >> g_log2) * sx_ld + m] = zbits;
       }
       // broadcast the four rows' values to all rows: b[u] = row u's value everywhere
       auto broadcast4 = [&](float v, float (&b)[4]) {
@@ -576,15 +575,10 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WA
       uint32_t P[4];
 #pragma unroll
       for (int u = 0; u < 4; u++) {
-        uint32_t pc = 0;
+        float v[8];
 #pragma unroll
-        for (int half = 0; half < 2; half++)
-#pragma unroll
-          for (int e = 0; e < 4; e++)
-            pc |= (ASYM ? quant_nibble_asym(acc[2 * u + half][j][e], zf[u], inv[u])
-                        : quant_nibble(acc[2 * u + half][j][e], inv[u]))
-                  << (16 * half + 4 * e);
-        P[u] = pc;
+        for (int e = 0; e < 8; e++) v[e] = acc[2 * u + (e >> 2)][j][e & 3];
+        P[u] = quant_pack8<ASYM>(v, zf[u], inv[u]);
       }
       transpose4(P);                                          // P[h] = row h's codes of unit hq
       // unit hq = 16 bytes: tile 2hq (low halves, rows 0..3 in channel order), then tile 2hq+1

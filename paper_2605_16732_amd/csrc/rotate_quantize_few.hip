@@ -213,12 +213,8 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
         sf = group_scale(hi, sbits);
       }
       const float inv = group_inv(sf);
-      uint32_t o = 0;
-#pragma unroll
-      for (int e = 0; e < 8; e++)
-        o |= (QM == 1 ? quant_nibble_asym(f[e], zf, inv) : quant_nibble(f[e], inv)) << (4 * e);
       if (valid) {
-        *(uint32_t*)(xl + (size_t)m * (KL / 2) + cl / 2) = o;
+        *(uint32_t*)(xl + (size_t)m * (KL / 2) + cl / 2) = quant_pack8<QM == 1>(f, zf, inv);
         if (cl % g == 0) {
           sx[(size_t)(cl / g) * M + m] = sbits;
           if constexpr (QM == 1) zx[(size_t)(cl / g) * M + m] = zbits;
