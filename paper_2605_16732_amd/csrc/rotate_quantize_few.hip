@@ -191,10 +191,10 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
         if (part == 0) pmax[(size_t)(cl >> 7) * M + m] = a;
       }
     } else {
-      // maximum (and minimum) over the group's 4, 8 or 16 lanes
-      float hi = QM == 1 ? f[0] : fabsf(f[0]), lo = f[0];
+      // maximum (and minimum) over the group's 4, 8 or 16 lanes (the absolute maximum from 0 on: a group of NaN has scale 0)
+      float hi = QM == 1 ? f[0] : 0.0f, lo = f[0];
 #pragma unroll
-      for (int e = 1; e < 8; e++) {
+      for (int e = 0; e < 8; e++) {
         hi = fmaxf(hi, QM == 1 ? f[e] : fabsf(f[e]));
         lo = fminf(lo, f[e]);
       }

@@ -10,7 +10,7 @@ import torch
 from oracle import dirotq_oracle as O
 from paper_2605_16732_amd import binding as B
 
-from gpu_util import dev, gpu_rotate_quantize
+from gpu_util import dev, dev_bf16, gpu_rotate_quantize, host_f16
 from test_gpu_parity_a8 import gpu_rq_a8
 from test_gpu_parity_asym import gpu_rq_asym
 
@@ -65,3 +65,25 @@ def test_extreme_magnitudes_int8_tokens():
     assert float(sx_r[0]) == 65504.0 and not qx_r[2].any()
     np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16))
     np.testing.assert_array_equal(qx_g, qx_r)
+
+
+@pytest.mark.parametrize("M,K,g", [
+    (8, 256, 64), (8, 256, 128), (8, 288, 32), (7000, 256, 64), (9000, 256, 64), (5000, 288, 32), (7000, 288, 32),
+    (21000, 256, 64), (33000, 256, 64),
+])
+def test_a_token_of_nan_gets_scale_zero_in_every_kernel(M, K, g):
+    """One NaN makes all rotated channels of its token NaN.  The absolute maximum ignores them, so the symmetric and the
+    8-bit scale are 0 and the codes the lower bound, in the few-token kernel as in the tiled ones that the larger token
+    counts reach; the other tokens do not change."""
+    print(f"[case] NaN token M={M} K={K} g={g}", flush=True)
+    x = O.round_to_bf16(np.random.default_rng(M).standard_normal((M, K)).astype(np.float32))
+    Qt = B.prepare_rotation(dev(np.eye(K, dtype=np.float32)))
+    clean = B.rotate_quantize(dev_bf16(O.bf16_bits(x)), Qt, 0, g) + B.rotate_quantize_a8(dev_bf16(O.bf16_bits(x)), Qt, 0)
+    x[M // 2, 5] = np.nan
+    bad = B.rotate_quantize(dev_bf16(O.bf16_bits(x)), Qt, 0, g) + B.rotate_quantize_a8(dev_bf16(O.bf16_bits(x)), Qt, 0)
+    torch.cuda.synchronize()
+    others = np.arange(M) != M // 2
+    for i, what in ((1, "codes"), (2, "scales"), (4, "8-bit codes"), (5, "8-bit scales")):
+        a, b = (host_f16(v).T if "scales" in what else v.cpu().numpy() for v in (clean[i], bad[i]))
+        np.testing.assert_array_equal(b[others], a[others], err_msg=what)
+        assert (b[M // 2] == (0 if "scales" in what else 0xFF)).all(), what
