@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "gemm_tail.h"
+#include "pipe_stage.h"
 
 namespace dirotq {
 
@@ -37,7 +38,6 @@ namespace pipe {
 
 constexpr int TNW = 256;                     // output channels per workgroup tile (4 waves of 64)
 constexpr int NT = 512;
-constexpr int SB = 64;                       // bytes per row and stage in LDS
 constexpr int NBUF = 3;
 constexpr int tmw(int nb) { return 64 * nb; }                     // tokens per workgroup tile (2 waves of 32 nb)
 constexpr int rows(int nb) { return TNW + tmw(nb); }
@@ -49,10 +49,6 @@ constexpr int slot_bytes(int nb, int gs) { return rows(nb) * SB + scale_bytes(gs
 constexpr int OUT_ROW = 144, OUT_WAVE_BYTES = 32 * OUT_ROW;
 constexpr int out_off(int nb, int gs) { return NBUF * slot_bytes(nb, gs); }
 constexpr int smem_bytes(int nb, int gs) { return out_off(nb, gs) + 8 * OUT_WAVE_BYTES; }
-
-// 16-B chunk c of row r sits in slot c ^ ((r >> 2) & 3): the 16 rows that a 16-byte LDS access serves per cycle
-// fall into 16 different slots of a 256-byte bank line
-__device__ __forceinline__ int stage_off(int row, int chunk) { return row * SB + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
 // 16 sign-magnitude nibbles (two dwords) -> 16 FP6 numbers [s 00 mmm] in three dwords.  Six-bit field f takes a nibble
 // that one of the shifts 0, +2, +4 over the 64-bit pair brings there (16 instructions); the order that results is the
@@ -165,14 +161,11 @@ __device__ __forceinline__ void run_tiles(
   // quarter t & 3 of row t >> 2 (NB = 2); the scales of row t of (weights, tokens)
   const int half = t & 1;
   const int xrow = WIDE_X ? t >> 1 : t >> 2, xpart = WIDE_X ? half : t & 3, xhalf = WIDE_X ? half : xpart >> 1;
-  // LDS offsets within a slot: where an expanded row half goes (16 + 8 bytes; groups of 32: 16 + 16), and a copied one
-  auto hi_off = [](int lo, int row) { return (lo ^ 16) + (GS == 32 ? 0 : 8 * ((row >> 4) & 1)); };   // (8-byte parts
-                                                                      // alternate within their chunks: all banks)
-  const int so_w = stage_off(t >> 1, 2 * half), so_wh = hi_off(so_w, t >> 1);
-  const int so_wb = GS == 32 ? stage_off(t >> 1, half) : so_w;
-  const int so_x = WIDE_X ? so_w + TNW * SB : stage_off(TNW + xrow, 2 * xhalf);
-  const int so_xh = WIDE_X ? so_wh + TNW * SB : hi_off(so_x, xrow);
-  const int so_xb = GS == 32 ? stage_off(TNW + xrow, xhalf) : so_x;
+  // LDS offsets within a slot (pipe_stage.h)
+  const RowPart part_w = row_part<GS>(t >> 1, half);
+  constexpr int XOFF = TNW * SB;                                      // (the token rows follow the weight rows)
+  const RowPart part_x = WIDE_X ? RowPart{part_w.at + XOFF, part_w.at_hi + XOFF, part_w.at_copy + XOFF}
+                                : row_part<GS>(TNW + xrow, xhalf);
   const bool short_last = GS == 32 && (KL % 64) != 0;                 // the last stage holds one 32-channel group
 
   // load cursor: the tile and stage the next load is for.  Uniform bases of the tile; per-lane byte offsets from
@@ -234,28 +227,28 @@ __device__ __forceinline__ void run_tiles(
   // One stage from registers to LDS.  `copy`: a stage of the 16-bit branch, stored as it is.  The kind selects values
   // and addresses, not code (a second copy of the loop bodies for it makes the compiler move accumulators between
   // register sets).  d0, d1: the two expanded 16-channel parts of a row half.
-  auto store_half = [&](unsigned char* sp, int at, int at_hi, int at_copy, bool copy, u32x4 v, const uint32_t (&d0)[3],
+  auto store_half = [&](unsigned char* sp, const RowPart& part, bool copy, u32x4 v, const uint32_t (&d0)[3],
                         const uint32_t (&d1)[3]) {
+    const Stores at = wide_stores<GS>(part, copy);
     if constexpr (GS == 32) {                                         // lane halves of the operand: d0 | d1 of the group
-      *(u32x4*)(sp + at_hi) = u32x4{d1[0], d1[1], d1[2], 0u};
-      *(u32x4*)(sp + (copy ? at_copy : at)) = copy ? v : u32x4{d0[0], d0[1], d0[2], 0u};
+      *(u32x4*)(sp + at.second) = u32x4{d1[0], d1[1], d1[2], 0u};
+      *(u32x4*)(sp + at.first) = copy ? v : u32x4{d0[0], d0[1], d0[2], 0u};
     } else {                                                          // lane half = row half: 24 bytes
-      *(u32x4*)(sp + at) = copy ? v : u32x4{d0[0], d0[1], d0[2], d1[0]};
-      *(u32x2*)(sp + at_hi) = u32x2{d1[1], d1[2]};
+      *(u32x4*)(sp + at.first) = copy ? v : u32x4{d0[0], d0[1], d0[2], d1[0]};
+      *(u32x2*)(sp + at.second) = u32x2{d1[1], d1[2]};
     }
   };
   auto put_x_narrow = [&](unsigned char* sp, bool copy, u32x2 v) {    // 8 bytes of a token row: one 16-channel part
     const int part = xpart & 1;
+    const Stores at = narrow_stores<GS>(part_x, part, copy);
     uint32_t d[3];
     unpack16_fp6(v[0], v[1], d);
     if constexpr (GS == 32) {
-      const int at = copy ? so_xb + 8 * part : part ? so_x ^ 16 : so_x;
-      *(u32x2*)(sp + at) = copy ? v : u32x2{d[0], d[1]};
-      *(u32x2*)(sp + (copy ? (so_xb ^ 32) + 8 * part : at + 8)) = u32x2{d[2], 0u};   // (16-bit stage: not read)
+      *(u32x2*)(sp + at.first) = copy ? v : u32x2{d[0], d[1]};
+      *(u32x2*)(sp + at.second) = u32x2{d[2], 0u};
     } else {                                                          // dwords 0 1 2 of the row half's six, or 3 4 5
-      *(uint32_t*)(sp + so_x + (part ? 12 : 8)) = part ? d[0] : d[2];
-      *(u32x2*)(sp + (copy ? so_xb + 8 * part : part ? so_xh : so_x)) =
-          copy ? v : u32x2{part ? d[1] : d[0], part ? d[2] : d[1]};
+      *(uint32_t*)(sp + at.second) = part ? d[0] : d[2];
+      *(u32x2*)(sp + at.first) = copy ? v : u32x2{part ? d[1] : d[0], part ? d[2] : d[1]};
     }
   };
   auto put_s = [&](auto set, int so) {
@@ -278,8 +271,7 @@ __device__ __forceinline__ void run_tiles(
   // lane half h reads chunk 2 h (of a 16-bit stage, and 16 of the 24 bytes) and the 8 bytes in chunk 2 h + 1; groups of
   // 32: chunk h (16-bit stage, group 0) and 2 + h (group 1).  Tile bases are multiples of 32 rows, so the lane's part of
   // an address is the same for weights and tokens.
-  const int ln_lo = stage_off(l & 31, GS == 32 ? h : 2 * h);
-  const int ln_hi = GS == 32 ? stage_off(l & 31, 2 + h) : hi_off(ln_lo, l & 31);
+  const int ln_lo = read_lo<GS>(l & 31, h), ln_hi = read_hi<GS>(l & 31, h);
   const int ln_s = SCALE_OFF + (l & 31) * 16 + h * 8;                 // (lanes 32..63, k-slots 4..7, read the zeros)
   const int rowA = wn * 64, rowB = TNW + wt * (32 * NB);
   // (of a 16-bit stage only the first 16 bytes mean something)
@@ -320,13 +312,13 @@ __device__ __forceinline__ void run_tiles(
     if (q == 0) unpack16_fp6(rw[set][0], rw[set][1], d0);
     if (q == 1) {
       unpack16_fp6(rw[set][2], rw[set][3], d1);
-      store_half(sp, so_w, so_wh, so_wb, copy, rw[set], d0, d1);
+      store_half(sp, part_w, copy, rw[set], d0, d1);
     }
     if constexpr (WIDE_X) {
       if (q == 2) unpack16_fp6(rx[set][0], rx[set][1], d0);
       if (q == 3) {
         unpack16_fp6(rx[set][2], rx[set][3], d1);
-        store_half(sp, so_x, so_xh, so_xb, copy, rx[set], d0, d1);
+        store_half(sp, part_x, copy, rx[set], d0, d1);
       }
     } else {
       if (q == 2) put_x_narrow(sp, copy, rx[set]);

@@ -1,0 +1,22 @@
+"""The LDS stage layout of the pipelined W4A4 kernel, checked on the host (tests/host/pipe_stage_map.cpp): every byte that is
+read has one writer among a workgroup's threads, and the reader finds the channels that it expects."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2605_16732_amd import build as BLD
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_every_byte_that_is_read_has_one_writer(tmp_path):
+    cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/lib/llvm/bin/clang++"
+    if not os.path.exists(cxx):
+        pytest.skip("no host compiler")
+    exe = str(tmp_path / "pipe_stage_map")
+    subprocess.run([cxx, "-O1", "-std=c++17", "-I", BLD.CSRC, os.path.join(ROOT, "tests", "host", "pipe_stage_map.cpp"), "-o", exe],
+                   check=True, capture_output=True)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0 and run.stdout.startswith("0 failure(s)"), run.stdout
