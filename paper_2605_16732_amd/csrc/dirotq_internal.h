@@ -138,10 +138,10 @@ int launch_export_weights(const void* blob, int N, int K, int r, int g, uint16_t
 // (Written as asm because the compiler lets every later LDS read wait for all such copies in flight; a wave that reads
 // its ring of slots waits for the copies of the slot it reads, with wait_copies.)
 __device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t voff, const void* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void copy4_to_lds(uint32_t lds, uint32_t voff, const void* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_copies() {             // until at most N copies (and other loads) are in flight
