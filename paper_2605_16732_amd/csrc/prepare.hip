@@ -96,61 +96,64 @@ __global__ __launch_bounds__(256) void fuse_rotation_fp64_kernel(const float* __
 }
 
 // ---- split + quantize rows of an fp32 matrix -------------------------------------
-// Bound: one read of the matrix.  A thread takes 8 consecutive channels of a row, the channels of the 16-bit part first
-// (unit u: row u / (r/8)), then those of the 4-bit part from unit n_hi_pad on; a group is 4, 8 or 16 neighbouring lanes.
-// (One thread per group, consecutive threads on consecutive rows, read 4 of every 64 bytes: 24 -> 5 us at N = K = 1536, 910 -> 35 us at N = 3072,
-// K = 12288.)
+// Bound: one read of the matrix.  A thread takes 8 consecutive channels of a row at a time, the channels of the 16-bit part
+// first (unit u: row u / (r/8)), then those of the 4-bit part from unit n_hi_pad on; a group is 4, 8 or 16 neighbouring
+// lanes.  (One thread per group, consecutive threads on consecutive rows, read 4 of every 64 bytes: 24 -> 5 us at
+// N = K = 1536, 910 -> 35 us at N = 3072, K = 12288.)
+constexpr long QUANT_BLOCKS = 1 << 16;               // (more units than these have threads: several runs of 256 per block)
 __global__ __launch_bounds__(256) void split_quantize_rows_kernel(const float* __restrict__ src, int rows,
-                                                                  int K, int r, int g, long n_hi_pad,
+                                                                  int K, int r, int g, long n_hi_pad, long n_blocks,
                                                                   uint16_t* __restrict__ hi,
                                                                   uint8_t* __restrict__ codes,
                                                                   uint16_t* __restrict__ scales,
                                                                   int16_t* __restrict__ wsum) {
-  const long u = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int KL = K - r;
-  if (u < n_hi_pad) {
-    if (u >= (long)rows * (r / 8)) return;
-    const long row = u / (r / 8);
-    const int c = (int)(u % (r / 8)) * 8;
-    const float4 a = *(const float4*)(src + row * K + c), b = *(const float4*)(src + row * K + c + 4);
-    uint4 o;
-    o.x = f32_to_bf16_bits(a.x) | (uint32_t)f32_to_bf16_bits(a.y) << 16;
-    o.y = f32_to_bf16_bits(a.z) | (uint32_t)f32_to_bf16_bits(a.w) << 16;
-    o.z = f32_to_bf16_bits(b.x) | (uint32_t)f32_to_bf16_bits(b.y) << 16;
-    o.w = f32_to_bf16_bits(b.z) | (uint32_t)f32_to_bf16_bits(b.w) << 16;
-    *(uint4*)(hi + row * r + c) = o;
-    return;
-  }
-  const long v = u - n_hi_pad;                       // (a multiple of 256 ahead: groups do not straddle waves)
-  const bool live = KL > 0 && v < (long)rows * (KL / 8);   // (whole groups are live or not)
-  const long row = live ? v / (KL / 8) : 0;
-  const int c = live ? (int)(v % (KL / 8)) * 8 : 0;
-  float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (live) {
-    const float4 a = *(const float4*)(src + row * K + r + c), b = *(const float4*)(src + row * K + r + c + 4);
-    f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
-  }
-  float amax = 0.0f;
+  for (long b = blockIdx.x; b < n_blocks; b += gridDim.x) {
+    const long u = b * 256 + threadIdx.x;
+    if (u < n_hi_pad) {                              // (a multiple of 256: the same for a whole block)
+      if (u >= (long)rows * (r / 8)) continue;
+      const long row = u / (r / 8);
+      const int c = (int)(u % (r / 8)) * 8;
+      const float4 lo = *(const float4*)(src + row * K + c), up = *(const float4*)(src + row * K + c + 4);
+      uint4 o;
+      o.x = f32_to_bf16_bits(lo.x) | (uint32_t)f32_to_bf16_bits(lo.y) << 16;
+      o.y = f32_to_bf16_bits(lo.z) | (uint32_t)f32_to_bf16_bits(lo.w) << 16;
+      o.z = f32_to_bf16_bits(up.x) | (uint32_t)f32_to_bf16_bits(up.y) << 16;
+      o.w = f32_to_bf16_bits(up.z) | (uint32_t)f32_to_bf16_bits(up.w) << 16;
+      *(uint4*)(hi + row * r + c) = o;
+      continue;
+    }
+    const long v = u - n_hi_pad;                     // (groups do not straddle waves)
+    const bool live = KL > 0 && v < (long)rows * (KL / 8);   // (whole groups are live or not)
+    const long row = live ? v / (KL / 8) : 0;
+    const int c = live ? (int)(v % (KL / 8)) * 8 : 0;
+    float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (live) {
+      const float4 lo = *(const float4*)(src + row * K + r + c), up = *(const float4*)(src + row * K + r + c + 4);
+      f[0] = lo.x, f[1] = lo.y, f[2] = lo.z, f[3] = lo.w, f[4] = up.x, f[5] = up.y, f[6] = up.z, f[7] = up.w;
+    }
+    float amax = 0.0f;
 #pragma unroll
-  for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf(f[e]));
-  for (int o = 1; o < g / 8; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
-  uint16_t sbits;
-  const float sf = group_scale(amax, sbits);
-  const float inv = group_inv(sf);
-  uint32_t p = 0;
-  int sum = 0;
+    for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf(f[e]));
+    for (int o = 1; o < g / 8; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+    uint16_t sbits;
+    const float sf = group_scale(amax, sbits);
+    const float inv = group_inv(sf);
+    uint32_t p = 0;
+    int sum = 0;
 #pragma unroll
-  for (int e = 0; e < 8; e++) {
-    const int q = quant_code(f[e], inv);
-    p |= code_nibble(q) << (4 * e);
-    sum += q;
-  }
-  for (int o = 1; o < g / 8; o <<= 1) sum += __shfl_xor(sum, o);   // |sum| <= 7 * 128
-  if (!live) return;
-  *(uint32_t*)(codes + row * (KL / 2) + c / 2) = p;
-  if (c % g == 0) {
-    scales[(size_t)(c / g) * rows + row] = sbits;
-    wsum[(size_t)(c / g) * rows + row] = (int16_t)sum;
+    for (int e = 0; e < 8; e++) {
+      const int q = quant_code(f[e], inv);
+      p |= code_nibble(q) << (4 * e);
+      sum += q;
+    }
+    for (int o = 1; o < g / 8; o <<= 1) sum += __shfl_xor(sum, o);   // |sum| <= 7 * 128
+    if (!live) continue;
+    *(uint32_t*)(codes + row * (KL / 2) + c / 2) = p;
+    if (c % g == 0) {
+      scales[(size_t)(c / g) * rows + row] = sbits;
+      wsum[(size_t)(c / g) * rows + row] = (int16_t)sum;
+    }
   }
 }
 
@@ -158,19 +161,19 @@ int launch_prepare_weights(const float* W, const float* Q, int N, int K, int r, 
                            float* scratch, hipStream_t s) {
   const BlobLayout L = blob_layout(N, K, r, g);
   char* bp = (char*)blob;
-  // 1-D grids (only shapes whose fp32 scratch alone would exceed 2^44 bytes are refused)
+  // (only shapes whose fp32 scratch alone would exceed 2^45 bytes are refused; both kernels loop over their work)
   const long n_tiles64 = (long)((K + 63) / 64) * (long)((N + 63) / 64);
+  if (n_tiles64 > 0x7FFFFFFFL) return DIROTQ_ERR_SHAPE;
   const long n_hi_pad = ((long)N * (r / 8) + 255) / 256 * 256;
   const long n_blocks = (n_hi_pad + (long)N * ((K - r) / 8) + 255) / 256;
-  if (n_tiles64 > 0x7FFFFFFFL || n_blocks > 0x7FFFFFFFL) return DIROTQ_ERR_SHAPE;
   const long n_tiles = (long)(K / FC) * (long)((N + FN - 1) / FN), per_xcd = (n_tiles + 7) / 8;
   const unsigned grid = (unsigned)(8 * (per_xcd < (1 << 18) ? per_xcd : (1 << 18)));   // (beyond: several tiles each)
   hipLaunchKernelGGL(fuse_rotation_fp64_kernel, dim3(grid), dim3(256), 0, s, W, Q, N, K, scratch, n_tiles, per_xcd);
   hipError_t e0 = hipGetLastError();
   if (e0 != hipSuccess) return hip_failed(e0);      // nothing else is enqueued on an unwritten scratch
-  hipLaunchKernelGGL(split_quantize_rows_kernel, dim3((unsigned)n_blocks), dim3(256), 0, s, scratch, N, K, r, g,
-                     n_hi_pad, (uint16_t*)(bp + L.off_wh), (uint8_t*)(bp + L.off_codes),
-                     (uint16_t*)(bp + L.off_sw), (int16_t*)(bp + L.off_wsum));
+  hipLaunchKernelGGL(split_quantize_rows_kernel, dim3((unsigned)(n_blocks < QUANT_BLOCKS ? n_blocks : QUANT_BLOCKS)),
+                     dim3(256), 0, s, scratch, N, K, r, g, n_hi_pad, n_blocks, (uint16_t*)(bp + L.off_wh),
+                     (uint8_t*)(bp + L.off_codes), (uint16_t*)(bp + L.off_sw), (int16_t*)(bp + L.off_wsum));
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2605_16732_amd import binding as B
 
@@ -155,6 +156,17 @@ def test_output_tilings_beyond_32_bit_grids_are_rejected():
     out = ctypes.c_size_t(0)
     assert L.dirotq_workspace_bytes(big, 1 << 20, 0, 32, ctypes.byref(out)) == B.OK     # sizes are 64-bit
     assert out.value > (1 << 42)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the pointers are made up: only where no launch can succeed")
+@pytest.mark.parametrize("N,K,r", [(1 << 22, 1 << 20, 0), (1 << 23, 1 << 20, 32), ((1 << 23) - 64, 1 << 20, 1 << 20)])
+def test_weights_up_to_the_stated_limit_are_not_refused(N, K, r):
+    """Up to 2^31 - 1 tiles of 64 x 64 pass the shape check (and end at the launch, as there is no device); one more does
+    not, whatever the units that the kernels count in."""
+    L, a = B.lib(), 0x1000
+    n_tiles = (N // 64) * (K // 64)
+    want = B.ERR_HIP if n_tiles <= 0x7FFFFFFF else B.ERR_SHAPE
+    assert L.dirotq_prepare_weights(a, a, N, K, r, 32, a, a, 1 << 62, None) == want
 
 
 def test_error_type_carries_message():

@@ -70,3 +70,20 @@ def test_rotation_input_beyond_2_31_elements():
     np.testing.assert_array_equal(_bf16_rows_to_f32(xh[idx]), xh_r)
     np.testing.assert_array_equal(unpack_codes(xl[idx].cpu().numpy()), qx_r)
     np.testing.assert_array_equal(host_f16(sx[:, idx].contiguous()).T.view(np.uint16), sx_r.view(np.uint16))
+
+
+def test_weight_preparation_with_several_runs_of_units_per_block():
+    """More units of 8 channels than the quantizer's grid has threads (65536 blocks of 256): the last rows equal those of a
+    call with these rows alone."""
+    N, K, r, g = (1 << 20) + 77, 160, 32, 64                # 82 thousand blocks' worth of units
+    _say(f"prepare_weights, {N * K / 8 / (1 << 24):.2f} x 2^24 units")
+    gen = torch.Generator(device="cuda").manual_seed(62)
+    W = torch.randn((N, K), generator=gen, device="cuda")
+    Q = torch.zeros((K, K), device="cuda")
+    Q[torch.randperm(K, generator=gen, device="cuda"), torch.arange(K, device="cuda")] = 1.0
+    Wh, codes, sw = B.export_weights(B.prepare_weights(W, Q, r, g), N, K, r, g)
+    n = 70001
+    for rows in (slice(0, n), slice(N - n, N)):
+        part = B.export_weights(B.prepare_weights(W[rows].contiguous(), Q, r, g), n, K, r, g)
+        for a, b in zip((Wh, codes, sw), part):
+            assert torch.equal(a[rows], b)
