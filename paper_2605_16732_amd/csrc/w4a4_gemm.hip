@@ -28,7 +28,7 @@
 // subnormals linearly), so the main loop is unchanged.  The zero-point term
 // sum_j z[m,j] * (s_w[n,j] * sum_k q_w[n,k]) is a small GEMM over the groups; it is added
 // after the main loop by bf16 MFMAs on exact bf16 splits of its factors (z = z1 + z2,
-// c = b1 + b2 + b3; every product but z2 b3, which is below 2^-24 of the term, is kept).
+// c = b1 + b2 + b3; every product but z2 b3, which is below 2^-22 of the term, is kept).
 //
 // Schedule.  The vector ALU is the binding unit (one fma per accumulator and group plus the
 // unpacking, against 64 cycles of fp8 MFMA per tile and 64-channel group), so the main loop
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void w4a4_gemm_kernel(
     if constexpr (ASYM) {
       // 12 groups per pass: thread t fills row t of a [256 rows][64 bf16] tile, 5 k-slots per group:
       // weight rows b1 b2 b3 b1 b2, token rows z1 z1 z1 z2 z2 (group-major sources: coalesced over
-      // rows).  z = z1 + z2 and c = b1 + b2 + b3 exactly; only z2 b3 (< 2^-24 of the term) is dropped.
+      // rows).  z = z1 + z2 and c = b1 + b2 + b3 exactly; only z2 b3 (z2 < 2^-7 z, b3 < 2^-15 c) is dropped.
       constexpr int GPP = 12;
       const bool is_w = t < TN;                             // uniform per wave
       const size_t ld = is_w ? (size_t)N : (size_t)M;

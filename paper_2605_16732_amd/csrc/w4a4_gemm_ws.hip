@@ -125,7 +125,7 @@ __device__ __forceinline__ void tile_origin(int logical, int n_mt, int n_nt, int
 // Asymmetric activations (ASYM): the codes of the token rows are unsigned nibbles, and the zero-point term
 // sum_j z[m,j] (s_w[n,j] sum_k q_w[n,k]) follows each tile's 4-bit stages as nzp more 16-bit stages whose rows the
 // staging waves form on the fly: per group five k-slots, weight rows b1 b2 b3 b1 b2, token rows z1 z1 z1 z2 z2,
-// with z = z1 + z2 and s_w sum q_w = b1 + b2 + b3 exact bf16 splits (only z2 b3, below 2^-24 of the term, is
+// with z = z1 + z2 and s_w sum q_w = b1 + b2 + b3 exact bf16 splits (only z2 b3, below 2^-22 of the term, is
 // dropped); six groups per stage (both 16-byte chunks of a lane's operand, two MFMAs per tile).
 template <int GS, bool OUT_F32, bool ASYM>
 __global__ __launch_bounds__(NT, 1) void w4a4_gemm_ws_kernel(

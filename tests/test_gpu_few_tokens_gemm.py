@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 ])
 def test_few_token_schedules_match_oracle(M, N, K, r, g, monkeypatch):
     """fp32 sums of at most G + r/16 partial terms per wave and 8 waves against a float64 sum: 1e-5 of the largest output
-    (2e-5 with zero-points, whose products z s_w sum(q) are split into bf16 pieces down to 2^-24 of the term)."""
+    (2e-5 with zero-points: six products of exact bf16 pieces per group more)."""
     print(f"[case] few-token w4a4 M={M} N={N} K={K} r={r} g={g}", flush=True)
     monkeypatch.setenv("DIROTQ_W4A4_KERNEL", "skinny")
     rng = np.random.default_rng([M, N, K])
@@ -43,3 +43,19 @@ def test_few_token_schedules_match_oracle(M, N, K, r, g, monkeypatch):
     packed = (ux[:, 0::2] | (ux[:, 1::2] << 4)).astype(np.uint8)
     got = B.w4a4_gemm_asym(xh_d, dev(packed), sx_d, zx_d, blob, M, N, K, r, g, bias=bias_d, out_dtype=torch.float32)
     assert np.abs(got.cpu().numpy() - want).max() <= 2e-5 * np.abs(want).max()
+
+
+def test_zero_point_term_is_multiplied_out(monkeypatch):
+    """All codes 0, one group: the output is z s_w sum(q_w), as six products of bf16 pieces in one fp32 accumulator.  The
+    numbers make the last one (z2 c3) as large as it gets, 2^-22.3 of the term.  With it the error is that of the sum and of
+    its result, at most 2^-24 each; without it 2.26 x 2^-24 were seen."""
+    print("[case] few-token w4a4 zero-point term", flush=True)
+    monkeypatch.setenv("DIROTQ_W4A4_KERNEL", "skinny")
+    qw = np.zeros((1, 64), np.int8)
+    qw[0, :58], qw[0, 58] = 7, 3
+    z, sw = np.float16(1.0068359375), np.float16(1.2568359375)
+    blob = import_blob(np.zeros((1, 0), np.float32), qw, np.full((1, 1), sw), 1, 64, 0, 64)
+    y = B.w4a4_gemm_asym(None, torch.zeros((1, 32), dtype=torch.uint8, device="cuda"), dev(np.ones((1, 1), np.float16)),
+                         dev(np.full((1, 1), z)), blob, 1, 1, 64, 0, 64, out_dtype=torch.float32)
+    want = float(z) * float(sw) * 409.0
+    assert abs(float(y) - want) <= 2.0 ** -23 * want
