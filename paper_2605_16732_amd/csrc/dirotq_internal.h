@@ -116,9 +116,6 @@ int launch_w4a4_gemm_ws(const uint16_t* xh, const uint8_t* xl, const uint16_t* s
 int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                           const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
                           long big_tokens, hipStream_t s);
-// how many of the first tokens go to its 256 x 256 tiles (the others to 256 x 128 ones); returns its time in units of a
-// 256 x 256 tile per CU
-double w4a4_pipe_plan(int M, int N, int cus, long& big_tokens);
 // few tokens: the K axis split over the waves of a workgroup (64 x 64 outputs each, or `small`: 32 x 32); zx as above
 int launch_w4a4_gemm_skinny(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
                             const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,

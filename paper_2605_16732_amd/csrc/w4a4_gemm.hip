@@ -40,6 +40,7 @@
 #include <cstring>
 
 #include "gemm_tail.h"
+#include "pipe_plan.h"
 
 namespace dirotq {
 

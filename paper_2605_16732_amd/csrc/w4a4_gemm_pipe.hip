@@ -30,13 +30,13 @@
 #include <type_traits>
 
 #include "gemm_tail.h"
+#include "pipe_plan.h"
 #include "pipe_stage.h"
 
 namespace dirotq {
 
 namespace pipe {
 
-constexpr int TNW = 256;                     // output channels per workgroup tile (4 waves of 64)
 constexpr int NT = 512;
 constexpr int NBUF = 3;
 constexpr int tmw(int nb) { return 64 * nb; }                     // tokens per workgroup tile (2 waves of 32 nb)
@@ -478,38 +478,6 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 }
 
 }  // namespace pipe
-
-// Where the tokens are split, so that the workgroup with the most work has least of it: in units of the time of a
-// 256 x 256 tile, a 256 x 128 one takes HALF (K = 3072: 44 against 66 us), and a workgroup that has both kinds drains
-// and refills its pipeline once in between.  N = 12288, M = 4608 (3.375 tiles of 256 x 256 per CU): 248 us with three
-// rounds of large tiles and one of small ones, 266 us with large ones only, 307 us with small ones only.
-double w4a4_pipe_plan(int M, int N, int cus, long& big_tokens) {
-  constexpr double HALF = 0.65, PHASE = 0.04;
-  const uint32_t wpx = (uint32_t)std::max(1, cus / 8);
-  const long n_nt = (N + pipe::TNW - 1) / pipe::TNW;
-  // Per XCD the large tiles are dealt to the slots 0, 1, ... in turn, the small ones to the slots from the other end.
-  auto most = [&](long big, long small) {
-    const uint32_t b = (uint32_t)((big + 7) / 8), h = (uint32_t)((small + 7) / 8);
-    const uint32_t bq = b / wpx, br = b % wpx, hq = h / wpx, hr = h % wpx;
-    auto time = [&](uint32_t nb, uint32_t nh) { return nb + HALF * nh + (nb && nh ? PHASE : 0.0); };
-    if (br + hr > wpx) return time(bq + 1, hq + 1);
-    return std::max(time(bq, hq), std::max(br ? time(bq + 1, hq) : 0.0, hr ? time(bq, hq + 1) : 0.0));
-  };
-  auto split_at = [&](long t) { return most(t * n_nt, t * 256 < M ? ((M - t * 256 + 127) / 128) * n_nt : 0); };
-  // (only a split within the last two rounds of large tiles, or none at all, can be the best one)
-  const long n_big = (M + 255) / 256, lo = std::max(1L, n_big - 2 - 16L * wpx / n_nt);
-  long best_t = n_big;
-  double best = split_at(n_big);
-  for (long t = n_big - 1; t >= 0; t = t > lo ? t - 1 : t ? 0 : -1) {
-    const double c = split_at(t);
-    if (c < best) {
-      best = c;
-      best_t = t;
-    }
-  }
-  big_tokens = std::min(best_t * 256, (long)M);
-  return best;
-}
 
 int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                           const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
