@@ -59,9 +59,10 @@
  *    The fp32 additions of an output are ordered differently in each, so a token's result
  *    is deterministic for a given
  *    (M, N, K, r, g) but not bit-identical across different M.  For testing, the
- *    environment variables DIROTQ_W4A4_KERNEL (pipe | large | small | ws | tile | skinny) and
- *    DIROTQ_W4A16_KERNEL (tile) are read at every launch and force a schedule wherever
- *    it applies; they are not needed in normal use.
+ *    environment variables DIROTQ_W4A4_KERNEL (pipe | large | small | ws | tile | skinny |
+ *    skinny32 | skinny64), DIROTQ_W4A8_KERNEL (few1 | few2 | medium1 | medium2 | medium4 |
+ *    tile) and DIROTQ_W4A16_KERNEL (tile) are read at every launch and force a schedule
+ *    wherever it applies; they are not needed in normal use.
  */
 #ifndef DIROTQ_H
 #define DIROTQ_H

@@ -447,9 +447,9 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 // below, costs in microseconds fitted to measurements at K = 1152 ... 12288 and N = 640 ... 9216 (within 15%) decide:
 // a round of 64 x 64 workgroups (one per CU) 6.3 + 2.1 K/1000; 32 x 32 ones, several per CU, 2.5 + 0.6 K/1000 and
 // 0.0087 (longer K: 0.0037 K/1000) each; 128 x 128 tiles 6 + 8 K/1000 while there is one per CU.
-// DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny in the environment forces one of them wherever it
-// applies (the tests use it to run all of them on the same inputs; large and small: the pipelined kernel with one kind
-// of tile).
+// DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny / skinny32 / skinny64 in the environment forces one of
+// them wherever it applies (the tests use it to run all of them on the same inputs; large and small: the pipelined
+// kernel with one kind of tile; skinny32 and skinny64: the split-K kernel with one of its two).
 enum class W4A4Schedule { kTile, kWs, kSkinny, kPipe };
 static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens,
                          bool& small_tiles) {
@@ -469,8 +469,10 @@ static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Sched
   small_tiles = cost32 <= cost64;
   if (const char* f = getenv("DIROTQ_W4A4_KERNEL")) {
     const bool large = !strcmp(f, "large"), small = !strcmp(f, "small"), ws = !strcmp(f, "ws");
+    const bool skinny32 = !strcmp(f, "skinny32"), skinny64 = !strcmp(f, "skinny64");
     if (!strcmp(f, "tile")) return DIROTQ_OK;
-    if (!strcmp(f, "skinny")) return sch = W4A4Schedule::kSkinny, DIROTQ_OK;
+    if (skinny32 || skinny64) small_tiles = skinny32;
+    if (skinny32 || skinny64 || !strcmp(f, "skinny")) return sch = W4A4Schedule::kSkinny, DIROTQ_OK;
     if (ws || large || small || !strcmp(f, "pipe")) {
       // (symmetric groups of 32 have no wave-specialised form, asymmetric layers no pipelined one)
       sch = asym || (ws && g != 32) ? W4A4Schedule::kWs : W4A4Schedule::kPipe;

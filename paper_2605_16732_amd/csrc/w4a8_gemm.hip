@@ -23,6 +23,9 @@
 #include <algorithm>
 #include <atomic>
 
+#include <cstdlib>
+#include <cstring>
+
 #include "gemm_tail.h"
 #include "gemm_halves.h"
 
@@ -531,6 +534,7 @@ static int launch_few8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx
   const char* bp = (const char*)blob;
   const int n_nt = (N + 31) / 32;
   const long n_blocks = (long)n_nt * ((M + 32 * NJ - 1) / (32 * NJ));
+  if (n_blocks > 0x7FFFFFFFL) return DIROTQ_ERR_SHAPE;   // (far beyond where it is chosen)
   hipLaunchKernelGGL((w4a8_few_kernel<GS, OUT_F32, NJ>), dim3((unsigned)n_blocks), dim3(FEW_NT), 0, s, xh, x8, sx,
                      (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes),
                      (const uint16_t*)(bp + L.off_sw), bias, M, N, K, r, y, n_nt);
@@ -763,6 +767,8 @@ static int launch_medium(const uint16_t* xh, const uint8_t* x8, const uint16_t* 
 // two workgroups fit a CU), per step of 128 channels.  N = K = 3072, us with 1 | 2 | 4: 512 tokens 28.3 | 23.7 | 35.2,
 // 1024: 39.7 | 38.6 | 37.6, 2048: 74.3 | 56.4 | 71.2, 4096: 136 | 109 | 107 (128 x 128 tiles: 39.5, 49.6, 65.0, 109).
 // The 128 x 128 tiles: two workgroups per CU in a round, 4 + 13.6 K/1000 if it has at most one each, 7.2 + 18 K/1000 beyond.
+// DIROTQ_W4A8_KERNEL=few1 / few2 / medium1 / medium2 / medium4 / tile in the environment forces one of them, with that many
+// token tiles per workgroup (the tests use it to run all of them on the same inputs).
 static double medium_us(long M, long N, long steps, int nj, int cus) {
   const long wgs = ((M + 32 * nj - 1) / (32 * nj)) * ((N + 127) / 128);
   const double more = (double)((wgs + cus - 1) / cus - 1), st = (double)steps;
@@ -794,10 +800,15 @@ static int launch_case8(const uint16_t* xh, const uint8_t* x8, const uint16_t* s
       nj = c;
     }
   }
-  if (t128 <= 2L * cus && few < tiled) {
-    return K >= 8192 && M > 32 && t32 >= 256 ? launch_few8<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s)
-                                             : launch_few8<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
+  int few_nj = 0;                                        // 0: not the split-K kernel
+  if (t128 <= 2L * cus && few < tiled) few_nj = K >= 8192 && M > 32 && t32 >= 256 ? 2 : 1;
+  if (const char* f = getenv("DIROTQ_W4A8_KERNEL")) {
+    if (!strcmp(f, "few1") || !strcmp(f, "few2")) few_nj = f[3] - '0';
+    if (!strcmp(f, "medium1") || !strcmp(f, "medium2") || !strcmp(f, "medium4")) few_nj = 0, nj = f[6] - '0';
+    if (!strcmp(f, "tile")) few_nj = nj = 0;
   }
+  if (few_nj == 1) return launch_few8<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
+  if (few_nj == 2) return launch_few8<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   if (nj == 1) return w8::launch_medium<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   if (nj == 2) return w8::launch_medium<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   if (nj == 4) return w8::launch_medium<GS, OUT_F32, 4>(xh, x8, sx, blob, bias, M, N, K, r, y, s);

@@ -114,10 +114,18 @@ def test_rotate_quantize_a8_hand_rows():
 
 
 # ------------------------------------------------------------------ GEMM
+@pytest.fixture(params=["few1", "few2", "medium1", "medium2", "medium4", "tile"])
+def a8_schedule(request, monkeypatch):
+    """The GEMM's schedules (K split over the waves of a workgroup for few tokens; 128 channels x 32, 64 or 128 tokens; 128 x
+    128 tiles): the library picks by problem size, the environment switch forces one on every input."""
+    monkeypatch.setenv("DIROTQ_W4A8_KERNEL", request.param)
+    return request.param
+
+
 @pytest.mark.parametrize("M,N,K,g", [(130, 200, 256, 32), (257, 136, 448, 64), (64, 129, 384, 128), (5, 8, 64, 32),
                                      (70, 40, 96, 32), (33, 130, 32, 32), (129, 257, 1152, 64)])
 @gpu
-def test_w4a8_integer_exact(M, N, K, g):
+def test_w4a8_integer_exact(M, N, K, g, a8_schedule):
     """Unit scales: y = sum_k q_x q_w with |q_x| <= 127, |q_w| <= 7 is an integer below 2^24, exact in
     fp32 (covers the extreme codes, odd 32-channel counts and every group size)."""
     _say(f"w4a8 integer M={M} N={N} K={K} g={g}")
@@ -139,7 +147,7 @@ def test_w4a8_integer_exact(M, N, K, g):
 
 
 @gpu
-def test_w4a8_one_hot_codes_address_every_channel():
+def test_w4a8_one_hot_codes_address_every_channel(a8_schedule):
     """A single nonzero activation code per token picks out one weight code: any slip in the
     even/odd byte order or in the plane split shows up as a wrong element."""
     K, N, g = 128, 64, 32
@@ -161,7 +169,7 @@ def test_w4a8_one_hot_codes_address_every_channel():
     (300, 264, 1152, 64, 64, False), (140, 72, 3072, 0, 64, False), (77, 50, 160, 64, 32, True),
 ])
 @gpu
-def test_w4a8_matches_oracle_on_identical_inputs(M, N, K, r, g, use_bias):
+def test_w4a8_matches_oracle_on_identical_inputs(M, N, K, r, g, use_bias, a8_schedule):
     """Same inputs on both sides: only the fp32 accumulation order differs (1e-5 of the largest output)."""
     _say(f"w4a8 vs oracle M={M} N={N} K={K} r={r} g={g} bias={use_bias}")
     rng = np.random.default_rng(34)

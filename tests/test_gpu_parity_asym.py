@@ -105,11 +105,12 @@ def test_rotate_quantize_asym_hand_rows():
 
 
 # ------------------------------------------------------------------ kernel B
-@pytest.fixture(params=["tile", "ws"])
+@pytest.fixture(params=["tile", "ws", "skinny64", "skinny32"])
 def asym_schedule(request, monkeypatch):
-    """Asymmetric layers run on two schedules of kernel B (128 x 128 tiles with the zero-point passes in the tail;
-    wave-specialised workgroups whose staging waves add zero-point stages to the stage stream); the library picks by
-    problem size and the environment switch forces one, so that both run on the same inputs."""
+    """Asymmetric layers run on several schedules of kernel B (128 x 128 tiles with the zero-point passes in the tail;
+    wave-specialised workgroups whose staging waves add zero-point stages to the stage stream; 64 x 64 or 32 x 32 outputs
+    with the K axis split over a workgroup's waves, the zero-point term once per group); the library picks by problem size
+    and the environment switch forces one, so that all run on the same inputs."""
     monkeypatch.setenv("DIROTQ_W4A4_KERNEL", request.param)
     return request.param
 

@@ -1,4 +1,4 @@
-"""The medium schedule of the W4A8 GEMM (1, 2 and 4 token tiles per workgroup, chosen by size) against a float64 product of
+"""The medium schedule of the W4A8 GEMM (1, 2 and 4 token tiles per workgroup, each forced) against a float64 product of
 the same numbers: cut tiles, an odd number of output channels, one stage, odd numbers of stages, a last stage of half the
 channels, no 8-bit part, 16-bit parts of half a 64-channel piece, several and none."""
 import numpy as np
@@ -13,15 +13,17 @@ from oracle import dirotq_oracle as O
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("tiles", [1, 2, 4])
 @pytest.mark.parametrize("M,N,K,r,g", [
-    (300, 2049, 416, 32, 32), (300, 2050, 448, 0, 64), (300, 2049, 416, 32, 128), (300, 2050, 512, 512, 64),   # 1 token tile
-    (1030, 1153, 608, 160, 32), (1030, 1160, 640, 64, 64),                                                   # 2
-    (2050, 1153, 1120, 96, 128), (2050, 1153, 1184, 32, 32), (2050, 1160, 1152, 256, 64),                    # 4
+    (300, 2049, 416, 32, 32), (300, 2050, 448, 0, 64), (300, 2049, 416, 32, 128), (300, 2050, 512, 512, 64),
+    (1030, 1153, 608, 160, 32), (1030, 1160, 640, 64, 64),
+    (2050, 1153, 1120, 96, 128), (2050, 1153, 1184, 32, 32), (2050, 1160, 1152, 256, 64),
 ])
-def test_medium_matches_float64(M, N, K, r, g):
+def test_medium_matches_float64(M, N, K, r, g, tiles, monkeypatch):
     """Group sums are exact (whole numbers below 2^24); an output is G scaled ones, r products, a token scale and a bias in
     fp32: at most G + r + 4 roundings of 2^-24 of the sum of the magnitudes.  The bf16 output is the rounded fp32 one."""
-    print(f"[case] w4a8 medium M={M} N={N} K={K} r={r} g={g}", flush=True)
+    print(f"[case] w4a8 medium M={M} N={N} K={K} r={r} g={g} tiles={tiles}", flush=True)
+    monkeypatch.setenv("DIROTQ_W4A8_KERNEL", f"medium{tiles}")
     rng = np.random.default_rng([M, N, K, r])
     G = (K - r) // g
     xh = O.round_to_bf16(rng.standard_normal((M, r)).astype(np.float32) * 20)
