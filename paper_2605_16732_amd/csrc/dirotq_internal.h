@@ -93,7 +93,7 @@ struct RqOut {
 };
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
                            hipStream_t s);
-// few tokens: tiles of `channels` (64: not for xf or groups of 128; or 128) x `tokens` (32 or 64), K split over the
+// few tokens: tiles of `channels` (64: not for xf or groups of 128; or 128) x `tokens` (32, 64 or 96), K split over the
 // waves of a workgroup; virtual channels as in rotate_quantize.hip
 int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
                                int r_pad, int Kv, int channels, int tokens, hipStream_t s);

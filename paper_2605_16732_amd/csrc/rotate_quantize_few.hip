@@ -10,10 +10,10 @@
 // 11.0 at M = 77, 13.7 at 256; K = 12288 (302 MB of basis): 86 -> 52 at one token.  About 4.5 us are launch, first
 // load and epilogue; the rest is 45-50 B per clock and CU.
 //
-// Here a workgroup owns C channels x T tokens (64 x 32, 64 x 64 or 128 x 32) and its four waves split K: wave w takes the
-// 64-channel chunks w, w + 4, ... of the rows.  Nothing is shared between the waves, so there is no barrier in the
+// Here a workgroup owns C channels x T tokens (64 x 32, 64 x 64, 64 x 96 or 128 x 32) and its four waves split K: wave w
+// takes the 64-channel chunks w, w + 4, ... of the rows.  Nothing is shared between the waves, so there is no barrier in the
 // loop: each wave copies its chunks (C + T rows of 128 bytes) straight from global memory into its own ring of LDS
-// slots (global_load_lds, no registers and no LDS store instructions on the way), one to three chunks ahead, waits for
+// slots (global_load_lds, no registers and no LDS store instructions on the way), one or two chunks ahead, waits for
 // its own copies only, and multiplies.  The four partial sums meet in LDS, where a thread then owns 8 channels of a
 // token: the absolute maximum of a group is an exchange over 4, 8 or 16 neighbouring lanes, 8 codes are one dword.
 #include <algorithm>
@@ -38,11 +38,11 @@ template <int C, int T>                                     // channels x tokens
 struct Tile {
   static constexpr int R = C + T;                           // rows of a chunk: channels, then tokens
   static constexpr int SLOT = R * ROWB;
-  static constexpr int D = std::min(4, 160 * 1024 / (NW * SLOT));    // slots per wave
+  static constexpr int D = 160 * 1024 / (NW * SLOT);        // slots per wave
   static constexpr int NI = R / RPI;                        // 1-KB copies per chunk
   static constexpr int PROW = (C + 4) * 4;                  // bytes per token of a partial sum (padded: no bank conflicts)
   static constexpr int SMEM = std::max(NW * D * SLOT, NW * T * PROW);
-  static_assert(D >= 2 && SMEM <= 160 * 1024, "LDS");
+  static_assert((D == 2 || D == 3) && SMEM <= 160 * 1024, "LDS");
 };
 
 // QM as in rotate_quantize.hip: 0 symmetric, 1 asymmetric, 2 fp32 values and the maxima of 128-channel tiles.
@@ -112,8 +112,7 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
     const int behind = min(F::D - 1, mine - 1 - n);
     if (behind == 0) wait_copies<0>();
     else if (behind == 1) wait_copies<F::NI>();
-    else if (behind == 2) wait_copies<(F::D > 2 ? 2 * F::NI : 0)>();
-    else wait_copies<(F::D > 3 ? 3 * F::NI : 0)>();
+    else wait_copies<(F::D > 2 ? 2 * F::NI : 0)>();
     const unsigned char* sp = smem + (size_t)w * (F::D * F::SLOT) + slot * F::SLOT;
     const int steps = half_last && w + n * NW == n_chunks - 1 ? 2 : KS;  // 16-channel MFMA steps of the chunk
     bf16x8 a[KS][CI], b[KS][TI];
