@@ -1,6 +1,8 @@
 """Extreme magnitudes through the three activation quantizers (Q = I, so the rotation is exact and
 the GPU must reproduce the oracle bit for bit): scales that saturate at the largest fp16 number,
-scales that are fp16 subnormals or round to zero, and a token that mixes both ranges."""
+scales that are fp16 subnormals or round to zero, and a token that mixes both ranges.  The rows are repeated up to the
+token counts at which the launcher takes each of its kernels (on 256 CUs: few tokens, 128 x 64 with K in two halves,
+128 x 128, 256 x 128, 256 x 256, and with K = 32 mod 64 the 128 x 128 and 256 x 128 tiles of 32-channel stages)."""
 import sys
 
 import numpy as np
@@ -31,40 +33,56 @@ def _rows(K):
     return O.round_to_bf16(x)
 
 
-@pytest.mark.parametrize("g", [32, 128])
-def test_extreme_magnitudes_symmetric(g):
-    K, r = 256, 0
+SIZES = [(6, 256), (7000, 256), (9000, 256), (21000, 256), (33000, 256), (6, 288), (5000, 288), (7000, 288)]
+
+
+def _tokens(M, K):
+    """M tokens, the six rows in turn; and how to bring the oracle's result for the six to M tokens."""
     x = _rows(K)
+    idx = np.arange(M) % len(x)
+    return x, x[idx], idx
+
+
+@pytest.mark.parametrize("M,K", SIZES)
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_extreme_magnitudes_symmetric(g, M, K):
+    r = K - 256
+    x, xm, idx = _tokens(M, K)
+    print(f"[case] extremes symmetric M={M} K={K} r={r} g={g}", flush=True)
     Qt = B.prepare_rotation(dev(np.eye(K, dtype=np.float32)))
     _, qx_r, sx_r = O.split_quantize(x, r, g)
-    _, (_, qx_g, sx_g) = gpu_rotate_quantize(O.bf16_bits(x), Qt, r, g)
+    _, (_, qx_g, sx_g) = gpu_rotate_quantize(O.bf16_bits(xm), Qt, r, g)
     assert float(sx_r[0].astype(np.float32).max()) == 65504.0 and not qx_r[2].any()
-    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16))
-    np.testing.assert_array_equal(qx_g, qx_r)
+    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16)[idx])
+    np.testing.assert_array_equal(qx_g, qx_r[idx])
 
 
-@pytest.mark.parametrize("g", [32, 64])
-def test_extreme_magnitudes_asymmetric(g):
-    K, r = 256, 0
-    x = _rows(K)
+@pytest.mark.parametrize("M,K", SIZES)
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_extreme_magnitudes_asymmetric(g, M, K):
+    r = K - 256
+    x, xm, idx = _tokens(M, K)
+    print(f"[case] extremes asymmetric M={M} K={K} r={r} g={g}", flush=True)
     Qt = B.prepare_rotation(dev(np.eye(K, dtype=np.float32)))
     _, qx_r, sx_r, zx_r = O.split_quantize_asym(x, r, g)
-    _, (_, qx_g, sx_g, zx_g) = gpu_rq_asym(O.bf16_bits(x), Qt, r, g)
+    _, (_, qx_g, sx_g, zx_g) = gpu_rq_asym(O.bf16_bits(xm), Qt, r, g)
     assert float(zx_r[5].astype(np.float32).min()) == 65504.0            # zero-point saturates
-    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16))
-    np.testing.assert_array_equal(zx_g.view(np.uint16), zx_r.view(np.uint16))
-    np.testing.assert_array_equal(qx_g, qx_r)
+    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16)[idx])
+    np.testing.assert_array_equal(zx_g.view(np.uint16), zx_r.view(np.uint16)[idx])
+    np.testing.assert_array_equal(qx_g, qx_r[idx])
 
 
-def test_extreme_magnitudes_int8_tokens():
-    K, r = 256, 0
-    x = _rows(K)
+@pytest.mark.parametrize("M,K", SIZES)
+def test_extreme_magnitudes_int8_tokens(M, K):
+    r = K - 256
+    x, xm, idx = _tokens(M, K)
+    print(f"[case] extremes int8 M={M} K={K} r={r}", flush=True)
     Qt = B.prepare_rotation(dev(np.eye(K, dtype=np.float32)))
     _, qx_r, sx_r = O.split_quantize_a8(x, r)
-    _, (_, qx_g, sx_g) = gpu_rq_a8(O.bf16_bits(x), Qt, r)
+    _, (_, qx_g, sx_g) = gpu_rq_a8(O.bf16_bits(xm), Qt, r)
     assert float(sx_r[0]) == 65504.0 and not qx_r[2].any()
-    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16))
-    np.testing.assert_array_equal(qx_g, qx_r)
+    np.testing.assert_array_equal(sx_g.view(np.uint16), sx_r.view(np.uint16)[idx])
+    np.testing.assert_array_equal(qx_g, qx_r[idx])
 
 
 @pytest.mark.parametrize("M,K,g", [

@@ -1,6 +1,7 @@
 """The few-token rotation + quantization kernel (64 x 32, 64 x 64, 64 x 96 and 128 x 32 tiles, K split over the waves of a
-workgroup) against the CPU oracle.  With a signed permutation as basis the rotation is exact in any order, so bf16
-part, codes, scales and zero-points must be equal bit for bit.  The last sizes lie beyond it (the tiled kernels)."""
+workgroup) and the tiled kernels beyond it against the CPU oracle.  With a signed permutation as basis the rotation is
+exact in any order, so bf16 part, codes, scales and zero-points must be equal bit for bit.  The launcher chooses by size;
+the comments name its choice on 256 CUs (for the 4-bit quantizers)."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +16,10 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (1, 32, 0, 32), (33, 32, 32, 64), (5, 96, 32, 64), (32, 160, 64, 32), (97, 288, 96, 64), (31, 2080, 32, 64),
     (640, 1152, 64, 64), (641, 1152, 64, 32), (1300, 768, 32, 32), (300, 1152, 128, 128), (40, 384, 32, 32),
-    (2300, 768, 64, 64),
+    (1000, 1152, 64, 64), (1343, 1152, 64, 32), (4000, 288, 32, 64),                       # 64 x 96
+    (5000, 288, 32, 32), (4033, 288, 32, 64), (3000, 288, 32, 128), (6200, 224, 64, 32),     # tiled, 128 x 128, 32-channel stages
+    (7001, 288, 32, 32), (6500, 288, 32, 64), (7001, 288, 32, 128), (7001, 352, 96, 64),     # tiled, 256 x 128, 32-channel stages
+    (2300, 768, 64, 64),                                                                   # tiled, K in two halves
 ]
 
 
@@ -52,7 +56,8 @@ def test_codes_and_scales_are_exact(M, K, r, g):
     np.testing.assert_array_equal(host_bf16_bits(xh_a), O.bf16_bits(xh_r))
 
 
-@pytest.mark.parametrize("M,K,r", [(1, 32, 0), (33, 160, 64), (130, 1152, 96), (250, 1184, 128)])
+@pytest.mark.parametrize("M,K,r", [(1, 32, 0), (33, 160, 64), (130, 1152, 96), (250, 1184, 128), (3000, 288, 32),
+                                   (7001, 288, 64)])
 def test_8_bit_codes_are_exact(M, K, r):
     print(f"[case] rotate few a8 M={M} K={K} r={r}", flush=True)
     x, Q = _inputs(M, K)
