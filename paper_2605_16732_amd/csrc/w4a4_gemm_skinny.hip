@@ -165,18 +165,19 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_skinny_kernel(
       if (GS != 128 || ((idx - nb) & 1) == 0) {
         auto hi16 = [](float v) { return __builtin_bit_cast(uint32_t, v) & 0xFFFF0000u; };
         auto f = [](uint32_t b) { return __builtin_bit_cast(float, b); };
+        auto pair = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };   // the upper halves
         uint4 ca[NI], cb[NJ];
 #pragma unroll
         for (int i = 0; i < NI; i++) {
           const float v = h ? 0.0f : f16_bits_to_f32(it.sa[i]) * (float)(int16_t)it.wa[i];
           const uint32_t p1 = hi16(v), p2 = hi16(v - f(p1)), p3 = hi16(v - f(p1) - f(p2));
-          ca[i] = make_uint4(p1 >> 16 | p2, p3 >> 16 | p1, p2 >> 16 | p3, 0u);
+          ca[i] = make_uint4(pair(p1, p2), pair(p3, p1), pair(p2, p3), 0u);
         }
 #pragma unroll
         for (int j = 0; j < NJ; j++) {
           const float v = h ? 0.0f : f16_bits_to_f32(it.zb[j]);
           const uint32_t p1 = hi16(v), p2 = hi16(v - f(p1));
-          cb[j] = make_uint4(p1 >> 16 | p1, p1 >> 16 | p2, p2 >> 16 | p2, 0u);
+          cb[j] = make_uint4(pair(p1, p1), pair(p1, p2), pair(p2, p2), 0u);
         }
 #pragma unroll
         for (int i = 0; i < NI; i++)
