@@ -40,7 +40,7 @@
 #include <cstring>
 
 #include "gemm_tail.h"
-#include "pipe_plan.h"
+#include "w4a4_plan.h"
 
 namespace dirotq {
 
@@ -436,43 +436,28 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
-// Which of the schedules runs a layer.  Large symmetric layers: the pipelined kernel (persistent workgroups, 256 x 256
-// and 256 x 128 tiles).  While its plan has less than a round of large tiles the wave-specialised kernel (256 x 128) is
-// the faster one on the same half-size tiles: a round of them takes 0.61 of a round of 256 x 256 tiles (M = 2048,
-// K = N = 3072: 42 against 46 us; M = 4096, K = 1152, N = 4608: 57 against 54 us); it also runs the asymmetric layers.
-// Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).  The kernel
-// in this file (128 x 128 tiles, two workgroups per CU) spreads a medium problem over more CUs; with few tokens all
-// leave most of the chip idle and the split-K kernels (64 x 64 or 32 x 32 outputs per workgroup, the K axis over its 8
-// waves) have the shortest latency.  From about 128 tiles of 256 x 128 on the persistent kernels are the faster ones;
-// below, costs in microseconds fitted to measurements at K = 1152 ... 12288 and N = 640 ... 9216 (within 15%) decide:
-// a round of 64 x 64 workgroups (one per CU) 6.3 + 2.1 K/1000; 32 x 32 ones, several per CU, 2.5 + 0.6 K/1000 and
-// 0.0087 (longer K: 0.0037 K/1000) each; 128 x 128 tiles 6 + 8 K/1000 while there is one per CU.
-// DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny / skinny32 / skinny64 in the environment forces one of
-// them wherever it applies (the tests use it to run all of them on the same inputs; large and small: the pipelined
-// kernel with one kind of tile; skinny32 and skinny64: the split-K kernel with one of its two).
-enum class W4A4Schedule { kTile, kWs, kSkinny, kPipe };
-static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens,
-                         bool& small_tiles) {
-  sch = W4A4Schedule::kTile;
-  big_tokens = 0;
-  small_tiles = false;
-  if (K - r <= 0) return DIROTQ_OK;
+// The schedule of a layer (w4a4_plan.h).  DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny / skinny32 /
+// skinny64 in the environment forces one of them wherever it applies (the tests use it to run all of them on the same
+// inputs; large and small: the pipelined kernel with one kind of tile; skinny32 and skinny64: the split-K kernel with one
+// of its two, skinny: with the cheaper one).
+static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_failed(e);
-  const auto tiles = [&](long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); };
-  const double k = K / 1000.0;
-  const double cost64 = (double)((tiles(64, 64) + cus - 1) / cus) * (6.3 + 2.1 * k);
-  const double cost32 = 2.5 + 0.6 * k + (double)tiles(32, 32) * (k > 2.35 ? 0.0037 * k : 0.0087);
-  const double cost128 = (6.0 + 8.0 * k) * (tiles(128, 128) <= cus ? 1.0 : 1.5);
-  small_tiles = cost32 <= cost64;
-  if (const char* f = getenv("DIROTQ_W4A4_KERNEL")) {
+  if (cus < 1) cus = 1;
+  const char* f = getenv("DIROTQ_W4A4_KERNEL");
+  if (f && K > r) {
     const bool large = !strcmp(f, "large"), small = !strcmp(f, "small"), ws = !strcmp(f, "ws");
-    const bool skinny32 = !strcmp(f, "skinny32"), skinny64 = !strcmp(f, "skinny64");
-    if (!strcmp(f, "tile")) return DIROTQ_OK;
-    if (skinny32 || skinny64) small_tiles = skinny32;
-    if (skinny32 || skinny64 || !strcmp(f, "skinny")) return sch = W4A4Schedule::kSkinny, DIROTQ_OK;
+    big_tokens = 0;
+    if (!strcmp(f, "tile")) return sch = W4A4Schedule::kTile, DIROTQ_OK;
+    if (!strcmp(f, "skinny32")) return sch = W4A4Schedule::kSkinny32, DIROTQ_OK;
+    if (!strcmp(f, "skinny64")) return sch = W4A4Schedule::kSkinny64, DIROTQ_OK;
+    if (!strcmp(f, "skinny")) {
+      const w4a4_plan::Cost cost(K, r, g, asym, cus);
+      sch = cost.skinny32(M, N) <= cost.skinny64(M, N) ? W4A4Schedule::kSkinny32 : W4A4Schedule::kSkinny64;
+      return DIROTQ_OK;
+    }
     if (ws || large || small || !strcmp(f, "pipe")) {
       // (symmetric groups of 32 have no wave-specialised form, asymmetric layers no pipelined one)
       sch = asym || (ws && g != 32) ? W4A4Schedule::kWs : W4A4Schedule::kPipe;
@@ -481,16 +466,7 @@ static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Sched
       return DIROTQ_OK;
     }
   }
-  const long half_tiles = tiles(128, 256);
-  if (half_tiles >= 128) {
-    sch = W4A4Schedule::kWs;
-    if (asym) return DIROTQ_OK;
-    const long slots = cus < 8 ? 8 : cus / 8 * 8;
-    const double rounds = w4a4_pipe_plan(M, N, cus, big_tokens);
-    if (g == 32 || rounds <= 0.61 * (double)((half_tiles + slots - 1) / slots)) sch = W4A4Schedule::kPipe;
-    return DIROTQ_OK;
-  }
-  if ((small_tiles ? cost32 : cost64) < cost128) sch = W4A4Schedule::kSkinny;
+  sch = w4a4_choose(M, N, K, r, g, asym, cus, big_tokens);
   return DIROTQ_OK;
 }
 
@@ -508,15 +484,14 @@ int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, 
     // (asymmetric layers: the wave-specialised schedule, the split-K ones or this file's kernel)
     W4A4Schedule sch;
     long big_tokens;
-    bool small_tiles;
-    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens, small_tiles);
+    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens);
     if (st) return st;
     if (sch == W4A4Schedule::kPipe)
       return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, big_tokens, s);
     if (sch == W4A4Schedule::kWs)
       return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
-    if (sch == W4A4Schedule::kSkinny)
-      return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, small_tiles, s);
+    if (sch != W4A4Schedule::kTile)
+      return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, sch == W4A4Schedule::kSkinny32, s);
   }
   switch (g) {
     DIROTQ_CASE(32)

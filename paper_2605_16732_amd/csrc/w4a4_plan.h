@@ -1,0 +1,76 @@
+// Host side of kernel B: which of its schedules runs a W4A4 layer.  Plain C++: a host test compares the choice with measured
+// times of all schedules (tests/golden/w4a4_schedule_times.txt).
+#pragma once
+
+#include "pipe_plan.h"
+
+namespace dirotq {
+
+enum class W4A4Schedule { kTile, kWs, kSkinny32, kSkinny64, kPipe };
+
+namespace w4a4_plan {
+
+inline long tiles(long M, long N, long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); }
+inline double rounds(long work, long slots) { return (double)((work + slots - 1) / slots); }
+
+// Costs in microseconds of the schedules for a layer that leaves the persistent kernels part of the chip idle: k = 1024
+// 4-bit channels, q = 128 16-bit ones.  Fitted to what kernel B adds to kernel A in 7250 whole layers (graph replay over
+// three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, up to 9000 tokens, all group sizes, r up to
+// 256): 6% (tile) to 11% off, root mean square.  The numbers that depend on the kind of code stand as {groups of 64, 128, 32
+// symmetric; the same asymmetric}; ragged: rows of y that do not begin at multiples of 8 bytes are stored value by value.
+struct Cost {
+  double k, q;
+  int kind, cus;
+  Cost(int K, int r, int g, bool asym, int cus)
+      : k((K - r) / 1024.0), q(r / 128.0), kind((g == 64 ? 0 : g == 128 ? 1 : 2) + (asym ? 3 : 0)), cus(cus) {}
+  // 64 x 64 outputs, one workgroup per CU (128 KB of LDS)
+  double skinny64(long M, long N) const {
+    static constexpr double K[6] = {2.07, 2.10, 3.40, 2.80, 3.35, 5.52};
+    const long T = tiles(M, N, 64, 64);
+    const double ragged = N % 4 ? 0.93 : 0.0;
+    return 2.10 + rounds(T, cus) * (1.41 + ragged + 0.66 * q + K[kind] * k) + (double)T / cus * (2.82 + 0.09 * k + 0.42 * q);
+  }
+  // 32 x 32 outputs, two workgroups per CU (registers)
+  double skinny32(long M, long N) const {
+    static constexpr double K[6] = {0.69, 0.68, 1.60, 0.75, 0.72, 1.67}, T1[6] = {0.44, 0.46, 0.51, 0.53, 0.54, 0.83};
+    const long T = tiles(M, N, 32, 32);
+    const double ragged = N % 4 ? 0.46 : 0.0;
+    return 2.31 + 0.56 * k + rounds(T, 2L * cus) * (0.40 * q + K[kind] * k) +
+           (double)T / cus * (0.70 + ragged + T1[kind] * k + 0.32 * q);
+  }
+  // 128 x 128 tiles, at most one per CU here
+  double tile(long M, long N) const {
+    static constexpr double K[6] = {9.18, 7.57, 13.28, 11.05, 8.81, 17.04};
+    const long T = tiles(M, N, 128, 128);
+    const double busy = ((double)T / cus - 0.25) / 0.75, u = busy > 0.0 ? busy : 0.0;
+    return 4.28 + 4.15 * u + (N % 4 ? 6.11 + 7.08 * u : 0.0) + rounds(T, cus) * (1.59 * q + K[kind] * k);
+  }
+};
+
+}  // namespace w4a4_plan
+
+// Large layers, from 128 tiles of 256 x 128 on: the pipelined kernel (persistent workgroups, 256 x 256 and 256 x 128 tiles),
+// or, while its plan does not pay, the wave-specialised one (256 x 128), which also runs all asymmetric layers.  A round of
+// the latter's tiles takes 0.61 of a 256 x 256 tile's time (M = 2048, K = N = 3072: 42 against 46 us; M = 4096, K = 1152,
+// N = 4608: 57 against 54 us; 937 whole layers: 4 slower than in the wave-specialised kernel by more than 2%, none by
+// more than 3.2%).  Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).
+// Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles:
+// 0.16% (mean) above the best of the three over those 7250 layers; by counts of 64 x 64 tiles, without the 32 x 32 form, it
+// is 43% (symmetric) and 125% (asymmetric).  big_tokens: see w4a4_pipe_plan.
+inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, int cus, long& big_tokens) {
+  using namespace w4a4_plan;
+  big_tokens = 0;
+  if (K - r <= 0) return W4A4Schedule::kTile;
+  const long half_tiles = tiles(M, N, 128, 256);
+  if (half_tiles >= 128) {
+    if (asym) return W4A4Schedule::kWs;
+    const double pipe = w4a4_pipe_plan(M, N, cus, big_tokens);
+    return g == 32 || pipe <= 0.61 * rounds(half_tiles, cus < 8 ? 8 : cus / 8 * 8) ? W4A4Schedule::kPipe : W4A4Schedule::kWs;
+  }
+  const Cost cost(K, r, g, asym, cus);
+  const double c32 = cost.skinny32(M, N), c64 = cost.skinny64(M, N), c128 = cost.tile(M, N);
+  if (c32 <= c64 && c32 <= c128) return W4A4Schedule::kSkinny32;
+  return c64 <= c128 ? W4A4Schedule::kSkinny64 : W4A4Schedule::kTile;
+}
+
+}  // namespace dirotq
