@@ -13,6 +13,7 @@
 #include <cstring>
 
 #include "gemm_halves.h"
+#include "w4a16_plan.h"
 
 namespace dirotq {
 
@@ -192,16 +193,6 @@ static int launch_large_one(const uint16_t* x, const void* blob, const uint16_t*
                      per_xcd);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
-}
-
-// Token tiles per workgroup: the cheapest of 1, 2, 4 and 5, by rounds of workgroups over the CUs times a round's time
-// per step of 128 channels (0.45, 0.63, 1.15 and 1.40 us: a larger tile costs less per output, 0.45 against 0.28 per 32 x
-// 128, a smaller one leaves less of the last round empty).  N = 1152, K = 4608, us with 1 | 2 | 4 | 5 token tiles:
-// 512 tokens 23.1 | 27.3 | 41.5 | 50.3, 2048: 50.3 | 44.6 | 42.8 | 50.2, 4096: 78.6 | 68.2 | 84.3 | 55.4.
-static double tile_us(long M, long N, long K, int nj, int cus) {
-  const double step_us[6] = {0, 0.45, 0.63, 0, 1.15, 1.40};
-  const long wgs = ((M + 32 * nj - 1) / (32 * nj)) * ((N + TN_ - 1) / TN_);
-  return 4.0 + step_us[nj] * (double)((K + 127) / 128) * (double)((wgs + cus - 1) / cus);
 }
 
 template <int GS, bool OUT_F32>
@@ -438,17 +429,8 @@ int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias,
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_failed(e);
-  int nj = 1;
-  for (int c : {2, 4, 5})
-    if (w16::tile_us(M, N, K, c, cus) < w16::tile_us(M, N, K, nj, cus)) nj = c;
-  // 33 to 64 tokens: two launches of the few-token kernel are faster where K is long (the tiles walk it with one workgroup
-  // per 128 channels, the stream with one per 32) or the second one is small.  A launch takes about 3.2 us plus 0.21 us per
-  // 128 channels and round of workgroups, up to 8 tokens 0.14; the second one starts 0.7 us earlier.  Two launches | tiles,
-  // us: 1152 x 1152, 48 tokens 9.8 | 8.8; 1152 x 4608, 33 tokens 18.0 | 21.3, 48: 20.7 | 21.4; 3072 x 12288 49.7 | 51.0;
-  // 12288 x 3072 29.4 | 16.1.
-  const double rounds = (double)(((long)(N + 31) / 32 + cus - 1) / cus), steps = (K + 127) / 128;
-  const double t_few = 5.7 + (0.21 + (M <= 40 ? 0.14 : 0.21)) * steps * rounds;
-  if (!force_tile && M <= 64 && t_few < w16::tile_us(M, N, K, nj, cus)) {
+  const int nj = w16::token_tiles(M, N, K, cus);
+  if (!force_tile && w16::two_few_launches(M, N, K, g, cus)) {
     const int st = few(x, y, 32);
     return st ? st : few(x + (size_t)32 * K, (char*)y + (size_t)32 * N * (y_dtype ? 4 : 2), M - 32);
   }
