@@ -27,8 +27,8 @@ namespace dirotq {
 // Bound: not the matrix pipe alone (32 cycles x 4 per 32 x 32 tile and stage, 43 % of the time at NJ = 5) but with it the
 // sweep and decode on the VALU and 28 KB of LDS traffic per 128 x 32 tile and stage (operand reads 16 KB, copies).  The
 // kernel it replaces (128 x 128 tiles, two workgroups per CU) decoded into LDS, whose writes run at a quarter of the rate
-// of reads, and had one stage of loads in flight.  Before -> now, us: 4096 x 4608 -> 1152 (M x K -> N) 111 -> 55 (788
-// TFLOP/s), 512 tokens 88 -> 23; 4096 x 3072 -> 12288 444 -> 370; 256 x 3072 -> 3072 52 -> 17.
+// of reads, and had one stage of loads in flight.  Before -> now, us: 4096 x 4608 -> 1152 (M x K -> N) 110 -> 57 (764
+// TFLOP/s), 512 tokens 87 -> 23; 4096 x 3072 -> 12288 454 -> 385; 256 x 3072 -> 3072 51 -> 17.
 namespace w16 {
 
 using namespace halves;

@@ -14,8 +14,8 @@
 // fast the matrix pipe is (FP6 operands alone gained nothing there).  Spread over the multiplying waves the same work
 // runs in the slots between the issue of a tile's MFMAs and their results.  Bound: the VALU.  A tile of 32 x 32 and a
 // group cost 16 fma + 8 unpacking (NB = 4; 12 with NB = 2) + ~3 other instructions = 114 cycles beside 64 of MFMA; it
-// runs at 152 (VALU active 73% of the SIMD-cycles, MFMA 39%).  256 x 256 tiles because the unpacking per tile and group
-// goes with (rows staged) / (tiles multiplied).
+// runs at 152 (of the busy CUs' SIMD-cycles VALU active 74%, MFMA 39%, both at once 16%; K = 12288, N = 3072).  256 x 256
+// tiles because the unpacking per tile and group goes with (rows staged) / (tiles multiplied).
 // Measured against the wave-specialised schedule (M = 4608, us): K = 3072, N = 9216 / 3072 / 12288: 204 / 67 / 248
 // against 261 / 79 / 272; K = 12288, N = 3072: 229 against 257; M = 32768, K = 1152, N = 4608: 294 against 356; groups
 // of 32 (K = 12288, N = 3072): 443 against 543.

@@ -399,8 +399,8 @@ static int launch_one8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx
 // operands straight from global memory in the MFMA operand layout, two items' loads in flight; the eight partial sums
 // meet in LDS.  D[token][n] orientation: a lane owns an output channel, so the group's weight scale is a per-lane number
 // and one fma per accumulator applies it (no scale-product MFMA); the token's scale multiplies a wave's sum once.
-// us, graph replay, 128 x 128 tiles -> this: N = K = 3072: M = 1 39.3 -> 7.9, M = 77 40.6 -> 13.8, M = 256 41.8 -> 22.3;
-// N = 3072, K = 12288, M = 77 154 -> 37.
+// us, graph replay, 128 x 128 tiles -> this: N = K = 3072: M = 1 39.0 -> 7.6, M = 77 40.5 -> 13.6; N = 3072, K = 12288,
+// M = 77 152 -> 37.
 constexpr int FEW_NT = 512;
 
 // 4 sign-magnitude bytes -> the two planes [s 0000 aaa], [s 000 bbbb]
@@ -549,9 +549,9 @@ static int launch_few8(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx
 // operations per token tile and stage, next to 128 cycles of MFMA and the scale sweep's 16 fma: 240 cycles, plus 700 per
 // step for the weight decode, the copies and the barrier): four waves repeat that split, which is why the 128 x 128 tiles,
 // which do it once in LDS, stay ahead where they fill whole rounds.
-// us, before -> this (r = 128, g = 64): N = K = 3072: 512 tokens 39.5 -> 23.7, 1024 49.6 -> 37.6, 2048 65.0 -> 56.4;
-// N = 12288: 128 tokens 39.8 -> 23.4; K = 12288, N = 3072: 512 tokens 112 -> 74, 1024 173 -> 120; N = 3456, K = 1152: 512
-// tokens 20.1 -> 12.6.
+// us, 128 x 128 tiles -> this (r = 128, g = 64): N = K = 3072: 512 tokens 41.9 -> 23.7, 1024 47.3 -> 37.1, 2048 62.6 -> 55.1;
+// N = 12288: 128 tokens 42.2 -> 24.0; K = 12288, N = 3072: 512 tokens 174 -> 77, 1024 172 -> 120; N = 3456, K = 1152: 512
+// tokens 19.5 -> 12.3.
 namespace w8 {
 using namespace halves;
 
