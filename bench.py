@@ -3,7 +3,7 @@
 
 A "step" is one pass of the whole hot path -- rotate + split + quantize (kernel A) and
 the mixed-precision GEMM (kernel B), i.e. one dirotq_linear call -- over each of the four
-FLUX.1-dev-shaped linears of benchmark configs[2] (M = 4608 tokens: fused QKV,
+FLUX.1-dev-shaped linears (M = 4608 tokens: fused QKV,
 attention out-projection, fc1, fc2), on seeded synthetic outlier activations that are
 resident in HBM before the timed region.  value = effective TOPS = sum(2 M N K) / time,
 the dense layers the path replaces.  Prints ONE JSON line.
@@ -22,7 +22,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
-PEAK_FP8_TOPS = 5000.0         # MI355X dense fp8 MFMA (the pipe the INT4 codes run on; int8 has the same peak)
+PEAK_FP8_TOPS = 5000.0         # MI355X dense fp8 MFMA (int8 has the same peak)
+PEAK_FP6_TOPS = 10000.0        # MI355X dense FP6 MFMA: the symmetric codes of large layers run on it; fractions of kernel B
+                               # keep the fp8 peak in every workload, so that they compare
 PEAK_HBM_GBS = 8000.0
 
 
@@ -139,8 +141,8 @@ def main() -> int:
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the oracle timing leg")
     ap.add_argument("--workload", default="flux", choices=["flux", "pixart", "small", "sweep", "ablation"],
-                    help="flux = the benchmark (configs[2]); pixart/small = configs[1]/[0]; sweep = token sweep "
-                         "(configs[3]); ablation = rank/group grid on the FLUX fc2 shape (configs[4])")
+                    help="flux = the benchmark; pixart = four PixArt-Sigma-shaped layers; small = M=256, K=N=1152; "
+                         "sweep = token sweep on the PixArt fc1 shape; ablation = rank/group grid on the FLUX fc2 shape")
     ap.add_argument("--residual-rotation", action="store_true",
                     help="fold a random orthogonal rotation of the 4-bit subspace into Q (Q = [U_h, U_l R])")
     ap.add_argument("--shared-input", action="store_true",
@@ -507,14 +509,15 @@ def main() -> int:
         "metric": "effective TOPS of fused rotate+quant+W4A4 linear, FLUX shapes",
         "value": round(value, 3), "unit": "TOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "fp8 e4m3 (exact int4 codes, fp32 accumulate) + bf16 (fp32 accumulate)", "data": "synthetic",
-        "config": {"workload": {"flux": "configs[2]: FLUX.1-dev-shaped block linears, M=4608 tokens, hidden 3072, "
+        "dtype": ("fp8 e4m3" if args.a8 or args.asym else "fp6 e2m3 (large layers) or fp8 e4m3") +
+                 " (exact integer codes, fp32 accumulate) + bf16 (fp32 accumulate)", "data": "synthetic",
+        "config": {"workload": {"flux": "FLUX.1-dev-shaped block linears, M=4608 tokens, hidden 3072, "
                                         "r=128, g=64: fused QKV (N=9216), out-proj (N=3072), fc1 (N=12288), "
                                         "fc2 (K=12288, N=3072); one dirotq_linear per layer per step",
-                                "pixart": "configs[1]: PixArt-Sigma-shaped block linears, M=4096",
-                                "small": "configs[0]: M=256, K=N=1152",
-                                "sweep": "configs[3]: token sweep on the PixArt fc1 shape, M in {1024..32768}",
-                                "ablation": "configs[4]: rank/group grid on the FLUX fc2 shape"}[args.workload],
+                                "pixart": "PixArt-Sigma-shaped block linears, M=4096",
+                                "small": "M=256, K=N=1152",
+                                "sweep": "token sweep on the PixArt fc1 shape, M in {1024..32768}",
+                                "ablation": "rank/group grid on the FLUX fc2 shape"}[args.workload],
                    "seed": 0, "effective_ops_per_step": total_ops, "residual_rotation": args.residual_rotation,
                    "activation_quantizer": "int8 per token" if args.a8 else "asymmetric" if args.asym else "symmetric",
                    "shared_input": bool(args.shared_input)},
@@ -523,7 +526,8 @@ def main() -> int:
         "graph_ms_per_step": None if graph_ms is None else round(graph_ms, 4),
         "roofline": {k: (round(v, 5) if isinstance(v, float) else v) for k, v in roofline.items()},
         "kernels": other,
-        "peaks": {"datasheet": {"bf16_tflops": PEAK_BF16_TFLOPS, "fp8_tops": PEAK_FP8_TOPS, "hbm_gbs": PEAK_HBM_GBS},
+        "peaks": {"datasheet": {"bf16_tflops": PEAK_BF16_TFLOPS, "fp8_tops": PEAK_FP8_TOPS, "fp6_tops": PEAK_FP6_TOPS,
+                                 "hbm_gbs": PEAK_HBM_GBS},
                   "measured_mfma_only": measured_peaks},
         "layers": per_layer,
         "cpu_baseline": cpu,

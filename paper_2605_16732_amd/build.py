@@ -14,7 +14,7 @@ PROBE_LIB = os.path.join(HERE, "libdirotq_probe.so")     # matrix-pipe rate prob
 SOURCES = ["dirotq_abi.hip", "rotate_quantize.hip", "rotate_quantize_few.hip", "w4a4_gemm.hip", "w4a4_gemm_pipe.hip", "w4a4_gemm_ws.hip", "w4a4_gemm_skinny.hip", "w4a8_gemm.hip", "w4a16_gemm.hip", "prepare.hip"]
 
 # packed-fp32 VALU instructions are switched off on purpose (they have produced wrong
-# results on the test machines); no fast-math: the quantizer relies on IEEE division.
+# results on gfx950); no fast-math: the quantizer relies on IEEE division.
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

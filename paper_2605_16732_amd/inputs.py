@@ -49,10 +49,10 @@ def _mk(name, M, K, N, r, g, n_out, cfg, lid):
     return LayerShape(name, M, K, N, r, g, n_out, cfg, lid)
 
 
-# configs[0]: the small case the oracle finishes in seconds.
+# The small case the oracle finishes in seconds.
 SMALL = _mk("small", 256, 1152, 1152, 64, 64, 8, 0, 0)
 
-# configs[1]: PixArt-Sigma-shaped block linears, 1024 px, batch 1.
+# PixArt-Sigma-shaped block linears, 1024 px, batch 1.
 PIXART = [
     _mk("pixart_qkv", 4096, 1152, 3456, 64, 64, 8, 1, 0),
     _mk("pixart_out", 4096, 1152, 1152, 64, 64, 8, 1, 1),
@@ -60,7 +60,7 @@ PIXART = [
     _mk("pixart_fc2", 4096, 4608, 1152, 64, 64, 8, 1, 3),
 ]
 
-# configs[2]: FLUX.1-dev-shaped linears (4096 image + 512 text tokens).
+# FLUX.1-dev-shaped linears (4096 image + 512 text tokens).
 FLUX = [
     _mk("flux_qkv", 4608, 3072, 9216, 128, 64, 16, 2, 0),
     _mk("flux_out", 4608, 3072, 3072, 128, 64, 16, 2, 1),
@@ -68,13 +68,13 @@ FLUX = [
     _mk("flux_fc2", 4608, 12288, 3072, 128, 64, 16, 2, 3),
 ]
 
-# configs[3]: token sweep on the PixArt fc1 shape.
+# Token sweep on the PixArt fc1 shape.
 TOKEN_SWEEP = [
     _mk(f"pixart_fc1_M{M}", M, 1152, 4608, 64, 64, 8, 3, i)
     for i, M in enumerate((1024, 4096, 16384, 32768))
 ]
 
-# configs[4]: rank / group ablation on the FLUX fc2 shape; the pairs of the
+# Rank / group ablation on the FLUX fc2 shape; the pairs of the
 # r x g grid for which K - r is a multiple of g.
 ABLATION = [
     _mk(f"flux_fc2_r{r}_g{g}", 4608, 12288, 3072, r, g, 16, 4, i)

@@ -291,7 +291,7 @@ def test_end_to_end_small_config():
 
 
 def test_end_to_end_small_config_with_library_prepared_weights():
-    # configs[0] with the blob from dirotq_prepare_weights (W Q in fp64 on the GPU) instead of the oracle's
+    # the small layer with the blob from dirotq_prepare_weights (W Q in fp64 on the GPU) instead of the oracle's
     _end_to_end(I.SMALL, blob_from="prepare")
 
 
