@@ -149,6 +149,18 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
 }
 
+// 8 sign-magnitude nibbles of a dword -> two dwords of fp8 (E4M3) bytes [s 0000 mmm], i.e. the values +-m * 2^-9
+// (subnormals, exact): even channels, odd channels
+__device__ __forceinline__ void unpack8(uint32_t p, uint32_t& even, uint32_t& odd) {
+  even = (p & 0x07070707u) | ((p & 0x08080808u) << 4);
+  odd = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
+}
+// 8 unsigned nibbles (asymmetric activations) -> fp8 bytes 0000uuuu = u * 2^-9, exact for u = 0..15
+__device__ __forceinline__ void unpack8u(uint32_t p, uint32_t& even, uint32_t& odd) {
+  even = p & 0x0F0F0F0Fu;
+  odd = (p >> 4) & 0x0F0F0F0Fu;
+}
+
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   // round to nearest even; inputs are finite in this library
   uint32_t u = __builtin_bit_cast(uint32_t, f);

@@ -35,7 +35,8 @@ using namespace halves;
 
 // 8 sign-magnitude nibbles of a dword -> 8 bf16 numbers in channel order
 __device__ __forceinline__ bf16x8 decode(uint32_t p) {
-  const uint32_t e = (p & 0x07070707u) | ((p & 0x08080808u) << 4), o = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
+  uint32_t e, o;
+  unpack8(p, e, o);
   const uint32_t lo = __builtin_amdgcn_perm(o, e, 0x05010400u), hi = __builtin_amdgcn_perm(o, e, 0x07030602u);
   uint4 r;                                               // bytes [s 0000 mmm] = m 2^-9 as fp8, times 2^9
   r.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, false));

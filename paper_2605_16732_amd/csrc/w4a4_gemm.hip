@@ -53,25 +53,12 @@ constexpr int scale_buf_bytes(int gs) { return (BKQ / gs) * ROWS * 8; }
 constexpr int zero_off(int gs) { return SCALE_OFF + 2 * scale_buf_bytes(gs); }
 constexpr int smem_bytes(int gs) { return zero_off(gs) + 256; }
 
-// 8 sign-magnitude nibbles of a dword -> two dwords of fp8 (E4M3) bytes [s 0000 mmm], i.e. the
-// values +-m * 2^-9 (subnormals, exact): even channels, odd channels
-__device__ __forceinline__ void unpack8(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = (p & 0x07070707u) | ((p & 0x08080808u) << 4);
-  odd = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
-}
-
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 // one 32x32x64 fp8 MFMA step (no block scaling)
 __device__ __forceinline__ f32x16 mfma_fp8_k64(i32x4 a_lo, i32x4 a_hi, i32x4 b_lo, i32x4 b_hi, f32x16 c) {
   const i32x8 a = __builtin_shufflevector(a_lo, a_hi, 0, 1, 2, 3, 4, 5, 6, 7);
   const i32x8 b = __builtin_shufflevector(b_lo, b_hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-}
-
-// 8 unsigned nibbles of a dword -> two dwords of fp8 bytes 0000uuuu = u * 2^-9
-__device__ __forceinline__ void unpack8u(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = p & 0x0F0F0F0Fu;
-  odd = (p >> 4) & 0x0F0F0F0Fu;
 }
 
 template <int GS, bool OUT_F32, bool ASYM>

@@ -29,15 +29,6 @@ constexpr int smem_bytes(int ni, int nj) { return NW * ni * nj * 4 * 64 * 16; } 
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
-__device__ __forceinline__ void unpack8(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = (p & 0x07070707u) | ((p & 0x08080808u) << 4);
-  odd = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
-}
-__device__ __forceinline__ void unpack8u(uint32_t p, uint32_t& even, uint32_t& odd) {   // unsigned codes, exact for 0..15
-  even = p & 0x0F0F0F0Fu;
-  odd = (p >> 4) & 0x0F0F0F0Fu;
-}
-
 // registers of one work item: the lane's operand bytes for NI weight tiles and NJ token tiles, their scales, and (with
 // asymmetric codes) the group's code sums and zero-points
 template <int NI, int NJ>

@@ -54,18 +54,6 @@ constexpr int smem_bytes(int gs) { return out_off(gs) + NMULT * OUT_WAVE_BYTES; 
 // fall into 16 different slots of a 256-byte bank line
 __device__ __forceinline__ int stage_off(int row, int chunk) { return row * SB + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
-// 8 sign-magnitude nibbles of a dword -> two dwords of fp8 (E4M3) bytes [s 0000 mmm] = +-m * 2^-9: even, odd channels
-__device__ __forceinline__ void unpack8(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = (p & 0x07070707u) | ((p & 0x08080808u) << 4);
-  odd = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
-}
-
-// 8 unsigned nibbles (asymmetric activations) -> fp8 bytes u * 2^-9, exact for u = 0..15
-__device__ __forceinline__ void unpack8u(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = p & 0x0F0F0F0Fu;
-  odd = (p >> 4) & 0x0F0F0F0Fu;
-}
-
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
 // bf16 store of a wave's 64 x 64 block whose output channels all exist (N a multiple of 8): in the accumulator

@@ -110,12 +110,6 @@ static_assert(2 * STAGE8 >= 32768, "the 16-bit branch reuses the stages as a [25
 // weights: 16-B chunk c (0..3) of 64-byte row r at slot c ^ ((r >> 2) & 3) (4 rows share a 256-byte bank line)
 __device__ __forceinline__ int w_off_bytes(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
-// 8 sign-magnitude nibbles of a dword -> fp8 bytes [s 0000 mmm]: even channels, odd channels
-__device__ __forceinline__ void unpack8_sm(uint32_t p, uint32_t& even, uint32_t& odd) {
-  even = (p & 0x07070707u) | ((p & 0x08080808u) << 4);
-  odd = ((p >> 4) & 0x07070707u) | (p & 0x80808080u);
-}
-
 typedef __attribute__((ext_vector_type(8))) int i32x8_t;
 
 template <int GS, bool OUT_F32>
@@ -201,10 +195,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void w4a8_gemm_kernel(
       unsigned char* sb = smem + buf * STAGE8;
       if (p == 0) {
         uint4 e, o;
-        unpack8_sm(rw.x, e.x, o.x);
-        unpack8_sm(rw.y, e.y, o.y);
-        unpack8_sm(rw.z, e.z, o.z);
-        unpack8_sm(rw.w, e.w, o.w);
+        unpack8(rw.x, e.x, o.x);
+        unpack8(rw.y, e.y, o.y);
+        unpack8(rw.z, e.z, o.z);
+        unpack8(rw.w, e.w, o.w);
         *(uint4*)(sb + w_off_bytes(wrow, 2 * wblk)) = e;
         *(uint4*)(sb + w_off_bytes(wrow, 2 * wblk + 1)) = o;
       } else if (p < 3) {
