@@ -91,13 +91,13 @@ struct RqOut {
   float* xf = nullptr;
   float* pmax = nullptr;
 };
-int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
-                           hipStream_t s);
-// few tokens: tiles of `channels` (64: not for xf or groups of 128; or 128) x `tokens` (32, 64 or 96), K split over the
-// waves of a workgroup; virtual channels as in rotate_quantize.hip
+// (out.pmax becomes NULL where the maxima are not written)
+int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, RqOut& out, hipStream_t s);
+// few tokens: tiles of `channels` x `tokens`, K split over the waves of a workgroup; virtual channels as in
+// rotate_quantize.hip.  channels: a multiple of the group size, 64 or 128; fp32 output (no maxima): 32 or 64
 int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
                                int r_pad, int Kv, int channels, int tokens, hipStream_t s);
-// per-token INT8 quantization of xf [M][KL] given pmax [ceil(KL/128)][M] -> x8 [M][KL], sx [M]
+// per-token INT8 quantization of xf [M][KL] given pmax [ceil(KL/128)][M] (NULL: reads xf twice) -> x8 [M][KL], sx [M]
 int launch_quantize_tokens(const float* xf, const float* pmax, int M, int KL, uint8_t* x8, uint16_t* sx,
                            hipStream_t s);
 int launch_w4a8_gemm(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob,

@@ -643,7 +643,7 @@ static int launch_cfg(const RqOut& o, const uint16_t* x, const uint16_t* Qt, int
   return launch_one<WGC, WGT, BK, MI, 0, WVT, KSP>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, m_off, sx_ld);
 }
 
-int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o,
+int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, RqOut& o,
                            hipStream_t s) {
   // Few tokens: rotate_quantize_few.hip.  Large problems: 256 x 256 workgroup tiles (8 waves); medium: 256 channels x
   // 128 tokens (4 waves); small: 128 x 128 as 4 waves of 128 channels x 32 tokens, or 128 x 64 with K split over two
@@ -668,16 +668,24 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
     if (cus < 1) cus = 1;
   }
   // Few tokens: the split-K kernel, as long as all its workgroups are resident at once (its LDS admits one per CU); in
-  // a second round it loses (K = 3072: 11.0 / 13.7 / 16.9 us at M = 77 / 256 / 384 against 20.1 / 20.0 / 20.9 here, 30
-  // against 20 us at M = 512; K = 1152: 6.7-10 against 11 us up to M = 1280; K = 12288: 52 / 78 against 86 / 90 us at
-  // M = 1 / 77).  The smallest token tile that fits: more workgroups, each with fewer bytes to pull.
-  if (o.xf || g == 128) {
-    if ((long)((Kv + 127) / 128) * ((M + 31) / 32) <= cus)
-      return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, 128, 32, s);
+  // a second round it loses (K = 3072: 8.4 / 9.6 / 12.7 / 16.9 us at M = 1 / 77 / 256 / 384 against 20.0-20.9 here, 30
+  // against 20 us at M = 512; K = 1152: 4.9-10 against 11 us up to M = 1280).  The smallest tile that fits: more workgroups,
+  // each with fewer rows to pull (M = 77, K = 3072: 16 instead of 32 tokens 10.2 -> 9.6 us).
+  struct FewTile { int channels, tokens; };
+  auto fits = [&](FewTile t) { return (long)((Kv + t.channels - 1) / t.channels) * ((M + t.tokens - 1) / t.tokens) <= cus; };
+  if (o.xf) {
+    // no groups: any channel tile (and the 4-bit part begins right behind the 16-bit one)
+    for (FewTile t : {FewTile{32, 8}, {32, 16}, {32, 24}, {32, 32}, {64, 24}, {64, 32}, {64, 64}, {64, 96}})
+      if ((long)((K + t.channels - 1) / t.channels) * ((M + t.tokens - 1) / t.tokens) <= cus) {
+        o.pmax = nullptr;
+        return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r, K, t.channels, t.tokens, s);
+      }
+  } else if (g == 128) {
+    for (FewTile t : {FewTile{128, 8}, {128, 16}, {128, 32}})
+      if (fits(t)) return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, t.channels, t.tokens, s);
   } else {
-    for (int tokens = 32; tokens <= 96; tokens += 32)
-      if ((long)((Kv + 63) / 64) * ((M + tokens - 1) / tokens) <= cus)
-        return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, 64, tokens, s);
+    for (FewTile t : {FewTile{64, 8}, {64, 16}, {64, 24}, {64, 32}, {64, 64}, {64, 96}})
+      if (fits(t)) return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, t.channels, t.tokens, s);
   }
   if (K % 64 != 0) {
     if (mid_tiles >= 100) return launch_cfg<2, 2, 32, 32>(o, x, Qt, M, K, r, g, s);

@@ -2,20 +2,23 @@
 // equation of Section 4.2 and the quantizer of Section 3 of the paper); the same results as rotate_quantize.hip up to
 // the order of the fp32 sums.
 //
-// Bound.  With few tokens the launch is a stream over the K x K basis: what counts is how many workgroups pull at it
-// and how many bytes each has in flight (64 B per clock and CU from the L2, ~2000 clocks of latency from memory: 128
-// KB per CU).  The tiled kernel walks K stage by stage with a barrier each and one stage of loads in flight.
+// Bound.  With few tokens the launch is a stream over the K x K basis, and what counts is the rows that one workgroup
+// pulls.  Its copies are held back three times: a wave issues one per 75 clocks (so four waves fill 46 of the 64 bytes per
+// clock that the L1 gives, eight all of them), every byte is written to LDS (64 B per clock) and read from it again (128),
+// and the L2s refill at about 9 TB/s together.
 //
-// Measured (graph replay, us, tiled kernel -> this one): K = 1152: 11.0 -> 6.7 at M = 77, 7.0 at 256; K = 3072: 20.1 ->
-// 11.0 at M = 77, 13.7 at 256; K = 12288 (302 MB of basis): 86 -> 52 at one token.  About 4.5 us are launch, first
-// load and epilogue; the rest is 45-50 B per clock and CU.
+// Here a workgroup owns C channels x T tokens and its W waves split K: wave w takes the 64-channel chunks w, w + W, ... of
+// the rows.  Nothing is shared between the waves, so there is no barrier in the loop: each wave copies its chunks (C + T rows
+// of 128 bytes) straight from global memory into its own ring of LDS slots (global_load_lds, no registers and no LDS store
+// instructions on the way), one or two chunks ahead, waits for its own copies only, and multiplies.  T goes down to 8: the
+// MFMA's other token rows are not copied (its lanes read the last one).  The partial sums meet in LDS, where a thread then
+// owns 8 channels of a token: the absolute maximum of a group is an exchange over 4, 8 or 16 neighbouring lanes, 8 codes are
+// one dword.
 //
-// Here a workgroup owns C channels x T tokens (64 x 32, 64 x 64, 64 x 96 or 128 x 32) and its four waves split K: wave w
-// takes the 64-channel chunks w, w + 4, ... of the rows.  Nothing is shared between the waves, so there is no barrier in the
-// loop: each wave copies its chunks (C + T rows of 128 bytes) straight from global memory into its own ring of LDS
-// slots (global_load_lds, no registers and no LDS store instructions on the way), one or two chunks ahead, waits for
-// its own copies only, and multiplies.  The four partial sums meet in LDS, where a thread then owns 8 channels of a
-// token: the absolute maximum of a group is an exchange over 4, 8 or 16 neighbouring lanes, 8 codes are one dword.
+// Measured (graph replay, us; four waves and 32 tokens or more -> now): K = 1152: 6.2 -> 4.9 at M = 1 and 64, 6.2 -> 5.2 at
+// 256; K = 3072: 10.6 -> 8.4 at M = 1, 10.9 -> 9.6 at 77; K = 12288 (302 MB of basis): 65 -> 55.  fp32 output with its
+// quantizer (128 x 32 tiles -> 32 x 8 to 32 x 32): K = 1152, M = 1 9.2 -> 5.8; K = 3072: M = 1 15.8 -> 9.3, M = 77 17.3 ->
+// 12.6; K = 12288, M = 1 93 -> 60.  Of this 1.7 us are launch, 0.4 arguments and addresses, 1.1 exchange and quantizer.
 #include <algorithm>
 #include <atomic>
 
@@ -25,7 +28,6 @@ namespace dirotq {
 
 namespace few {
 
-constexpr int NW = 4, NT = NW * 64;
 constexpr int KC = 64, KS = KC / 16;                         // channels of a chunk, its MFMA steps
 constexpr int ROWB = KC * 2, CPR = KC / 8;                  // bytes and 16-byte pieces of a row and chunk (32 channels,
 constexpr int RPI = 1024 / ROWB;                            // 64-byte rows: slower on every shape); rows per 1-KB copy
@@ -34,25 +36,26 @@ constexpr int RPI = 1024 / ROWB;                            // 64-byte rows: slo
 // 16-byte slots of a 256-byte bank line
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
-template <int C, int T>                                     // channels x tokens of a workgroup
+template <int C, int T, int W>                              // channels x tokens of a workgroup, waves
 struct Tile {
+  static constexpr int NT = W * 64;
   static constexpr int R = C + T;                           // rows of a chunk: channels, then tokens
   static constexpr int SLOT = R * ROWB;
-  static constexpr int D = 160 * 1024 / (NW * SLOT);        // slots per wave
+  static constexpr int D = std::min(160 * 1024 / (W * SLOT), 3);   // slots per wave
   static constexpr int NI = R / RPI;                        // 1-KB copies per chunk
   static constexpr int PROW = (C + 4) * 4;                  // bytes per token of a partial sum (padded: no bank conflicts)
-  static constexpr int SMEM = std::max(NW * D * SLOT, NW * T * PROW);
-  static_assert((D == 2 || D == 3) && SMEM <= 160 * 1024, "LDS");
+  static constexpr int SMEM = std::max(W * D * SLOT, W * T * PROW);
+  static_assert(T % RPI == 0 && (T < 32 || T % 32 == 0) && D >= 1 && D <= 3 && SMEM <= 160 * 1024, "LDS");
 };
 
-// QM as in rotate_quantize.hip: 0 symmetric, 1 asymmetric, 2 fp32 values and the maxima of 128-channel tiles.
-template <int C, int T, int QM>
-__global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
+// QM as in rotate_quantize.hip: 0 symmetric, 1 asymmetric, 2 fp32 values (without the maxima: the quantizer reads twice).
+template <int C, int T, int W, int QM>
+__global__ __launch_bounds__(W * 64, 1) void rotate_quantize_few_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ Qt, int M, int K, int r, int g,
     uint16_t* __restrict__ xh, uint8_t* __restrict__ xl, uint16_t* __restrict__ sx, uint16_t* __restrict__ zx,
-    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int n_ct, int n_tt, int per_xcd) {
-  using F = Tile<C, T>;
-  constexpr int CI = C / 32, TI = T / 32;
+    float* __restrict__ xf, int r_pad, int n_ct, int n_tt, int per_xcd) {
+  using F = Tile<C, T, W>;
+  constexpr int CI = C / 32, TI = (T + 31) / 32, NT = F::NT;
   extern __shared__ __align__(16) unsigned char smem[];
   // consecutive workgroup ids go to different XCDs: each XCD gets a run of channel tiles with all their token tiles, so
   // that a basis row is read from memory by one XCD only
@@ -78,11 +81,18 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
   const unsigned char* xbase = (const unsigned char*)(x + (size_t)m0 * K);
   const uint32_t ring = lds_address(smem) + w * (F::D * F::SLOT);
   const int n_chunks = (K + KC - 1) / KC;
-  const int mine = (n_chunks - w + NW - 1) / NW;                      // chunks of this wave
+  const int mine = (n_chunks - w + W - 1) / W;                      // chunks of this wave
   // (a last chunk of 32 channels: its upper half would lie past the row's end; it is read from the lower one, unused)
   const bool half_last = (K & 63) != 0;
+  // each channel tile begins somewhere else in K: with rows of a multiple of 4 KB all rows of a chunk lie in one or two of
+  // the L2's channels (K = 12288, M = 1: 60 -> 55 us; larger token tiles share their tokens in the L2 and stay in step)
+  const int turn = T > 32 ? 0 : logical / n_tt % 8 * n_chunks / 8;   // (below n_chunks)
+  auto chunk = [&](int n) {
+    const int k = w + n * W + turn;
+    return k >= n_chunks ? k - n_chunks : k;
+  };
   auto issue = [&](int n, int slot) {                                 // this wave's n-th chunk
-    const int k = (w + n * NW);
+    const int k = chunk(n);
     const size_t off = (size_t)k * ROWB;
     const bool cut = half_last && k == n_chunks - 1;
     const uint32_t lds = ring + slot * F::SLOT;
@@ -106,6 +116,7 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
   for (int n = 0; n < F::D; n++)
     if (n < mine) issue(n, n);
   const int lrow = l & 31, h = l >> 5, sw = swz(lrow);         // (tile bases are multiples of 32 rows)
+  const int trow = min(lrow, T - 1), swt = swz(trow);         // (tokens past the copied rows: results not used)
   int slot = 0;
   for (int n = 0; n < mine; n++) {
     // chunk n has landed when only the copies of the chunks behind it are in flight
@@ -114,15 +125,15 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
     else if (behind == 1) wait_copies<F::NI>();
     else wait_copies<(F::D > 2 ? 2 * F::NI : 0)>();
     const unsigned char* sp = smem + (size_t)w * (F::D * F::SLOT) + slot * F::SLOT;
-    const int steps = half_last && w + n * NW == n_chunks - 1 ? 2 : KS;  // 16-channel MFMA steps of the chunk
+    const int steps = half_last && chunk(n) == n_chunks - 1 ? 2 : KS;  // 16-channel MFMA steps of the chunk
     bf16x8 a[KS][CI], b[KS][TI];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      const int at = ((2 * ks + h) ^ sw) << 4;
+      const int at = ((2 * ks + h) ^ sw) << 4, att = ((2 * ks + h) ^ swt) << 4;
 #pragma unroll
       for (int i = 0; i < CI; i++) a[ks][i] = *(const bf16x8*)(sp + (i * 32 + lrow) * ROWB + at);
 #pragma unroll
-      for (int j = 0; j < TI; j++) b[ks][j] = *(const bf16x8*)(sp + (C + j * 32 + lrow) * ROWB + at);
+      for (int j = 0; j < TI; j++) b[ks][j] = *(const bf16x8*)(sp + (C + j * 32 + trow) * ROWB + att);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // the slot has been read: it may be filled again
     if (n + F::D < mine) issue(n + F::D, slot);
@@ -145,20 +156,21 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
     for (int j = 0; j < TI; j++)
 #pragma unroll
       for (int q = 0; q < 4; q++)
-        *(float4*)(smem + (w * T + j * 32 + lrow) * F::PROW + (i * 32 + 8 * q + 4 * h) * 4) =
+        if (T >= 32 || lrow < T) *(float4*)(smem + (w * T + j * 32 + lrow) * F::PROW + (i * 32 + 8 * q + 4 * h) * 4) =
             make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
   __syncthreads();
   // thread: 8 channels of a token; C / 8 neighbouring lanes hold a token's C channels
-  constexpr int LPT = C / 8, PASSES = T * LPT / NT;
+  constexpr int LPT = C / 8, TASKS = T * LPT, PASSES = (TASKS + NT - 1) / NT;
   const int part = t % LPT, KL = K - r;
   const int v = v0 + part * 8;                                        // first virtual channel of the thread
   const int cl = v - r_pad;                                           // first 4-bit channel (negative: 16-bit part)
 #pragma unroll
   for (int p = 0; p < PASSES; p++) {
+    if (TASKS % NT != 0 && p * NT + t >= TASKS) break;                // (whole tokens)
     const int tok = p * (NT / LPT) + t / LPT, m = m0 + tok;
     float f[8];
 #pragma unroll
-    for (int ww = 0; ww < NW; ww++) {
+    for (int ww = 0; ww < W; ww++) {
       const float4* src = (const float4*)(smem + (ww * T + tok) * F::PROW + part * 32);
       const float4 lo = src[0], hi = src[1];
       const float u[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -177,17 +189,10 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
     }
     const bool valid = cl >= 0 && cl < KL && m < M;
     if constexpr (QM == 2) {
-      // (the 4-bit part begins at a multiple of 128 virtual channels here, so C = 128 channels are one tile of maxima)
-      float a = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; e++) a = fmaxf(a, cl < KL ? fabsf(f[e]) : 0.0f);
-#pragma unroll
-      for (int o = 1; o < LPT; o <<= 1) a = fmaxf(a, __shfl_xor(a, o));
       if (valid) {
         float4* d = (float4*)(xf + (size_t)m * KL + cl);
         d[0] = make_float4(f[0], f[1], f[2], f[3]);
         d[1] = make_float4(f[4], f[5], f[6], f[7]);
-        if (part == 0) pmax[(size_t)(cl >> 7) * M + m] = a;
       }
     } else {
       // maximum (and minimum) over the group's 4, 8 or 16 lanes (the absolute maximum from 0 on: a group of NaN has scale 0)
@@ -223,45 +228,60 @@ __global__ __launch_bounds__(NT, 1) void rotate_quantize_few_kernel(
   }
 }
 
-template <int C, int T, int QM>
+template <int C, int T, int W, int QM>
 static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o, int r_pad,
                       int Kv, hipStream_t s) {
+  using F = Tile<C, T, W>;
   const int n_ct = (Kv + C - 1) / C, n_tt = (M + T - 1) / T;
   const int per_xcd = (n_ct * n_tt + 7) / 8;
   // (idempotent: two threads racing here would both set the same attribute)
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)rotate_quantize_few_kernel<C, T, QM>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, Tile<C, T>::SMEM);
+    hipError_t e = hipFuncSetAttribute((const void*)rotate_quantize_few_kernel<C, T, W, QM>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, F::SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((rotate_quantize_few_kernel<C, T, QM>), dim3(per_xcd * 8), dim3(NT), (Tile<C, T>::SMEM), s, x, Qt, M,
-                     K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, r_pad, n_ct, n_tt, per_xcd);
+  hipLaunchKernelGGL((rotate_quantize_few_kernel<C, T, W, QM>), dim3(per_xcd * 8), dim3(F::NT), F::SMEM, s, x, Qt, M,
+                     K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, r_pad, n_ct, n_tt, per_xcd);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
-template <int C, int T>
+template <int C, int T, int W>
 static int launch_tile(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o, int r_pad,
                        int Kv, hipStream_t s) {
-  if (o.xf) {
-    if constexpr (C == 128) return launch_one<C, T, 2>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
-    return DIROTQ_ERR_UNSUPPORTED;
+  if constexpr (C < 128) {
+    if (o.xf) return launch_one<C, T, W, 2>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
   }
-  if (o.zx) return launch_one<C, T, 1>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
-  return launch_one<C, T, 0>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+  if constexpr (C > 32) {
+    if (o.zx) return launch_one<C, T, W, 1>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+    if (!o.xf) return launch_one<C, T, W, 0>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+  }
+  return DIROTQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace few
 
 int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o,
                                int r_pad, int Kv, int channels, int tokens, hipStream_t s) {
-  if (channels == 64)
-    return tokens == 32   ? few::launch_tile<64, 32>(x, Qt, M, K, r, g, o, r_pad, Kv, s)
-           : tokens == 64 ? few::launch_tile<64, 64>(x, Qt, M, K, r, g, o, r_pad, Kv, s)
-                          : few::launch_tile<64, 96>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
-  return few::launch_tile<128, 32>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
+#define DIROTQ_FEW(C, T, W) \
+  if (channels == C && tokens == T) return few::launch_tile<C, T, W>(x, Qt, M, K, r, g, o, r_pad, Kv, s)
+  DIROTQ_FEW(32, 8, 8);
+  DIROTQ_FEW(32, 16, 8);
+  DIROTQ_FEW(32, 24, 8);
+  DIROTQ_FEW(32, 32, 8);
+  DIROTQ_FEW(64, 8, 8);
+  DIROTQ_FEW(64, 16, 8);
+  DIROTQ_FEW(64, 24, 6);
+  DIROTQ_FEW(64, 32, 6);
+  DIROTQ_FEW(64, 64, 4);
+  DIROTQ_FEW(64, 96, 4);
+  DIROTQ_FEW(128, 8, 8);
+  DIROTQ_FEW(128, 16, 4);
+  DIROTQ_FEW(128, 32, 4);
+#undef DIROTQ_FEW
+  return DIROTQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace dirotq

@@ -46,7 +46,16 @@ __global__ __launch_bounds__(256) void quantize_tokens_kernel(const float* __res
   const int m = blockIdx.x * (4 / WPT) + threadIdx.x / LANES;
   const int n_tiles = (KL + 127) / 128, mc = min(m, M - 1);
   float a = 0.0f;
-  for (int i = t; i < n_tiles; i += LANES) a = fmaxf(a, pmax[(size_t)i * M + mc]);
+  if (pmax) {
+    for (int i = t; i < n_tiles; i += LANES) a = fmaxf(a, pmax[(size_t)i * M + mc]);
+  } else {
+    const float4* row = (const float4*)(xf + (size_t)mc * KL);
+#pragma unroll 4
+    for (int i = t; i < KL / 4; i += LANES) {
+      const float4 v = row[i];
+      a = fmaxf(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))), a);
+    }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
   if constexpr (WPT == 4) {

@@ -1,0 +1,62 @@
+"""Every tile of the few-token rotation + quantization kernel, at the token counts on both sides of each switch (256 CUs:
+the smallest token tile whose workgroups are all resident), with whole and half last chunks of K.  The basis is a signed
+permutation, so all results must equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dirotq_oracle as O
+from paper_2605_16732_amd import binding as B
+
+from gpu_util import dev, dev_bf16, gpu_rotate_quantize, host_bf16_bits, host_f16
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(M, K):
+    rng = np.random.default_rng([M, K, 3])
+    Q = np.zeros((K, K), np.float32)
+    Q[rng.permutation(K), np.arange(K)] = rng.choice([-1.0, 1.0], size=K)
+    x = O.round_to_bf16((rng.standard_normal((M, K)) * rng.lognormal(0, 1.5, size=(1, K))).astype(np.float32))
+    return x, Q
+
+
+# 18 channel tiles of 64: 8, 16, 24, 32, 64 and 96 tokens up to 14 token tiles each; 9 of 128: 8, 16 and 32 up to 28
+@pytest.mark.parametrize("M,K,r,g", [(M, K, r, 64) for M in (7, 8, 9, 112, 113, 224, 225, 336, 337, 448, 449, 896, 897)
+                                     for K, r in ((1152, 64), (1120, 32))]
+                         + [(M, 1152, 128, 128) for M in (8, 9, 224, 225, 448, 449)] + [(77, 3104, 32, 64), (3, 4128, 32, 128)])
+def test_codes_and_scales_are_exact(M, K, r, g):
+    print(f"[case] rotate few tiles M={M} K={K} r={r} g={g}", flush=True)
+    x, Q = _inputs(M, K)
+    Qt = B.prepare_rotation(dev(Q))
+    xhat = O.rotate(x, Q)
+    _, (xh, qx, sx) = gpu_rotate_quantize(O.bf16_bits(x), Qt, r, g)
+    xh_r, qx_r, sx_r = O.split_quantize(xhat, r, g)
+    np.testing.assert_array_equal(xh, xh_r)
+    np.testing.assert_array_equal(sx.view(np.uint16), sx_r.view(np.uint16))
+    np.testing.assert_array_equal(qx, qx_r)
+    _, xl_a, sx_a, zx_a = B.rotate_quantize_asym(dev_bf16(O.bf16_bits(x)), Qt, r, g)
+    torch.cuda.synchronize()
+    _, qx_r, sx_r, zx_r = O.split_quantize_asym(xhat, r, g)
+    p = xl_a.cpu().numpy()
+    np.testing.assert_array_equal(np.stack([p & 15, p >> 4], axis=-1).reshape(M, K - r), qx_r)
+    np.testing.assert_array_equal(host_f16(sx_a).T.view(np.uint16), sx_r.view(np.uint16))
+    np.testing.assert_array_equal(host_f16(zx_a).T.view(np.uint16), zx_r.view(np.uint16))
+
+
+# 8 bits: 36 channel tiles of 32 with 8, 16, 24 or 32 tokens up to 7 token tiles, then 18 of 64 with 24, 32, 64 or 96 up
+# to 14; beyond, the kernel that writes the maxima; the 4-bit part begins inside a tile of 64 (r = 32)
+@pytest.mark.parametrize("M,r", [(M, r) for M in (1, 56, 57, 112, 113, 168, 169, 224, 225, 336, 337, 448, 449, 896, 897, 1344, 1345)
+                                 for r in (0, 32)])
+def test_8_bit_codes_are_exact(M, r):
+    K = 1152 if r == 0 else 1120
+    print(f"[case] rotate few tiles a8 M={M} K={K} r={r}", flush=True)
+    x, Q = _inputs(M, K)
+    xh, x8, sx = B.rotate_quantize_a8(dev_bf16(O.bf16_bits(x)), B.prepare_rotation(dev(Q)), r)
+    torch.cuda.synchronize()
+    xh_r, qx_r, sx_r = O.split_quantize_a8(O.rotate(x, Q), r)
+    b = x8.cpu().numpy().astype(np.int32).reshape(M, (K - r) // 32, 2, 16)   # blocks of 32: even channels, odd ones
+    q = np.where(b & 0x80, -(b & 0x7F), b).transpose(0, 1, 3, 2).reshape(M, K - r)
+    np.testing.assert_array_equal(q, qx_r)
+    np.testing.assert_array_equal(host_f16(sx).view(np.uint16), np.asarray(sx_r).reshape(-1).view(np.uint16))
+    np.testing.assert_array_equal(host_bf16_bits(xh), O.bf16_bits(xh_r))
