@@ -91,7 +91,9 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # handle of the current device's current stream; torch.cuda.current_stream() builds a Stream object first, a quarter of
+    # what the host needs for a small layer (2.8 us against 0.3)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _size(fn_name: str, *ints) -> int:
@@ -185,9 +187,8 @@ def w4a4_gemm(xh, xl, sx, blob, M, N, K, r, g, bias=None, out_dtype=torch.bfloat
 
 def linear(x, Qt, blob, N, r, g, bias=None, workspace=None, out=None):
     M, K = x.shape
-    nws = workspace_bytes(M, K, r, g)
     if workspace is None:
-        workspace = _new((nws,), torch.uint8, x)
+        workspace = _new((workspace_bytes(M, K, r, g),), torch.uint8, x)
     y = out if out is not None else _new((M, N), torch.bfloat16, x)
     _check(lib().dirotq_linear(_ptr(x), _ptr(Qt), _ptr(blob), _ptr(bias), M, N, K, r, g, _ptr(y),
                                _ptr(workspace), workspace.numel(), _stream()), "dirotq_linear")
@@ -232,9 +233,8 @@ def w4a4_gemm_asym(xh, xl, sx, zx, blob, M, N, K, r, g, bias=None, out_dtype=tor
 
 def linear_asym(x, Qt, blob, N, r, g, bias=None, workspace=None, out=None):
     M, K = x.shape
-    nws = workspace_bytes(M, K, r, g)
     if workspace is None:
-        workspace = _new((nws,), torch.uint8, x)
+        workspace = _new((workspace_bytes(M, K, r, g),), torch.uint8, x)
     y = out if out is not None else _new((M, N), torch.bfloat16, x)
     _check(lib().dirotq_linear_asym(_ptr(x), _ptr(Qt), _ptr(blob), _ptr(bias), M, N, K, r, g, _ptr(y),
                                     _ptr(workspace), workspace.numel(), _stream()), "dirotq_linear_asym")
