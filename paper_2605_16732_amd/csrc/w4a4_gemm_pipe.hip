@@ -32,6 +32,7 @@
 #include "gemm_tail.h"
 #include "pipe_plan.h"
 #include "pipe_stage.h"
+#include "pipe_unpack.h"
 
 namespace dirotq {
 
@@ -49,22 +50,6 @@ constexpr int slot_bytes(int nb, int gs) { return rows(nb) * SB + scale_bytes(gs
 constexpr int OUT_ROW = 144, OUT_WAVE_BYTES = 32 * OUT_ROW;
 constexpr int out_off(int nb, int gs) { return NBUF * slot_bytes(nb, gs); }
 constexpr int smem_bytes(int nb, int gs) { return out_off(nb, gs) + 8 * OUT_WAVE_BYTES; }
-
-// 16 sign-magnitude nibbles (two dwords) -> 16 FP6 numbers [s 00 mmm] in three dwords.  Six-bit field f takes a nibble
-// that one of the shifts 0, +2, +4 over the 64-bit pair brings there (16 instructions); the order that results is the
-// same for weights and tokens, so a dot product does not see it.
-__device__ __forceinline__ void unpack16_fp6(uint32_t p0, uint32_t p1, uint32_t (&d)[3]) {
-  auto and_or = [](uint32_t v, uint32_t mask, uint32_t o) -> uint32_t {   // (the compiler would build it from four
-    uint32_t r;                                                           // instructions per three terms)
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(o));
-    return r;
-  };
-  const uint32_t s2 = p0 << 2, s4 = p0 << 4;
-  const uint32_t t2 = __builtin_amdgcn_alignbit(p1, p0, 30), t4 = __builtin_amdgcn_alignbit(p1, p0, 28);
-  d[0] = and_or(s4, 0x00800800u, and_or(s2, 0xE01E01E0u, p0 & 0x07007007u));
-  d[1] = and_or(t4, 0x08008008u, and_or(t2, 0x01E01E01u, p1 & 0x70070070u));
-  d[2] = and_or(t4, 0x80080080u, and_or(t2, 0x1C01C01Cu, and_or(s2, 0x02002000u, and_or(p0, 0x00700700u, (p1 >> 30) & 2u))));
-}
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(2))) int i32x2;

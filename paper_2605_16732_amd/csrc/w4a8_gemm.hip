@@ -770,7 +770,7 @@ static int launch_medium(const uint16_t* xh, const uint8_t* x8, const uint16_t* 
 // two workgroups fit a CU), per step of 128 channels.  N = K = 3072, us with 1 | 2 | 4: 512 tokens 28.3 | 23.7 | 35.2,
 // 1024: 39.7 | 38.6 | 37.6, 2048: 74.3 | 56.4 | 71.2, 4096: 136 | 109 | 107 (128 x 128 tiles: 39.5, 49.6, 65.0, 109).
 // The 128 x 128 tiles: two workgroups per CU in a round, 4 + 13.6 K/1000 if it has at most one each, 7.2 + 18 K/1000 beyond.
-// DIROTQ_W4A8_KERNEL=few1 / few2 / medium1 / medium2 / medium4 / tile in the environment forces one of them, with that many
+// DIROTQ_W4A8_KERNEL=few1 / few2 / medium1 / medium2 / medium4 / tile / pipe in the environment forces one of them, with that many
 // token tiles per workgroup (the tests use it to run all of them on the same inputs).
 static double medium_us(long M, long N, long steps, int nj, int cus) {
   const long wgs = ((M + 32 * nj - 1) / (32 * nj)) * ((N + 127) / 128);
@@ -778,6 +778,19 @@ static double medium_us(long M, long N, long steps, int nj, int cus) {
   if (nj == 1) return 5.4 + 0.55 * st + more * (1.0 + 0.44 * st);
   if (nj == 2) return 6.2 + 0.70 * st + more * (2.5 + 0.63 * st);
   return (1.0 + more) * (8.0 + 1.17 * st);
+}
+
+// The pipelined kernel (w4a8_gemm_pipe.hip; groups of 64 and 128): rounds of 256 x 256 tiles, 1.38 us per 64 8-bit channels and
+// 0.6 per 16 16-bit ones, up to 18% more on a chip that is full (power, the stores of all workgroups at once).  5% off, root mean
+// square, over 170 layers of 90 to 1200 tiles; the other schedules' estimate is 11% off, hence the 5% that it has to be
+// ahead: in those 170 it is then chosen where it is faster, but for 2.6% in one, and all but 1% of what it can give is taken
+// (16% on average, up to 1.4 times).  M = 4096, us: N = 3456, K = 1152 56 -> 45; N = K = 3072 109 -> 89; N = 12288 and M = 4608
+// 434 -> 348.
+static double pipe_us(long M, long N, long K, long r, int cus) {
+  const long tiles = ((M + 255) / 256) * ((N + 255) / 256), rounds = (tiles + cus - 1) / cus;
+  const double fill = (double)tiles / ((double)rounds * cus);
+  const double nq = (double)(((K - r + 63) / 64 + 1) / 2 * 2);
+  return (3.0 + (double)rounds * (9.0 + 1.38 * nq + 0.6 * (double)(r / 16))) * (1.0 + 0.18 * fill * fill);
 }
 
 template <int GS, bool OUT_F32>
@@ -805,11 +818,14 @@ static int launch_case8(const uint16_t* xh, const uint8_t* x8, const uint16_t* s
   }
   int few_nj = 0;                                        // 0: not the split-K kernel
   if (t128 <= 2L * cus && few < tiled) few_nj = K >= 8192 && M > 32 && t32 >= 256 ? 2 : 1;
+  bool pipe = GS != 32 && K > r && !few_nj && pipe_us(M, N, K, r, cus) < 0.95 * tiled;
   if (const char* f = getenv("DIROTQ_W4A8_KERNEL")) {
     if (!strcmp(f, "few1") || !strcmp(f, "few2")) few_nj = f[3] - '0';
     if (!strcmp(f, "medium1") || !strcmp(f, "medium2") || !strcmp(f, "medium4")) few_nj = 0, nj = f[6] - '0';
     if (!strcmp(f, "tile")) few_nj = nj = 0;
+    pipe = !strcmp(f, "pipe") && GS != 32 && K > r;
   }
+  if (pipe) return launch_w4a8_gemm_pipe(xh, x8, sx, blob, bias, M, N, K, r, g, y, OUT_F32, cus, s);
   if (few_nj == 1) return launch_few8<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   if (few_nj == 2) return launch_few8<GS, OUT_F32, 2>(xh, x8, sx, blob, bias, M, N, K, r, y, s);
   if (nj == 1) return w8::launch_medium<GS, OUT_F32, 1>(xh, x8, sx, blob, bias, M, N, K, r, y, s);

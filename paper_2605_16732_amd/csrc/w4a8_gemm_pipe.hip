@@ -1,0 +1,390 @@
+// W4A8 GEMM, large schedule: y = x_h W'_h^T + s_x[m] sum_j s_w[n,j] (q8_x,j q4_w,j^T), groups of 64 or 128 channels.
+//
+// Arithmetic.  An INT8 code is sign (16 a + b): its high nibble [s aaa] and [s bbbb] are exact FP6 (E2M3) numbers, [s 00 aaa]
+// = a 2^-3 and [s 0 bbbb] = b 2^-3 (the first binade continues the subnormals linearly).  Two block-scaled 32x32x64 MFMAs, the
+// first with 2^4 more on its activations, return the exact integer dot of 64 channels in 70 cycles; as fp8 planes, which
+// the other schedules use, they take 128.  D[token][n] orientation: a lane owns an output channel, so the group's weight
+// scale is a per-lane number and one fma per accumulator applies it; the token's scale multiplies the sums once, between the
+// 8-bit stages and the 16-bit ones.
+//
+// Schedule: the one of the pipelined W4A4 kernel (w4a4_gemm_pipe.hip).  Eight waves, two per SIMD, that both stage and
+// multiply: 128 output channels x 64 tokens each, 256 x 256 per workgroup (a wave reads 12 KB of operands a stage; as 64 x
+// 128 it would be 15).  In interval s the waves multiply stage s, read the first operands of stage s+1, write stage s+2
+// into the LDS ring (three slots) and load stage s+4 into the registers that this frees; one barrier per interval;
+// persistent workgroups, the stage stream continuous across a workgroup's tiles.
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+#include "dirotq_internal.h"
+#include "pipe_stage.h"
+#include "pipe_unpack.h"
+
+namespace dirotq {
+
+namespace pipe8 {
+
+using pipe::hi_off;
+using pipe::row_part;
+using pipe::RowPart;
+using pipe::SB;
+
+constexpr int NT = 512, NBUF = 3, TN_ = 256, TM_ = 256;
+constexpr int XB = 128;                      // bytes per token row and stage: per 32 channels the plane of a, then of b
+constexpr int X_OFF = TN_ * SB, SCALE_OFF = X_OFF + TM_ * XB;
+constexpr int SLOT = SCALE_OFF + 512 * 4;    // (scales as fp32; the upper half takes the stores of the waves that have none)
+static_assert(SLOT >= 8 * 16 * 272, "finished rows pass through a slot");
+constexpr int SX_OFF = NBUF * SLOT, SMEM = SX_OFF + TM_ * 4;
+static_assert(SMEM <= 160 * 1024, "LDS");
+
+// 16-byte chunk c of token row r at slot c ^ ((r >> 1) & 7): 16 consecutive rows fall into 16 slots of a 256-byte bank line
+__device__ __forceinline__ int x_off(int row, int chunk) { return row * XB + ((chunk ^ ((row >> 1) & 7)) << 4); }
+
+typedef __attribute__((ext_vector_type(8))) int i32x8;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+#define GLOBAL __attribute__((address_space(1)))
+typedef const GLOBAL uint8_t* gptr;
+
+__device__ __forceinline__ void tile_origin(int logical, int n_mt, int n_nt, int& m0, int& n0) {
+  constexpr int GN = 4;
+  const int grp = logical / (GN * n_mt), in_grp = logical % (GN * n_mt), gn = min(n_nt - grp * GN, GN);
+  n0 = (grp * GN + in_grp % gn) * TN_;
+  m0 = (in_grp / gn) * TM_;
+}
+
+template <int GS, bool OUT_F32>
+__global__ __launch_bounds__(NT, 2) void w4a8_gemm_pipe_kernel(
+    const uint16_t* __restrict__ xh, const uint8_t* __restrict__ x8, const uint16_t* __restrict__ sx,
+    const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
+    const uint16_t* __restrict__ bias, int M, int N, int K, int r, void* __restrict__ y, int wpx) {
+  static_assert(GS == 64 || GS == 128, "group size");
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int n_mt = (M + TM_ - 1) / TM_, n_nt = (N + TN_ - 1) / TN_;
+  const int per_xcd = (n_mt * n_nt + 7) / 8;
+  const int run0 = (blockIdx.x & 7) * per_xcd, first = blockIdx.x >> 3;
+  const int run_len = min(per_xcd, n_mt * n_nt - run0);
+  if (first >= run_len) return;
+  const int T = (run_len - first + wpx - 1) / wpx;                    // tiles of this workgroup (>= 1)
+
+  const int t = threadIdx.x, l = t & 63, h = l >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wn = w & 1, wt = w >> 1;
+  const int KL = K - r, G = KL / GS;                                  // (KL > 0, a multiple of 64)
+  // stages of a tile: 8-bit (padded to an even number: the extra one has zero scales), then 16-bit (an even number)
+  const int nq_real = KL / 64, nq = (nq_real + 1) / 2 * 2, nbf = r / 16, nst = nq + nbf;
+  const int ldq = KL / 2;
+
+  // ---- staging role: 16-byte half (t & 1) of weight row t >> 1, 32 bytes of token row t >> 1, the scale of weight row t
+  const int half = t & 1, srow = t >> 1;
+  const RowPart part_w = row_part<64>(srow, half);
+  const int xa = X_OFF + x_off(srow, 4 * half), xa_hi = X_OFF + x_off(srow, 4 * half + 1) + 8 * ((srow >> 4) & 1);
+  const int xb = X_OFF + x_off(srow, 4 * half + 2), xb_hi = X_OFF + x_off(srow, 4 * half + 3) + 8 * ((srow >> 4) & 1);
+
+  gptr wq_b, x8_b, wh_b, xh_b, sc_b;
+  uint32_t row_w, row_x, vos;
+  int lt = 0, lst = 0;
+  auto set_tile = [&](int it) {
+    int m0, n0;
+    tile_origin(run0 + first + it * wpx, n_mt, n_nt, m0, n0);
+    wq_b = (gptr)wq + (size_t)n0 * ldq;
+    x8_b = (gptr)x8 + (size_t)m0 * KL;
+    wh_b = (gptr)wh + (size_t)n0 * (2 * r);
+    xh_b = (gptr)xh + (size_t)m0 * (2 * r);
+    row_w = (uint32_t)(min(n0 + srow, N - 1) - n0);
+    row_x = (uint32_t)(min(m0 + srow, M - 1) - m0);
+    sc_b = (gptr)sw + (size_t)n0 * 2;
+    vos = 2u * (uint32_t)(min(n0 + (t & 255), N - 1) - n0);
+  };
+  set_tile(0);
+
+  // two register sets, one stage each; loads are straight-line code of one shape, whatever the stage's kind
+  u32x4 rw[2], rx[2][2];
+  uint16_t rs[2];
+  auto gload = [&](auto set) {
+    const bool is_b = lst >= nq;
+    const int sq = min(lst, nq_real - 1), sb16 = max(lst - nq, 0);
+    const gptr wb = is_b ? wh_b + (size_t)sb16 * 32 : wq_b + (size_t)sq * 32;
+    const gptr xbp = is_b ? xh_b + (size_t)sb16 * 32 : x8_b + (size_t)sq * 64;
+    const uint32_t ow = __umul24(row_w, is_b ? 2 * r : ldq) + half * 16;
+    const uint32_t ox = __umul24(row_x, is_b ? 2 * r : KL) + (is_b ? half * 16 : half * 32);
+    rw[set] = *(const GLOBAL u32x4*)(wb + ow);
+    rx[set][0] = *(const GLOBAL u32x4*)(xbp + ox);
+    rx[set][1] = *(const GLOBAL u32x4*)(xbp + (ox + (is_b ? 0 : 16)));
+    rs[set] = *(const GLOBAL uint16_t*)(sc_b + (size_t)(GS == 128 ? sq >> 1 : sq) * (size_t)N * 2 + vos);
+    lst++;
+  };
+  auto wrap_loads = [&]() {
+    if (lst == nst) {
+      lst = 0;
+      if (lt + 1 < T) set_tile(++lt);
+    }
+  };
+  int sst = 0;                                                        // store cursor: stage within its tile
+  constexpr int STEPS = 8;
+  uint32_t d0[3], d1[3], e0[3];
+  // Step q of writing the store cursor's stage from register set `set` into the ring slot at `so` and reloading the set
+  auto stage_step = [&](auto set, int q, int so) {
+    const bool copy = sst >= nq;
+    unsigned char* sp = smem + so;
+    if (q == 0) pipe::unpack16_fp6(pipe::low_nibbles(rw[set][0], rw[set][1]), pipe::low_nibbles(rw[set][2], rw[set][3]), d0);
+    if (q == 1) {
+      pipe::unpack16_fp6(pipe::high_nibbles(rw[set][0], rw[set][1]), pipe::high_nibbles(rw[set][2], rw[set][3]), d1);
+      *(u32x4*)(sp + part_w.at) = copy ? rw[set] : u32x4{d0[0], d0[1], d0[2], d1[0]};
+      *(u32x2*)(sp + part_w.at_hi) = u32x2{d1[1], d1[2]};
+    }
+    auto x_hi = [&](int e, uint32_t (&d)[3]) {                        // 16 channels: fields [s 00 aaa]
+      pipe::unpack16_fp6(pipe::high_nibbles(rx[set][e][0], rx[set][e][1]), pipe::high_nibbles(rx[set][e][2], rx[set][e][3]), d);
+    };
+    auto x_lo = [&](int e, const uint32_t (&sign)[3], uint32_t (&d)[3]) {   // fields [s 0 bbbb]
+      pipe::spread16_fp6(pipe::low_nibbles(rx[set][e][0], rx[set][e][1]), pipe::low_nibbles(rx[set][e][2], rx[set][e][3]), sign, d);
+    };
+    if (q == 2) x_hi(0, d0);
+    if (q == 3) {
+      x_hi(1, d1);
+      *(u32x4*)(sp + xa) = copy ? rx[set][0] : u32x4{d0[0], d0[1], d0[2], d1[0]};
+      *(u32x2*)(sp + xa_hi) = u32x2{d1[1], d1[2]};
+    }
+    if (q == 4) x_lo(0, d0, e0);
+    if (q == 5) {
+      x_lo(1, d1, d0);
+      *(u32x4*)(sp + xb) = u32x4{e0[0], e0[1], e0[2], d0[0]};
+      *(u32x2*)(sp + xb_hi) = u32x2{d0[1], d0[2]};
+    }
+    if (q == 6) *(float*)(sp + SCALE_OFF + t * 4) = sst < nq_real ? f16_bits_to_f32(rs[set]) : 0.0f;
+    if (q == 7) gload(set);
+  };
+
+  // ---- multiplying role: lane half h reads the 24 bytes of 32-channel block h of a row (16-bit stage: 16 bytes, 8 channels)
+  i32x4 wl[2], ta[2], tb[2];
+  i32x2 wh2[2], ta2[2], tb2[2];
+  float sc[2];
+  const int lr = l & 31;
+  const int ln_w = pipe::read_lo<64>(lr, h), ln_w_hi = pipe::read_hi<64>(lr, h);   // (tile bases are multiples of 32 rows)
+  const int hi8 = 8 * ((lr >> 4) & 1);
+  const int ln_a = x_off(lr, 4 * h), ln_a_hi = x_off(lr, 4 * h + 1) + hi8, ln_b = x_off(lr, 4 * h + 2), ln_b_hi = x_off(lr, 4 * h + 3) + hi8;
+  auto read_w = [&](int i, int so) {
+    const unsigned char* p = smem + (so + (wn * 128 + i * 32) * SB);
+    wl[i & 1] = *(const i32x4*)(p + ln_w);
+    wh2[i & 1] = *(const i32x2*)(p + ln_w_hi);
+    sc[i & 1] = *(const float*)(smem + (so + SCALE_OFF + (wn * 128 + i * 32) * 4) + lr * 4);
+  };
+  auto read_x = [&](int j, int so) {
+    const unsigned char* p = smem + (so + X_OFF + (wt * 64 + j * 32) * XB);
+    ta[j] = *(const i32x4*)(p + ln_a);
+    ta2[j] = *(const i32x2*)(p + ln_a_hi);
+    tb[j] = *(const i32x4*)(p + ln_b);
+    tb2[j] = *(const i32x2*)(p + ln_b_hi);
+  };
+
+  f32x16 acc[4][2];
+  int cur = 0, nxt = SLOT, fill = 2 * SLOT;
+  auto interval = [&](auto set, auto is_b) {
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int i = q >> 1, j = q & 1;
+      auto between = [&]() {
+        // behind the issue of the tile's MFMAs: operands that have fallen free are refilled
+        if (j == 0) {
+          if (i + 1 < 4) read_w(i + 1, cur);
+        } else if (i == 3) {
+          read_w(0, nxt);
+        }
+        if (i == 3) read_x(j, nxt);
+        stage_step(set, q, fill);                                     // and a share of the staging work
+      };
+      if constexpr (is_b) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[j]), __builtin_bit_cast(bf16x8, wl[i & 1]),
+                                                            acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between();
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        auto six = [](i32x4 lo, i32x2 hi) {
+          return __builtin_shufflevector(lo, __builtin_shufflevector(hi, hi, 0, 1, -1, -1), 0, 1, 2, 3, 4, 5, -1, -1);
+        };
+        f32x16 z;
+#pragma unroll
+        for (int v = 0; v < 16; v++) z[v] = 0.0f;
+        const i32x8 wv = six(wl[i & 1], wh2[i & 1]);
+        const float s = sc[i & 1];
+        constexpr int E = 127 + 3;                                    // E8M0: 2^3 on every operand, 2^4 more on the a-plane
+        z = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(six(ta[j], ta2[j]), wv, z, 2, 2, 0, E + 4, 0, E);
+        z = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(six(tb[j], tb2[j]), wv, z, 2, 2, 0, E, 0, E);
+        __builtin_amdgcn_sched_barrier(0);
+        between();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[i][j][v] = fmaf(z[v], s, acc[i][j][v]);
+        asm volatile("" : "+v"(acc[i][j]));                           // (accumulated in place)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // this wave's stores into the ring are done
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int freed = cur;
+    cur = nxt;
+    nxt = fill;
+    fill = freed;
+    if (++sst == nst) sst = 0;
+  };
+
+  typedef std::integral_constant<int, 0> S0;
+  typedef std::integral_constant<int, 1> S1;
+  gload(S0{});
+  gload(S1{});
+  wrap_loads();
+#pragma unroll
+  for (int q = 0; q < STEPS; q++) stage_step(S0{}, q, cur);
+  sst++;
+#pragma unroll
+  for (int q = 0; q < STEPS; q++) stage_step(S1{}, q, nxt);
+  if (++sst == nst) sst = 0;
+  __syncthreads();
+  read_w(0, cur);
+  read_x(0, cur);
+  read_x(1, cur);
+
+  for (int it = 0; it < T; it++) {
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+    int m0, n0;
+    tile_origin(run0 + first + it * wpx, n_mt, n_nt, m0, n0);
+    // the tokens' scales reach LDS behind the first two stages (whose barriers separate them from the last tile's)
+    const uint16_t sxv = sx[min(m0 + (t & 255), M - 1)];
+    for (int st = 0; st < nq; st += 2) {
+      wrap_loads();
+      interval(S0{}, std::false_type{});
+      interval(S1{}, std::false_type{});
+      if (st == 0 && w < 4) *(float*)(smem + SX_OFF + t * 4) = f16_bits_to_f32(sxv);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const float4 s4 = *(const float4*)(smem + SX_OFF + (wt * 64 + j * 32 + 8 * q + 4 * h) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          acc[i][j][4 * q] *= s4.x;
+          acc[i][j][4 * q + 1] *= s4.y;
+          acc[i][j][4 * q + 2] *= s4.z;
+          acc[i][j][4 * q + 3] *= s4.w;
+        }
+      }
+    for (int st = 0; st < nbf; st += 2) {
+      wrap_loads();
+      interval(S0{}, std::true_type{});
+      interval(S1{}, std::true_type{});
+    }
+    // accumulator v of lane (h, c): token 8 (v / 4) + 4 h + v % 4 of its tile, output channel c.  bf16 rows: two channels of a
+    // token in one dword (neighbouring lanes exchange, the even one keeps token v, the odd one v + 1), then 16 tokens x 128
+    // channels at a time through the slot that no stage is in now, so that a store writes whole 256-byte rows
+    const int mw = m0 + wt * 64, nw = n0 + wn * 128;
+    if (!OUT_F32 && (N & 7) == 0 && nw + 128 <= N) {
+      constexpr int ROW = 272;                                        // (256 bytes, padded)
+      unsigned char* tb = smem + fill + w * (16 * ROW);
+      int lw = l;
+      asm volatile("" : "+v"(lw));                                    // (addresses formed here, not carried through the loops)
+      const int lh = lw >> 5;
+      const uint32_t sel = lw & 1 ? 0x03020706u : 0x05040100u;
+      unsigned char* wr = tb + (4 * lh + (lw & 1)) * ROW + (lw & 30) * 2;
+      const unsigned char* rd = tb + (lw >> 4) * ROW + (lw & 15) * 16;
+      uint16_t* dst = (uint16_t*)y + (size_t)(mw + (lw >> 4)) * N + nw + 8 * (lw & 15);
+      float bn[4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) bn[i] = bias ? bf16_bits_to_f32(bias[nw + i * 32 + (lw & 31)]) : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int qp = 0; qp < 2; qp++) {
+#pragma unroll
+          for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              const int v = 8 * qp + 2 * e;                           // registers v, v + 1: rows 8 (e / 2) + 4 h + 2 (e % 2), + 1
+              const float y0 = bias ? acc[i][j][v] + bn[i] : acc[i][j][v], y1 = bias ? acc[i][j][v + 1] + bn[i] : acc[i][j][v + 1];
+              const uint32_t own = f32x2_to_bf16x2_bits(y0, y1);
+              const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
+              *(uint32_t*)(wr + (8 * (e >> 1) + 2 * (e & 1)) * ROW + i * 64) = __builtin_amdgcn_perm(got, own, sel);
+            }
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const uint4 d = *(const uint4*)(rd + k * 4 * ROW);
+            const int mr = j * 32 + 16 * qp + 4 * k;
+            if (mw + mr + (lw >> 4) < M) *(uint4*)(dst + (size_t)mr * N) = d;
+          }
+        }
+    } else {
+      int lw = l;
+      asm volatile("" : "+v"(lw));
+      const int lh = lw >> 5;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int n = nw + i * 32 + (lw & 31);
+        const float bn = bias && n < N ? bf16_bits_to_f32(bias[n]) : 0.0f;
+        if (n < N)
+#pragma unroll
+          for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+              const int m = mw + j * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+              const float o = bias ? acc[i][j][v] + bn : acc[i][j][v];
+              if (m < M) {
+                if (OUT_F32) ((float*)y)[(size_t)m * N + n] = o;
+                else ((uint16_t*)y)[(size_t)m * N + n] = f32_to_bf16_bits(o);
+              }
+            }
+      }
+    }
+    if (it + 1 < T) {                                                 // (all waves are done with the slot before it is filled)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+  }
+}
+
+template <int GS, bool OUT_F32>
+static int launch_one(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias, int M,
+                      int N, int K, int r, void* y, int cus, hipStream_t s) {
+  const BlobLayout L = blob_layout(N, K, r, GS);
+  const char* bp = (const char*)blob;
+  const long tiles = (long)((M + TM_ - 1) / TM_) * ((N + TN_ - 1) / TN_);
+  if (tiles > 0x7FFFFFF0L) return DIROTQ_ERR_SHAPE;
+  const int wpx = (int)std::max(1L, std::min((long)cus / 8, (tiles + 7) / 8));
+  // (idempotent: two threads racing here would both set the same attribute)
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)w4a8_gemm_pipe_kernel<GS, OUT_F32>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return hip_failed(e);
+    attr_done.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((w4a8_gemm_pipe_kernel<GS, OUT_F32>), dim3(wpx * 8), dim3(NT), SMEM, s, xh, x8, sx,
+                     (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw),
+                     bias, M, N, K, r, y, wpx);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+}  // namespace pipe8
+
+int launch_w4a8_gemm_pipe(const uint16_t* xh, const uint8_t* x8, const uint16_t* sx, const void* blob, const uint16_t* bias,
+                          int M, int N, int K, int r, int g, void* y, int y_dtype, int cus, hipStream_t s) {
+  if (g == 64)
+    return y_dtype ? pipe8::launch_one<64, true>(xh, x8, sx, blob, bias, M, N, K, r, y, cus, s)
+                   : pipe8::launch_one<64, false>(xh, x8, sx, blob, bias, M, N, K, r, y, cus, s);
+  if (g == 128)
+    return y_dtype ? pipe8::launch_one<128, true>(xh, x8, sx, blob, bias, M, N, K, r, y, cus, s)
+                   : pipe8::launch_one<128, false>(xh, x8, sx, blob, bias, M, N, K, r, y, cus, s);
+  return DIROTQ_ERR_UNSUPPORTED;
+}
+
+}  // namespace dirotq
