@@ -97,6 +97,9 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
 // rotate_quantize.hip.  channels: a multiple of the group size, 64 or 128; fp32 output (no maxima): 32 or 64
 int launch_rotate_quantize_few(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out,
                                int r_pad, int Kv, int channels, int tokens, hipStream_t s);
+// tiles of 128 channels x 128, 160, 192 or 256 tokens, or of 256 x 128; sx_ld: row length of s_x (and of the maxima)
+int launch_rotate_quantize_dma(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& out, int r_pad,
+                               int Kv, int channels, int tokens, hipStream_t s, int sx_ld);
 // per-token INT8 quantization of xf [M][KL] given pmax [ceil(KL/128)][M] (NULL: reads xf twice) -> x8 [M][KL], sx [M]
 int launch_quantize_tokens(const float* xf, const float* pmax, int M, int KL, uint8_t* x8, uint16_t* sx,
                            hipStream_t s);

@@ -19,9 +19,11 @@
 // XOR swizzle applied on the global side, so that the 16-byte MFMA operand reads of 16
 // consecutive rows are bank-conflict free.  While stage kt is multiplied, the registers
 // holding stage kt+1 (loaded during stage kt-1) are written to the other LDS stage and
-// refilled with stage kt+2; every store/load pair sits between MFMAs.  (On gfx950 this
-// beats the direct global_load_lds path: those instructions hold up the matrix pipe of the
-// issuing SIMD far longer than a register load plus an LDS store.)
+// refilled with stage kt+2; every store/load pair sits between MFMAs.  (With one or two waves of
+// 128 x 64 outputs per SIMD this beats global_load_lds, which holds its wave up longer than a register load plus
+// an LDS store; more and smaller waves turn it round: rotate_quantize_dma.hip.)  A last stage of 32 channels
+// (K = 32 mod 64) gets zeros for its upper half; stages of 32 channels throughout, us: M = 4608, K = 3104 112 against 86;
+// M = 32768, K = 1184 130 against 108; M = 3000, K = 6176 312 against 243.
 #include <atomic>
 
 #include "dirotq_internal.h"
@@ -31,8 +33,9 @@ namespace dirotq {
 // KSP = 2: the workgroup holds two such sets of waves, each with LDS stages of its own, and each walks one half of
 // K; the halves' accumulators are added through LDS before the epilogue (small launches: half as long a chain of
 // stage latencies).
-template <int WGC, int WGT, int BK, int WVT = 64, int KSP = 1>
+template <int WGC, int WGT, int WVT = 64, int KSP = 1>
 struct RQ {
+  static constexpr int BK = 64;                            // channels per stage
   static constexpr int WAVE_C = 128, WAVE_T = WVT;         // wave tile: channels x tokens (64, or 32 for the
                                                            // small launches: half the arithmetic per wave and stage)
   static constexpr int TC = WGC * WAVE_C, TT = WGT * WAVE_T;
@@ -48,16 +51,17 @@ struct RQ {
   static constexpr int WAVES_PER_SIMD = (NW * KSP <= 4 && 2 * SMEM > 160 * 1024) ? 1 : 2;
   static_assert(KSP == 1 || (KSP == 2 && SMEM >= NW * 64 * (WAVE_C * WAVE_T / 64) * 4), "the second part's accumulators pass through the stage buffers");
   static_assert((TC + TT) * CPR % (64 * NW) == 0, "loads must divide evenly over waves");
-  static_assert(BK == 32 || BK == 64, "BK");
   static_assert(IPW % KS == 0 && PP >= 1 && PP <= 4, "store/load pairs are spread over the 4 MFMA rows of a k-step");
 
   // chunk c of row `row` is stored in 16-B slot c ^ swz(row)
   // (LDS has 64 banks: a 16-byte read is served 16 lanes per cycle, so 16 consecutive rows
-  // must land in 16 different 16-byte slots of a 256-byte bank line)
-  // 128-byte rows (BK = 64): row&1 picks the half line, (row>>1)&7 permutes the 8 chunks;
-  // 64-byte rows (BK = 32): row&3 picks the quarter line, (row>>2)&3 permutes the 4 chunks.
-  __device__ static __forceinline__ int swz(int row) { return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
+  // must land in 16 different 16-byte slots of a 256-byte bank line: row&1 picks the half line,
+  // (row>>1)&7 permutes the 8 chunks)
+  __device__ static __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 };
+
+// what a last stage of 32 channels (K = 32 mod 64) has in the place of its upper half
+static __device__ const uint4 kZeros = {0, 0, 0, 0};
 
 // Epilogue of a wave whose accumulators are 4 x WT tiles of 32 channels x 32 tokens (32x32 MFMA layout: a lane
 // owns one token and 4 consecutive channels per register quad): the split at r, the per-group quantizer and the
@@ -197,12 +201,13 @@ __device__ __forceinline__ void rq_epilogue32(const f32x16 (&acc)[4][WT], int vb
 // like sx), 2 = no quantizer here: the fp32 values go to xf [M][K-r] and the absolute maximum of
 // every 128-channel wave tile to pmax [ceil((K-r)/128)][M] (per-token 8-bit quantization needs the
 // maximum over all channels of a token, which no single workgroup sees).
-template <int WGC, int WGT, int BK, int MI, int QM, int WVT, int KSP>
-__global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WAVES_PER_SIMD)) void rotate_quantize_kernel(
+template <int WGC, int WGT, int MI, int QM, int WVT, int KSP, bool TAIL>
+__global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, WVT, KSP>::WAVES_PER_SIMD)) void rotate_quantize_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ Qt, int M, int K, int r, int g,
     uint16_t* __restrict__ xh, uint8_t* __restrict__ xl, uint16_t* __restrict__ sx, uint16_t* __restrict__ zx,
     float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int Kv, int n_ct, int n_tt, int per_xcd, int sx_ld) {
-  using C = RQ<WGC, WGT, BK, WVT, KSP>;
+  using C = RQ<WGC, WGT, WVT, KSP>;
+  constexpr int BK = C::BK;
   static_assert(WVT == 64 || (WVT == 32 && MI == 32), "32-token wave tiles are written for the 32x32 loop only");
   static_assert(KSP == 1 || MI == 32, "the K split is written for the 32x32 loop only");
   constexpr bool ASYM = QM == 1;
@@ -246,12 +251,17 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, BK, WVT, KSP>::WA
     gsrc[i] = base + logical_chunk * 8 + kp * (K / KSP);
   }
   i32x4 staged[C::IPW];
-  auto gload = [&](int q, int kt) { staged[q] = *(const i32x4*)(gsrc[q] + kt * BK); };
+  const int nk = TAIL ? K / BK + 1 : K / (BK * KSP);        // (else K % (BK KSP) == 0); nk >= 1
+  auto gload = [&](int q, int kt) {
+    typedef const __attribute__((address_space(1))) uint16_t* gptr;   // (else the choice below makes it a flat load)
+    gptr p = (gptr)(gsrc[q] + kt * BK);
+    // (a lane's chunk of load q is in the upper half of the stage: bit 2 of its number, row / 8 = w IPW + q)
+    if (TAIL && kt == nk - 1 && (((l >> 2) ^ (w * C::IPW + q)) & 1)) p = (gptr)&kZeros;
+    staged[q] = *(const __attribute__((address_space(1))) i32x4*)p;
+  };
   auto swrite = [&](int q, int buf) {
     *(i32x4*)(smem + buf * C::STAGE_BYTES + (w * C::IPW + q) * 1024 + l * 16) = staged[q];
   };
-
-  const int nk = K / (BK * KSP);                            // the launcher guarantees K % (BK KSP) == 0, nk >= 1
 
   // prologue: stage 0 into LDS, stage 1 into the registers.  Loads past the last stage re-read
   // it: unconditional loads keep the outstanding-load count the same in every iteration, so
@@ -601,20 +611,10 @@ static void virtual_channels(int K, int r, int g, bool fp32_out, int& r_pad, int
   Kv = (r_pad + (K - r) + 127) / 128 * 128;
 }
 
-template <int WGC, int WGT, int BK, int MI, int QM, int WVT, int KSP>
+template <int WGC, int WGT, int MI, int QM, int WVT, int KSP, bool TAIL>
 static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, uint16_t* xh,
-                      uint8_t* xl, uint16_t* sx, uint16_t* zx, float* xf, float* pmax, hipStream_t s, int m_off,
-                      int sx_ld) {
-  // tokens [m_off, m_off + M) of the caller's arrays; sx_ld = total token count (row length of s_x)
-  if (sx_ld == 0) sx_ld = M;
-  x += (size_t)m_off * K;
-  if (xh) xh += (size_t)m_off * r;
-  if (xl) xl += (size_t)m_off * ((K - r) / 2);
-  if (sx) sx += m_off;
-  if (zx) zx += m_off;
-  if (xf) xf += (size_t)m_off * (K - r);
-  if (pmax) pmax += m_off;
-  using C = RQ<WGC, WGT, BK, WVT, KSP>;
+                      uint8_t* xl, uint16_t* sx, uint16_t* zx, float* xf, float* pmax, hipStream_t s, int sx_ld) {
+  using C = RQ<WGC, WGT, WVT, KSP>;
   int r_pad, Kv;
   virtual_channels(K, r, g, QM == 2, r_pad, Kv);
   const int n_ct = (Kv + C::TC - 1) / C::TC;
@@ -624,41 +624,37 @@ static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r
   // (idempotent: two threads racing here would both set the same attribute)
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)rotate_quantize_kernel<WGC, WGT, BK, MI, QM, WVT, KSP>,
+    hipError_t e = hipFuncSetAttribute((const void*)rotate_quantize_kernel<WGC, WGT, MI, QM, WVT, KSP, TAIL>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((rotate_quantize_kernel<WGC, WGT, BK, MI, QM, WVT, KSP>), dim3(per_xcd * 8), dim3(C::NT), C::SMEM, s, x,
+  hipLaunchKernelGGL((rotate_quantize_kernel<WGC, WGT, MI, QM, WVT, KSP, TAIL>), dim3(per_xcd * 8), dim3(C::NT), C::SMEM, s, x,
                      Qt, M, K, r, g, xh, xl, sx, zx, xf, pmax, r_pad, Kv, n_ct, n_tt, per_xcd, sx_ld);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
-template <int WGC, int WGT, int BK, int MI, int WVT = 64, int KSP = 1>
+template <int WGC, int WGT, int MI, int WVT = 64, int KSP = 1, bool TAIL = false>
 static int launch_cfg(const RqOut& o, const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g,
-                      hipStream_t s, int m_off = 0, int sx_ld = 0) {
-  if (o.xf) return launch_one<WGC, WGT, BK, MI, 2, WVT, KSP>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, m_off, sx_ld);
-  if (o.zx) return launch_one<WGC, WGT, BK, MI, 1, WVT, KSP>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, m_off, sx_ld);
-  return launch_one<WGC, WGT, BK, MI, 0, WVT, KSP>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, m_off, sx_ld);
+                      hipStream_t s, int sx_ld) {
+  if (o.xf) return launch_one<WGC, WGT, MI, 2, WVT, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
+  if (o.zx) return launch_one<WGC, WGT, MI, 1, WVT, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
+  return launch_one<WGC, WGT, MI, 0, WVT, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
 }
 
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, RqOut& o,
                            hipStream_t s) {
-  // Few tokens: rotate_quantize_few.hip.  Large problems: 256 x 256 workgroup tiles (8 waves); medium: 256 channels x
-  // 128 tokens (4 waves); small: 128 x 128 as 4 waves of 128 channels x 32 tokens, or 128 x 64 with K split over two
-  // sets of such waves (below).  A small launch is a chain of latencies (a few dozen workgroups, each alone
-  // on its CU, walk K stage by stage), so its waves carry half the arithmetic per stage: 13 instead of 20 us
-  // at M = 256, K = 1152.
+  // Few tokens: rotate_quantize_few.hip.  While one workgroup per CU holds everything: 128 x 64 tiles with K split over two
+  // sets of waves, 128 x 128 tiles, then tiles of 128 x 160 to 128 x 256 fed by copies (rotate_quantize_dma.hip).  Beyond: 256
+  // x 256 tiles (8 waves), and 256 x 128 or 128 x 256 ones fed by copies.
   // The large tiles run long enough to be limited by power (the shader clock drops under
   // sustained MFMA work on random data); there the 16x16x32 MFMA, which moves half the
   // accumulator bytes per multiply-add, is the faster one.  The smaller, latency-bound
   // launches are faster with the 32x32x16 MFMA and its shorter epilogue.
   int r_pad, Kv;
   virtual_channels(K, r, g, o.xf != nullptr, r_pad, Kv);
-  const long n_tc256 = (Kv + 255) / 256;
-  const long big_tiles = n_tc256 * ((M + 255) / 256);    // 256 channels x 256 tokens
-  const long mid_tiles = n_tc256 * ((M + 127) / 128);    // 256 channels x 128 tokens
+  auto tiles = [&](long channels, long tokens) { return ((Kv + channels - 1) / channels) * ((M + tokens - 1) / tokens); };
   int cus = 0;
   {
     int dev = 0;
@@ -687,32 +683,39 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
     for (FewTile t : {FewTile{64, 8}, {64, 16}, {64, 24}, {64, 32}, {64, 64}, {64, 96}})
       if (fits(t)) return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, t.channels, t.tokens, s);
   }
-  if (K % 64 != 0) {
-    if (mid_tiles >= 100) return launch_cfg<2, 2, 32, 32>(o, x, Qt, M, K, r, g, s);
-    return launch_cfg<1, 4, 32, 32, 32>(o, x, Qt, M, K, r, g, s);
-  }
-  // A launch this small is held back by what one CU can load per cycle (each workgroup streams its 128 basis rows
-  // over all of K) and by the chain of stage latencies: with 128 x 64 tiles and the two halves of K on two sets
-  // of waves per workgroup it has twice the workgroups and half the stages (11 instead of 13 us at M = 256,
-  // K = 1152; 21 instead of 26 at K = 3072), as long as that is still a single round of workgroups.
-  const long n_tc128 = (Kv + 127) / 128;
-  const long small_tiles = n_tc128 * ((M + 63) / 64);      // 128 channels x 64 tokens
-  if (K % 128 == 0 && small_tiles <= 256) return launch_cfg<1, 2, 64, 32, 32, 2>(o, x, Qt, M, K, r, g, s);
-  // 128 x 128 tiles (two such workgroups fit a CU) while they are resident all at once, or nearly: 14.6 instead
-  // of 22.7 us at M = 3072, K = 1152 (216 workgroups against 120 of 256 x 128); K = 3072 prefers the larger tile
-  // from one full round on (M = 1536: 44 against 49 us)
-  const long tiles128 = n_tc128 * ((M + 127) / 128);
-  if (tiles128 <= 256 || (K <= 2048 && tiles128 <= 320)) return launch_cfg<1, 4, 64, 32, 32>(o, x, Qt, M, K, r, g, s);
-  // Beyond that: rounds of 256 workgroups.  A round of 256 x 128 tiles takes about 0.62 of a round of 256 x 256
-  // ones (K = 3072: 53 against 81 us, K = 12288: 186 against 300-320), so the plans compared are: all big, all
-  // half-size, or k full rounds of big tiles and the remaining tokens in a second launch of half-size ones.
-  auto rounds = [&](long tiles) { return (double)((tiles + cus - 1) / cus); };
-  constexpr double MID = 0.62, SECOND_LAUNCH = 0.03;
+  // A launch this small is held back by the chain of stage latencies: with 128 x 64 tiles and the two halves of K on two sets
+  // of waves per workgroup it has twice the workgroups and half the stages (11 instead of 13 us at M = 256, K = 1152; 21
+  // instead of 26 at K = 3072).
+  if (K % 128 == 0 && tiles(128, 64) <= cus) return launch_cfg<1, 2, 32, 32, 2>(o, x, Qt, M, K, r, g, s, M);
+  auto copied = [&](int channels, int tokens) {
+    return launch_rotate_quantize_dma(x, Qt, M, K, r, g, o, r_pad, Kv, channels, tokens, s, M);
+  };
+  // 128 x 128: staged through registers, but fed by copies where K is short (M = 6144, K = 640: 10.1 against 10.9 us; equal at
+  // K = 1152; M = 1024, K = 3072: 30.3 against 27.7) or ends in half a stage (M = 1792, K = 2080: 23.5 us, 35.4 in stages of 32)
+  if (tiles(128, 128) <= cus)
+    return K % 64 != 0 || K <= 1024 ? copied(128, 128) : launch_cfg<1, 4, 32, 32>(o, x, Qt, M, K, r, g, s, M);
+  // Then the smallest tile that still is one round, us against two of the above or a round of larger ones: M = 3931, K =
+  // 1152 16.6 (128 x 160) against 22.2; M = 5211 18.8 (192) against 23.1; M = 7003 22.3 (256) against 30.7; K = 3072, M =
+  // 1371 / 1883 / 2523: 35.5 / 40.8 / 50.1 against 42.4 / 45.3 / 52.8; K = 6144, M = 731 / 1115: 69.9 / 94 against 78.5 / 97.9.
+  for (int tokens : {160, 192, 256})
+    if (tiles(128, tokens) <= cus) return copied(128, tokens);
+  // Beyond that: rounds of workgroups, in units of a round of 256 x 256 tiles (K = 3072: 81 us, K = 12288: 300-320).  One of
+  // half-size tiles takes about 0.62 of it (K = 3072: 50; fed through registers 53), one of 128 x 256 tiles 0.66 (they fit
+  // better where K / 128 is odd: M = 13403, K = 1152 43 us against 56 in two rounds of the largest).  The plans compared are:
+  // one kind for all, or k full rounds of big tiles and the remaining tokens in a second launch of half-size ones.
+  const long n_tc256 = (Kv + 255) / 256, big_tiles = tiles(256, 256);
+  auto rounds = [&](long t) { return (double)((t + cus - 1) / cus); };
+  constexpr double MID = 0.62, LOW = 0.66, SECOND_LAUNCH = 0.03;
   double best = rounds(big_tiles);                          // plan: one launch of big tiles
-  int plan_tt = -1;                                         // -1: all big, 0: all half-size, > 0: token tiles in the big launch
-  if (rounds(mid_tiles) * MID < best) {
-    best = rounds(mid_tiles) * MID;
-    plan_tt = 0;
+  enum { kBig = -1, kMid = 0, kLow = -2 };
+  int plan_tt = kBig;                                       // or > 0: token tiles in the big launch
+  if (rounds(tiles(256, 128)) * MID < best) {
+    best = rounds(tiles(256, 128)) * MID;
+    plan_tt = kMid;
+  }
+  if (rounds(tiles(128, 256)) * LOW < best) {
+    best = rounds(tiles(128, 256)) * LOW;
+    plan_tt = kLow;
   }
   for (long k = 1; k * cus < big_tiles; k++) {
     const long tt = k * cus / n_tc256;                      // token tiles of 256 that k rounds hold
@@ -724,11 +727,23 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
       plan_tt = (int)tt;
     }
   }
-  if (plan_tt < 0) return launch_cfg<2, 4, 64, 16>(o, x, Qt, M, K, r, g, s);
-  if (plan_tt == 0) return launch_cfg<2, 2, 64, 32>(o, x, Qt, M, K, r, g, s);
-  const int st = launch_cfg<2, 4, 64, 16>(o, x, Qt, plan_tt * 256, K, r, g, s, 0, M);
+  if (plan_tt == kMid) return copied(256, 128);
+  if (plan_tt == kLow) return copied(128, 256);
+  auto big = [&](int tokens) {
+    return K % 64 != 0 ? launch_cfg<2, 4, 16, 64, 1, true>(o, x, Qt, tokens, K, r, g, s, M)
+                       : launch_cfg<2, 4, 16>(o, x, Qt, tokens, K, r, g, s, M);
+  };
+  if (plan_tt == kBig) return big(M);
+  const int first = plan_tt * 256, st = big(first);
   if (st) return st;
-  return launch_cfg<2, 2, 64, 32>(o, x, Qt, M - plan_tt * 256, K, r, g, s, plan_tt * 256, M);
+  RqOut rest = o;                                           // (the tokens behind the first ones)
+  if (o.xh) rest.xh += (size_t)first * r;
+  if (o.xl) rest.xl += (size_t)first * ((K - r) / 2);
+  if (o.sx) rest.sx += first;
+  if (o.zx) rest.zx += first;
+  if (o.xf) rest.xf += (size_t)first * (K - r);
+  if (o.pmax) rest.pmax += first;
+  return launch_rotate_quantize_dma(x + (size_t)first * K, Qt, M - first, K, r, g, rest, r_pad, Kv, 256, 128, s, M);
 }
 
 }  // namespace dirotq

@@ -1,0 +1,67 @@
+"""Rotation + quantization beyond the few-token kernel: every tile fed by copies (128 channels x 128, 160, 192, 256 tokens, 256 x
+128), the 256 x 256 tiles, and both in one call, with whole and half last stages, at the token counts on both sides of each
+switch on 256 CUs.  The basis is a signed permutation, so all results must equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dirotq_oracle as O
+from paper_2605_16732_amd import binding as B
+
+from gpu_util import dev, dev_bf16, gpu_rotate_quantize, host_bf16_bits, host_f16
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # K = 288: three channel tiles of 128 (two of 256), a last stage of 32 channels
+    (4897, 288, 32, 64), (10880, 288, 32, 32), (10881, 288, 32, 64), (13600, 288, 32, 128), (13601, 288, 32, 32),
+    (16321, 288, 32, 128), (21760, 288, 0, 32), (25000, 288, 32, 64), (33000, 288, 32, 128),
+    # K = 768: six (three)
+    (5376, 768, 64, 64), (5377, 768, 128, 128), (6721, 768, 64, 32), (8065, 768, 64, 64), (10753, 768, 0, 128), (10800, 768, 64, 64),
+    (22000, 768, 64, 64),
+    # K = 640: five channel tiles: two rounds of 128 x 256
+    (24155, 640, 64, 64),
+]
+
+
+def _inputs(M, K):
+    rng = np.random.default_rng([M, K, 5])
+    Q = np.zeros((K, K), np.float32)
+    perm, sign = rng.permutation(K), rng.choice([-1.0, 1.0], size=K).astype(np.float32)
+    Q[perm, np.arange(K)] = sign
+    x = O.round_to_bf16((rng.standard_normal((M, K), dtype=np.float32) * rng.lognormal(0, 1.5, size=(1, K)).astype(np.float32)))
+    return x, Q, x[:, perm] * sign + np.float32(0)          # (what O.rotate returns: one term per sum; no negative zeros)
+
+
+@pytest.mark.parametrize("M,K,r,g", CASES)
+def test_codes_and_scales_are_exact(M, K, r, g):
+    print(f"[case] rotate copied tiles M={M} K={K} r={r} g={g}", flush=True)
+    x, Q, xhat = _inputs(M, K)
+    Qt = B.prepare_rotation(dev(Q))
+    _, (xh, qx, sx) = gpu_rotate_quantize(O.bf16_bits(x), Qt, r, g)
+    xh_r, qx_r, sx_r = O.split_quantize(xhat, r, g)
+    np.testing.assert_array_equal(xh, xh_r)
+    np.testing.assert_array_equal(sx.view(np.uint16), sx_r.view(np.uint16))
+    np.testing.assert_array_equal(qx, qx_r)
+    _, xl_a, sx_a, zx_a = B.rotate_quantize_asym(dev_bf16(O.bf16_bits(x)), Qt, r, g)
+    torch.cuda.synchronize()
+    _, qx_r, sx_r, zx_r = O.split_quantize_asym(xhat, r, g)
+    p = xl_a.cpu().numpy()
+    np.testing.assert_array_equal(np.stack([p & 15, p >> 4], axis=-1).reshape(M, K - r), qx_r)
+    np.testing.assert_array_equal(host_f16(sx_a).T.view(np.uint16), sx_r.view(np.uint16))
+    np.testing.assert_array_equal(host_f16(zx_a).T.view(np.uint16), zx_r.view(np.uint16))
+
+
+@pytest.mark.parametrize("M,K,r", [(8200, 288, 32), (10881, 288, 96), (15000, 288, 32), (20000, 288, 64), (33000, 288, 32),
+                                   (10800, 768, 64), (22000, 768, 64)])
+def test_8_bit_codes_are_exact(M, K, r):
+    print(f"[case] rotate copied tiles a8 M={M} K={K} r={r}", flush=True)
+    x, Q, xhat = _inputs(M, K)
+    xh, x8, sx = B.rotate_quantize_a8(dev_bf16(O.bf16_bits(x)), B.prepare_rotation(dev(Q)), r)
+    torch.cuda.synchronize()
+    xh_r, qx_r, sx_r = O.split_quantize_a8(xhat, r)
+    b = x8.cpu().numpy().astype(np.int32).reshape(M, (K - r) // 32, 2, 16)   # blocks of 32: even channels, odd ones
+    q = np.where(b & 0x80, -(b & 0x7F), b).transpose(0, 1, 3, 2).reshape(M, K - r)
+    np.testing.assert_array_equal(q, qx_r)
+    np.testing.assert_array_equal(host_f16(sx).view(np.uint16), np.asarray(sx_r).reshape(-1).view(np.uint16))
+    np.testing.assert_array_equal(host_bf16_bits(xh), O.bf16_bits(xh_r))
