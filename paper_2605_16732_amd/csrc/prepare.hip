@@ -24,74 +24,80 @@ int launch_prepare_rotation(const float* Q, int K, uint16_t* Qt, hipStream_t s) 
 }
 
 // ---- Wp[n][c] = fp32( sum_k W[n][k] Q[k][c] ) with fp64 accumulation ------------
-// Bound: the fp64 matrix pipe (78.6 TFLOP/s, as much as the fp64 VALU, but a 16x16x4 MFMA takes two operand registers
-// for 64 cycles of work where the VALU form needed an LDS read per two fma).  64 (n) x 32 (c) outputs per workgroup, four
-// waves of 32 x 16, 32 k per LDS stage; operands stay fp32 in LDS and become fp64 in registers (exact).  The small tile
-// spreads N = K = 1536 over 4.5 workgroups per CU (64 x 64: 2.25, a quarter of the chip idle in the last third).
-// N = K = 1536: 268 -> 158 us (46 TFLOP/s); N = 3072, K = 12288: 24.9 -> 16.9 ms (55 TFLOP/s).  What is left beside the
-// MFMAs are the conversions (24 per 16 MFMAs and wave).
+// Bound: the fp64 matrix pipe (78.6 TFLOP/s; a 16x16x4 MFMA takes 64 cycles).  A workgroup owns 32 (n) x 32 (c) outputs and
+// its four waves split K: wave w takes the runs of 16 k w, w + 4, ..., operands straight from global memory in the MFMA
+// layout (fp32, made fp64 in registers: exact; 16 conversions and 10 loads beside 16 MFMAs), the next run's loads in
+// flight; no LDS and no barrier in the loop.  The four partial sums meet in LDS, in wave order.  The unit of work is what a
+// SIMD can be left with too many of: at N = K = 1536 a SIMD has 9 of these, and 4 or 5 of 32 x 16 outputs over all of K
+// (the form before: 64 x 32 per workgroup through LDS).  Four waves per SIMD (128 registers; three: 5% slower).
+// Fusion and quantizer, us: N = K = 1536 152 -> 135, 640 24.8 -> 19.1, N = 320, K = 1408 46.5 -> 34.0; N = 3072, K = 12288 15.4
+// -> 14.4 ms (64 TFLOP/s).
 // Within a run of 16 k lane group q = l / 16 takes k = 4 q .. 4 q + 3, one per MFMA, on both operands.
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-constexpr int FN = 64, FC = 32, FK = 32, FROW = FK + 4;   // (rows of 144 bytes: 16 rows start in 16 different bank groups)
-__global__ __launch_bounds__(256) void fuse_rotation_fp64_kernel(const float* __restrict__ W,
-                                                                 const float* __restrict__ Q, int N, int K,
-                                                                 float* __restrict__ Wp, long n_tiles, long per_xcd) {
-  __shared__ __align__(16) float Ws[2][FN][FROW];
-  __shared__ __align__(16) float Qs[2][FC][FROW];         // [c][k]
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
-  const int n_ct = K / FC;
+constexpr int FN = 32, FC = 32, FK = 16, FW = 4;
+__global__ __launch_bounds__(FW * 64, 4) void fuse_rotation_fp64_kernel(const float* __restrict__ W,
+                                                                     const float* __restrict__ Q, int N, int K,
+                                                                     float* __restrict__ Wp, long n_tiles, long per_xcd) {
+  __shared__ __align__(16) f64x4 part[FW][4][64];
+  const int t = threadIdx.x, l = t & 63, r16 = l & 15, q4 = (l >> 4) * 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n_ct = K / FC, runs = K / FK;
   // consecutive workgroup ids go to different XCDs: each XCD gets a run of tiles, c fastest (its rows of W stay in its L2)
   for (long b = blockIdx.x; b < 8 * per_xcd; b += gridDim.x) {
     const long tile = (b & 7) * per_xcd + (b >> 3);
     if (tile >= n_tiles) continue;
     const int n0 = (int)(tile / n_ct) * FN, c0 = (int)(tile % n_ct) * FC;
-    const int lr = t >> 3, lk = (t & 7) * 4;              // W: rows lr, lr + 32, k lk .. lk + 3; Q: k lr, c lk .. lk + 3
-    const float* w0 = W + (size_t)min(n0 + lr, N - 1) * K + lk;
-    const float* w1 = W + (size_t)min(n0 + lr + 32, N - 1) * K + lk;
-    const float* q0 = Q + (size_t)lr * K + c0 + lk;
-    float4 rw0, rw1, rq;
-    auto load = [&](int k0) {
-      rw0 = *(const float4*)(w0 + k0);
-      rw1 = *(const float4*)(w1 + k0);
-      rq = *(const float4*)(q0 + (size_t)k0 * K);
+    const float* w0 = W + (size_t)min(n0 + r16, N - 1) * K + q4;
+    const float* w1 = W + (size_t)min(n0 + 16 + r16, N - 1) * K + q4;
+    const float* q0 = Q + (size_t)q4 * K + c0 + r16;
+    float4 a[2][2];
+    float bq[2][2][4];
+    auto load = [&](int set, int k0) {
+      a[set][0] = *(const float4*)(w0 + k0);
+      a[set][1] = *(const float4*)(w1 + k0);
+#pragma unroll
+      for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) bq[set][j][s] = q0[(size_t)(k0 + s) * K + 16 * j];
     };
-    auto store = [&](int buf) {
-      *(float4*)&Ws[buf][lr][lk] = rw0;
-      *(float4*)&Ws[buf][lr + 32][lk] = rw1;
-      Qs[buf][lk][lr] = rq.x;
-      Qs[buf][lk + 1][lr] = rq.y;
-      Qs[buf][lk + 2][lr] = rq.z;
-      Qs[buf][lk + 3][lr] = rq.w;
-    };
-    const int rn = (w & 1) * 32 + (l & 15), rc = (w >> 1) * 16 + (l & 15), q4 = (l >> 4) * 4;
-    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-    load(0);
-    store(0);
-    __syncthreads();
-    for (int k0 = 0, buf = 0; k0 < K; k0 += FK, buf ^= 1) {
-      if (k0 + FK < K) load(k0 + FK);
-#pragma unroll
-      for (int kk = 0; kk < FK; kk += 16) {
-        const float4 a0 = *(const float4*)&Ws[buf][rn][kk + q4], a1 = *(const float4*)&Ws[buf][rn + 16][kk + q4];
-        const float4 bq = *(const float4*)&Qs[buf][rc][kk + q4];
-        const float av[2][4] = {{a0.x, a0.y, a0.z, a0.w}, {a1.x, a1.y, a1.z, a1.w}}, bv[4] = {bq.x, bq.y, bq.z, bq.w};
-#pragma unroll
-        for (int s = 0; s < 4; s++)
-#pragma unroll
-          for (int i = 0; i < 2; i++)
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[i][s], (double)bv[s], acc[i], 0, 0, 0);
-      }
-      if (k0 + FK < K) store(buf ^ 1);
-      __syncthreads();                                    // the next stage is complete; this one may be overwritten
-    }
-    // accumulator e of lane l: row 4 e + l / 16, column l % 16 of its 16 x 16 tile
+    f64x4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const int n = n0 + (w & 1) * 32 + i * 16 + 4 * e + (l >> 4);
-        if (n < N) Wp[(size_t)n * K + c0 + rc] = (float)acc[i][e];
-      }
+      for (int j = 0; j < 2; j++) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    auto multiply = [&](int set) {
+      const float av[2][4] = {{a[set][0].x, a[set][0].y, a[set][0].z, a[set][0].w}, {a[set][1].x, a[set][1].y, a[set][1].z, a[set][1].w}};
+#pragma unroll
+      for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int j = 0; j < 2; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[i][s], (double)bq[set][j][s], acc[i][j], 0, 0, 0);
+    };
+    if (w < runs) load(0, w * FK);
+    for (int run = w; run < runs; run += 2 * FW) {
+      if (run + FW < runs) load(1, (run + FW) * FK);
+      multiply(0);
+      if (run + 2 * FW < runs) load(0, (run + 2 * FW) * FK);
+      if (run + FW < runs) multiply(1);
+    }
+    // wave w finishes tile (w / 2, w % 2)
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) part[w][2 * i + j][l] = acc[i][j];
+    __syncthreads();
+    f64x4 sum = part[0][w][l];
+#pragma unroll
+    for (int ww = 1; ww < FW; ww++) sum += part[ww][w][l];
+    // accumulator e of lane l: row 4 e + l / 16, column l % 16 of its 16 x 16 tile
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int n = n0 + (w >> 1) * 16 + 4 * e + (l >> 4);
+      if (n < N) Wp[(size_t)n * K + c0 + (w & 1) * 16 + r16] = (float)sum[e];
+    }
+    __syncthreads();                                      // (before the next tile's sums)
   }
 }
 
@@ -168,7 +174,7 @@ int launch_prepare_weights(const float* W, const float* Q, int N, int K, int r, 
   const long n_blocks = (n_hi_pad + (long)N * ((K - r) / 8) + 255) / 256;
   const long n_tiles = (long)(K / FC) * (long)((N + FN - 1) / FN), per_xcd = (n_tiles + 7) / 8;
   const unsigned grid = (unsigned)(8 * (per_xcd < (1 << 18) ? per_xcd : (1 << 18)));   // (beyond: several tiles each)
-  hipLaunchKernelGGL(fuse_rotation_fp64_kernel, dim3(grid), dim3(256), 0, s, W, Q, N, K, scratch, n_tiles, per_xcd);
+  hipLaunchKernelGGL(fuse_rotation_fp64_kernel, dim3(grid), dim3(FW * 64), 0, s, W, Q, N, K, scratch, n_tiles, per_xcd);
   hipError_t e0 = hipGetLastError();
   if (e0 != hipSuccess) return hip_failed(e0);      // nothing else is enqueued on an unwritten scratch
   hipLaunchKernelGGL(split_quantize_rows_kernel, dim3((unsigned)(n_blocks < QUANT_BLOCKS ? n_blocks : QUANT_BLOCKS)),
