@@ -29,18 +29,18 @@ __device__ __forceinline__ bool tile_of(int n_mt, int n_nt, int per_xcd, int tm,
   return true;
 }
 
-// The weight scales (fp16 [group][N]) of a wave's 32 channels from nw on: a copy brings a window of dwords that begins at
-// the dword of the first one; with two groups the upper half of the lanes fetches the second one's.
+// The weight scales (fp16 [group][N]) of a wave's 32 (48: DWORDS = 28) channels from nw on: a copy brings a window of dwords
+// that begins at the dword of the first one; with two groups the upper half of the lanes fetches the second one's.
 struct ScaleRows {
   const unsigned char* base;
   size_t last;                                           // byte offset of the dword of the last scale
   int N, nw;
   __device__ __forceinline__ size_t at(int g) const { return ((size_t)g * N + nw) * 2 & ~(size_t)3; }
-  template <bool TWO>
+  template <bool TWO, int DWORDS = 20>
   __device__ __forceinline__ void copy(uint32_t lds, int g0, int g1) const {
     const int l = threadIdx.x & 63;
     const size_t e0 = at(g0);
-    uint32_t v = min(TWO ? l & 31 : l, 19) * 4;
+    uint32_t v = min(TWO ? l & 31 : l, DWORDS - 1) * 4;
     if (TWO && l >= 32) v += (uint32_t)(at(g1) - e0);
     copy4_to_lds(lds, min(v, (uint32_t)min(last - e0, (size_t)0x7ffffffc)), base + e0);
   }

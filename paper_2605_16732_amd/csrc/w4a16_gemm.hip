@@ -6,8 +6,10 @@
 // the bf16 matrix pipe with nothing rounded before the fp32 accumulator; the per-group weight
 // scale is applied afterwards, by one fma per accumulator and group.
 //
-// Two schedules: up to 32 tokens a stream over the packed weights, beyond that MFMA tiles (launch_w4a16_gemm).
+// Up to 32 tokens a stream over the packed weights (one kernel up to 8, one beyond), then MFMA tiles (launch_w4a16_gemm).
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include <cstdlib>
 #include <cstring>
@@ -209,9 +211,9 @@ static int launch_large(const uint16_t* x, const void* blob, const uint16_t* bia
 
 }  // namespace w16
 
-// ---- few tokens (M <= 32): every weight is used once, so the kernel is a stream over the packed weights
-// (HBM-bound).  One workgroup (8 waves) = 32 output channels.  K is walked in chunks of KC channels (1024
-// for up to 8 tokens, 512 for up to 32): the chunk's codes (32 rows x KC/2 B), activations (MT rows x 2 KC B)
+// ---- up to 8 tokens: every weight is used once, so the kernel is a stream over the packed weights.
+// One workgroup (8 waves) = 32 output channels.  K is walked in chunks of 1024 channels:
+// the chunk's codes (32 rows x 512 B), activations (8 rows x 2 KB)
 // and scales go through registers into one of two LDS buffers, every thread loading consecutive 16-byte
 // pieces of a row, while the waves multiply the previous chunk (wave w takes scale groups w, w + 8, ...).
 // Orientation D[token][n]: the activations are the row operand of the 32x32x16 MFMA (tokens padded to 32 by
@@ -221,10 +223,8 @@ static int launch_large(const uint16_t* x, const void* blob, const uint16_t* bia
 // operands are kept in the order c0 c2 c4 c6 c1 c3 c5 c7 (the activations are permuted once when they
 // are staged), which saves the last round of byte permutes of the weight decode.  The 8 waves' partial
 // sums are added through LDS in wave order.
-template <int MT>
-struct Few {
-  static_assert(MT == 8 || MT == 32, "token capacity");
-  static constexpr int KC = MT == 8 ? 1024 : 512;   // channels per chunk
+struct Eight {
+  static constexpr int MT = 8, KC = 1024;           // token capacity, channels per chunk
   static constexpr int WROW = KC / 2 + 16;          // bytes per LDS row of codes
   static constexpr int XROW = KC * 2 + 16;          // bytes per LDS row of activations
   static constexpr int CODES_B = 32 * WROW;
@@ -251,13 +251,13 @@ __device__ __forceinline__ uint4 nibbles_to_bf16_eo(uint32_t p) {
   return r;
 }
 
-template <int GS, bool OUT_F32, int MT>
-__global__ __launch_bounds__(512) void w4a16_few_kernel(
+template <int GS, bool OUT_F32>
+__global__ __launch_bounds__(512) void w4a16_eight_kernel(
     const uint16_t* __restrict__ x, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
     const uint16_t* __restrict__ bias, int M, int N, int K, void* __restrict__ y, int sw_shift) {
   static_assert(GS == 32 || GS == 64, "scale granularity");
-  using F = Few<MT>;
-  constexpr int KC = F::KC, STEPS = GS / 16, GPC = KC / GS, BUF = F::buf_bytes(GS), NV = F::NV;
+  using F = Eight;
+  constexpr int MT = F::MT, KC = F::KC, STEPS = GS / 16, GPC = KC / GS, BUF = F::buf_bytes(GS), NV = F::NV;
   constexpr int CPT = KC / 512;                 // 16-byte code pieces per thread and chunk (32 rows x KC/32 pieces)
   constexpr int XPT = MT * (KC / 8) / 512;      // 16-byte activation pieces per thread and chunk
   constexpr int SPT = (GPC * 32 + 511) / 512;   // scales per thread and chunk
@@ -365,60 +365,237 @@ __global__ __launch_bounds__(512) void w4a16_few_kernel(
 #pragma unroll
   for (int v = 0; v < NV; v++) red[(w * NV + v) * 64 + l] = acc[v];
   __syncthreads();
-  constexpr int RPW = (NV + 7) / 8;                       // registers finished by each wave
-  if (n < N) {
+  const int m = 4 * h + w;                                // wave w < 4: register w, tokens w and 4 + w
+  if (n < N && w < NV && m < M) {
     const float b = bias ? bf16_bits_to_f32(bias[n]) : 0.0f;
+    float r = red[w * 64 + l];
 #pragma unroll
-    for (int e = 0; e < RPW; e++) {
-      const int v = w * RPW + e, m = 8 * (v >> 2) + 4 * h + (v & 3);
-      if (v < NV && m < M) {
-        float r = red[v * 64 + l];
-#pragma unroll
-        for (int p2 = 1; p2 < 8; p2++) r += red[(p2 * NV + v) * 64 + l];
-        r += b;
-        if (OUT_F32) ((float*)y)[(size_t)m * N + n] = r;
-        else ((uint16_t*)y)[(size_t)m * N + n] = f32_to_bf16_bits(r);
-      }
-    }
+    for (int p2 = 1; p2 < 8; p2++) r += red[(p2 * NV + w) * 64 + l];
+    r += b;
+    if (OUT_F32) ((float*)y)[(size_t)m * N + n] = r;
+    else ((uint16_t*)y)[(size_t)m * N + n] = f32_to_bf16_bits(r);
   }
 }
 
-template <int GS, bool OUT_F32, int MT>
-static int launch_few16(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
+template <int GS, bool OUT_F32>
+static int launch_eight(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
                         hipStream_t s) {
   const BlobLayout L = blob_layout(N, K, 0, g);
   const char* bp = (const char*)blob;
-  constexpr int SMEM = Few<MT>::smem_bytes(GS);
+  constexpr int SMEM = Eight::smem_bytes(GS);
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)w4a16_few_kernel<GS, OUT_F32, MT>,
+    hipError_t e = hipFuncSetAttribute((const void*)w4a16_eight_kernel<GS, OUT_F32>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((w4a16_few_kernel<GS, OUT_F32, MT>), dim3((N + 31) / 32), dim3(512), SMEM, s, x,
+  hipLaunchKernelGGL((w4a16_eight_kernel<GS, OUT_F32>), dim3((N + 31) / 32), dim3(512), SMEM, s, x,
                      (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw), bias, M, N, K, y,
                      g == 2 * GS ? 1 : 0);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
 
+// ---- 9 to 32 tokens: the same stream.  One workgroup (8 waves) = 32 output channels, or 48 (a second MFMA tile of which 16
+// lanes are real) where 32 leave some CUs two workgroups and 48 do not (32 tokens, K = 3072, N = 9216 on 256 CUs: 13.9 ->
+// 10.7 us).  K is walked in panels of 512 channels: codes, activations and scales come by global-to-LDS copies of whole
+// lines into a ring of up to four panels, all of them in flight from the start, and the waves multiply a panel's scale
+// groups in turn (wave w takes groups w, w + 8, ...).  Orientation as above.  The 8 waves' partial sums are added through LDS
+// in wave order.
+// Bound: launch (1.7 us), the copies, one memory latency and the decode.  Through registers into two buffers, with the next
+// panel's 32 to 64 KB in flight, -> now, us: K = 3072, N = 9216: 12 tokens 14.9 -> 10.5, 32: 16.4 -> 10.7; N = 3072, 16: 7.4 ->
+// 6.8; K = 12288, N = 3072, 20 tokens 24.3 -> 19.7.
+template <int NCH>
+struct Few {
+  static constexpr int KC = 512;                          // channels per panel
+  static constexpr int CROW = KC / 2, XROW = KC * 2;      // bytes per row of codes and of activations
+  static constexpr int CT = (NCH + 31) / 32, CC = (NCH * CROW + 8191) / 8192;   // column tiles; copies of codes per wave and panel
+  static constexpr int sc(int gs) { return KC / gs / 16 > 0 ? KC / gs / 16 : 1; }   // and of scales (two groups each)
+  static constexpr int scales_at = CC * 8192;
+  static constexpr int x_at(int gs) { return scales_at + sc(gs) * 2048; }
+  static constexpr int panel_bytes(int gs, int xc) { return x_at(gs) + xc * 8192; }
+};
+
+// XC: copies of activations per wave and panel (8 rows by all waves)
+template <int GS, bool OUT_F32, int NCH, int XC>
+__global__ __launch_bounds__(512) void w4a16_few_kernel(
+    const uint16_t* __restrict__ x, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
+    const uint16_t* __restrict__ bias, int M, int N, int K, void* __restrict__ y, int sw_shift, int nbuf) {
+  static_assert(GS == 32 || GS == 64, "scale granularity");
+  using F = Few<NCH>;
+  constexpr int CT = F::CT;
+  constexpr int KC = F::KC, STEPS = GS / 16, GPC = KC / GS, NV = 16, PANEL = F::panel_bytes(GS, XC), SC = F::sc(GS);
+  constexpr int CPP = F::CROW / 16, XPP = F::XROW / 16;   // 16-byte pieces per row
+  constexpr int COPIES = F::CC + SC + XC;                 // per wave and panel
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n0 = blockIdx.x * NCH;
+  const int np = (K + KC - 1) / KC, G = K / GS;           // (stored groups hold GS << sw_shift channels)
+  const uint32_t lds = lds_address(smem);
+  const halves::ScaleRows scales = {(const unsigned char*)sw, ((size_t)(((G - 1) >> sw_shift) + 1) * N * 2 - 1) & ~(size_t)3, N, n0};
+  const unsigned char* wb = wq + (size_t)n0 * (K / 2);
+  // Panel p into the ring slot at `at`.  Piece q of code row `row` sits at q ^ (row & 15), of activation row `row` at q ^ (row &
+  // 7): rows that are read together start in different banks.  What lies past the end of a row, past the last row or
+  // the last group is read from inside, unused.
+  const bool has_x = w * XC * 1024 < M * F::XROW;           // (this wave's copies of activations are of real rows)
+  auto wait_panel = [&](auto behind) {                    // until only the copies of `behind` later panels are in flight
+    if (has_x) wait_copies<decltype(behind)::value * COPIES>();
+    else wait_copies<decltype(behind)::value * (COPIES - XC)>();
+  };
+  auto issue = [&](int p, uint32_t at) {
+    const int last = (K - p * KC) / 32 - 1;               // last piece of codes in this panel's rows (may be past its end)
+#pragma unroll
+    for (int i = 0; i < F::CC; i++) {
+      const int f = (w * F::CC + i) * 64 + l, row = f / CPP, q = (f % CPP) ^ (row & 15);
+      copy_to_lds(lds + at + (w * F::CC + i) * 1024, (uint32_t)min(min(row, NCH - 1), N - 1 - n0) * (uint32_t)(K / 2) + min(q, last) * 16,
+                  wb + (size_t)p * F::CROW);
+    }
+#pragma unroll
+    for (int i = 0; i < SC; i++) {
+      const int k = w * SC + i, g0 = min(p * GPC + 2 * k, G - 1), g1 = min(p * GPC + 2 * k + 1, G - 1);
+      scales.copy<true, NCH == 32 ? 20 : 28>(lds + at + F::scales_at + k * 256, g0 >> sw_shift, g1 >> sw_shift);
+    }
+    const int xlast = 4 * last + 3;
+    if (!has_x) return;
+#pragma unroll
+    for (int i = 0; i < XC; i++) {
+      const int f = (w * XC + i) * 64 + l, row = f / XPP, q = (f % XPP) ^ (row & 7);
+      copy_to_lds(lds + at + F::x_at(GS) + (w * XC + i) * 1024, (uint32_t)min(row, M - 1) * (uint32_t)(2 * K) + min(q, xlast) * 16,
+                  (const unsigned char*)x + (size_t)p * F::XROW);
+    }
+  };
+  f32x16 acc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[ct][v] = 0.0f;
+  for (int p = 0; p < nbuf; p++)
+    if (p < np) issue(p, p * PANEL);
+  const int mrow = min(c, M - 1);
+  int cur = 0;
+  for (int p = 0; p < np; p++) {
+    // this wave's copies of panel p have landed, and (barrier) all waves'; panel p - 1 has been read by all of them
+    const int behind = min(np - 1 - p, p == 0 ? nbuf - 1 : nbuf - 2);
+    if (behind <= 0) wait_panel(std::integral_constant<int, 0>{});
+    else if (behind == 1) wait_panel(std::integral_constant<int, 1>{});
+    else if (behind == 2) wait_panel(std::integral_constant<int, 2>{});
+    else wait_panel(std::integral_constant<int, 3>{});
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (p > 0 && p - 1 + nbuf < np) issue(p - 1 + nbuf, (cur == 0 ? nbuf - 1 : cur - 1) * PANEL);
+    const unsigned char* sb = smem + cur * PANEL;
+    const int groups = min(GPC, (K - p * KC) / GS);
+    for (int gi = w; gi < groups; gi += 8) {
+      const unsigned char* xs = sb + F::x_at(GS) + mrow * F::XROW;
+      bf16x8 xa[STEPS];
+#pragma unroll
+      for (int s2 = 0; s2 < STEPS; s2++) xa[s2] = *(const bf16x8*)(xs + (((gi * (GS / 8) + h * (GS / 16) + s2) ^ (mrow & 7)) << 4));
+      const int j = (p * GPC + gi) >> sw_shift;
+#pragma unroll
+      for (int ct = 0; ct < CT; ct++) {
+        const int row = ct * 32 + (ct + 1 == CT && NCH % 32 != 0 ? c & 15 : c);   // (lanes past the last channel: one of the others)
+        uint32_t cw[STEPS];
+        if constexpr (GS == 64) {
+          const uint4 v = *(const uint4*)(sb + row * F::CROW + (((2 * gi + h) ^ (row & 15)) << 4));
+          cw[0] = v.x, cw[1] = v.y, cw[2] = v.z, cw[3] = v.w;
+        } else {
+          const uint2 v = *(const uint2*)(sb + row * F::CROW + ((gi ^ (row & 15)) << 4) + 8 * h);
+          cw[0] = v.x, cw[1] = v.y;
+        }
+        f32x16 z;
+#pragma unroll
+        for (int v = 0; v < 16; v++) z[v] = 0.0f;
+#pragma unroll
+        for (int s2 = 0; s2 < STEPS; s2++) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[s2], w16::decode(cw[s2]), z, 0, 0, 0);
+        const float sf = scales.read(sb + F::scales_at + (gi >> 1) * 256 + (gi & 1) * 128, j, row);
+        // accumulator register v holds token 8 (v / 4) + 4 h + v % 4
+#pragma unroll
+        for (int v = 0; v < NV; v++) acc[ct][v] = fmaf(z[v], sf, acc[ct][v]);
+      }
+    }
+    cur = cur + 1 == nbuf ? 0 : cur + 1;
+  }
+  // partial sums of the 8 waves, added in wave order: red[wave][register][lane]
+  constexpr int RPW = NV / 8;                             // registers finished by each wave
+  float* red = (float*)smem;
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++) {
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; v++) red[(w * NV + v) * 64 + l] = acc[ct][v];
+    __syncthreads();
+    const int n = n0 + ct * 32 + c;
+    if (n < N && ct * 32 + c < NCH) {
+      const float b = bias ? bf16_bits_to_f32(bias[n]) : 0.0f;
+#pragma unroll
+      for (int e = 0; e < RPW; e++) {
+        const int v = w * RPW + e, m = 8 * (v >> 2) + 4 * h + (v & 3);
+        if (m < M) {
+          float r = red[v * 64 + l];
+#pragma unroll
+          for (int p2 = 1; p2 < 8; p2++) r += red[(p2 * NV + v) * 64 + l];
+          r += b;
+          if (OUT_F32) ((float*)y)[(size_t)m * N + n] = r;
+          else ((uint16_t*)y)[(size_t)m * N + n] = f32_to_bf16_bits(r);
+        }
+      }
+    }
+  }
+}
+
+template <int GS, bool OUT_F32, int NCH, int XC>
+static int launch_few16(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y, int cus,
+                        hipStream_t s) {
+  const BlobLayout L = blob_layout(N, K, 0, g);
+  const char* bp = (const char*)blob;
+  constexpr int KC = Few<NCH>::KC, PANEL = Few<NCH>::panel_bytes(GS, XC), RED = 8 * 16 * 256;
+  static_assert(2 * PANEL >= RED && 2 * PANEL <= 160 * 1024, "LDS");
+  // up to four panels; more than one workgroup per CU: as many as leave room for two, at least two
+  const int wgs = (N + NCH - 1) / NCH;
+  int nbuf = std::min(4, 160 * 1024 / PANEL);
+  if (wgs > cus) nbuf = std::min(nbuf, std::max(2, 80 * 1024 / PANEL));
+  nbuf = std::max(2, std::min(nbuf, (K + KC - 1) / KC));
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)w4a16_few_kernel<GS, OUT_F32, NCH, XC>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, std::min(4, 160 * 1024 / PANEL) * PANEL);
+    if (e != hipSuccess) return hip_failed(e);
+    attr_done.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((w4a16_few_kernel<GS, OUT_F32, NCH, XC>), dim3(wgs), dim3(512), nbuf * PANEL, s, x,
+                     (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw), bias, M, N, K, y,
+                     g == 2 * GS ? 1 : 0, nbuf);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
+template <int GS, bool OUT_F32>
+static int launch_few(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y, int cus,
+                      hipStream_t s) {
+  const bool wide = (N + 31) / 32 > cus && (N + 47) / 48 <= cus;
+#define DIROTQ_FEW16(XC)                                                                  \
+  return wide ? launch_few16<GS, OUT_F32, 48, XC>(x, blob, bias, M, N, K, g, y, cus, s)   \
+              : launch_few16<GS, OUT_F32, 32, XC>(x, blob, bias, M, N, K, g, y, cus, s)
+  if (M <= 8) return launch_eight<GS, OUT_F32>(x, blob, bias, M, N, K, g, y, s);
+  if (M <= 16) DIROTQ_FEW16(2);
+  DIROTQ_FEW16(4);
+#undef DIROTQ_FEW16
+}
+
 int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
                       int y_dtype, hipStream_t s) {
-  const int gs = g == 32 ? 32 : 64;
+  int dev = 0, cus = 256;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_failed(e);
   auto few = [&](const uint16_t* xs, void* ys, int Ms) -> int {   // up to 32 tokens
-    if (Ms <= 8) {
-      if (gs == 32)
-        return y_dtype ? launch_few16<32, true, 8>(xs, blob, bias, Ms, N, K, g, ys, s)
-                       : launch_few16<32, false, 8>(xs, blob, bias, Ms, N, K, g, ys, s);
-      return y_dtype ? launch_few16<64, true, 8>(xs, blob, bias, Ms, N, K, g, ys, s)
-                     : launch_few16<64, false, 8>(xs, blob, bias, Ms, N, K, g, ys, s);
-    }
-    if (gs == 32)
-      return y_dtype ? launch_few16<32, true, 32>(xs, blob, bias, Ms, N, K, g, ys, s)
-                     : launch_few16<32, false, 32>(xs, blob, bias, Ms, N, K, g, ys, s);
-    return y_dtype ? launch_few16<64, true, 32>(xs, blob, bias, Ms, N, K, g, ys, s)
-                   : launch_few16<64, false, 32>(xs, blob, bias, Ms, N, K, g, ys, s);
+    if (g == 32)
+      return y_dtype ? launch_few<32, true>(xs, blob, bias, Ms, N, K, g, ys, cus, s)
+                     : launch_few<32, false>(xs, blob, bias, Ms, N, K, g, ys, cus, s);
+    return y_dtype ? launch_few<64, true>(xs, blob, bias, Ms, N, K, g, ys, cus, s)
+                   : launch_few<64, false>(xs, blob, bias, Ms, N, K, g, ys, cus, s);
   };
   // DIROTQ_W4A16_KERNEL=tile in the environment bars the few-token kernel above 32 tokens (the tests use it to
   // run the same rows through both kernels whatever the cost model below says)
@@ -426,10 +603,6 @@ int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias,
   const bool force_tile = force && !strcmp(force, "tile");
   // few tokens: the weight stream, not the matrix pipe, is the bound
   if (M <= 32) return few(x, y, M);
-  int dev = 0, cus = 256;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return hip_failed(e);
   const int nj = w16::token_tiles(M, N, K, cus);
   if (!force_tile && w16::two_few_launches(M, N, K, g, cus)) {
     const int st = few(x, y, 32);
