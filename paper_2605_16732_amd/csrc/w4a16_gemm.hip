@@ -56,6 +56,10 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   constexpr int GPS = GS == 32 ? 2 : 1;                  // groups per stage
   constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 128, SLOT = slot_bytes(128, NJ);
   constexpr int COPIES = NJ + 2;                         // per wave and stage: activations, codes, scales
+  // The copies of a stage sit behind the MFMAs of its token tiles (a copy holds its wave up for about 75 clocks, and with
+  // all of them at the barrier all waves wait at once): M = 4096, K = 4608, N = 1152 59.5 -> 54.8 us, N = 12288, K = 3072 400 ->
+  // 373; with a single token tile they come first (M = 256, N = K = 3072 16.2, spread 17.2).
+  constexpr bool SPREAD = NJ > 1;
   int m0, n0;
   if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
   const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
@@ -79,17 +83,19 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   const uint32_t ring = lds_address(smem) + kh * (NBUF * SLOT);
   const ScaleRows scales = {(const unsigned char*)sw, ((size_t)G * N * 2 - 1) & ~(size_t)3, N, nw};
   auto group = [&](int s, int jj) { return min(GS == 32 ? 2 * s + jj : GS == 128 ? s >> 1 : s, G - 1); };
-  auto issue = [&](int s, int slot) {                    // (past the last stage: that one again, unused)
+  // copies first .. end - 1 of a stage: activations (below NJ), codes, scales (past the last stage: that one again, unused)
+  auto issue = [&](int s, int slot, int first, int end) {
     s = min(s, nst - 1);
     const uint32_t at = ring + slot;
     const bool cut = short_last && s == nst - 1;         // (the missing upper half: the lower one again)
 #pragma unroll
-    for (int i = 0; i < NJ; i++) {
-      const int row = 8 * NJ * w + 8 * i + (l >> 3), piece = (l & 7) ^ ((row >> 1) & 7);
-      copy_to_lds(at + (8 * NJ * w + 8 * i) * 128, vo_x[i] - (cut && piece >= 4 ? 64u : 0u), xb + (size_t)s * 128);
-    }
-    copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
-    scales.copy<GS == 32>(at + X_BYTES + W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
+    for (int i = 0; i < NJ; i++)
+      if (i >= first && i < end) {
+        const int row = 8 * NJ * w + 8 * i + (l >> 3), piece = (l & 7) ^ ((row >> 1) & 7);
+        copy_to_lds(at + (8 * NJ * w + 8 * i) * 128, vo_x[i] - (cut && piece >= 4 ? 64u : 0u), xb + (size_t)s * 128);
+      }
+    if (NJ >= first && NJ < end) copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
+    if (end == COPIES) scales.copy<GS == 32>(at + X_BYTES + W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
   };
 
   f32x16 acc[NJ];
@@ -103,8 +109,8 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   int ln_x[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) ln_x[ks] = c * 128 + (((GS == 32 ? 2 * ks + h : 4 * h + ks) ^ swx) << 4);
-  issue(kh, 0);
-  issue(2 + kh, SLOT);
+  issue(kh, 0, 0, COPIES);
+  issue(2 + kh, SLOT, 0, COPIES);
   int cur = 0;
   for (int step = 0; step < steps; step++) {
     const int s = 2 * step + kh;
@@ -113,7 +119,7 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
     asm volatile("" ::: "memory");
     int fill = cur + 2 * SLOT;
     if (fill >= 3 * SLOT) fill -= 3 * SLOT;
-    issue(s + 4, fill);
+    if constexpr (!SPREAD) issue(s + 4, fill, 0, COPIES);
     if (s >= nst) break;                                 // (an odd number of stages: the other half has the last one)
     const bool half_stage = short_last && s == nst - 1;
     const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
@@ -157,6 +163,10 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
           I[j & 1][jj] = z;
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (SPREAD) {                          // a share of the copies of stage s + 4
+          issue(s + 4, fill, j * COPIES / NJ, (j + 1) * COPIES / NJ);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       if (j > 0) {
 #pragma unroll

@@ -567,6 +567,7 @@ __global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
   constexpr int GPS = GS == 32 ? 2 : 1;                  // groups per stage
   constexpr int TM_ = 32 * NJ, X_BYTES = TM_ * 64, SLOT = slot_bytes(64, NJ);
   constexpr int XC = (NJ + 1) / 2, COPIES = XC + 2;      // per wave and stage: activations; codes, scales
+  constexpr bool SPREAD = NJ > 1;                        // copies behind the MFMAs of the token tiles, as in the W4A16 tiles
   int m0, n0;
   if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
   const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
@@ -592,15 +593,16 @@ __global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
   const uint32_t ring = lds_address(smem) + kh * (NBUF * SLOT);
   const ScaleRows scales = {(const unsigned char*)sw, ((size_t)G * N * 2 - 1) & ~(size_t)3, N, nw};
   auto group = [&](int s, int jj) { return min(GS == 32 ? 2 * s + jj : GS == 128 ? s >> 1 : s, G - 1); };
-  auto issue = [&](int s, int slot) {                    // (past the last stage: that one again, unused)
+  // copies first .. end - 1 of a stage: activations (below XC), codes, scales (past the last stage: that one again, unused)
+  auto issue = [&](int s, int slot, int first, int end) {
     s = min(s, nst - 1);
     const uint32_t at = ring + slot;
     const bool cut = short_last && s == nst - 1;         // (the missing upper half: the lower one again)
 #pragma unroll
     for (int i = 0; i < XC; i++)
-      copy_to_lds(at + at_x[i], vo_x[i] - (cut && x_piece >= 2 ? 32u : 0u), xb + (size_t)s * 64);
-    copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
-    scales.copy<GS == 32>(at + X_BYTES + halves::W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
+      if (i >= first && i < end) copy_to_lds(at + at_x[i], vo_x[i] - (cut && x_piece >= 2 ? 32u : 0u), xb + (size_t)s * 64);
+    if (XC >= first && XC < end) copy_to_lds(at + X_BYTES + w * 1024, vo_w - (cut && w_half ? 16u : 0u), wb + (size_t)s * 32);
+    if (end == COPIES) scales.copy<GS == 32>(at + X_BYTES + halves::W_BYTES + w * 256, group(s, 0), group(s, GPS - 1));
   };
 
   f32x16 acc[NJ];
@@ -614,8 +616,8 @@ __global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
 #pragma unroll
     for (int p = 0; p < 2; p++) ln_x[p] = c * 64 + (((2 * p + h) ^ ((c >> 2) & 3)) << 4);
     const int sc_x = h ? 127 + 9 : 127 + 13, sc_w = 127 + 9;
-    issue(kh, 0);
-    issue(2 + kh, SLOT);
+    issue(kh, 0, 0, COPIES);
+    issue(2 + kh, SLOT, 0, COPIES);
     int cur = 0;
     for (int step = 0; step < steps; step++) {
       const int s = 2 * step + kh;
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
       asm volatile("" ::: "memory");
       int fill = cur + 2 * SLOT;
       if (fill >= 3 * SLOT) fill -= 3 * SLOT;
-      issue(s + 4, fill);
+      if constexpr (!SPREAD) issue(s + 4, fill, 0, COPIES);
       if (s >= nst) break;                               // (an odd number of stages: the other half has the last one)
       const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
       const unsigned char* sc_p = sp + X_BYTES + halves::W_BYTES + w * 256;
@@ -675,6 +677,10 @@ __global__ __launch_bounds__(NT, 1) void w4a8_medium_kernel(
             I[j & 1][GPS == 2 ? p : 0] = z;
           }
           __builtin_amdgcn_sched_barrier(0);
+          if constexpr (SPREAD) {                          // a share of the copies of stage s + 4
+            issue(s + 4, fill, j * COPIES / NJ, (j + 1) * COPIES / NJ);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
         if (j > 0) {
 #pragma unroll
