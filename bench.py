@@ -119,7 +119,7 @@ def bench_w4a16(args, shapes, B, I, np, torch) -> int:
         nbytes = sum(Ld["shape"].N * Ld["shape"].K // 2 + 2 * Ld["shape"].N * (Ld["shape"].K // Ld["shape"].g) +
                      2 * Ld["shape"].M * (Ld["shape"].K + Ld["shape"].N) for Ld in layers)
         gbs = nbytes / (sum_ms * 1e-3) / 1e9
-        roof = {"kernel": "w4a16_few_kernel", "bound": "hbm", "achieved": round(gbs, 1), "peak": 8000.0, "unit": "GB/s",
+        roof = {"kernel": "w4a16_eight_kernel" if args.tokens <= 8 else "w4a16_few_kernel", "bound": "hbm", "achieved": round(gbs, 1), "peak": 8000.0, "unit": "GB/s",
                 "frac": round(gbs / 8000.0, 5), "avg_launch_ms": round(sum_ms / len(layers), 5),
                 "algorithmic_bytes_per_launch": nbytes / len(layers), "traffic": None}
     out = {"metric": "effective TOPS of the W4A16 linear (16-bit activations, 4-bit per-group weights)",
@@ -509,7 +509,7 @@ def main() -> int:
         "metric": "effective TOPS of fused rotate+quant+W4A4 linear, FLUX shapes",
         "value": round(value, 3), "unit": "TOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": ("fp8 e4m3" if args.a8 or args.asym else "fp6 e2m3 (large layers) or fp8 e4m3") +
+        "dtype": ("fp8 e4m3" if args.asym else "fp6 e2m3 (large layers) or fp8 e4m3") +
                  " (exact integer codes, fp32 accumulate) + bf16 (fp32 accumulate)", "data": "synthetic",
         "config": {"workload": {"flux": "FLUX.1-dev-shaped block linears, M=4608 tokens, hidden 3072, "
                                         "r=128, g=64: fused QKV (N=9216), out-proj (N=3072), fc1 (N=12288), "

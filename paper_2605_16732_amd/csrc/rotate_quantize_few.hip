@@ -251,7 +251,7 @@ static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r
 template <int C, int T, int W>
 static int launch_tile(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, const RqOut& o, int r_pad,
                        int Kv, hipStream_t s) {
-  if constexpr (C < 128) {
+  if constexpr (C == 32 || (C == 64 && T >= 24)) {
     if (o.xf) return launch_one<C, T, W, 2>(x, Qt, M, K, r, g, o, r_pad, Kv, s);
   }
   if constexpr (C > 32) {
