@@ -12,12 +12,14 @@ namespace pipe {
 
 constexpr int TNW = 256;                     // output channels per workgroup tile (4 waves of 64)
 
+constexpr double HALF = 0.65;                // time of a 256 x 128 tile, in units of a 256 x 256 one
+
 // Time of the workgroup that has most to do with `big` 256 x 256 tiles and `small` 256 x 128 ones, in units of a large
 // tile, a small one takes HALF (K = 3072: 44 against 66 us), and a workgroup that has both kinds drains and refills its
 // pipeline once in between.  Per XCD (wpx workgroups) the large tiles are dealt to the slots 0, 1, ... in turn, the small
 // ones to the slots from the other end.
 inline double most(long big, long small, uint32_t wpx) {
-  constexpr double HALF = 0.65, PHASE = 0.04;
+  constexpr double PHASE = 0.04;
   const uint32_t b = (uint32_t)((big + 7) / 8), h = (uint32_t)((small + 7) / 8);
   const uint32_t bq = b / wpx, br = b % wpx, hq = h / wpx, hr = h % wpx;
   auto time = [&](uint32_t nb, uint32_t nh) { return nb + HALF * nh + (nb && nh ? PHASE : 0.0); };

@@ -23,6 +23,14 @@ __device__ __forceinline__ void unpack16_fp6(uint32_t p0, uint32_t p1, uint32_t 
   d[2] = and_or(t4, 0x80080080u, and_or(t2, 0x1C01C01Cu, and_or(s2, 0x02002000u, and_or(p0, 0x00700700u, (p1 >> 30) & 2u))));
 }
 
+// 16 unsigned nibbles -> 16 FP6 numbers [s 0 bbbb] with sign 0 (values 0 ... 15 in units of 2^-3), in the fields of unpack16_fp6
+__device__ __forceinline__ void spread16u_fp6(uint32_t p0, uint32_t p1, uint32_t (&d)[3]) {
+  const uint32_t s2 = p0 << 2, t2 = __builtin_amdgcn_alignbit(p1, p0, 30);
+  d[0] = and_or(s2, 0xC03C03C0u, p0 & 0x0F00F00Fu);
+  d[1] = and_or(t2, 0x03C03C03u, p1 & 0xF00F00F0u);
+  d[2] = and_or(t2, 0x3C03C03Cu, p0 & 0x00F00F00u);
+}
+
 // The low (high) nibbles of the bytes of two dwords in one: nibble 2 i from byte i of a, 2 i + 1 from byte i of b
 __device__ __forceinline__ uint32_t low_nibbles(uint32_t a, uint32_t b) { return (a & 0x0F0F0F0Fu) | ((b << 4) & 0xF0F0F0F0u); }
 __device__ __forceinline__ uint32_t high_nibbles(uint32_t a, uint32_t b) { return ((a >> 4) & 0x0F0F0F0Fu) | (b & 0xF0F0F0F0u); }

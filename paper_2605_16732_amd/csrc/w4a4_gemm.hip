@@ -1,427 +1,471 @@
 // Kernel B: y = x_h W'_h^T + sum_j s_x[:,j] s_w[:,j]^T * (q_x,j q_w,j^T)
-// (forward-computation equation of Section 4.2 of the paper).
+// (forward-computation equation of Section 4.2 of the paper): layers of a few hundred to a few thousand tokens.
 //
-// Orientation.  D[n][token]: output channels on the MFMA row axis, tokens on the column
-// axis, so a lane owns one token and 4 consecutive output channels per register quad
-// (one 8-byte bf16 store).  Workgroup tile 128 n x 128 tokens, 4 waves as 2 (n) x 2
-// (tokens), each 64 n x 64 tokens = 2 x 2 MFMA tiles; two workgroups share a CU so that
-// one's barrier / staging phase overlaps the other's arithmetic.
+// Arithmetic.  A 4-bit code is an exact FP6 (E2M3) number: the nibble [s mmm] becomes [s 00 mmm] = +-m * 2^-3 (an unsigned one
+// of asymmetric activations [0 0 u uuu]), and the block-scaled 32x32x64 MFMA with the E8M0 scale 2^3 on both operands
+// returns the exact integer dot of a group in fp32.  The scale product of a group is an outer product of fp16 vectors: one
+// fp16 MFMA (scales in k-slot 0) forms it exactly, one fma per accumulator and group applies it.  The 16-bit branch runs on
+// bf16 MFMAs into the same accumulators.  Groups of 32: a stage holds two, each multiplied with the other's half of the
+// weight operand cleared.
 //
-// Integer part.  A stored code is a sign-magnitude nibble.  On its way into LDS (once per
-// workgroup) it becomes the byte [sign 0000 magnitude], which read as fp8 (E4M3) is the
-// subnormal q * 2^-9: the fp8 matrix pipe then multiplies and adds the codes exactly
-// (products and sums of small integers times 2^-18, far inside fp32) and hands back the
-// group dot as a float, so no integer-to-float conversion is left for the vector ALU.
-// Even and odd channels of an 8-channel dword land in different operand registers; both
-// operands use the same permutation, so the dot product is unchanged.  One 32x32x64 MFMA
-// covers a 64-channel group (two for 128, a half-empty one for 32).
+// Asymmetric activations.  The zero-point term sum_j z[m,j] (s_w[n,j] sum_k q_w[n,k]) is added by bf16 MFMAs on exact splits of
+// its factors (z = z1 + z2, c = b1 + b2 + b3, all six products): the k-slots of one lane half hold a group, {z1 z2}
+// three times against {b1 b1} {b2 b2} {b3 b3}, so that the token operand is one dword repeated and one MFMA takes two groups.
 //
-// Dequantisation.  The per-group scale product P[n][token] = s_w[n,j] * s_x[token,j] is an
-// outer product of fp16 vectors: it is produced exactly (fp16 x fp16 fits fp32) by one
-// fp16 MFMA whose operands carry the scales in k-slot 0 and zeros elsewhere, which
-// leaves the vector ALU one fma per accumulator and group: acc += (2^-18 I) * P.  The
-// common factor 2^18 is applied once at the end (exact), before the 16-bit branch is
-// accumulated on top by bf16 MFMAs.
-//
-// Asymmetric activations (ASYM).  Codes are then unsigned nibbles, whose zero-extended byte
-// is again an exact fp8 number (u * 2^-9 for u in 0..15: the first binade continues the
-// subnormals linearly), so the main loop is unchanged.  The zero-point term
-// sum_j z[m,j] * (s_w[n,j] * sum_k q_w[n,k]) is a small GEMM over the groups; it is added
-// after the main loop by bf16 MFMAs on exact bf16 splits of its factors (z = z1 + z2,
-// c = b1 + b2 + b3; every product but z2 b3, which is below 2^-22 of the term, is kept).
-//
-// Schedule.  The vector ALU is the binding unit (one fma per accumulator and group plus the
-// unpacking, against 64 cycles of fp8 MFMA per tile and 64-channel group), so the main loop
-// is software-pipelined by hand: the MFMAs of tile s+1 are issued before the fma sweep of
-// tile s, and the LDS operand reads of the next group are issued one sweep ahead.
+// Schedule.  128 channels x 128 tokens per workgroup, eight waves: four of 32 channels, twice, for the even and the odd
+// stages of 64 channels of K.  A wave loads its channels' codes straight into the lanes that multiply them and unpacks them
+// there: weights never pass through LDS and are unpacked once.  Tokens are unpacked once per workgroup, by the four
+// waves of a part of K, and lie in LDS in the order in which the lanes read them (no bank conflicts, no swizzle; a lane's
+// second 16 bytes hold the rest of its codes and its scale).  A wave multiplies 32 x 128 outputs per stage; the fma sweep of
+// a token tile follows the MFMAs of the next one, and each part of the next stages' work (unpacking, LDS stores two
+// stages ahead, loads three and four ahead) has its place between two tiles.  One barrier per stage.  One tile per
+// workgroup: what walking several tiles costs in every stage (a compare, a branch, pointers) is more than it saves.
+// Bound: instruction issue.  A tile of 32 x 32 and a group takes 64 cycles of MFMA, 40 of fma and about 26 integer
+// operations of 4.3 cycles, which add up (measured 200 cycles; three waves per SIMD with K in three parts: 190, lost
+// again in the exchange of their sums).  The 128 x 128 tiles before it had four waves that staged both operands through LDS
+// as fp8: M = 1000, K = N = 3072 34.3 -> 26.5 us (asymmetric 39.0 -> 28.4).
 #include <atomic>
 
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
-#include "gemm_tail.h"
+#include "pipe_unpack.h"
+#include "tile_walk.h"
 #include "w4a4_plan.h"
+
+#include "dirotq_internal.h"
 
 namespace dirotq {
 
-constexpr int BKQ = 128;        // 4-bit channels per LDS stage (one 128-byte fp8 row)
-constexpr int ROWS = TN + TM;
-constexpr int STAGE_BYTES = ROWS * 128;              // fp8 [256 rows][128 B] (= bf16 [256][64])
-constexpr int SCALE_OFF = 2 * STAGE_BYTES;           // u64 [2 bufs][4 groups][256 rows]: {fp16 scale, 0, 0, 0}
-// per buffer: (groups per stage) x ROWS x 8 bytes, then 8 zero bytes read by lanes 32..63
-constexpr int scale_buf_bytes(int gs) { return (BKQ / gs) * ROWS * 8; }
-constexpr int zero_off(int gs) { return SCALE_OFF + 2 * scale_buf_bytes(gs); }
-constexpr int smem_bytes(int gs) { return zero_off(gs) + 256; }
+namespace tile {
 
+constexpr int NT = 512, NJ = 4, KS = 2, NBUF = 3;
+constexpr int TNW = 128, TMW = 128;          // output channels, tokens of a workgroup
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-// one 32x32x64 fp8 MFMA step (no block scaling)
-__device__ __forceinline__ f32x16 mfma_fp8_k64(i32x4 a_lo, i32x4 a_hi, i32x4 b_lo, i32x4 b_hi, f32x16 c) {
-  const i32x8 a = __builtin_shufflevector(a_lo, a_hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  const i32x8 b = __builtin_shufflevector(b_lo, b_hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+#define GLOBAL __attribute__((address_space(1)))
+typedef const GLOBAL uint8_t* gptr;
+
+// A fragment: what 32 tokens x 64 channels are in LDS, in the order in which the lanes read it.
+//   64 x 16 B: first 16 of a lane's 24 bytes of codes | 64 x {8 bytes of codes, s, 0} (lanes 32..63: s = 0) |
+//   groups of 32: 64 x {s of the second group, 0} (same) | asymmetric: zero-points 64 x {Z, Z, Z, 0}
+constexpr int gps(int gs) { return gs == 32 ? 2 : 1; }
+constexpr int HI = 1024, SC1 = 2048;
+constexpr int zp_at(int gs) { return SC1 + (gs == 32 ? 512 : 0); }
+constexpr int frag_bytes(int gs, bool asym) { return zp_at(gs) + (asym ? 1024 : 0); }
+
+template <int GS, bool OUT_F32, bool ASYM>
+struct Geo {
+  static constexpr int FRAG = frag_bytes(GS, ASYM), SLOT = NJ * FRAG, RING = NBUF * KS * SLOT;
+  static constexpr int B_SLOT = NJ * 1024;                            // 16-bit branch: two slots per part of K, behind the ring
+  // the exchange: per wave two tiles of partial sums; then the rows of y
+  static constexpr int X_WAVE = 2 * 4096, OUT_ROW = TNW * (OUT_F32 ? 4 : 2) + 16;
+  static constexpr int X_BYTES = 8 * X_WAVE + TMW * OUT_ROW;
+  static constexpr int LOOP = RING + 2 * KS * B_SLOT, SMEM = LOOP > X_BYTES ? LOOP : X_BYTES;
+};
+
+__device__ __forceinline__ void barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 template <int GS, bool OUT_F32, bool ASYM>
-__global__ __launch_bounds__(NTHREADS, 2) void w4a4_gemm_kernel(
+__global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
     const uint16_t* __restrict__ xh, const uint8_t* __restrict__ xl, const uint16_t* __restrict__ sx,
     const uint16_t* __restrict__ zx, const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq,
-    const uint16_t* __restrict__ sw, const int16_t* __restrict__ wsum, const uint16_t* __restrict__ bias, int M,
-    int N, int K, int r, void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
+    const uint16_t* __restrict__ sw, const int16_t* __restrict__ wsum, const uint16_t* __restrict__ bias, int M, int N,
+    int K, int r, void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
   extern __shared__ __align__(16) unsigned char smem[];
+  typedef Geo<GS, OUT_F32, ASYM> g_;
+  constexpr int GPS = gps(GS), FRAG = g_::FRAG, SLOT = g_::SLOT, ZP = zp_at(GS);
 
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (logical >= n_mt * n_nt) return;
-  // within an XCD's run, sweep GN output tiles per token tile (shared operands stay in L2)
-  constexpr int GN = 4;
-  const int grp = logical / (GN * n_mt), in_grp = logical % (GN * n_mt);
-  const int gn = min(n_nt - grp * GN, GN);
-  const int nt = grp * GN + in_grp % gn, mt = in_grp / gn;
-  const int m0 = mt * TM, n0 = nt * TN;
+  if ((int)(blockIdx.x >> 3) >= per_xcd || logical >= n_mt * n_nt) return;
+  int m0, n0;
+  tile_origin<4, TNW, TMW>(logical, n_mt, n_nt, m0, n0);
 
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
-  const int wn = w & 1, wt = w >> 1;
-  const int h = l >> 5;
-  const int KL = K - r;            // number of 4-bit channels
-  const int G = KL / GS;
-  constexpr int GPS = BKQ / GS;    // groups per stage
-  constexpr int MPG = GS / 32;     // 16-byte operand chunks (32 channels over the lane pair) per group
-  constexpr int SCALE_BUF_BYTES = scale_buf_bytes(GS), ZERO_OFF = zero_off(GS);
+  const int t = threadIdx.x, l = t & 63, row = l & 31, half = l >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ws = w & 3, kh = w >> 2;                                  // 32 channels (and the token tile that is staged), part of K
+  const int KL = K - r, G = KL / GS, ldq = KL / 2;
+  const int nq = (KL + 63) / 64, nqi = (nq + 1) / 2;                  // stages, intervals
+  const int nbf = r / 16, nbi = nbf / 2;
+  const bool short_last = GS == 32 && (KL % 64) != 0;
+  const uint32_t rn = (uint32_t)(min(n0 + 32 * ws + row, N - 1) - n0), rm = (uint32_t)(min(m0 + 32 * ws + row, M - 1) - m0);
+  const uint32_t lane16 = l * 16, lower = half ? 0u : 0xFFFFu;
 
-  if (t < 64) ((uint32_t*)(smem + ZERO_OFF))[t] = 0u;   // read as the zero operand half
+  f32x16 acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[j][v] = 0.0f;
 
-  f32x16 acc[2][2];
+  // ---- 16-bit branch: loads of step st (16 channels; part kh takes the steps 2 st + kh)
+  u32x4 bw[2], bx[2];
+  const uint32_t vbw = __umul24(rn, 2 * r) + half * 16, vbx = __umul24(rm, 2 * r) + half * 16;
+  const gptr bw_b = (gptr)wh + (size_t)n0 * (2 * r) + kh * 32, bx_b = (gptr)xh + (size_t)m0 * (2 * r) + kh * 32;
+  auto load_b = [&](int st, int set) {
+    const size_t o = (size_t)min(st, nbi - 1) * 64;
+    bw[set] = *(const GLOBAL u32x4*)(bw_b + o + vbw);
+    bx[set] = *(const GLOBAL u32x4*)(bx_b + o + vbx);
+  };
+  auto branch16 = [&]() {
+    unsigned char* reg = smem + g_::RING + kh * (2 * g_::B_SLOT);
+    for (int st = 0; st < nbi; st++) {
+      unsigned char* sp = reg + (st & 1) * g_::B_SLOT;
+      const u32x4 wv = bw[0];
+      *(u32x4*)(sp + ws * 1024 + lane16) = bx[0];
+      bx[0] = bx[1];
+      bw[0] = bw[1];
+      load_b(st + 2, 1);
+      barrier();
 #pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
-
-  // operand rows of this lane: A = weights (rows 0..127 of a stage), B = tokens (128..255)
-  int rowA[2], rowB[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++) rowA[i] = wn * 64 + i * 32 + (l & 31);
-#pragma unroll
-  for (int j = 0; j < 2; j++) rowB[j] = TN + wt * 64 + j * 32 + (l & 31);
-  const int swz = ((l & 31) >> 1) & 7;                 // tile bases are multiples of 32 rows
-
-  // ---- 4-bit branch ---------------------------------------------------------------
-  if (KL > 0) {
-    const size_t ldq = (size_t)KL / 2;        // packed bytes per row
-    const int prow = t >> 2, pchunk = t & 3;  // 4 rows (stride 64) x one 16-B packed chunk per thread
-    const int pc16 = min(pchunk * 16, (int)ldq - 16);   // this thread's chunk, kept inside the row
-    const uint8_t* gq[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int row = prow + 64 * i;
-      gq[i] = (row < TN ? wq + (size_t)min(n0 + row, N - 1) * ldq : xl + (size_t)min(m0 + row - TN, M - 1) * ldq) +
-              pc16;
+      for (int j = 0; j < NJ; j++) {
+        const i32x4 bv = *(const i32x4*)(sp + j * 1024 + lane16);
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv), __builtin_bit_cast(bf16x8, bv), acc[j], 0, 0, 0);
+      }
     }
-    // scale staging: thread t owns row t of the stage (weights then tokens)
-    const int ts = t;
-    const uint16_t* gs = ts < TN ? sw + min(n0 + ts, N - 1) : sx + min(m0 + ts - TN, M - 1);
-    const size_t s_ld = t < TN ? (size_t)N : (size_t)M;
+  };
 
-    // Staging registers: chunk i (i < 4) / the scales (i == 4) of one stage.  Each piece is
-    // reloaded for stage s+2 right after it has been unpacked into LDS for stage s+1, so a
-    // global load has a whole stage of arithmetic to complete.
-    uint4 rq[4];
-    uint16_t rs[GPS];
-    // Loads are unconditional (straight-line code keeps the outstanding-load count exact):
-    // a chunk past the end of the row is re-read from the row's last chunk and belongs to a
-    // group >= G, whose scale is forced to zero, so it contributes exactly nothing.
-    const int last_chunk = (int)ldq - 16 - pc16;            // largest in-row offset for this thread (>= 0)
-    auto gload_piece = [&](int st, int i) {
-      if (i < 4) {
-        rq[i] = *(const uint4*)(gq[i] + min(st * (BKQ / 2), last_chunk));
+  if (nq == 0) {
+    load_b(0, 0);
+    load_b(1, 1);
+    branch16();
+  } else {
+    // ---- loads of the 4-bit part: the part's stage i holds the 64 channels from 64 (2 i + kh) on
+    const uint32_t vw = __umul24(rn, ldq) + half * 16, vx = __umul24(rm, ldq) + half * 16;
+    const int first = min(kh, nq - 1);
+    gptr wq_p = (gptr)wq + (size_t)n0 * ldq + first * 32, xl_p = (gptr)xl + (size_t)m0 * ldq + first * 32;
+    u32x4 rw[2], rx[2];
+    uint16_t rsw[2], rsx[2], rzs[2], rzx[2];
+    int16_t rzw[2];
+    int lw = 0, lx = 0;                                               // stage of the next load
+    // a row's last 32 channels alone: both halves read them
+    auto cut = [&](int sq) { return short_last && sq >= nq - 1 ? half * 16u : 0u; };
+    // scales: group of lane half h of stage sq; a lane keeps its column and multiplies its row out
+    const gptr sw_c = (gptr)(sw + n0 + rn), sx_c = (gptr)(sx + m0 + rm);
+    const gptr sc_c = half ? sx_c : sw_c;                             // groups of 64, 128: one load for both, x one stage ahead
+    const uint32_t sc_ld = half ? 2u * M : 2u * N;
+    auto group = [&](int sq) { return GS == 128 ? sq >> 1 : GS == 64 ? sq : 2 * sq + half; };
+    auto load_w = [&](auto set) {
+      const int sq = 2 * lw + kh;
+      rw[set] = *(const GLOBAL u32x4*)(wq_p + (GS == 32 ? vw - cut(sq) : vw));
+      if constexpr (GS == 32) {
+        rsw[set] = *(const GLOBAL uint16_t*)(sw_c + (uint64_t)(uint32_t)min(group(sq), G - 1) * (2u * N));
       } else {
+        rsw[set] = *(const GLOBAL uint16_t*)(sc_c + (uint64_t)(uint32_t)min(group(sq + 2 * half), G - 1) * sc_ld);
+      }
+      if constexpr (ASYM) {
+        if (GS == 32 || set == 0) {
+          const int jz = min((GS == 32 ? sq : (lw >> 1) * KS + kh) * 2 + half, G - 1);
+          const uint64_t o = (uint64_t)(uint32_t)jz * (2u * N);
+          rzs[set] = *(const GLOBAL uint16_t*)(sw_c + o);
+          rzw[set] = *(const GLOBAL int16_t*)((gptr)(wsum + n0 + rn) + o);
+        }
+      }
+      lw++;
+      wq_p += 2 * lw + kh < nq ? 64 : 0;
+    };
+    auto load_x = [&](auto set) {
+      const int sq = 2 * lx + kh;
+      rx[set] = *(const GLOBAL u32x4*)(xl_p + (GS == 32 ? vx - cut(sq) : vx));
+      if constexpr (GS == 32) rsx[set] = *(const GLOBAL uint16_t*)(sx_c + (uint64_t)(uint32_t)min(group(sq), G - 1) * (2u * M));
+      if constexpr (ASYM) {
+        if (GS == 32 || set == 0) {
+          const int jz = min((GS == 32 ? sq : (lx >> 1) * KS + kh) * 2 + half, G - 1);
+          rzx[set] = *(const GLOBAL uint16_t*)((gptr)(zx + m0 + rm) + (uint64_t)(uint32_t)jz * (2u * M));
+        }
+      }
+      lx++;
+      xl_p += 2 * lx + kh < nq ? 64 : 0;
+    };
+
+    // ---- weights: raw -> operand registers (stage iw)
+    i32x8 a[2];
+    i32x2 sa[2][GPS];
+    u32x4 za;
+    int iw = 0;
+    auto unpack_w = [&](auto set, int part) {
+      uint32_t d[3];
+      pipe::unpack16_fp6(rw[set][2 * part], rw[set][2 * part + 1], d);
+#pragma unroll
+      for (int e = 0; e < 3; e++) a[set][3 * part + e] = (int)d[e];
+    };
+    auto scale_w = [&](auto set) {
+      const int sq = 2 * iw + kh;
+      if constexpr (GS == 32) {
+        // lanes 0..31 take both groups' scales: the second one's lie in the upper half
+        const auto v = __builtin_amdgcn_permlane32_swap((uint32_t)rsw[set], (uint32_t)rsw[set], false, false);
+        sa[set][0] = i32x2{(int)(v[0] & (2 * sq < G ? lower : 0u)), 0};
+        sa[set][1] = i32x2{(int)(v[1] & (2 * sq + 1 < G ? lower : 0u)), 0};
+      } else {
+        sa[set][0] = i32x2{(int)(rsw[set] & (sq < nq ? lower : 0u)), 0};
+      }
+      if constexpr (ASYM) {
+        if (GS == 32 || set == 0) {
+          const int jz = (GS == 32 ? sq : (iw >> 1) * KS + kh) * 2 + half;
+          const float c = jz < G ? f16_bits_to_f32(rzs[set]) * (float)rzw[set] : 0.0f;
+          const uint32_t p1 = __builtin_bit_cast(uint32_t, c) & 0xFFFF0000u;
+          const float c1 = c - __builtin_bit_cast(float, p1);
+          const uint32_t p2 = __builtin_bit_cast(uint32_t, c1) & 0xFFFF0000u;
+          const float c2 = c1 - __builtin_bit_cast(float, p2);
+          const uint32_t p3 = __builtin_bit_cast(uint32_t, c2) & 0xFFFF0000u;
+          za = u32x4{p1 | p1 >> 16, p2 | p2 >> 16, p3 | p3 >> 16, 0u};
+        }
+      }
+      iw++;
+    };
+    // ---- tokens: raw -> LDS (stage ix)
+    int ix = 0;
+    const int frag = ws * FRAG;
+    auto put_x = [&](auto set, uint16_t scale, int so) {
+      uint32_t d0[3], d1[3];
+      const u32x4 v = rx[set];
+      if constexpr (ASYM) {
+        pipe::spread16u_fp6(v[0], v[1], d0);
+        pipe::spread16u_fp6(v[2], v[3], d1);
+      } else {
+        pipe::unpack16_fp6(v[0], v[1], d0);
+        pipe::unpack16_fp6(v[2], v[3], d1);
+      }
+      unsigned char* f = smem + (so + frag);
+      const int sq = 2 * ix + kh;
+      uint32_t s;
+      if constexpr (GS == 32) {
+        s = scale & (2 * sq + half < G ? 0xFFFFu : 0u);
+      } else {
+        s = __builtin_amdgcn_permlane32_swap((uint32_t)scale, (uint32_t)scale, false, false)[1] & (sq < nq ? lower : 0u);
+      }
+      *(u32x4*)(f + lane16) = u32x4{d0[0], d0[1], d0[2], d1[0]};
+      *(u32x4*)(f + HI + lane16) = u32x4{d1[1], d1[2], GS == 32 && half ? 0u : s, 0u};
+      if constexpr (GS == 32) *(u32x2*)(f + SC1 + ((half ^ 1) * 32 + row) * 8) = u32x2{half ? s : 0u, 0u};
+      if constexpr (ASYM) {
+        if (GS == 32 || set == 0) {
+          const int jz = (GS == 32 ? sq : (ix >> 1) * KS + kh) * 2 + half;
+          const float z = jz < G ? f16_bits_to_f32(rzx[set]) : 0.0f;
+          const uint32_t z1 = __builtin_bit_cast(uint32_t, z) & 0xFFFF0000u;
+          const uint32_t z2 = __builtin_bit_cast(uint32_t, z - __builtin_bit_cast(float, z1));
+          const uint32_t Z = __builtin_amdgcn_perm(z2, z1, 0x07060302u);
+          *(u32x4*)(f + ZP + lane16) = u32x4{Z, Z, Z, 0u};
+        }
+      }
+      ix++;
+    };
+    // ---- operands of token tile j
+    i32x8 b[2];
+    i32x2 sb1[2];
+    i32x4 zb[2];
+    auto read_b = [&](auto zset, int j, int so) {
+      const unsigned char* f = smem + (so + j * FRAG);
+      b[j & 1] = __builtin_shufflevector(*(const i32x4*)(f + lane16), *(const i32x4*)(f + HI + lane16), 0, 1, 2, 3, 4, 5, 6, 7);
+      if (GS == 32) sb1[j & 1] = *(const i32x2*)(f + SC1 + l * 8);
+      if constexpr (ASYM) {
+        if (GS == 32 || zset == 0) zb[j & 1] = *(const i32x4*)(f + ZP + lane16);
+      }
+    };
+
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    int cur = kh * (NBUF * SLOT), nxt = cur + SLOT, fill = cur + 2 * SLOT;
+    f32x16 I[2], P[2];
+    const int low_keep = half ? 0 : -1;
+    auto interval = [&](auto set) {
+      constexpr int other = 1 - set;
+      std::integral_constant<int, other> next;
+#pragma unroll
+      for (int j = 0; j < NJ; j++) {
 #pragma unroll
         for (int jj = 0; jj < GPS; jj++) {
-          const int j = st * GPS + jj;
-          const uint16_t v = gs[(size_t)min(j, G - 1) * s_ld];
-          rs[jj] = (uint16_t)(v & (j < G ? 0xFFFFu : 0u));
-        }
-      }
-    };
-    // unpack one staged chunk (or the scales) into the LDS stage `buf`
-    auto sstore_piece = [&](int buf, int i) {
-      unsigned char* sb = smem + buf * STAGE_BYTES;
-      if (i < 4) {
-        const int row = prow + 64 * i;
-        uint4 e, o;
-        if (ASYM && i >= 2) {                 // rows 128..255 of a stage are tokens: unsigned codes
-          unpack8u(rq[i].x, e.x, o.x);
-          unpack8u(rq[i].y, e.y, o.y);
-          unpack8u(rq[i].z, e.z, o.z);
-          unpack8u(rq[i].w, e.w, o.w);
-        } else {
-          unpack8(rq[i].x, e.x, o.x);
-          unpack8(rq[i].y, e.y, o.y);
-          unpack8(rq[i].z, e.z, o.z);
-          unpack8(rq[i].w, e.w, o.w);
-        }
-        *(uint4*)(sb + tile_off_bytes(row, 2 * pchunk)) = e;
-        *(uint4*)(sb + tile_off_bytes(row, 2 * pchunk + 1)) = o;
-      } else {
-        uint2* sdst = (uint2*)(smem + SCALE_OFF + buf * SCALE_BUF_BYTES);
+          f32x16 z;
 #pragma unroll
-        for (int jj = 0; jj < GPS; jj++)
-          sdst[jj * ROWS + t] = make_uint2(rs[jj], 0u);
-      }
-    };
-
-    // per-lane LDS addresses: operand chunk k (0..3) of each tile row, and the scale words
-    // (k-slot 0 of the outer-product MFMA lives in lanes 0..31; lanes 32..63 read zeros)
-    int adA[2][4], adB[2][4];
+          for (int v = 0; v < 16; v++) z[v] = 0.0f;
+          i32x8 av = a[set];
+          if constexpr (GS == 32) {
+            const int keep = jj ? ~low_keep : low_keep;
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const int off = ((2 * k + h) ^ swz) << 4;
-#pragma unroll
-      for (int i = 0; i < 2; i++) adA[i][k] = rowA[i] * 128 + off;
-#pragma unroll
-      for (int j = 0; j < 2; j++) adB[j][k] = rowB[j] * 128 + off;
-    }
-    int soffA[2], soffB[2];
-#pragma unroll
-    for (int i = 0; i < 2; i++) soffA[i] = h ? ZERO_OFF : SCALE_OFF + rowA[i] * 8;
-#pragma unroll
-    for (int j = 0; j < 2; j++) soffB[j] = h ? ZERO_OFF : SCALE_OFF + rowB[j] * 8;
-    const int sstep = h ? 0 : ROWS * 8;       // per group within a stage
-    const int sbufstep = h ? 0 : SCALE_BUF_BYTES;
-
-    const int nst = (KL + BKQ - 1) / BKQ;
-#pragma unroll
-    for (int i = 0; i < 5; i++) gload_piece(0, i);
-#pragma unroll
-    for (int i = 0; i < 5; i++) {
-      sstore_piece(0, i);
-      gload_piece(min(1, nst - 1), i);
-    }
-    __syncthreads();
-    for (int st = 0; st < nst; st++) {
-      const int buf = st & 1;
-      const int st2 = min(st + 2, nst - 1);     // past the end: harmless re-load, never used
-      const unsigned char* sb = smem + buf * STAGE_BYTES;
-      const unsigned char* ssb = smem + buf * sbufstep;
-      // operands of one group: fp8 codes of 2 weight tiles and 2 token tiles, and their scales
-      i32x4 a[2][MPG], b[2][MPG];
-      f16x4 sa[2], sbv[2];
-      auto load_ops = [&](int jj) {
-#pragma unroll
-        for (int kk = 0; kk < MPG; kk++) {
-#pragma unroll
-          for (int i = 0; i < 2; i++) a[i][kk] = *(const i32x4*)(sb + adA[i][jj * MPG + kk]);
-#pragma unroll
-          for (int j = 0; j < 2; j++) b[j][kk] = *(const i32x4*)(sb + adB[j][jj * MPG + kk]);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; i++) sa[i] = *(const f16x4*)(ssb + soffA[i] + jj * sstep);
-#pragma unroll
-        for (int j = 0; j < 2; j++) sbv[j] = *(const f16x4*)(ssb + soffB[j] + jj * sstep);
-      };
-      f32x16 I[2], P[2];
-      auto issue = [&](int i, int j, int slot) {     // 2^-18 I and the scale product of tile (i, j)
-        // (for 128-channel groups the scale-product MFMA sits between the two dependent code
-        // MFMAs, so the second one finds its accumulator ready instead of stalling the wave)
-        const i32x4 zero4 = {0, 0, 0, 0};
-        f32x16 z, p;
-#pragma unroll
-        for (int v = 0; v < 16; v++) z[v] = p[v] = 0.0f;
-        if (MPG == 1) z = mfma_fp8_k64(a[i][0], zero4, b[j][0], zero4, z);     // 32 channels: upper k half empty
-        else z = mfma_fp8_k64(a[i][0], a[i][1], b[j][0], b[j][1], z);
-        P[slot] = __builtin_amdgcn_mfma_f32_32x32x8f16(sa[i], sbv[j], p, 0, 0, 0);
-        if (MPG == 4) z = mfma_fp8_k64(a[i][2], a[i][3], b[j][2], b[j][3], z);
-        I[slot] = z;
-      };
-      auto sweep = [&](int i, int j, int slot) {     // acc += (2^-18 I) * P for tile (i, j)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc[i][j][v] = fmaf(I[slot][v], P[slot][v], acc[i][j][v]);
-        asm volatile("" : "+v"(acc[i][j]));            // pin the sweep here (keeps I/P live ranges short)
-      };
-      // the next stage's unpack work is spread over the tile sweeps of this stage
-      constexpr int NSTEP = GPS * 4;
-      auto stage_piece = [&](int step) {
-        // chunk i goes with step (i + 1) * NSTEP / 4 - 1: evenly spread over the stage
-        if ((step + 1) % (NSTEP / 4) == 0) {                 // (after the last stage: unused)
-          const int i = (step + 1) / (NSTEP / 4) - 1;
-          sstore_piece(buf ^ 1, i);
-          gload_piece(st2, i);
-          if (step == NSTEP - 1) {                           // scales
-            sstore_piece(buf ^ 1, 4);
-            gload_piece(st2, 4);
+            for (int e = 0; e < 6; e++) av[e] &= keep;
           }
-        }
-      };
-      // One pipeline step = the MFMAs of the next tile interleaved with the fma sweep of
-      // the current one (so that neither the matrix pipe nor the vector ALU waits for the other
-      // inside a wave): 1 MFMA, then a share of the VALU work, repeated.
-      auto interleave = [&](bool valu_first) {
-        constexpr int NM = (MPG == 4 ? 2 : 1) + 1, PER = 16 / NM;
-        if (valu_first) __builtin_amdgcn_sched_group_barrier(0x002, PER, 0);
-#pragma unroll
-        for (int q = 0; q < NM; q++) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
-          __builtin_amdgcn_sched_group_barrier(0x002, PER, 0);    // PER VALU instructions
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      load_ops(0);
-      issue(0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < GPS; jj++) {
-        const bool more = jj + 1 < GPS;              // compile-time after unrolling
-        issue(0, 1, 1);
-        sweep(0, 0, 0);
-        stage_piece(jj * 4 + 0);
-        interleave(false);
-        issue(1, 0, 0);
-        sweep(0, 1, 1);
-        stage_piece(jj * 4 + 1);
-        interleave(false);
-        issue(1, 1, 1);
-        sweep(1, 0, 0);
-        stage_piece(jj * 4 + 2);
-        interleave(false);
-        asm volatile("" ::: "memory");               // keep the next group's LDS reads below this point
-        if (more) {
-          load_ops(jj + 1);                          // every MFMA of this group is issued
+          const i32x2 sbv = jj ? sb1[j & 1] : __builtin_shufflevector(b[j & 1], b[j & 1], 6, 7);
+          const int sc = 127 + 3, s = (GPS * j + jj) & 1;
+          P[s] = __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(f16x4, sa[set][jj]), __builtin_bit_cast(f16x4, sbv), z, 0, 0, 0);
+          I[s] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, b[j & 1], z, 2, 2, 0, sc, 0, sc);
           __builtin_amdgcn_sched_barrier(0);
-          issue(0, 0, 0);
-        }
-        sweep(1, 1, 1);
-        stage_piece(jj * 4 + 3);
-        interleave(true);     // the fresh LDS operands get a few VALU slots to arrive
-      }
-      __syncthreads();
-    }
-    // undo the two 2^-9 operand factors (exact power of two)
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc[i][j][v] *= 262144.0f;
-
-    // ---- zero-point term of asymmetric activations: acc += sum_j z[m,j] c[n,j], c = s_w * sum_k q_w
-    if constexpr (ASYM) {
-      // 12 groups per pass: thread t fills row t of a [256 rows][64 bf16] tile, 5 k-slots per group:
-      // weight rows b1 b2 b3 b1 b2, token rows z1 z1 z1 z2 z2 (group-major sources: coalesced over
-      // rows).  z = z1 + z2 and c = b1 + b2 + b3 exactly; only z2 b3 (z2 < 2^-7 z, b3 < 2^-15 c) is dropped.
-      constexpr int GPP = 12;
-      const bool is_w = t < TN;                             // uniform per wave
-      const size_t ld = is_w ? (size_t)N : (size_t)M;
-      const size_t col = is_w ? (size_t)min(n0 + t, N - 1) : (size_t)min(m0 + t - TN, M - 1);
-      // Raw factors are fetched two passes ahead (a pass is much shorter than a load's latency).
-      // Loads only here, straight-line per wave: the arithmetic on them waits until they are used.
-      uint32_t ra[2][GPP];                                  // s_w bits, or z bits
-      int rb[2][GPP];                                       // code sums (weight rows only)
-      // (token rows read their z twice rather than branch: no control flow between the loads)
-      const uint16_t* src_a = is_w ? sw : zx;
-      const int16_t* src_b = is_w ? wsum : (const int16_t*)zx;
-      auto fetch = [&](int u, int j0) {
-#pragma unroll
-        for (int gg = 0; gg < GPP; gg++) {
-          const size_t idx = (size_t)min(j0 + gg, G - 1) * ld + col;
-          ra[u][gg] = src_a[idx];
-          rb[u][gg] = src_b[idx];
-        }
-      };
-      // v = p1 + p2 + p3 with each piece a bf16 number: truncating splits (exact, the residuals
-      // need no rounding); a piece is kept as fp32 bits with the low half clear
-      auto hi16 = [](float v) { return __builtin_bit_cast(uint32_t, v) & 0xFFFF0000u; };
-      auto pair = [](uint32_t lo, uint32_t hi) { return (lo >> 16) | hi; };   // two bf16 slots in a dword
-      auto pass = [&](int u, int j0) {
-        uint32_t slot[64];                                  // fp32-bit pieces, one per k-slot
-#pragma unroll
-        for (int k = 60; k < 64; k++) slot[k] = 0;
-        if (is_w) {
-#pragma unroll
-          for (int gg = 0; gg < GPP; gg++) {
-            const float v = j0 + gg < G ? f16_bits_to_f32((uint16_t)ra[u][gg]) * (float)rb[u][gg] : 0.0f;
-            const uint32_t p1 = hi16(v);
-            const float r1 = v - __builtin_bit_cast(float, p1);
-            const uint32_t p2 = hi16(r1);
-            const uint32_t p3 = hi16(r1 - __builtin_bit_cast(float, p2));
-            slot[5 * gg + 0] = p1;
-            slot[5 * gg + 1] = p2;
-            slot[5 * gg + 2] = p3;
-            slot[5 * gg + 3] = p1;
-            slot[5 * gg + 4] = p2;
+          if constexpr (ASYM) {
+            if (jj == 0 && (GS == 32 || set == 0)) {
+              acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, za), __builtin_bit_cast(bf16x8, zb[j & 1]), acc[j], 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+            }
           }
+          if (jj == GPS - 1) {
+            if (j + 1 < NJ) read_b(set, j + 1, cur);
+            else read_b(next, 0, nxt);
+            if (j == 0) {
+              unpack_w(next, 0);
+              unpack_w(next, 1);
+            }
+            if (j == 1) {
+              // (the scale of this wave's tokens travels with the weights' of the stage before)
+              put_x(set, GS == 32 ? rsx[set] : rsw[next], fill);
+            }
+            if (j == 2) {
+              load_x(set);
+            }
+            if (j == 3) {
+              scale_w(next);
+              load_w(next);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          const int u = GPS * j + jj - 1;                             // the sweep of the tile before
+          if (u >= 0) {
+            const int jp = u / GPS;
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[jp][v] = fmaf(I[s ^ 1][v], P[s ^ 1][v], acc[jp][v]);
+            asm volatile("" : "+v"(acc[jp]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[NJ - 1][v] = fmaf(I[1][v], P[1][v], acc[NJ - 1][v]);
+      asm volatile("" : "+v"(acc[NJ - 1]));
+      __builtin_amdgcn_sched_barrier(0);
+      barrier();
+      const int freed = cur;
+      cur = nxt;
+      nxt = fill;
+      fill = freed;
+    };
+
+    // ---- prologue: stages 0 and 1 of the tokens in LDS, 2 and 3 on their way; stage 0 of the weights unpacked
+    uint16_t s0;
+    if constexpr (GS != 32) s0 = *(const GLOBAL uint16_t*)(sc_c + (uint64_t)(uint32_t)min(group(kh), G - 1) * sc_ld);
+    load_x(S0{});
+    load_w(S0{});
+    load_x(S1{});
+    load_w(S1{});
+    if (nbi) {
+      load_b(0, 0);
+      load_b(1, 1);
+    }
+    put_x(S0{}, GS == 32 ? rsx[0] : s0, cur);
+    load_x(S0{});
+    put_x(S1{}, GS == 32 ? rsx[1] : rsw[0], nxt);
+    load_x(S1{});
+    unpack_w(S0{}, 0);
+    unpack_w(S0{}, 1);
+    scale_w(S0{});
+    load_w(S0{});
+    branch16();
+    barrier();
+    read_b(S0{}, 0, cur);
+    int i = 0;
+    for (; i + 1 < nqi; i += 2) {
+      interval(S0{});
+      interval(S1{});
+    }
+    if (i < nqi) interval(S0{});
+  }
+
+  // ---- the two parts of K exchange: part kh finishes the token tiles kh and 2 + kh
+  barrier();
+  float4* mine = (float4*)(smem + w * g_::X_WAVE);
+#pragma unroll
+  for (int p = 0; p < 2; p++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      float4 v;
+      v.x = kh ? acc[2 * p][4 * q] : acc[2 * p + 1][4 * q];
+      v.y = kh ? acc[2 * p][4 * q + 1] : acc[2 * p + 1][4 * q + 1];
+      v.z = kh ? acc[2 * p][4 * q + 2] : acc[2 * p + 1][4 * q + 2];
+      v.w = kh ? acc[2 * p][4 * q + 3] : acc[2 * p + 1][4 * q + 3];
+      mine[(4 * p + q) * 64 + l] = v;
+    }
+  barrier();
+  const float4* theirs = (const float4*)(smem + (w ^ 4) * g_::X_WAVE);
+  unsigned char* rows = smem + 8 * g_::X_WAVE;
+#pragma unroll
+  for (int p = 0; p < 2; p++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const float4 o = theirs[(4 * p + q) * 64 + l];
+      const int c = 32 * ws + 8 * q + 4 * half;                       // this lane's four channels of the quad
+      float v[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+      for (int e = 0; e < 4; e++) v[e] += kh ? acc[2 * p + 1][4 * q + e] : acc[2 * p][4 * q + e];
+      if (bias) {
+        const int n = n0 + c;
+        if (n + 4 <= N) {
+          const uint2 bb = *(const uint2*)(bias + n);
+          v[0] += bf16_bits_to_f32((uint16_t)(bb.x & 0xFFFF));
+          v[1] += bf16_bits_to_f32((uint16_t)(bb.x >> 16));
+          v[2] += bf16_bits_to_f32((uint16_t)(bb.y & 0xFFFF));
+          v[3] += bf16_bits_to_f32((uint16_t)(bb.y >> 16));
         } else {
 #pragma unroll
-          for (int gg = 0; gg < GPP; gg++) {
-            const float v = j0 + gg < G ? f16_bits_to_f32((uint16_t)ra[u][gg]) : 0.0f;   // an fp16 value: two pieces hold it
-            const uint32_t p1 = hi16(v);
-            const uint32_t p2 = hi16(v - __builtin_bit_cast(float, p1));
-            slot[5 * gg + 0] = p1;
-            slot[5 * gg + 1] = p1;
-            slot[5 * gg + 2] = p1;
-            slot[5 * gg + 3] = p2;
-            slot[5 * gg + 4] = p2;
-          }
+          for (int e = 0; e < 4; e++) v[e] += bf16_bits_to_f32(bias[min(n + e, N - 1)]);
         }
-        fetch(u, j0 + 2 * GPP);                             // past the end: clamped, never used
-        __syncthreads();                                    // the previous use of this LDS tile is over
+      }
+      unsigned char* d = rows + (32 * (2 * p + kh) + row) * g_::OUT_ROW;
+      if (OUT_F32) {
+        *(float4*)(d + 4 * c) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
+        *(uint2*)(d + 2 * c) = make_uint2(f32x2_to_bf16x2_bits(v[0], v[1]), f32x2_to_bf16x2_bits(v[2], v[3]));
+      }
+    }
+  barrier();
+  // ---- rows of y: 16 bytes a lane where they are aligned, else value by value
+  constexpr int ES = OUT_F32 ? 4 : 2, LPR = TNW * ES / 16, EPL = 16 / ES;
+  unsigned char* yb = (unsigned char*)y;
+  if (N % EPL == 0) {
+    const int c = (t % LPR) * EPL;
 #pragma unroll
-        for (int c8 = 0; c8 < 8; c8++)
-          *(uint4*)(smem + tile_off_bytes(t, c8)) =
-              make_uint4(pair(slot[8 * c8], slot[8 * c8 + 1]), pair(slot[8 * c8 + 2], slot[8 * c8 + 3]),
-                         pair(slot[8 * c8 + 4], slot[8 * c8 + 5]), pair(slot[8 * c8 + 6], slot[8 * c8 + 7]));
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-          bf16x8 a[2], b[2];
-          const int chunk = 2 * ks + h;
-#pragma unroll
-          for (int i = 0; i < 2; i++) a[i] = *(const bf16x8*)(smem + rowA[i] * 128 + ((chunk ^ swz) << 4));
-#pragma unroll
-          for (int j = 0; j < 2; j++) b[j] = *(const bf16x8*)(smem + rowB[j] * 128 + ((chunk ^ swz) << 4));
-#pragma unroll
-          for (int i = 0; i < 2; i++)
-#pragma unroll
-            for (int j = 0; j < 2; j++)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-      };
-      fetch(0, 0);
-      fetch(1, GPP);
-      for (int j0 = 0; j0 < G; j0 += 2 * GPP) {
-#pragma unroll
-        for (int u = 0; u < 2; u++)
-          if (j0 + u * GPP < G) pass(u, j0 + u * GPP);
+    for (int k = 0; k < TMW * LPR / NT; k++) {
+      const int tok = k * (NT / LPR) + t / LPR;
+      const uint4 d = *(const uint4*)(rows + tok * g_::OUT_ROW + c * ES);
+      if (m0 + tok < M && n0 + c < N) *(uint4*)(yb + ((size_t)(m0 + tok) * N + n0 + c) * ES) = d;
+    }
+  } else {
+    const int c = t % TNW;
+#pragma unroll 4
+    for (int k = 0; k < TMW * TNW / NT; k++) {
+      const int tok = k * (NT / TNW) + t / TNW;
+      if (m0 + tok < M && n0 + c < N) {
+        if (OUT_F32) ((float*)y)[(size_t)(m0 + tok) * N + n0 + c] = *(const float*)(rows + tok * g_::OUT_ROW + c * 4);
+        else ((uint16_t*)y)[(size_t)(m0 + tok) * N + n0 + c] = *(const uint16_t*)(rows + tok * g_::OUT_ROW + c * 2);
       }
     }
   }
-
-  gemm_tail<OUT_F32>(acc, smem, xh, wh, bias, y, M, N, r, m0, n0, rowA, rowB);
 }
 
 template <int GS, bool OUT_F32, bool ASYM>
-static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
-                      const void* blob, const uint16_t* bias, int M, int N, int K, int r, void* y,
-                      hipStream_t s) {
+static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx, const void* blob,
+                      const uint16_t* bias, int M, int N, int K, int r, void* y, hipStream_t s) {
+  typedef Geo<GS, OUT_F32, ASYM> g_;
   const BlobLayout L = blob_layout(N, K, r, GS);
   const char* bp = (const char*)blob;
-  const int n_mt = (M + TM - 1) / TM, n_nt = (N + TN - 1) / TN;
-  const long n_blocks = (long)n_mt * n_nt;
-  const int per_xcd = (int)((n_blocks + 7) / 8);
+  const int n_mt = (M + TMW - 1) / TMW, n_nt = (N + TNW - 1) / TNW;
+  const int per_xcd = (int)(((long)n_mt * n_nt + 7) / 8);
   // (idempotent: two threads racing here would both set the same attribute)
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute((const void*)w4a4_gemm_kernel<GS, OUT_F32, ASYM>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes(GS));
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, g_::SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((w4a4_gemm_kernel<GS, OUT_F32, ASYM>), dim3(per_xcd * 8), dim3(NTHREADS), smem_bytes(GS), s, xh,
-                     xl, sx, zx, (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes),
-                     (const uint16_t*)(bp + L.off_sw), (const int16_t*)(bp + L.off_wsum), bias, M, N, K, r, y,
-                     n_mt, n_nt, per_xcd);
+  hipLaunchKernelGGL((w4a4_gemm_kernel<GS, OUT_F32, ASYM>), dim3(per_xcd * 8), dim3(NT), g_::SMEM, s, xh, xl, sx, zx,
+                     (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw),
+                     (const int16_t*)(bp + L.off_wsum), bias, M, N, K, r, y, n_mt, n_nt, per_xcd);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
+
+}  // namespace tile
 
 // The schedule of a layer (w4a4_plan.h).  DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny / skinny32 /
 // skinny64 in the environment forces one of them wherever it applies (the tests use it to run all of them on the same
@@ -463,10 +507,10 @@ int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, 
 #define DIROTQ_CASE(GS)                                                                               \
   case GS:                                                                                            \
     if (zx)                                                                                           \
-      return y_dtype ? launch_one<GS, true, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)       \
-                     : launch_one<GS, false, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);     \
-    return y_dtype ? launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)        \
-                   : launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
+      return y_dtype ? tile::launch_one<GS, true, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s) \
+                     : tile::launch_one<GS, false, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s); \
+    return y_dtype ? tile::launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)  \
+                   : tile::launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
   {
     // (asymmetric layers: the wave-specialised schedule, the split-K ones or this file's kernel)
     W4A4Schedule sch;

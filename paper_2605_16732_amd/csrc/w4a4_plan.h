@@ -13,11 +13,11 @@ namespace w4a4_plan {
 inline long tiles(long M, long N, long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); }
 inline double rounds(long work, long slots) { return (double)((work + slots - 1) / slots); }
 
-// Costs in microseconds of the schedules for a layer that leaves the persistent kernels part of the chip idle: k = 1024
-// 4-bit channels, q = 128 16-bit ones.  Fitted to what kernel B adds to kernel A in 7250 whole layers (graph replay over
-// three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, up to 9000 tokens, all group sizes, r up to
-// 256): 6% (tile) to 11% off, root mean square.  The numbers that depend on the kind of code stand as {groups of 64, 128, 32
-// symmetric; the same asymmetric}; ragged: rows of y that do not begin at multiples of 8 bytes are stored value by value.
+// Costs in microseconds of the schedules: k = 1024 4-bit channels, q = 128 16-bit ones.  Fitted to what kernel B adds to
+// kernel A in whole layers (graph replay over three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, up
+// to 9000 tokens, all group sizes, r up to 256): the split-K forms to 7250 layers, the others to 1940 (5% (tile) to 11% off, root
+// mean square).  The numbers that depend on the kind of code stand as {groups of 64, 128, 32 symmetric; the same
+// asymmetric}; ragged: rows of y that do not begin at multiples of 8 bytes (tile: 16) are stored value by value.
 struct Cost {
   double k, q;
   int kind, cus;
@@ -38,12 +38,24 @@ struct Cost {
     return 2.31 + 0.56 * k + rounds(T, 2L * cus) * (0.40 * q + K[kind] * k) +
            (double)T / cus * (0.70 + ragged + T1[kind] * k + 0.32 * q);
   }
-  // 128 x 128 tiles, at most one per CU here
+  // 128 x 128 tiles, one per CU (LDS, registers)
   double tile(long M, long N) const {
-    static constexpr double K[6] = {9.18, 7.57, 13.28, 11.05, 8.81, 17.04};
+    static constexpr double K[6] = {5.28, 5.17, 8.43, 6.10, 5.99, 9.72};
     const long T = tiles(M, N, 128, 128);
-    const double busy = ((double)T / cus - 0.25) / 0.75, u = busy > 0.0 ? busy : 0.0;
-    return 4.28 + 4.15 * u + (N % 4 ? 6.11 + 7.08 * u : 0.0) + rounds(T, cus) * (1.59 * q + K[kind] * k);
+    const double ragged = N % 8 ? 1.55 : 0.0;
+    return 2.89 + rounds(T, cus) * (3.82 + ragged + 2.16 * q + K[kind] * k) + (double)T / cus * (1.89 + 0.49 * k);
+  }
+  // 256 x 128 tiles of the wave-specialised kernel
+  double ws(long M, long N) const {
+    static constexpr double K[6] = {9.01, 8.59, 0.0, 11.47, 10.60, 27.13};
+    const double ragged = N % 4 ? 15.42 : 0.0;
+    return 6.08 + rounds(tiles(M, N, 128, 256), cus) * (6.06 + ragged + 2.42 * q + K[kind] * k);
+  }
+  // the pipelined kernel, whose plan takes the time of `large` 256 x 256 tiles
+  double pipe(double large, long N) const {
+    static constexpr double K[3] = {17.22, 16.95, 27.36};
+    const double ragged = N % 4 ? 25.55 : 0.0;
+    return 4.34 + large * (8.02 + ragged + 6.15 * q + K[kind] * k);
   }
 };
 
@@ -54,21 +66,31 @@ struct Cost {
 // the latter's tiles takes 0.61 of a 256 x 256 tile's time (M = 2048, K = N = 3072: 42 against 46 us; M = 4096, K = 1152,
 // N = 4608: 57 against 54 us; 937 whole layers: 4 slower than in the wave-specialised kernel by more than 2%, none by
 // more than 3.2%).  Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).
-// Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles:
-// 0.16% (mean) above the best of the three over those 7250 layers; by counts of 64 x 64 tiles, without the 32 x 32 form, it
-// is 43% (symmetric) and 125% (asymmetric).  big_tokens: see w4a4_pipe_plan.
+// Where the 128 x 128 tiles fill their rounds better they are cheaper than either (M = 1500, N = 6000, K = 2080, asymmetric:
+// 56 against 66 us; of 526 such layers 191: asymmetric ones 1.08 times as fast in the mean, symmetric ones 1.03).
+// Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles.
+// Over those 1940 layers the choice is 0.19% above the best schedule (mean).  big_tokens: see w4a4_pipe_plan.
 inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, int cus, long& big_tokens) {
   using namespace w4a4_plan;
   big_tokens = 0;
   if (K - r <= 0) return W4A4Schedule::kTile;
+  const Cost cost(K, r, g, asym, cus);
+  const double c128 = cost.tile(M, N);
   const long half_tiles = tiles(M, N, 128, 256);
   if (half_tiles >= 128) {
-    if (asym) return W4A4Schedule::kWs;
-    const double pipe = w4a4_pipe_plan(M, N, cus, big_tokens);
-    return g == 32 || pipe <= 0.61 * rounds(half_tiles, cus < 8 ? 8 : cus / 8 * 8) ? W4A4Schedule::kPipe : W4A4Schedule::kWs;
+    bool piped = false;
+    double persistent = 0.0;
+    if (!asym) {
+      const double plan = w4a4_pipe_plan(M, N, cus, big_tokens);
+      const double whole = rounds(half_tiles, cus < 8 ? 8 : cus / 8 * 8);
+      piped = g == 32 || plan <= 0.61 * whole;
+      if (piped) persistent = cost.pipe(g == 32 ? pipe::HALF * whole : plan, N);   // (groups of 32: half-size tiles only)
+    }
+    if (!piped) persistent = cost.ws(M, N);
+    if (c128 < persistent) return W4A4Schedule::kTile;
+    return piped ? W4A4Schedule::kPipe : W4A4Schedule::kWs;
   }
-  const Cost cost(K, r, g, asym, cus);
-  const double c32 = cost.skinny32(M, N), c64 = cost.skinny64(M, N), c128 = cost.tile(M, N);
+  const double c32 = cost.skinny32(M, N), c64 = cost.skinny64(M, N);
   if (c32 <= c64 && c32 <= c128) return W4A4Schedule::kSkinny32;
   return c64 <= c128 ? W4A4Schedule::kSkinny64 : W4A4Schedule::kTile;
 }
