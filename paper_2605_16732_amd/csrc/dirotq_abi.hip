@@ -3,6 +3,7 @@
 #include <mutex>
 
 #include "dirotq_internal.h"
+#include "w4a4_plan.h"
 
 namespace dirotq {
 
@@ -50,6 +51,28 @@ int check_shape(long M, long N, long K, long r, long g) {
   // the GEMM grids are one workgroup per 128 x 128 output tile, indexed with 32-bit integers
   if (((M + 127) / 128) * ((N + 127) / 128) > (1L << 30)) return DIROTQ_ERR_SHAPE;
   return DIROTQ_OK;
+}
+
+// A whole W4A4 layer whose intermediates lie at xh, xl, sx (asymmetric: and zx): kernel A writes the codes in the form that the
+// kernel B of the layer's plan reads fastest
+static int linear_w4a4(const uint16_t* x, const uint16_t* Qt, const RqOut& out, const void* blob, const uint16_t* bias, int M,
+                       int N, int K, int r, int g, uint16_t* y, hipStream_t s) {
+  W4A4Plan plan;
+  int st = w4a4_plan_layer(M, N, K, r, g, out.zx != nullptr, plan);
+  if (st) return st;
+  RqOut o = out;
+  o.fields = !o.zx && plan.reads_fields();
+  st = launch_rotate_quantize(x, Qt, M, K, r, g, o, s);
+  if (st) return st;
+  return launch_w4a4_gemm(plan, o.fields, o.xh, o.xl, o.sx, o.zx, blob, bias, M, N, K, r, g, y, 0, s);
+}
+// kernel B alone, on nibbles
+static int gemm_w4a4(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx, const void* blob,
+                     const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype, hipStream_t s) {
+  W4A4Plan plan;
+  const int st = w4a4_plan_layer(M, N, K, r, g, zx != nullptr, plan);
+  if (st) return st;
+  return launch_w4a4_gemm(plan, false, xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
 }
 
 }  // namespace dirotq
@@ -169,8 +192,7 @@ int dirotq_w4a4_gemm(const uint16_t* xh_bf16, const uint8_t* xl_packed, const ui
   if (misaligned(xh_bf16) || misaligned(xl_packed) || misaligned(sx_fp16) || misaligned(blob) ||
       misaligned(bias_bf16) || misaligned(y))
     return DIROTQ_ERR_ALIGN;
-  return launch_w4a4_gemm(xh_bf16, xl_packed, sx_fp16, nullptr, blob, bias_bf16, M, N, K, r, g, y, y_dtype,
-                          (hipStream_t)stream);
+  return gemm_w4a4(xh_bf16, xl_packed, sx_fp16, nullptr, blob, bias_bf16, M, N, K, r, g, y, y_dtype, (hipStream_t)stream);
 }
 
 int dirotq_linear(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* blob,
@@ -191,9 +213,7 @@ int dirotq_linear(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* b
   uint16_t* sx = (uint16_t*)(ws + L.off_sx);
   RqOut o;
   o.xh = xh, o.xl = xl, o.sx = sx;
-  st = launch_rotate_quantize(x_bf16, Qt_bf16, M, K, r, g, o, (hipStream_t)stream);
-  if (st) return st;
-  return launch_w4a4_gemm(xh, xl, sx, nullptr, blob, bias_bf16, M, N, K, r, g, y_bf16, 0, (hipStream_t)stream);
+  return linear_w4a4(x_bf16, Qt_bf16, o, blob, bias_bf16, M, N, K, r, g, y_bf16, (hipStream_t)stream);
 }
 
 int dirotq_linear_static(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* blob,
@@ -218,9 +238,7 @@ int dirotq_linear_static(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const 
   o.xh = xh, o.xl = xl, o.sx = sx;
   // every byte of the intermediates that the GEMM reads is written by the rotation kernel of
   // this call, so nothing of the previous call's contents has to be cleared
-  st = launch_rotate_quantize(x_bf16, Qt_bf16, M, K, r, g, o, (hipStream_t)stream);
-  if (st) return st;
-  return launch_w4a4_gemm(xh, xl, sx, nullptr, blob, bias_bf16, M, N, K, r, g, y_bf16, 0, (hipStream_t)stream);
+  return linear_w4a4(x_bf16, Qt_bf16, o, blob, bias_bf16, M, N, K, r, g, y_bf16, (hipStream_t)stream);
 }
 
 int dirotq_linear_shared(const uint16_t* x_bf16, const uint16_t* Qt_bf16, int n_out, const void* const* blobs,
@@ -247,10 +265,17 @@ int dirotq_linear_shared(const uint16_t* x_bf16, const uint16_t* Qt_bf16, int n_
   uint16_t* sx = (uint16_t*)(ws + L.off_sx);
   RqOut o;
   o.xh = xh, o.xl = xl, o.sx = sx;
+  W4A4Plan plans[16];
+  o.fields = true;                           // (where every output's kernel reads it)
+  for (int i = 0; i < n_out; i++) {
+    const int st = w4a4_plan_layer(M, Ns[i], K, r, g, false, plans[i]);
+    if (st) return st;
+    o.fields = o.fields && plans[i].reads_fields();
+  }
   int st = launch_rotate_quantize(x_bf16, Qt_bf16, M, K, r, g, o, (hipStream_t)stream);
   for (int i = 0; i < n_out && !st; i++)
-    st = launch_w4a4_gemm(xh, xl, sx, nullptr, blobs[i], biases ? biases[i] : nullptr, M, Ns[i], K, r, g, ys[i], 0,
-                          (hipStream_t)stream);
+    st = launch_w4a4_gemm(plans[i], o.fields, xh, xl, sx, nullptr, blobs[i], biases ? biases[i] : nullptr, M, Ns[i], K, r, g,
+                          ys[i], 0, (hipStream_t)stream);
   return st;
 }
 
@@ -285,8 +310,8 @@ int dirotq_w4a4_gemm_asym(const uint16_t* xh_bf16, const uint8_t* xl_packed, con
   if (misaligned(xh_bf16) || misaligned(xl_packed) || misaligned(sx_fp16) || misaligned(zx_fp16) ||
       misaligned(blob) || misaligned(bias_bf16) || misaligned(y))
     return DIROTQ_ERR_ALIGN;
-  return launch_w4a4_gemm(xh_bf16, xl_packed, sx_fp16, r < K ? zx_fp16 : nullptr, blob, bias_bf16, M, N, K, r, g, y,
-                          y_dtype, (hipStream_t)stream);
+  return gemm_w4a4(xh_bf16, xl_packed, sx_fp16, r < K ? zx_fp16 : nullptr, blob, bias_bf16, M, N, K, r, g, y, y_dtype,
+                   (hipStream_t)stream);
 }
 
 int dirotq_linear_asym(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* blob,
@@ -308,9 +333,7 @@ int dirotq_linear_asym(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const vo
   uint16_t* zx = r < K ? (uint16_t*)(ws + L.off_zx) : nullptr;
   RqOut o;
   o.xh = xh, o.xl = xl, o.sx = sx, o.zx = zx;
-  st = launch_rotate_quantize(x_bf16, Qt_bf16, M, K, r, g, o, (hipStream_t)stream);
-  if (st) return st;
-  return launch_w4a4_gemm(xh, xl, sx, zx, blob, bias_bf16, M, N, K, r, g, y_bf16, 0, (hipStream_t)stream);
+  return linear_w4a4(x_bf16, Qt_bf16, o, blob, bias_bf16, M, N, K, r, g, y_bf16, (hipStream_t)stream);
 }
 
 int dirotq_a8_scratch_bytes(int M, int K, int r, size_t* bytes) {

@@ -90,8 +90,9 @@ struct RqOut {
   uint16_t* zx = nullptr;
   float* xf = nullptr;
   float* pmax = nullptr;
+  bool fields = false;                       // (symmetric codes) xl in field form (pipe_unpack.h) instead of nibbles
 };
-// (out.pmax becomes NULL where the maxima are not written)
+// (out.pmax becomes NULL where the maxima are not written, out.fields false where the codes are nibbles all the same)
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, RqOut& out, hipStream_t s);
 // few tokens: tiles of `channels` x `tokens`, K split over the waves of a workgroup; virtual channels as in
 // rotate_quantize.hip.  channels: a multiple of the group size, 64 or 128; fp32 output (no maxima): 32 or 64
@@ -111,8 +112,11 @@ int launch_w4a8_gemm_pipe(const uint16_t* xh, const uint8_t* x8, const uint16_t*
                           int M, int N, int K, int r, int g, void* y, int y_dtype, int cus, hipStream_t s);
 int launch_w4a16_gemm(const uint16_t* x, const void* blob, const uint16_t* bias, int M, int N, int K, int g, void* y,
                       int y_dtype, hipStream_t s);
-int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
-                     const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,
+struct W4A4Plan;                             // w4a4_plan.h
+int w4a4_plan_layer(int M, int N, int K, int r, int g, bool asym, W4A4Plan& plan);
+// fields: xl is in field form (symmetric codes, only where the plan reads it, bf16 output)
+int launch_w4a4_gemm(const W4A4Plan& plan, bool fields, const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
+                     const uint16_t* zx, const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,
                      int y_dtype, hipStream_t s);
 // 4-bit part not empty (wave-specialised schedule of the same arithmetic); zx: zero-points of asymmetric
 // activation codes, or NULL for symmetric ones
@@ -121,7 +125,7 @@ int launch_w4a4_gemm_ws(const uint16_t* xh, const uint8_t* xl, const uint16_t* s
 // symmetric activation codes, large: persistent workgroups whose waves all stage and multiply
 int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                           const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
-                          long big_tokens, hipStream_t s);
+                          long big_tokens, bool fields, hipStream_t s);
 // few tokens: the K axis split over the waves of a workgroup (64 x 64 outputs each, or `small`: 32 x 32); zx as above
 int launch_w4a4_gemm_skinny(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
                             const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,

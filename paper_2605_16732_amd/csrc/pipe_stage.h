@@ -47,6 +47,14 @@ constexpr Stores narrow_stores(RowPart p, int part, bool copy) {
   return {at, copy ? (p.at_copy ^ 32) + 8 * part : at + 8};
 }
 
+// the same of the field form.  Part 0 expands to dwords 0 1 | 5 of the row half's six, part 1 to 2 3 | 4.  Groups of 64 and 128: 8
+// bytes (dwords 0 1, 2 3), then 4; groups of 32: 8 (0 1, 3 4) and 8 (5 0, 2 0)
+template <int GS>
+constexpr Stores narrow_fields_stores(RowPart p, int part, bool copy) {
+  if (GS != 32) return {p.at + 8 * part, copy ? (p.at ^ 16) + (part ? 12 : 8) : p.at_hi + (part ? 0 : 4)};
+  return {copy ? p.at_copy + 8 * part : part ? p.at ^ 16 : p.at, copy ? (p.at_copy ^ 32) + 8 * part : part ? p.at + 8 : (p.at ^ 16) + 8};
+}
+
 // what lane half h reads of a row: 16 bytes, then 8 (groups of 32: 16); of a 16-bit stage only the first 16 are used
 template <int GS>
 constexpr int read_lo(int row, int h) { return stage_off(row, GS == 32 ? h : 2 * h); }

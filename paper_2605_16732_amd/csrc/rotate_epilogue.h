@@ -5,7 +5,7 @@
 // point lies inside the wave's channels).
 #pragma once
 
-#include "dirotq_internal.h"
+#include "pipe_unpack.h"
 
 namespace dirotq {
 namespace rq {
@@ -104,10 +104,10 @@ __device__ __forceinline__ void store_f32(const f32x16 (&acc)[CI][TI], int cl0, 
   }
 }
 
-// 4-bit part: the codes and scales (and zero-points) of the groups
+// 4-bit part: the codes (nibbles, or in field form) and scales (and zero-points) of the groups
 template <int QM, int CI, int TI>
 __device__ __forceinline__ void store_low(const f32x16 (&acc)[CI][TI], const float (&tmax)[TI][CI], const float (&tmin)[TI][CI], int cl0,
-                                          int tok_base, int M, int KL, int g, uint8_t* xl, uint16_t* sx, uint16_t* zx, int sx_ld) {
+                                          int tok_base, int M, int KL, int g, uint8_t* xl, uint16_t* sx, uint16_t* zx, int sx_ld, bool fields) {
   constexpr bool ASYM = QM == 1;
   const int l = threadIdx.x & 63, h = l >> 5;
   const size_t xl_ld = (size_t)KL / 2;
@@ -146,6 +146,7 @@ __device__ __forceinline__ void store_low(const f32x16 (&acc)[CI][TI], const flo
       uint2 o;
       o.x = (lo & 0xFFFFu) | (hi << 16);
       o.y = (lo >> 16) | (hi & 0xFFFF0000u);
+      if (!ASYM && fields) o = pipe::to_fields_pair(o, h);
       if (valid) *(uint2*)(xl + (size_t)m * xl_ld + cl / 2 + 8 * h) = o;
     }
   }

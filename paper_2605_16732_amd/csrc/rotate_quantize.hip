@@ -72,7 +72,8 @@ template <int WGC, int WGT, int MI, int QM, int KSP, bool TAIL>
 __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, MI, KSP>::WAVES_PER_SIMD)) void rotate_quantize_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ Qt, int M, int K, int r, int g,
     uint16_t* __restrict__ xh, uint8_t* __restrict__ xl, uint16_t* __restrict__ sx, uint16_t* __restrict__ zx,
-    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int Kv, int n_ct, int n_tt, int per_xcd, int sx_ld) {
+    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int Kv, int n_ct, int n_tt, int per_xcd, int sx_ld,
+    bool fields) {
   using C = RQ<WGC, WGT, MI, KSP>;
   constexpr int BK = C::BK;
   static_assert(KSP == 1 || MI == 32, "the K split is written for the 32x32 loop only");
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, MI, KSP>::WAVES_P
       float tmax[1][4], tmin[1][4];
       rq::tile_extremes<QM>(acc, tmax, tmin);
       rq::group_extremes(g, tmax, tmin);
-      rq::store_low<QM>(acc, tmax, tmin, vb - r_pad, tok_base, M, K - r, g, xl, sx, zx, sx_ld);
+      rq::store_low<QM>(acc, tmax, tmin, vb - r_pad, tok_base, M, K - r, g, xl, sx, zx, sx_ld, fields);
     }
   } else {
     // ======== 16x16x32 MFMA: wave tile = 8 x 4 tiles of 16 channels x 16 tokens =========
@@ -466,6 +467,7 @@ __global__ __launch_bounds__(WGC* WGT* KSP * 64, (RQ<WGC, WGT, MI, KSP>::WAVES_P
       o.y = (P[2] & 0xFFFFu) | (P[3] << 16);
       o.z = (P[0] >> 16) | (P[1] & 0xFFFF0000u);
       o.w = (P[2] >> 16) | (P[3] & 0xFFFF0000u);
+      if (!ASYM && fields) o = pipe::to_fields(o);
       if (valid) *(uint4*)(xl + (size_t)m * xl_ld + clu / 2) = o;
     }
   }
@@ -482,7 +484,7 @@ static void virtual_channels(int K, int r, int g, bool fp32_out, int& r_pad, int
 
 template <int WGC, int WGT, int MI, int QM, int KSP, bool TAIL>
 static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, uint16_t* xh,
-                      uint8_t* xl, uint16_t* sx, uint16_t* zx, float* xf, float* pmax, hipStream_t s, int sx_ld) {
+                      uint8_t* xl, uint16_t* sx, uint16_t* zx, float* xf, float* pmax, hipStream_t s, int sx_ld, bool fields) {
   using C = RQ<WGC, WGT, MI, KSP>;
   int r_pad, Kv;
   virtual_channels(K, r, g, QM == 2, r_pad, Kv);
@@ -499,7 +501,7 @@ static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r
     attr_done.store(true, std::memory_order_release);
   }
   hipLaunchKernelGGL((rotate_quantize_kernel<WGC, WGT, MI, QM, KSP, TAIL>), dim3(per_xcd * 8), dim3(C::NT), C::SMEM, s, x,
-                     Qt, M, K, r, g, xh, xl, sx, zx, xf, pmax, r_pad, Kv, n_ct, n_tt, per_xcd, sx_ld);
+                     Qt, M, K, r, g, xh, xl, sx, zx, xf, pmax, r_pad, Kv, n_ct, n_tt, per_xcd, sx_ld, fields);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }
@@ -507,9 +509,9 @@ static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r
 template <int WGC, int WGT, int MI, int KSP = 1, bool TAIL = false>
 static int launch_cfg(const RqOut& o, const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g,
                       hipStream_t s, int sx_ld) {
-  if (o.xf) return launch_one<WGC, WGT, MI, 2, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
-  if (o.zx) return launch_one<WGC, WGT, MI, 1, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
-  return launch_one<WGC, WGT, MI, 0, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld);
+  if (o.xf) return launch_one<WGC, WGT, MI, 2, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld, o.fields);
+  if (o.zx) return launch_one<WGC, WGT, MI, 1, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld, o.fields);
+  return launch_one<WGC, WGT, MI, 0, KSP, TAIL>(x, Qt, M, K, r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, s, sx_ld, o.fields);
 }
 
 int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, int r, int g, RqOut& o,
@@ -538,6 +540,9 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
   // each with fewer rows to pull (M = 77, K = 3072: 16 instead of 32 tokens 10.2 -> 9.6 us).
   struct FewTile { int channels, tokens; };
   auto fits = [&](FewTile t) { return (long)((Kv + t.channels - 1) / t.channels) * ((M + t.tokens - 1) / t.tokens) <= cus; };
+  // (it writes nibbles whatever is asked for: the field form's code would cost every small call 0.05 us)
+  const bool fields = o.fields;
+  o.fields = false;
   if (o.xf) {
     // no groups: any channel tile (and the 4-bit part begins right behind the 16-bit one)
     for (FewTile t : {FewTile{32, 8}, {32, 16}, {32, 24}, {32, 32}, {64, 24}, {64, 32}, {64, 64}, {64, 96}})
@@ -552,6 +557,7 @@ int launch_rotate_quantize(const uint16_t* x, const uint16_t* Qt, int M, int K, 
     for (FewTile t : {FewTile{64, 8}, {64, 16}, {64, 24}, {64, 32}, {64, 64}, {64, 96}})
       if (fits(t)) return launch_rotate_quantize_few(x, Qt, M, K, r, g, o, r_pad, Kv, t.channels, t.tokens, s);
   }
+  o.fields = fields;
   // A launch this small is held back by the chain of stage latencies: with 128 x 64 tiles and the two halves of K on two sets
   // of waves per workgroup it has twice the workgroups and half the stages (11 instead of 13 us at M = 256, K = 1152; 21
   // instead of 26 at K = 3072).

@@ -42,7 +42,8 @@ template <int TI, int WC, int WT, int QM>
 __global__ __launch_bounds__(WC* WT * 64, (WC * WT + 3) / 4) void rotate_quantize_dma_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ Qt, int M, int K, int r, int g,
     uint16_t* __restrict__ xh, uint8_t* __restrict__ xl, uint16_t* __restrict__ sx, uint16_t* __restrict__ zx,
-    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int Kv, int n_ct, int n_tt, int per_xcd, int sx_ld) {
+    float* __restrict__ xf, float* __restrict__ pmax, int r_pad, int Kv, int n_ct, int n_tt, int per_xcd, int sx_ld,
+    bool fields) {
   using F = Tile<TI, WC, WT>;
   constexpr bool ASYM = QM == 1;
   constexpr int NBUF = F::NBUF;
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(WC* WT * 64, (WC * WT + 3) / 4) void rotate_quantiz
       rq::store_bf16(acc, vb, tok_base, M, r, xh);
       if (vb + 32 * CI <= r_pad) return;
     }
-    rq::store_low<QM>(acc, tm, tn, vb - r_pad, tok_base, M, K - r, g, xl, sx, zx, sx_ld);
+    rq::store_low<QM>(acc, tm, tn, vb - r_pad, tok_base, M, K - r, g, xl, sx, zx, sx_ld, fields);
   }
 }
 
@@ -222,7 +223,7 @@ static int launch_one(const uint16_t* x, const uint16_t* Qt, int M, int K, int r
     attr_done.store(true, std::memory_order_release);
   }
   hipLaunchKernelGGL((rotate_quantize_dma_kernel<TI, WC, WT, QM>), dim3(per_xcd * 8), dim3(F::NT), F::SMEM, s, x, Qt, M, K,
-                     r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, r_pad, Kv, n_ct, n_tt, per_xcd, sx_ld);
+                     r, g, o.xh, o.xl, o.sx, o.zx, o.xf, o.pmax, r_pad, Kv, n_ct, n_tt, per_xcd, sx_ld, o.fields);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
 }

@@ -73,7 +73,7 @@ __device__ __forceinline__ void barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <int GS, bool OUT_F32, bool ASYM>
+template <int GS, bool OUT_F32, bool ASYM, bool FIELDS>
 __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
     const uint16_t* __restrict__ xh, const uint8_t* __restrict__ xl, const uint16_t* __restrict__ sx,
     const uint16_t* __restrict__ zx, const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq,
@@ -225,12 +225,11 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
     auto put_x = [&](auto set, uint16_t scale, int so) {
       uint32_t d0[3], d1[3];
       const u32x4 v = rx[set];
-      if constexpr (ASYM) {
-        pipe::spread16u_fp6(v[0], v[1], d0);
-        pipe::spread16u_fp6(v[2], v[3], d1);
+      if constexpr (FIELDS) {
+        pipe::expand32_fp6(v, d0, d1);
       } else {
-        pipe::unpack16_fp6(v[0], v[1], d0);
-        pipe::unpack16_fp6(v[2], v[3], d1);
+        pipe::half16_fp6<ASYM>(v[0], v[1], d0);
+        pipe::half16_fp6<ASYM>(v[2], v[3], d1);
       }
       unsigned char* f = smem + (so + frag);
       const int sq = 2 * ix + kh;
@@ -442,7 +441,7 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
   }
 }
 
-template <int GS, bool OUT_F32, bool ASYM>
+template <int GS, bool OUT_F32, bool ASYM, bool FIELDS>
 static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx, const void* blob,
                       const uint16_t* bias, int M, int N, int K, int r, void* y, hipStream_t s) {
   typedef Geo<GS, OUT_F32, ASYM> g_;
@@ -453,12 +452,12 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
   // (idempotent: two threads racing here would both set the same attribute)
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)w4a4_gemm_kernel<GS, OUT_F32, ASYM>,
+    hipError_t e = hipFuncSetAttribute((const void*)w4a4_gemm_kernel<GS, OUT_F32, ASYM, FIELDS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, g_::SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((w4a4_gemm_kernel<GS, OUT_F32, ASYM>), dim3(per_xcd * 8), dim3(NT), g_::SMEM, s, xh, xl, sx, zx,
+  hipLaunchKernelGGL((w4a4_gemm_kernel<GS, OUT_F32, ASYM, FIELDS>), dim3(per_xcd * 8), dim3(NT), g_::SMEM, s, xh, xl, sx, zx,
                      (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes), (const uint16_t*)(bp + L.off_sw),
                      (const int16_t*)(bp + L.off_wsum), bias, M, N, K, r, y, n_mt, n_nt, per_xcd);
   hipError_t e = hipGetLastError();
@@ -471,7 +470,9 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 // skinny64 in the environment forces one of them wherever it applies (the tests use it to run all of them on the same
 // inputs; large and small: the pipelined kernel with one kind of tile; skinny32 and skinny64: the split-K kernel with one
 // of its two, skinny: with the cheaper one).
-static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Schedule& sch, long& big_tokens) {
+int w4a4_plan_layer(int M, int N, int K, int r, int g, bool asym, W4A4Plan& plan) {
+  W4A4Schedule& sch = plan.schedule;
+  long& big_tokens = plan.big_tokens;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -501,35 +502,29 @@ static int w4a4_schedule(int M, int N, int K, int r, int g, bool asym, W4A4Sched
   return DIROTQ_OK;
 }
 
-int launch_w4a4_gemm(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const uint16_t* zx,
-                     const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,
+int launch_w4a4_gemm(const W4A4Plan& plan, bool fields, const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
+                     const uint16_t* zx, const void* blob, const uint16_t* bias, int M, int N, int K, int r, int g, void* y,
                      int y_dtype, hipStream_t s) {
-#define DIROTQ_CASE(GS)                                                                               \
-  case GS:                                                                                            \
-    if (zx)                                                                                           \
-      return y_dtype ? tile::launch_one<GS, true, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s) \
-                     : tile::launch_one<GS, false, true>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s); \
-    return y_dtype ? tile::launch_one<GS, true, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)  \
-                   : tile::launch_one<GS, false, false>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s);
-  {
-    // (asymmetric layers: the wave-specialised schedule, the split-K ones or this file's kernel)
-    W4A4Schedule sch;
-    long big_tokens;
-    const int st = w4a4_schedule(M, N, K, r, g, zx != nullptr, sch, big_tokens);
-    if (st) return st;
-    if (sch == W4A4Schedule::kPipe)
-      return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, big_tokens, s);
-    if (sch == W4A4Schedule::kWs)
-      return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
-    if (sch != W4A4Schedule::kTile)
-      return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, sch == W4A4Schedule::kSkinny32, s);
-  }
+  // (asymmetric layers: the wave-specialised schedule, the split-K ones or this file's kernel)
+  if (plan.schedule == W4A4Schedule::kPipe)
+    return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, plan.big_tokens, fields, s);
+  if (plan.schedule == W4A4Schedule::kWs)
+    return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
+  if (plan.schedule != W4A4Schedule::kTile)
+    return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, plan.schedule == W4A4Schedule::kSkinny32, s);
+#define DIROTQ_TILE(GS, OUT, ASYM, FIELDS) tile::launch_one<GS, OUT, ASYM, FIELDS>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)
+#define DIROTQ_CASE(GS)                                                                                          \
+  case GS:                                                                                                       \
+    if (fields) return DIROTQ_TILE(GS, false, false, true);                                                      \
+    if (zx) return y_dtype ? DIROTQ_TILE(GS, true, true, false) : DIROTQ_TILE(GS, false, true, false);           \
+    return y_dtype ? DIROTQ_TILE(GS, true, false, false) : DIROTQ_TILE(GS, false, false, false);
   switch (g) {
     DIROTQ_CASE(32)
     DIROTQ_CASE(64)
     DIROTQ_CASE(128)
   }
 #undef DIROTQ_CASE
+#undef DIROTQ_TILE
   return DIROTQ_ERR_SHAPE;
 }
 

@@ -15,7 +15,8 @@
 // runs in the slots between the issue of a tile's MFMAs and their results.  Bound: the VALU.  A tile of 32 x 32 and a
 // group cost 16 fma + 8 unpacking (NB = 4; 12 with NB = 2) + ~3 other instructions = 114 cycles beside 64 of MFMA; it
 // runs at 152 (of the busy CUs' SIMD-cycles VALU active 74%, MFMA 39%, both at once 16%; K = 12288, N = 3072).  256 x 256
-// tiles because the unpacking per tile and group goes with (rows staged) / (tiles multiplied).
+// tiles because the unpacking per tile and group goes with (rows staged) / (tiles multiplied).  In whole layers the
+// activations come in field form (FIELDS; pipe_unpack.h), which takes 5 instead of 8 of these operations (7 of 12).
 // Measured against the wave-specialised schedule (M = 4608, us): K = 3072, N = 9216 / 3072 / 12288: 204 / 67 / 248
 // against 261 / 79 / 272; K = 12288, N = 3072: 229 against 257; M = 32768, K = 1152, N = 4608: 294 against 356; groups
 // of 32 (K = 12288, N = 3072): 443 against 543.
@@ -102,7 +103,7 @@ __device__ __forceinline__ void store_block_rows(const f32x16 (&acc)[2][NB], con
 // The tiles of one workgroup among the tokens [m_begin, m_end) (m_begin a multiple of the tile).  gridDim.x = 8 * wpx;
 // workgroup b runs on XCD b & 7 and takes, of that XCD's run of per_xcd consecutive logical tiles, the tiles
 // slot + it * wpx, it = 0, 1, ...
-template <int GS, bool OUT_F32, int NB>
+template <int GS, bool OUT_F32, int NB, bool FIELDS>
 __device__ __forceinline__ void run_tiles(
     const uint16_t* __restrict__ xh, const uint8_t* __restrict__ xl, const uint16_t* __restrict__ sx,
     const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
@@ -215,8 +216,22 @@ __device__ __forceinline__ void run_tiles(
   };
   auto put_x_narrow = [&](unsigned char* sp, bool copy, u32x2 v) {    // 8 bytes of a token row: one 16-channel part
     const int part = xpart & 1;
-    const Stores at = narrow_stores<GS>(part_x, part, copy);
+    const Stores at = FIELDS ? narrow_fields_stores<GS>(part_x, part, copy) : narrow_stores<GS>(part_x, part, copy);
     uint32_t d[3];
+    if constexpr (FIELDS) {
+      const uint32_t k0 = part ? kOwn2 : kOwn03, k1 = part ? kOwn03 : kOwn1;
+      d[0] = v[0] & k0;
+      d[1] = v[1] & k1;
+      d[2] = (v[1] & ~k1) | (v[0] & ~k0);
+      if constexpr (GS == 32) {
+        *(u32x2*)(sp + at.first) = copy ? v : u32x2{part ? d[1] : d[0], part ? d[2] : d[1]};
+        *(u32x2*)(sp + at.second) = u32x2{part ? d[0] : d[2], 0u};
+      } else {
+        *(uint32_t*)(sp + at.second) = d[2];
+        *(u32x2*)(sp + at.first) = copy ? v : u32x2{d[0], d[1]};
+      }
+      return;
+    }
     unpack16_fp6(v[0], v[1], d);
     if constexpr (GS == 32) {
       *(u32x2*)(sp + at.first) = copy ? v : u32x2{d[0], d[1]};
@@ -266,6 +281,9 @@ __device__ __forceinline__ void run_tiles(
   };
 
   f32x16 acc[2][NB];
+  // the same during the 4-bit stages, value by value: as one register group the compiler gives the sweep three-address fma
+  // instructions, which take 2.7 cycles beside MFMAs instead of 2.4 (1% of the kernel)
+  float fa[2][NB][16];
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < 2; i++)
@@ -290,9 +308,10 @@ __device__ __forceinline__ void run_tiles(
       store_half(sp, part_w, copy, rw[set], d0, d1);
     }
     if constexpr (WIDE_X) {
-      if (q == 2) unpack16_fp6(rx[set][0], rx[set][1], d0);
+      if (!FIELDS && q == 2) unpack16_fp6(rx[set][0], rx[set][1], d0);
       if (q == 3) {
-        unpack16_fp6(rx[set][2], rx[set][3], d1);
+        if constexpr (FIELDS) expand32_fp6(rx[set], d0, d1);
+        else unpack16_fp6(rx[set][2], rx[set][3], d1);
         store_half(sp, part_x, copy, rx[set], d0, d1);
       }
     } else {
@@ -346,8 +365,10 @@ __device__ __forceinline__ void run_tiles(
           if (jj == GPS - 1) between();
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int v = 0; v < 16; v++) acc[i][j][v] = fmaf(I[v], P[v], acc[i][j][v]);
-          asm volatile("" : "+v"(acc[i][j]));                  // (accumulated in place)
+          for (int v = 0; v < 16; v++) {
+            fa[i][j][v] = fmaf(I[v], P[v], fa[i][j][v]);
+            asm volatile("" : "+v"(fa[i][j][v]));              // (accumulated in place)
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -389,11 +410,23 @@ __device__ __forceinline__ void run_tiles(
       interval(S0{}, Yes{});
       interval(S1{}, Yes{});
     }
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) fa[i][j][v] = acc[i][j][v];
     for (int st = 0; st < nq; st += 2) {
       wrap_loads();
       interval(S0{}, No{});
       interval(S1{}, No{});
     }
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[i][j][v] = fa[i][j][v];
     int m0, n0;
     tile_origin<NB == 4 ? 4 : 2, TNW, TM_>(run0 + first + it * wpx, n_mt, n_nt, m0, n0);
     m0 += m_begin + wt * (32 * NB);
@@ -411,22 +444,22 @@ __device__ __forceinline__ void run_tiles(
 }
 
 // Tokens [0, m_split) in tiles of 256 x 256, the others in tiles of 256 x 128 (GS = 32: m_split = 0).
-template <int GS, bool OUT_F32, bool BIG>
+template <int GS, bool OUT_F32, bool BIG, bool FIELDS>
 __global__ __launch_bounds__(NT, 2) void w4a4_gemm_pipe_kernel(
     const uint16_t* __restrict__ xh, const uint8_t* __restrict__ xl, const uint16_t* __restrict__ sx,
     const uint16_t* __restrict__ wh, const uint8_t* __restrict__ wq, const uint16_t* __restrict__ sw,
     const uint16_t* __restrict__ bias, int M, int N, int K, int r, void* __restrict__ y, int m_split, int wpx) {
   const int slot = blockIdx.x >> 3;
   if constexpr (BIG) {
-    run_tiles<GS, OUT_F32, 4>(xh, xl, sx, wh, wq, sw, bias, M, N, K, r, y, 0, m_split, slot, wpx);
+    run_tiles<GS, OUT_F32, 4, FIELDS>(xh, xl, sx, wh, wq, sw, bias, M, N, K, r, y, 0, m_split, slot, wpx);
     if (m_split >= M) return;
     __syncthreads();                                                  // (the ring is laid out anew)
   }
   // (from the other end: the workgroups that had one large tile less come first)
-  run_tiles<GS, OUT_F32, 2>(xh, xl, sx, wh, wq, sw, bias, M, N, K, r, y, m_split, M, wpx - 1 - slot, wpx);
+  run_tiles<GS, OUT_F32, 2, FIELDS>(xh, xl, sx, wh, wq, sw, bias, M, N, K, r, y, m_split, M, wpx - 1 - slot, wpx);
 }
 
-template <int GS, bool OUT_F32, bool BIG>
+template <int GS, bool OUT_F32, bool BIG, bool FIELDS>
 static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                       const uint16_t* bias, int M, int N, int K, int r, void* y, int m_split, int cus, hipStream_t s) {
   const BlobLayout L = blob_layout(N, K, r, GS);
@@ -440,12 +473,12 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
   // (idempotent: two threads racing here would both set the same attribute)
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)w4a4_gemm_pipe_kernel<GS, OUT_F32, BIG>,
+    hipError_t e = hipFuncSetAttribute((const void*)w4a4_gemm_pipe_kernel<GS, OUT_F32, BIG, FIELDS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
     if (e != hipSuccess) return hip_failed(e);
     attr_done.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((w4a4_gemm_pipe_kernel<GS, OUT_F32, BIG>), dim3(wpx * 8), dim3(NT), SMEM, s, xh, xl, sx,
+  hipLaunchKernelGGL((w4a4_gemm_pipe_kernel<GS, OUT_F32, BIG, FIELDS>), dim3(wpx * 8), dim3(NT), SMEM, s, xh, xl, sx,
                      (const uint16_t*)(bp + L.off_wh), (const uint8_t*)(bp + L.off_codes),
                      (const uint16_t*)(bp + L.off_sw), bias, M, N, K, r, y, m_split, wpx);
   hipError_t e = hipGetLastError();
@@ -456,7 +489,7 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 
 int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx, const void* blob,
                           const uint16_t* bias, int M, int N, int K, int r, int g, void* y, int y_dtype,
-                          long big_tokens, hipStream_t s) {
+                          long big_tokens, bool fields, hipStream_t s) {
   int cus = 0;
   {
     int dev = 0;
@@ -466,9 +499,11 @@ int launch_w4a4_gemm_pipe(const uint16_t* xh, const uint8_t* xl, const uint16_t*
   }
   // (32-channel groups: 256 x 128 tiles only, two groups' operands and 128 accumulators do not fit the register file)
   const int m_split = g == 32 ? 0 : (int)big_tokens;
-#define DIROTQ_PIPE(GS, BIG)                                                                                         \
-  return y_dtype ? pipe::launch_one<GS, true, BIG>(xh, xl, sx, blob, bias, M, N, K, r, y, m_split, cus, s)           \
-                 : pipe::launch_one<GS, false, BIG>(xh, xl, sx, blob, bias, M, N, K, r, y, m_split, cus, s)
+  // (field form: between the two kernels of a whole layer, whose output is bf16)
+#define DIROTQ_PIPE(GS, BIG)                                                                                           \
+  return fields ? pipe::launch_one<GS, false, BIG, true>(xh, xl, sx, blob, bias, M, N, K, r, y, m_split, cus, s)       \
+       : y_dtype ? pipe::launch_one<GS, true, BIG, false>(xh, xl, sx, blob, bias, M, N, K, r, y, m_split, cus, s)      \
+                 : pipe::launch_one<GS, false, BIG, false>(xh, xl, sx, blob, bias, M, N, K, r, y, m_split, cus, s)
   switch (g) {
     case 32: DIROTQ_PIPE(32, false);
     case 64:

@@ -8,6 +8,13 @@ namespace dirotq {
 
 enum class W4A4Schedule { kTile, kWs, kSkinny32, kSkinny64, kPipe };
 
+struct W4A4Plan {
+  W4A4Schedule schedule = W4A4Schedule::kTile;
+  long big_tokens = 0;                       // (kPipe: see w4a4_pipe_plan)
+  // whether kernel A writes the symmetric activation codes of a whole layer in field form (pipe_unpack.h) for it
+  bool reads_fields() const { return schedule == W4A4Schedule::kTile || schedule == W4A4Schedule::kPipe; }
+};
+
 namespace w4a4_plan {
 
 inline long tiles(long M, long N, long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); }
