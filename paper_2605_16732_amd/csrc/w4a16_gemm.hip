@@ -30,7 +30,7 @@ namespace dirotq {
 // sweep and decode on the VALU and 28 KB of LDS traffic per 128 x 32 tile and stage (operand reads 16 KB, copies).  The
 // kernel it replaces (128 x 128 tiles, two workgroups per CU) decoded into LDS, whose writes run at a quarter of the rate
 // of reads, and had one stage of loads in flight.  Graph replay on one layer's weights, that kernel -> this one, us: 4096 x 4608 ->
-// 1152 (M x K -> N) 111 -> 53 (820 TFLOP/s), 512 tokens 87 -> 23; 4096 x 3072 -> 12288 454 -> 355; 256 x 3072 -> 3072 51 -> 17.
+// 1152 (M x K -> N) 111 -> 53 (now 51: 850 TFLOP/s), 512 tokens 87 -> 23; 4096 x 3072 -> 12288 454 -> 355 (now 344); 256 x 3072 -> 3072 51 -> 17.
 namespace w16 {
 
 using namespace halves;
@@ -61,6 +61,13 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   // 4608, N = 1152 56.3 -> 53.7, 2048 tokens 43.5 -> 38.0, K = 3072, N = 12288 397 -> 386; with a single token tile they come
   // first (M = 256, N = K = 3072 16.2, spread 17.2).
   constexpr bool SPREAD = NJ > 1;
+  // With 4 or 5 token tiles each MFMA is followed by what the VALU can do beside it (32 cycles): four fma of the last tile's sweep,
+  // across stages too, and a piece of the next stage's decode, whose codes and scales the wave has copied itself, so that
+  // no barrier has to open them.  A tile's MFMAs, then the sweep, and the decode in front of a stage -> this, us: M = 4096, K =
+  // 4608, N = 1152 53.0 -> 51.2, 2048 tokens 38.3 -> 36.7, K = 3072, N = 12288 360 -> 352; groups of 32, 2048 tokens 47.5 -> 46.6
+  // (5 tiles: too many registers, equal).  Waves of 64 channels x half the tokens, which read half as much from LDS and decode
+  // twice as much: 53.3 to 57.5 us for the first of these layers.
+  constexpr bool FLOW = NJ > 2 && !(GS == 32 && NJ == 5);
   int m0, n0;
   if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
   const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
@@ -113,72 +120,197 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   issue(kh, 0, 0, COPIES);
   issue(2 + kh, SLOT, 0, COPIES);
   int cur = 0;
-  for (int step = 0; step < steps; step++) {
-    const int s = 2 * step + kh;
-    wait_copies<COPIES>();                               // this wave's copies of stage s have landed, and (barrier) all
-    __builtin_amdgcn_s_barrier();                        // waves'; stage s - 2 has been read by all of them
-    asm volatile("" ::: "memory");
-    int fill = cur + 2 * SLOT;
-    if (fill >= 3 * SLOT) fill -= 3 * SLOT;
-    if constexpr (!SPREAD) issue(s + 4, fill, 0, COPIES);
-    if (s >= nst) break;                                 // (an odd number of stages: the other half has the last one)
-    const bool half_stage = short_last && s == nst - 1;
-    const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
-    const unsigned char* sc_p = sp + X_BYTES + W_BYTES + w * 256;
-    float sc[GPS];
+  if constexpr (FLOW) {
+    constexpr int SUBS = NJ * GPS, KS = 4 / GPS;         // groups of a stage's tiles, MFMAs of each
+    constexpr int CODES_AT = NJ / 2 - 1, SLOTS = (NJ - 1 - CODES_AT) * 4;
+    float fa[NJ][16];                                    // (value by value, so that they are accumulated in place)
 #pragma unroll
-    for (int jj = 0; jj < GPS; jj++) sc[jj] = scales.read(sc_p + jj * 128, group(s, jj), c);
-    const unsigned char* wp = sp + X_BYTES + w * 1024 + c * 32;
-    bf16x8 b[4];
-    if constexpr (GS == 32) {
-      const uint4 lo = *(const uint4*)(wp + (swz << 4)), hi = *(const uint4*)(wp + ((1 ^ swz) << 4));
-      b[0] = decode(h ? lo.y : lo.x);
-      b[1] = decode(h ? lo.w : lo.z);
-      b[2] = decode(h ? hi.y : hi.x);
-      b[3] = decode(h ? hi.w : hi.z);
-    } else {
-      const uint4 p = *(const uint4*)(wp + ((h ^ swz) << 4));
-      b[0] = decode(p.x);
-      b[1] = decode(p.y);
-      b[2] = decode(p.z);
-      b[3] = decode(p.w);
-    }
-    bf16x8 a[2][4];
+    for (int j = 0; j < NJ; j++)
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++) a[0][ks] = *(const bf16x8*)(sp + ln_x[ks]);
-    f32x16 I[2][GPS];
+      for (int e = 0; e < 16; e++) fa[j][e] = 0.0f;
+    uint32_t p[4];
+    bf16x8 a[2][4], b[2][4];
+    f32x16 I[2];
+    float sc[2][GPS];
 #pragma unroll
-    for (int j = 0; j <= NJ; j++) {
-      if (j < NJ - 1)
+    for (int v = 0; v < 16; v++) I[1][v] = 0.0f;         // (the tile before the first one)
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) a[(j + 1) & 1][ks] = *(const bf16x8*)(sp + ln_x[ks] + (j + 1) * (32 * 128));
-      if (j < NJ) {
+    for (int jj = 0; jj < GPS; jj++) sc[1][jj] = 0.0f;
+    auto fetch_codes = [&](int s, int slot, auto to) {
+      const unsigned char *sp = smem + kh * (NBUF * SLOT) + slot + X_BYTES, *wp = sp + w * 1024 + c * 32;
+      if constexpr (GS == 32) {
+        const uint4 lo = *(const uint4*)(wp + (swz << 4)), hi = *(const uint4*)(wp + ((1 ^ swz) << 4));
+        p[0] = h ? lo.y : lo.x;
+        p[1] = h ? lo.w : lo.z;
+        p[2] = h ? hi.y : hi.x;
+        p[3] = h ? hi.w : hi.z;
+      } else {
+        const uint4 v = *(const uint4*)(wp + ((h ^ swz) << 4));
+        p[0] = v.x, p[1] = v.y, p[2] = v.z, p[3] = v.w;
+      }
 #pragma unroll
-        for (int jj = 0; jj < GPS; jj++) {
-          f32x16 z;
+      for (int jj = 0; jj < GPS; jj++) sc[to][jj] = scales.read(sp + W_BYTES + w * 256 + jj * 128, group(min(s, nst - 1), jj), c);
+    };
+    auto fetch_a = [&](int j) {
+      const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
 #pragma unroll
-          for (int v = 0; v < 16; v++) z[v] = 0.0f;
+      for (int ks = 0; ks < 4; ks++) a[j & 1][ks] = *(const bf16x8*)(sp + ln_x[ks] + j * (32 * 128));
+    };
+    auto stage = [&](int s, auto P_) {
+      constexpr int P = decltype(P_)::value;
+      int nxt = cur + SLOT, fill = cur + 2 * SLOT;
+      if (nxt >= 3 * SLOT) nxt -= 3 * SLOT;
+      if (fill >= 3 * SLOT) fill -= 3 * SLOT;
+      const bool half_stage = short_last && s == nst - 1;
+      fetch_a(0);
 #pragma unroll
-          for (int ks = jj * (4 / GPS); ks < (jj + 1) * (4 / GPS); ks++)
-            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ks], b[ks], z, 0, 0, 0);
-          I[j & 1][jj] = z;
+      for (int v = 0; v < SUBS; v++) {
+        const int j = v / GPS, jj = v % GPS;
+        const int now = (P * SUBS + v) & 1, pv = (v + SUBS - 1) % SUBS, pj = pv / GPS, pjj = pv % GPS;
+        if (jj == 0 && j == CODES_AT) {                  // (the wave's own copies: no barrier)
+          wait_copies<CODES_AT * COPIES / NJ>();
+          fetch_codes(s + 2, nxt, std::integral_constant<int, P ^ 1>{});
         }
+        if (jj == 0 && j + 1 < NJ) fetch_a(j + 1);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (SPREAD) {                          // a share of the copies of stage s + 4
-          issue(s + 4, fill, j * COPIES / NJ, (j + 1) * COPIES / NJ);
+#pragma unroll
+        for (int k = 0; k < KS; k++) {
+          const int ks = jj * KS + k;
+          if (k == 0) {
+            f32x16 z;
+#pragma unroll
+            for (int e = 0; e < 16; e++) z[e] = 0.0f;
+            I[now] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ks], b[P][ks], z, 0, 0, 0);
+          } else {
+            I[now] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ks], b[P][ks], I[now], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (pjj == 0 || v == 0 || !half_stage)         // (not 0 x: an infinity would become a NaN)
+#pragma unroll
+            for (int e = k * 16 / KS; e < (k + 1) * 16 / KS; e++) {
+              fa[pj][e] = fmaf(I[now ^ 1][e], sc[v == 0 ? P ^ 1 : P][pjj], fa[pj][e]);
+              asm volatile("" : "+v"(fa[pj][e]));
+            }
+          if (j > CODES_AT) {
+            const int slot = (j - CODES_AT - 1) * 4 + ks;
+#pragma unroll
+            for (int q = slot * 4 / SLOTS; q < (slot + 1) * 4 / SLOTS; q++) b[P ^ 1][q] = decode(p[q]);
+          }
+          if (k == KS - 1 && jj == GPS - 1) issue(s + 4, fill, j * COPIES / NJ, (j + 1) * COPIES / NJ);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      if (j > 0) {
+      cur = nxt;
+    };
+    wait_copies<COPIES>();
+    fetch_codes(kh, 0, std::integral_constant<int, 0>{});
 #pragma unroll
-        for (int jj = 0; jj < GPS; jj++)
-          if (jj == 0 || !half_stage)                    // (not 0 x: an infinity would become a NaN)
+    for (int ks = 0; ks < 4; ks++) b[0][ks] = decode(p[ks]);
+    int s = kh;
+    auto enter = [&]() {                                 // this wave's copies of stage s have landed, and (barrier) all waves';
+      wait_copies<COPIES>();                             // stage s - 2 has been read by all of them
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    auto last = [&](auto P_) {                           // the last tile of the last stage
+      constexpr int P = decltype(P_)::value;
+      if (GPS == 1 || !short_last || s - 2 != nst - 1)
 #pragma unroll
-          for (int v = 0; v < 16; v++) acc[j - 1][v] = fmaf(I[(j - 1) & 1][jj][v], sc[jj], acc[j - 1][v]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+        for (int e = 0; e < 16; e++) {
+          fa[NJ - 1][e] = fmaf(I[(P * SUBS + SUBS - 1) & 1][e], sc[P][GPS - 1], fa[NJ - 1][e]);
+          asm volatile("" : "+v"(fa[NJ - 1][e]));
+        }
+    };
+    const int mine = (nst - kh + 1) / 2;                 // stages of this half
+    for (int i = 1; i < mine; i += 2) {
+      enter();
+      stage(s, std::integral_constant<int, 0>{});
+      s += 2;
+      enter();
+      stage(s, std::integral_constant<int, 1>{});
+      s += 2;
     }
-    cur = cur + SLOT >= 3 * SLOT ? 0 : cur + SLOT;
+    if (mine & 1) {
+      enter();
+      stage(s, std::integral_constant<int, 0>{});
+      s += 2;
+      last(std::integral_constant<int, 0>{});
+    } else if (mine) {
+      last(std::integral_constant<int, 1>{});
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[j][e] = fa[j][e];
+    if (mine < steps) __builtin_amdgcn_s_barrier();      // (an odd number of stages: the other half has the last one)
+  } else {
+    for (int step = 0; step < steps; step++) {
+      const int s = 2 * step + kh;
+      wait_copies<COPIES>();                               // this wave's copies of stage s have landed, and (barrier) all
+      __builtin_amdgcn_s_barrier();                        // waves'; stage s - 2 has been read by all of them
+      asm volatile("" ::: "memory");
+      int fill = cur + 2 * SLOT;
+      if (fill >= 3 * SLOT) fill -= 3 * SLOT;
+      if constexpr (!SPREAD) issue(s + 4, fill, 0, COPIES);
+      if (s >= nst) break;                                 // (an odd number of stages: the other half has the last one)
+      const bool half_stage = short_last && s == nst - 1;
+      const unsigned char* sp = smem + kh * (NBUF * SLOT) + cur;
+      const unsigned char* sc_p = sp + X_BYTES + W_BYTES + w * 256;
+      float sc[GPS];
+#pragma unroll
+      for (int jj = 0; jj < GPS; jj++) sc[jj] = scales.read(sc_p + jj * 128, group(s, jj), c);
+      const unsigned char* wp = sp + X_BYTES + w * 1024 + c * 32;
+      bf16x8 b[4];
+      if constexpr (GS == 32) {
+        const uint4 lo = *(const uint4*)(wp + (swz << 4)), hi = *(const uint4*)(wp + ((1 ^ swz) << 4));
+        b[0] = decode(h ? lo.y : lo.x);
+        b[1] = decode(h ? lo.w : lo.z);
+        b[2] = decode(h ? hi.y : hi.x);
+        b[3] = decode(h ? hi.w : hi.z);
+      } else {
+        const uint4 p = *(const uint4*)(wp + ((h ^ swz) << 4));
+        b[0] = decode(p.x);
+        b[1] = decode(p.y);
+        b[2] = decode(p.z);
+        b[3] = decode(p.w);
+      }
+      bf16x8 a[2][4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) a[0][ks] = *(const bf16x8*)(sp + ln_x[ks]);
+      f32x16 I[2][GPS];
+#pragma unroll
+      for (int j = 0; j <= NJ; j++) {
+        if (j < NJ - 1)
+#pragma unroll
+          for (int ks = 0; ks < 4; ks++) a[(j + 1) & 1][ks] = *(const bf16x8*)(sp + ln_x[ks] + (j + 1) * (32 * 128));
+        if (j < NJ) {
+#pragma unroll
+          for (int jj = 0; jj < GPS; jj++) {
+            f32x16 z;
+#pragma unroll
+            for (int v = 0; v < 16; v++) z[v] = 0.0f;
+#pragma unroll
+            for (int ks = jj * (4 / GPS); ks < (jj + 1) * (4 / GPS); ks++)
+              z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ks], b[ks], z, 0, 0, 0);
+            I[j & 1][jj] = z;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (SPREAD) {                          // a share of the copies of stage s + 4
+            issue(s + 4, fill, j * COPIES / NJ, (j + 1) * COPIES / NJ);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        if (j > 0) {
+#pragma unroll
+          for (int jj = 0; jj < GPS; jj++)
+            if (jj == 0 || !half_stage)                    // (not 0 x: an infinity would become a NaN)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[j - 1][v] = fmaf(I[(j - 1) & 1][jj][v], sc[jj], acc[j - 1][v]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      cur = cur + SLOT >= 3 * SLOT ? 0 : cur + SLOT;
+    }
   }
   wait_copies<0>();                                      // (nothing may land in LDS after the workgroup has ended)
 
