@@ -366,6 +366,10 @@ static int launch_large(const uint16_t* x, const void* blob, const uint16_t* bia
 // operands are kept in the order c0 c2 c4 c6 c1 c3 c5 c7 (the activations are permuted once when they
 // are staged), which saves the last round of byte permutes of the weight decode.  The 8 waves' partial
 // sums are added through LDS in wave order.
+// Bound: the decode and the staging beside it, not the stream: a second or third chunk in flight makes it slower (four layers' weights
+// in turn, one token, K = 3072, N = 9216: 8.4 -> 8.8, 9.4 us).  Activation rows past M are not stored to LDS (8.4 -> 8.15) and the
+// decode is the scaled conversion instead of byte tables (8.15 -> 7.6).  Both, us: K = 12288, N = 3072 16.4 -> 14.4; 3072,
+// 3072 5.6 -> 5.1; 6144, 12288 13.9 -> 12.4; 8 tokens, 3072, 9216 8.6 -> 8.1.
 struct Eight {
   static constexpr int MT = 8, KC = 1024;           // token capacity, channels per chunk
   static constexpr int WROW = KC / 2 + 16;          // bytes per LDS row of codes
@@ -377,20 +381,15 @@ struct Eight {
   static constexpr int smem_bytes(int gs) { return 2 * buf_bytes(gs) > 8 * NV * 256 ? 2 * buf_bytes(gs) : 8 * NV * 256; }
 };
 
-// 8 sign-magnitude nibbles -> bf16 in the order c0 c2 c4 c6 c1 c3 c5 c7
+// 8 sign-magnitude nibbles -> bf16 in the order c0 c2 c4 c6 c1 c3 c5 c7 (10 instructions, with byte tables 14: below)
 __device__ __forceinline__ uint4 nibbles_to_bf16_eo(uint32_t p) {
-  const uint32_t sel_e = p & 0x07070707u, sel_o = (p >> 4) & 0x07070707u;
-  const uint32_t lo_e = __builtin_amdgcn_perm(0xE0C0A080u, 0x40008000u, sel_e);
-  const uint32_t lo_o = __builtin_amdgcn_perm(0xE0C0A080u, 0x40008000u, sel_o);
-  uint32_t hi_e = __builtin_amdgcn_perm(0x40404040u, 0x40403F00u, sel_e);
-  uint32_t hi_o = __builtin_amdgcn_perm(0x40404040u, 0x40403F00u, sel_o);
-  hi_e |= (p & 0x08080808u) << 4;
-  hi_o |= p & 0x80808080u;
-  uint4 r;
-  r.x = __builtin_amdgcn_perm(hi_e, lo_e, 0x05010400u);   // c0, c2
-  r.y = __builtin_amdgcn_perm(hi_e, lo_e, 0x07030602u);   // c4, c6
-  r.z = __builtin_amdgcn_perm(hi_o, lo_o, 0x05010400u);   // c1, c3
-  r.w = __builtin_amdgcn_perm(hi_o, lo_o, 0x07030602u);   // c5, c7
+  uint32_t e, o;
+  unpack8(p, e, o);
+  uint4 r;                                               // bytes [s 0000 mmm] = m 2^-9 as fp8, times 2^9
+  r.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(e, 512.0f, false));   // c0, c2
+  r.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(e, 512.0f, true));    // c4, c6
+  r.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(o, 512.0f, false));   // c1, c3
+  r.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(o, 512.0f, true));    // c5, c7
   return r;
 }
 
@@ -450,6 +449,7 @@ __global__ __launch_bounds__(512) void w4a16_eight_kernel(
     for (int i = 0; i < CPT; i++) *(uint4*)(sb + crow[i] * F::WROW + cpiece[i] * 16) = rc[i];
 #pragma unroll
     for (int i = 0; i < XPT; i++) {
+      if (__builtin_amdgcn_readfirstlane(xrow[i]) >= M) continue;   // (nobody reads it; a wave's pieces are of one row)
       uint4 v;                                            // c0c1 c2c3 c4c5 c6c7 -> c0c2 c4c6 c1c3 c5c7
       v.x = __builtin_amdgcn_perm(rx[i].y, rx[i].x, 0x05040100u);
       v.y = __builtin_amdgcn_perm(rx[i].w, rx[i].z, 0x05040100u);
