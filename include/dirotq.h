@@ -100,7 +100,7 @@ int dirotq_weights_bytes(int N, int K, int r, int g, size_t* bytes /*host out*/)
 /* Bytes of scratch dirotq_prepare_weights needs (the fp32 fused weight W Q). */
 int dirotq_prepare_scratch_bytes(int N, int K, size_t* bytes /*host out*/);
 
-/* Bytes of workspace dirotq_linear needs (x_h, packed x_l and s_x of one call). */
+/* Bytes of workspace dirotq_linear, dirotq_linear_asym and dirotq_linear_shared need (the intermediates of one call). */
 int dirotq_workspace_bytes(int M, int K, int r, int g, size_t* bytes /*host out*/);
 
 /* ---- offline ------------------------------------------------------------------- */
@@ -171,9 +171,11 @@ int dirotq_w4a4_gemm(const uint16_t* xh_bf16, const uint8_t* xl_packed, const ui
                      void* y /*out*/, int y_dtype, void* stream);
 
 /*
- * The fused layer: dirotq_rotate_quantize into `workspace`, then dirotq_w4a4_gemm,
- * both on `stream`.  y_bf16 [M,N].  workspace: dirotq_workspace_bytes bytes, 256-byte
- * aligned; its contents afterwards are the intermediates of this call.
+ * The fused layer: the results of dirotq_rotate_quantize followed by dirotq_w4a4_gemm, both
+ * kernels on `stream`.  y_bf16 [M,N].  workspace: dirotq_workspace_bytes bytes, 256-byte
+ * aligned; contents undefined afterwards (private to the call: between the kernels of a whole
+ * layer the codes may be packed in another way than the two calls exchange them.  A caller
+ * that wants the intermediates gets them from dirotq_rotate_quantize).
  */
 int dirotq_linear(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* blob,
                   const uint16_t* bias_bf16, int M, int N, int K, int r, int g,
@@ -182,7 +184,7 @@ int dirotq_linear(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const void* b
 /*
  * dirotq_linear for callers that cannot allocate or pass device memory for intermediates
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same two kernels, with x_h, packed x_l and s_x kept in a fixed 64 MiB array in device
+ * the same two kernels, with their intermediates kept in a fixed 64 MiB array in device
  * memory that belongs to the library (one copy per GPU, held until the process ends).  The
  * call allocates and frees nothing.  DIROTQ_STATIC_SCRATCH_BYTES bounds what
  * dirotq_workspace_bytes(M, K, r, g) may return (FLUX-shaped fc2, M = 4608, K = 12288:
@@ -199,11 +201,12 @@ int dirotq_linear_static(const uint16_t* x_bf16, const uint16_t* Qt_bf16, const 
 /*
  * Several layers that read the same activations (fused QKV next to the MLP's first
  * projection in a block whose branches share their input, Section 5.1's FLUX blocks):
- * one dirotq_rotate_quantize into `workspace`, then one dirotq_w4a4_gemm per output.
+ * one rotation and quantization of the activations, then one product per output.
  * All outputs share K, r, g and the rotation; output i has N = Ns[i], weights blobs[i],
  * bias biases[i] (the array or any entry may be NULL) and result ys[i] bf16 [M, Ns[i]].
  * blobs, biases, Ns, ys are HOST arrays of n_out entries (1 <= n_out <= 16) holding
- * device pointers.  Results are bit-identical to n_out dirotq_linear calls.
+ * device pointers.  Results are bit-identical to n_out dirotq_linear calls.  workspace as
+ * in dirotq_linear: contents undefined afterwards.
  */
 int dirotq_linear_shared(const uint16_t* x_bf16, const uint16_t* Qt_bf16, int n_out,
                          const void* const* blobs /*host*/, const uint16_t* const* biases /*host*/,

@@ -53,6 +53,17 @@ def test_size_queries():
     assert B.a8_workspace_bytes(M, K, r) == pad(M * r * 2) + pad(M * KL) + pad(M * 2) + scratch
 
 
+@pytest.mark.parametrize("call", ["dirotq_linear", "dirotq_linear_shared"])
+def test_header_does_not_promise_the_workspace_of_whole_layers(call):
+    """Between the kernels of a whole symmetric layer the codes may be in field form, which dirotq_w4a4_gemm does not read: the
+    header leaves the workspace's contents open instead of calling them the intermediates."""
+    with open(os.path.join(ROOT, "include", "dirotq.h")) as f:
+        header = f.read()
+    comment = " ".join(header[:header.index(f"int {call}(")].rsplit("/*", 1)[1].replace("*", " ").split())
+    assert "contents undefined afterwards" in comment, comment
+    assert "into `workspace`" not in comment and "are the intermediates" not in comment, comment
+
+
 @pytest.mark.parametrize("N,K,r,g", [
     (0, 64, 0, 32),      # N < 1
     (8, 48, 0, 32),      # K % 32
