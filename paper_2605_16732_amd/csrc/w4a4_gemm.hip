@@ -24,6 +24,7 @@
 // operations of 4.3 cycles, which add up (measured 200 cycles; three waves per SIMD with K in three parts: 190, lost
 // again in the exchange of their sums).  The 128 x 128 tiles before it had four waves that staged both operands through LDS
 // as fp8: M = 1000, K = N = 3072 34.3 -> 26.5 us (asymmetric 39.0 -> 28.4).
+#include <algorithm>
 #include <atomic>
 
 #include <cstdlib>
@@ -482,7 +483,7 @@ int w4a4_plan_layer(int M, int N, int K, int r, int g, bool asym, W4A4Plan& plan
   if (f && K > r) {
     const bool large = !strcmp(f, "large"), small = !strcmp(f, "small"), ws = !strcmp(f, "ws");
     big_tokens = 0;
-    if (!strcmp(f, "tile")) return sch = W4A4Schedule::kTile, DIROTQ_OK;
+    if (!strcmp(f, "tile") && w4a4_plan::tiles(M, N, tile::TMW, tile::TNW) <= w4a4_plan::MOST_TILES) return sch = W4A4Schedule::kTile, DIROTQ_OK;
     if (!strcmp(f, "skinny32")) return sch = W4A4Schedule::kSkinny32, DIROTQ_OK;
     if (!strcmp(f, "skinny64")) return sch = W4A4Schedule::kSkinny64, DIROTQ_OK;
     if (!strcmp(f, "skinny")) {
@@ -512,6 +513,15 @@ int launch_w4a4_gemm(const W4A4Plan& plan, bool fields, const uint16_t* xh, cons
     return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
   if (plan.schedule != W4A4Schedule::kTile)
     return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, plan.schedule == W4A4Schedule::kSkinny32, s);
+  // (without 4-bit channels the activations are rows of x_h alone, so that the slabs need nothing but their first token)
+  const long slab = w4a4_plan::slab_tokens(N);
+  if (K == r && M > slab) {
+    int st = DIROTQ_OK;
+    for (long m = 0; m < M && !st; m += slab)
+      st = launch_w4a4_gemm(plan, fields, xh + (size_t)m * r, xl, sx, zx, blob, bias, (int)std::min(slab, M - m), N, K, r, g,
+                            (char*)y + (size_t)m * N * (y_dtype ? 4 : 2), y_dtype, s);
+    return st;
+  }
 #define DIROTQ_TILE(GS, OUT, ASYM, FIELDS) tile::launch_one<GS, OUT, ASYM, FIELDS>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)
 #define DIROTQ_CASE(GS)                                                                                          \
   case GS:                                                                                                       \

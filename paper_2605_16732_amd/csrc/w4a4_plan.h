@@ -17,6 +17,10 @@ struct W4A4Plan {
 
 namespace w4a4_plan {
 
+// 128 x 128 tiles of a launch, at most: its grid (512 threads a tile) stays below 2^32 threads.  Layers with 4-bit channels that
+// have more go to the persistent kernels, others in several launches (slab_tokens).
+constexpr long MOST_TILES = 1L << 22;
+
 inline long tiles(long M, long N, long m, long n) { return ((M + m - 1) / m) * ((N + n - 1) / n); }
 inline double rounds(long work, long slots) { return (double)((work + slots - 1) / slots); }
 
@@ -66,6 +70,9 @@ struct Cost {
   }
 };
 
+// Tokens of a launch of the 128 x 128 tiles: as many whole tiles as MOST_TILES allows
+inline long slab_tokens(long N) { return MOST_TILES / ((N + 127) / 128) * 128; }
+
 }  // namespace w4a4_plan
 
 // Large layers, from 128 tiles of 256 x 128 on: the pipelined kernel (persistent workgroups, 256 x 256 and 256 x 128 tiles),
@@ -94,7 +101,7 @@ inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, in
       if (piped) persistent = cost.pipe(g == 32 ? pipe::HALF * whole : plan, N);   // (groups of 32: half-size tiles only)
     }
     if (!piped) persistent = cost.ws(M, N);
-    if (c128 < persistent) return W4A4Schedule::kTile;
+    if (c128 < persistent && tiles(M, N, 128, 128) <= MOST_TILES) return W4A4Schedule::kTile;
     return piped ? W4A4Schedule::kPipe : W4A4Schedule::kWs;
   }
   const double c32 = cost.skinny32(M, N), c64 = cost.skinny64(M, N);

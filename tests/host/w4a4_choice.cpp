@@ -1,5 +1,7 @@
 // Host check of the W4A4 schedule choice (w4a4_plan.h) against measured times: reads the table given as argument and prints,
-// for the choices on 256 CUs, how far they are from the best schedule of each row.
+// for the choices on 256 CUs, how far they are from the best schedule of each row, and whether every grid of the 128 x 128
+// tiles stays below 2^32 threads.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -42,5 +44,18 @@ int main(int, char** argv) {
   std::fclose(f);
   small.print("split_k_or_tiles");
   large.print("persistent");
+  // the largest outputs that the shape rules admit, narrow and wide, with and without 4-bit channels
+  int big = 0;
+  for (long N : {1L, 33L, 129L, 6001L, 8065L, 12288L, 1L << 20, 1L << 24})
+    for (long K : {32L, 640L, 12288L})
+      for (int g : {32, 64})
+        for (int kind = 0; kind < 3; kind++) {            // symmetric, asymmetric, 16-bit channels only
+          const long M = std::min(1L << 24, (1L << 30) / ((N + 127) / 128) * 128);
+          long split = 0;
+          if (w4a4_choose((int)M, (int)N, (int)K, kind == 2 ? (int)K : 0, g, kind == 1, 256, split) != W4A4Schedule::kTile) continue;
+          const long slab = w4a4_plan::slab_tokens(N), tokens = kind == 2 ? std::min(M, slab) : M;
+          big += slab < 128 || slab % 128 != 0 || 512 * w4a4_plan::tiles(tokens, N, 128, 128) >= 1L << 32;
+        }
+  std::printf("w4a4_grids: rows 0 mean_excess 0 over5 %d worst 1\n", big);
   return 0;
 }

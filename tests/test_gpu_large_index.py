@@ -48,6 +48,30 @@ def test_gemm_output_beyond_2_31_elements():
     np.testing.assert_array_equal(got, ybf)                  # integers times powers of two: exact
 
 
+def test_16_bit_layer_with_more_tiles_than_one_launch_takes():
+    """2^17 x 33 tiles of 128 x 128, in two launches; small integers, so that every output is exact."""
+    M, N, K = 1 << 24, 4097, 32
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 150 << 30:
+        pytest.skip("needs 150 GiB of device memory")
+    _say(f"w4a4_gemm, r = K, {M // 128 * ((N + 127) // 128) / 2**22:.2f} x 2^22 tiles")
+    gen = torch.Generator(device="cuda").manual_seed(63)
+    xh = torch.empty((M, K), dtype=torch.bfloat16, device="cuda")
+    step = 1 << 16
+    for m0 in range(0, M, step):
+        xh[m0:m0 + step] = torch.randint(-1, 2, (step, K), generator=gen, device="cuda").to(torch.bfloat16)
+    Wh = torch.randint(-2, 3, (N, K), generator=gen, device="cuda").to(torch.bfloat16)
+    blob = B.import_weights(Wh, None, None, N, K, K, 64)
+    y = B.w4a4_gemm(xh, None, None, blob, M, N, K, K, 64)
+    wrong = torch.zeros((), dtype=torch.int64, device="cuda")
+    Wt = Wh.float().T.contiguous()
+    for m0 in range(0, M, step):
+        wrong += (y[m0:m0 + step] != (xh[m0:m0 + step].float() @ Wt).to(torch.bfloat16)).sum()
+    assert wrong.item() == 0
+    del y, xh
+    torch.cuda.empty_cache()
+
+
 def test_rotation_input_beyond_2_31_elements():
     M, K, r, g = 524288 + 256, 4096, 128, 64                 # M * K = 2.15e9 elements (4.3 GB of bf16)
     _say(f"rotate_quantize with {M * K / 2**31:.2f} x 2^31 input elements")
