@@ -67,7 +67,9 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   // 4608, N = 1152 53.0 -> 51.2, 2048 tokens 38.3 -> 36.7, K = 3072, N = 12288 360 -> 352; groups of 32, 2048 tokens 47.5 -> 46.6
   // (5 tiles: too many registers, equal).  Waves of 64 channels x half the tokens, which read half as much from LDS and decode
   // twice as much: 53.3 to 57.5 us for the first of these layers.
-  constexpr bool FLOW = NJ > 2 && !(GS == 32 && NJ == 5);
+  // 1 and 2 tiles keep the plain order: the next stage's codes and scales may come in behind the first tile only, beside which the
+  // last stage's scales are still in use, and their decode needs a further tile.
+  constexpr bool FLOW = NJ >= 4 && !(GS == 32 && NJ == 5);
   int m0, n0;
   if (!tile_of(n_mt, n_nt, per_xcd, TM_, m0, n0)) return;
   const int t = threadIdx.x, l = t & 63, h = l >> 5, c = l & 31;
@@ -123,6 +125,8 @@ __global__ __launch_bounds__(NT, 1) void w4a16_large_kernel(
   if constexpr (FLOW) {
     constexpr int SUBS = NJ * GPS, KS = 4 / GPS;         // groups of a stage's tiles, MFMAs of each
     constexpr int CODES_AT = NJ / 2 - 1, SLOTS = (NJ - 1 - CODES_AT) * 4;
+    // (fetch_codes replaces the scales of the stage before, whose last tile is swept beside tile 0)
+    static_assert(CODES_AT >= 1 && SLOTS >= 4, "codes and scales of the next stage come behind tile 0 and are decoded behind them");
     float fa[NJ][16];                                    // (value by value, so that they are accumulated in place)
 #pragma unroll
     for (int j = 0; j < NJ; j++)
