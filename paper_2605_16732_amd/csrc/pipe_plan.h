@@ -12,10 +12,12 @@ namespace pipe {
 
 constexpr int TNW = 256;                     // output channels per workgroup tile (4 waves of 64)
 
-constexpr double HALF = 0.65;                // time of a 256 x 128 tile, in units of a 256 x 256 one
+// Time of a 256 x 128 tile, in units of a 256 x 256 one: median of 189 layers of more than three rounds of small tiles,
+// all in large or all in small ones, with the field form
+constexpr double HALF = 0.65;
 
 // Time of the workgroup that has most to do with `big` 256 x 256 tiles and `small` 256 x 128 ones, in units of a large
-// tile, a small one takes HALF (K = 3072: 44 against 66 us), and a workgroup that has both kinds drains and refills its
+// tile, a small one takes HALF (field form, M = 8192, K = 3072, N = 9216: 4.5 rounds 310 us, 9 small ones 377), and a workgroup that has both kinds drains and refills its
 // pipeline once in between.  Per XCD (wpx workgroups) the large tiles are dealt to the slots 0, 1, ... in turn, the small
 // ones to the slots from the other end.
 inline double most(long big, long small, uint32_t wpx) {

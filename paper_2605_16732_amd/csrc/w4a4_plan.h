@@ -25,10 +25,13 @@ inline long tiles(long M, long N, long m, long n) { return ((M + m - 1) / m) * (
 inline double rounds(long work, long slots) { return (double)((work + slots - 1) / slots); }
 
 // Costs in microseconds of the schedules: k = 1024 4-bit channels, q = 128 16-bit ones.  Fitted to what kernel B adds to
-// kernel A in whole layers (graph replay over three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, up
-// to 9000 tokens, all group sizes, r up to 256): the split-K forms to 7250 layers, the others to 1940 (5% (tile) to 11% off, root
-// mean square).  The numbers that depend on the kind of code stand as {groups of 64, 128, 32 symmetric; the same
-// asymmetric}; ragged: rows of y that do not begin at multiples of 8 bytes (tile: 16) are stored value by value.
+// kernel A in whole layers (graph replay over three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, all
+// group sizes, r up to 256): the split-K forms to 7250 layers, the 128 x 128 tiles to 1940 (5% off, the others up to 11%, root mean
+// square).  Symmetric layers became 3 to 5% faster in the tiles and the pipelined kernel with the field form; the persistent
+// kernels are fitted to 650 layers with it, up to 32768 tokens, times 1.05 (groups of 32: 1.03), which is what the tiles' cost
+// is above their present times: only the comparisons matter.  The numbers that depend on the kind of code stand as
+// {groups of 64, 128, 32 symmetric; the same asymmetric}; ragged: rows of y that do not begin at multiples of 8 (persistent
+// kernels: 8 or 16, tile: 16) bytes are stored in smaller pieces, down to single values.
 struct Cost {
   double k, q;
   int kind, cus;
@@ -56,17 +59,19 @@ struct Cost {
     const double ragged = N % 8 ? 1.55 : 0.0;
     return 2.89 + rounds(T, cus) * (3.82 + ragged + 2.16 * q + K[kind] * k) + (double)T / cus * (1.89 + 0.49 * k);
   }
+  // Large layers: outputs of a 256 x 256 tile for every CU, as a measure for rows that are stored value by value
+  double outputs(long M, long N) const { return (double)M * (double)N / (65536.0 * cus); }
   // 256 x 128 tiles of the wave-specialised kernel
   double ws(long M, long N) const {
-    static constexpr double K[6] = {9.01, 8.59, 0.0, 11.47, 10.60, 27.13};
-    const double ragged = N % 4 ? 15.42 : 0.0;
-    return 6.08 + rounds(tiles(M, N, 128, 256), cus) * (6.06 + ragged + 2.42 * q + K[kind] * k);
+    static constexpr double K[6] = {9.91, 9.70, 0.0, 12.90, 11.76, 27.29};
+    const double ragged = N % 4 ? 41.50 : N % 8 ? 8.70 : 0.0;
+    return 6.11 + rounds(tiles(M, N, 128, 256), cus) * (4.50 + 2.60 * q + K[kind] * k) + ragged * outputs(M, N);
   }
   // the pipelined kernel, whose plan takes the time of `large` 256 x 256 tiles
-  double pipe(double large, long N) const {
-    static constexpr double K[3] = {17.22, 16.95, 27.36};
-    const double ragged = N % 4 ? 25.55 : 0.0;
-    return 4.34 + large * (8.02 + ragged + 6.15 * q + K[kind] * k);
+  double pipe(double large, long M, long N) const {
+    static constexpr double K[3] = {17.40, 17.31, 27.92};
+    const double ragged = N % 4 ? 43.15 : N % 8 ? 7.65 : 0.0;
+    return 5.12 + large * (5.78 + 5.46 * q + K[kind] * k) + ragged * outputs(M, N);
   }
 };
 
@@ -75,15 +80,15 @@ inline long slab_tokens(long N) { return MOST_TILES / ((N + 127) / 128) * 128; }
 
 }  // namespace w4a4_plan
 
-// Large layers, from 128 tiles of 256 x 128 on: the pipelined kernel (persistent workgroups, 256 x 256 and 256 x 128 tiles),
-// or, while its plan does not pay, the wave-specialised one (256 x 128), which also runs all asymmetric layers.  A round of
-// the latter's tiles takes 0.61 of a 256 x 256 tile's time (M = 2048, K = N = 3072: 42 against 46 us; M = 4096, K = 1152,
-// N = 4608: 57 against 54 us; 937 whole layers: 4 slower than in the wave-specialised kernel by more than 2%, none by
-// more than 3.2%).  Groups of 32 are always faster in the pipelined kernel (M = 1999, N = 2500, K = 2080: 46 against 52 us).
-// Where the 128 x 128 tiles fill their rounds better they are cheaper than either (M = 1500, N = 6000, K = 2080, asymmetric:
-// 56 against 66 us; of 526 such layers 191: asymmetric ones 1.08 times as fast in the mean, symmetric ones 1.03).
-// Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles.
-// Over those 1940 layers the choice is 0.19% above the best schedule (mean).  big_tokens: see w4a4_pipe_plan.
+// Large layers, from 128 tiles of 256 x 128 on: the cheapest of the pipelined kernel (symmetric; persistent workgroups, 256 x 256
+// and 256 x 128 tiles), the wave-specialised one (256 x 128; not symmetric groups of 32) and the 128 x 128 tiles.  What kernel B
+// takes, us, pipelined | wave-specialised | tiles: M = 4096, N = 3072, K = 1152 28 | 35 | 33; M = 4096, K = 3072, N = 1152 41 | 37 |
+// 43, N = 6144 (1.5 rounds of 256 x 256 tiles) 127 | 112 | 140; N = 4026, K = 1536, whose rows are stored value by value, 75 | 78
+// | 58; M = 10814, K = 3072, N = 2263, asymmetric - | 199 | 185.  500 layers that were not in the fit: on average 0.05% (symmetric,
+// at most 4%) and 0.18% (asymmetric, at most 8%) above the best of the three; 0.61% (at most 20%) and 0.25% with the rule from
+// before the field form.
+// Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles:
+// 0.27% above the best of 1206 layers (mean).  big_tokens: see w4a4_pipe_plan.
 inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, int cus, long& big_tokens) {
   using namespace w4a4_plan;
   big_tokens = 0;
@@ -92,17 +97,15 @@ inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, in
   const double c128 = cost.tile(M, N);
   const long half_tiles = tiles(M, N, 128, 256);
   if (half_tiles >= 128) {
-    bool piped = false;
-    double persistent = 0.0;
+    double persistent = asym || g != 32 ? cost.ws(M, N) : 0.0;
+    W4A4Schedule sch = W4A4Schedule::kWs;
     if (!asym) {
       const double plan = w4a4_pipe_plan(M, N, cus, big_tokens);
-      const double whole = rounds(half_tiles, cus < 8 ? 8 : cus / 8 * 8);
-      piped = g == 32 || plan <= 0.61 * whole;
-      if (piped) persistent = cost.pipe(g == 32 ? pipe::HALF * whole : plan, N);   // (groups of 32: half-size tiles only)
+      // (groups of 32: half-size tiles only, and no wave-specialised form)
+      const double c = cost.pipe(g == 32 ? pipe::HALF * rounds(half_tiles, cus < 8 ? 8 : cus / 8 * 8) : plan, M, N);
+      if (g == 32 || c <= persistent) persistent = c, sch = W4A4Schedule::kPipe;
     }
-    if (!piped) persistent = cost.ws(M, N);
-    if (c128 < persistent && tiles(M, N, 128, 128) <= MOST_TILES) return W4A4Schedule::kTile;
-    return piped ? W4A4Schedule::kPipe : W4A4Schedule::kWs;
+    return c128 < persistent && tiles(M, N, 128, 128) <= MOST_TILES ? W4A4Schedule::kTile : sch;
   }
   const double c32 = cost.skinny32(M, N), c64 = cost.skinny64(M, N);
   if (c32 <= c64 && c32 <= c128) return W4A4Schedule::kSkinny32;
