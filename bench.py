@@ -23,8 +23,8 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_FP8_TOPS = 5000.0         # MI355X dense fp8 MFMA (int8 has the same peak)
-PEAK_FP6_TOPS = 10000.0        # MI355X dense FP6 MFMA: the symmetric codes of large layers run on it; fractions of kernel B
-                               # keep the fp8 peak in every workload, so that they compare
+PEAK_FP6_TOPS = 10000.0        # MI355X dense FP6 MFMA: the codes of the pipelined and the 128 x 128 tiled kernels run on it;
+                               # fractions of kernel B keep the fp8 peak in every workload, so that they compare
 PEAK_HBM_GBS = 8000.0
 
 
@@ -509,7 +509,7 @@ def main() -> int:
         "metric": "effective TOPS of fused rotate+quant+W4A4 linear, FLUX shapes",
         "value": round(value, 3), "unit": "TOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": ("fp8 e4m3" if args.asym else "fp6 e2m3 (large layers) or fp8 e4m3") +
+        "dtype": ("fp8 e4m3 or fp6 e2m3 (128 x 128 tiles)" if args.asym else "fp6 e2m3 (large layers) or fp8 e4m3") +
                  " (exact integer codes, fp32 accumulate) + bf16 (fp32 accumulate)", "data": "synthetic",
         "config": {"workload": {"flux": "FLUX.1-dev-shaped block linears, M=4608 tokens, hidden 3072, "
                                         "r=128, g=64: fused QKV (N=9216), out-proj (N=3072), fc1 (N=12288), "

@@ -53,9 +53,9 @@
  *    sign-magnitude form: bit 3 = sign, bits 0-2 = |q|; zero is always 0x0.
  *  - Activation scales are group-major: s_x[j * M + m] for group j, token m.
  *  - The GEMM calls pick one of several schedules of the same arithmetic from the problem
- *    size (few tokens: K split over the waves of a workgroup; medium: 128 x 128 tiles;
- *    large: persistent workgroups, whose waves all stage and multiply or are specialised for
- *    one of the two: asymmetric layers use the specialised ones).
+ *    size (few tokens: K split over the waves of a workgroup; medium, and large where they fit
+ *    the chip better: 128 x 128 tiles; large: persistent workgroups, whose waves all stage and
+ *    multiply (symmetric layers) or are specialised for one of the two).
  *    The fp32 additions of an output are ordered differently in each, so a token's result
  *    is deterministic for a given
  *    (M, N, K, r, g) but not bit-identical across different M.  For testing, the

@@ -385,7 +385,7 @@ struct Eight {
   static constexpr int smem_bytes(int gs) { return 2 * buf_bytes(gs) > 8 * NV * 256 ? 2 * buf_bytes(gs) : 8 * NV * 256; }
 };
 
-// 8 sign-magnitude nibbles -> bf16 in the order c0 c2 c4 c6 c1 c3 c5 c7 (10 instructions, with byte tables 14: below)
+// 8 sign-magnitude nibbles -> bf16 in the order c0 c2 c4 c6 c1 c3 c5 c7 (10 instructions)
 __device__ __forceinline__ uint4 nibbles_to_bf16_eo(uint32_t p) {
   uint32_t e, o;
   unpack8(p, e, o);

@@ -1,8 +1,9 @@
 // Kernel B, wave-specialised form (symmetric activation codes; the asymmetric ones: see the kernel's comment):
 //   y = x_h W'_h^T + sum_j s_x[:,j] s_w[:,j]^T * (q_x,j q_w,j^T)
-// (forward-computation equation of Section 4.2 of the paper).  Arithmetic as in w4a4_gemm.hip: codes run on the
-// fp8 matrix pipe as exact subnormals, the scale product of a group comes from a small fp16 MFMA, one fma per
-// accumulator and group applies it, the 16-bit branch runs on bf16 MFMAs.
+// (forward-computation equation of Section 4.2 of the paper).  Arithmetic: codes run on the fp8 matrix pipe as exact
+// subnormals (w4a4_gemm.hip, w4a4_gemm_pipe.hip: FP6, which a lone staging wave cannot unpack fast enough), the scale
+// product of a group comes from a small fp16 MFMA, one fma per accumulator and group applies it, the 16-bit branch
+// runs on bf16 MFMAs.
 //
 // Why another schedule.  On this chip a wave issues in order, and two waves of the same kind on a SIMD mostly
 // want the same issue port.  When every wave both stages operands (global loads, nibble unpacking, LDS stores)

@@ -125,7 +125,7 @@ def test_rotate_quantize_ties_and_clip():
 # ------------------------------------------------------------------ kernel B, exact
 @pytest.fixture(params=["tile", "ws", "pipe", "skinny64", "skinny32"])
 def schedule(request, monkeypatch):
-    """Kernel B has several schedules of the same arithmetic (128 x 128 tiles, two workgroups per CU; persistent
+    """Kernel B has several schedules of the same arithmetic (128 x 128 tiles, one workgroup per CU; persistent
     workgroups on 256 x 128 tiles, wave-specialised, or on 256 x 256 and 256 x 128 ones, pipelined; 64 x 64 or 32 x 32
     outputs per workgroup with the K axis split over its waves, for few tokens); the library picks by problem size.  The
     environment switch read at every launch forces one, so that all of them run on the same inputs."""
