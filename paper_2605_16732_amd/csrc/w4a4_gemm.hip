@@ -31,6 +31,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "gemm_tail.h"
 #include "pipe_unpack.h"
 #include "tile_walk.h"
 #include "w4a4_plan.h"
@@ -61,11 +62,11 @@ constexpr int frag_bytes(int gs, bool asym) { return zp_at(gs) + (asym ? 1024 : 
 template <int GS, bool OUT_F32, bool ASYM>
 struct Geo {
   static constexpr int FRAG = frag_bytes(GS, ASYM), SLOT = NJ * FRAG, RING = NBUF * KS * SLOT;
-  static constexpr int B_SLOT = NJ * 1024;                            // 16-bit branch: two slots per part of K, behind the ring
+  static constexpr int PASS = (TNW + TMW) * 128;                      // 16-bit branch: a buffer of 64 channels
   // the exchange: per wave two tiles of partial sums; then the rows of y
   static constexpr int X_WAVE = 2 * 4096, OUT_ROW = TNW * (OUT_F32 ? 4 : 2) + 16;
   static constexpr int X_BYTES = 8 * X_WAVE + TMW * OUT_ROW;
-  static constexpr int LOOP = RING + 2 * KS * B_SLOT, SMEM = LOOP > X_BYTES ? LOOP : X_BYTES;
+  static constexpr int LOOP = RING > 2 * PASS ? RING : 2 * PASS, SMEM = LOOP > X_BYTES ? LOOP : X_BYTES;
 };
 
 __device__ __forceinline__ void barrier() {
@@ -94,7 +95,6 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
   const int ws = w & 3, kh = w >> 2;                                  // 32 channels (and the token tile that is staged), part of K
   const int KL = K - r, G = KL / GS, ldq = KL / 2;
   const int nq = (KL + 63) / 64, nqi = (nq + 1) / 2;                  // stages, intervals
-  const int nbf = r / 16, nbi = nbf / 2;
   const bool short_last = GS == 32 && (KL % 64) != 0;
   const uint32_t rn = (uint32_t)(min(n0 + 32 * ws + row, N - 1) - n0), rm = (uint32_t)(min(m0 + 32 * ws + row, M - 1) - m0);
   const uint32_t lane16 = l * 16, lower = half ? 0u : 0xFFFFu;
@@ -105,38 +105,58 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
 #pragma unroll
     for (int v = 0; v < 16; v++) acc[j][v] = 0.0f;
 
-  // ---- 16-bit branch: loads of step st (16 channels; part kh takes the steps 2 st + kh)
-  u32x4 bw[2], bx[2];
-  const uint32_t vbw = __umul24(rn, 2 * r) + half * 16, vbx = __umul24(rm, 2 * r) + half * 16;
-  const gptr bw_b = (gptr)wh + (size_t)n0 * (2 * r) + kh * 32, bx_b = (gptr)xh + (size_t)m0 * (2 * r) + kh * 32;
-  auto load_b = [&](int st, int set) {
-    const size_t o = (size_t)min(st, nbi - 1) * 64;
-    bw[set] = *(const GLOBAL u32x4*)(bw_b + o + vbw);
-    bx[set] = *(const GLOBAL u32x4*)(bx_b + o + vbx);
-  };
+  // ---- 16-bit branch, ahead of everything else: 64 channels at a time of all rows, 128 bytes of a row by eight lanes, through two
+  // LDS buffers; part kh multiplies 32 of them.  Bound: the LDS writes (32 KB a pass).  Loaded in the order of the MFMA lanes, 32
+  // bytes of a row each, it got 15 bytes per clock and CU, also beside the first loads of the 4-bit part: M = 1000, K = N = 3072,
+  // r = 64 / 256 / 1536 / 2944 26.1 / 26.4 / 39.3 / 52.2 us, now 24.7 / 24.1 / 30.3 / 30.9 (the four-wave kernel before: 34.6 /
+  // 34.1 / 37.7 / 41.4).
   auto branch16 = [&]() {
-    unsigned char* reg = smem + g_::RING + kh * (2 * g_::B_SLOT);
-    for (int st = 0; st < nbi; st++) {
-      unsigned char* sp = reg + (st & 1) * g_::B_SLOT;
-      const u32x4 wv = bw[0];
-      *(u32x4*)(sp + ws * 1024 + lane16) = bx[0];
-      bx[0] = bx[1];
-      bw[0] = bw[1];
-      load_b(st + 2, 1);
-      barrier();
+    const int lrow = t >> 3, lchunk = t & 7, np = (r + 63) / 64;
+    gptr src[4];
 #pragma unroll
-      for (int j = 0; j < NJ; j++) {
-        const i32x4 bv = *(const i32x4*)(sp + j * 1024 + lane16);
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv), __builtin_bit_cast(bf16x8, bv), acc[j], 0, 0, 0);
+    for (int i = 0; i < 4; i++)
+      src[i] = i < 2 ? (gptr)wh + (size_t)min(n0 + lrow + 64 * i, N - 1) * (2 * r)
+                     : (gptr)xh + (size_t)min(m0 + lrow + 64 * (i - 2), M - 1) * (2 * r);
+    u32x4 v[2][4];
+    auto fetch = [&](auto set, int p) {                               // (past the end: the row's last 16 bytes, never used)
+      const int off = min(p * 128 + lchunk * 16, 2 * r - 16);
+#pragma unroll
+      for (int i = 0; i < 4; i++) v[set][i] = *(const GLOBAL u32x4*)(src[i] + off);
+    };
+    auto pass = [&](auto set, int p) {
+      unsigned char* buf = smem + set * g_::PASS;                     // [128 weight rows, 128 token rows][128 bytes]
+#pragma unroll
+      for (int i = 0; i < 4; i++) *(u32x4*)(buf + tile_off_bytes(lrow + 64 * i, lchunk)) = v[set][i];
+      fetch(set, p + 2);
+      barrier();
+      if (kh == 0 || 64 * p + 32 < r) {
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          const int chunk = 2 * (2 * kh + e) + half;
+          const i32x4 av = *(const i32x4*)(buf + tile_off_bytes(32 * ws + row, chunk));
+#pragma unroll
+          for (int j = 0; j < NJ; j++) {
+            const i32x4 bv = *(const i32x4*)(buf + tile_off_bytes(TNW + 32 * j + row, chunk));
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc[j], 0, 0, 0);
+          }
+        }
       }
+    };
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    fetch(even, 0);
+    fetch(odd, 1);
+    for (int p = 0;;) {
+      pass(even, p);
+      if (++p == np) break;
+      pass(odd, p);
+      if (++p == np) break;
     }
+    barrier();                                                        // (the buffers become the 4-bit part's ring)
   };
 
-  if (nq == 0) {
-    load_b(0, 0);
-    load_b(1, 1);
-    branch16();
-  } else {
+  if (r > 0) branch16();
+  if (nq > 0) {
     // ---- loads of the 4-bit part: the part's stage i holds the 64 channels from 64 (2 i + kh) on
     const uint32_t vw = __umul24(rn, ldq) + half * 16, vx = __umul24(rm, ldq) + half * 16;
     const int first = min(kh, nq - 1);
@@ -348,10 +368,6 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
     load_w(S0{});
     load_x(S1{});
     load_w(S1{});
-    if (nbi) {
-      load_b(0, 0);
-      load_b(1, 1);
-    }
     put_x(S0{}, GS == 32 ? rsx[0] : s0, cur);
     load_x(S0{});
     put_x(S1{}, GS == 32 ? rsx[1] : rsw[0], nxt);
@@ -360,7 +376,6 @@ __global__ __launch_bounds__(NT, 2) void w4a4_gemm_kernel(
     unpack_w(S0{}, 1);
     scale_w(S0{});
     load_w(S0{});
-    branch16();
     barrier();
     read_b(S0{}, 0, cur);
     int i = 0;
@@ -467,6 +482,44 @@ static int launch_one(const uint16_t* xh, const uint8_t* xl, const uint16_t* sx,
 
 }  // namespace tile
 
+// Layers without 4-bit channels, more than one tile per CU: several workgroups of four waves per CU, of which one stores while
+// others multiply, and no exchange of partial sums.  us, the tiles above | this: M = 32768, K = 1152, N = 4608 498 | 450; M =
+// 4608, K = 3072, N = 12288 455 | 414; M = 4608, K = 12288, N = 3072 465 | 447; with a tile per CU or less the ones above are
+// faster: M = 1000, K = N = 3072 33.6 | 41.
+template <bool OUT_F32>
+__global__ __launch_bounds__(NTHREADS, 2) void dense_gemm_kernel(const uint16_t* __restrict__ xh, const uint16_t* __restrict__ wh,
+                                                                 const uint16_t* __restrict__ bias, int M, int N, int r,
+                                                                 void* __restrict__ y, int n_mt, int n_nt, int per_xcd) {
+  __shared__ __align__(16) unsigned char smem[(TN + TM) * 128];
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= n_mt * n_nt) return;
+  int m0, n0;
+  tile_origin<4, TN, TM>(logical, n_mt, n_nt, m0, n0);
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  f32x16 acc[2][2];
+  int rowA[2], rowB[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    rowA[i] = (w & 1) * 64 + i * 32 + (l & 31);
+    rowB[i] = TN + (w >> 1) * 64 + i * 32 + (l & 31);
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+  }
+  gemm_tail<OUT_F32>(acc, smem, xh, wh, bias, y, M, N, r, m0, n0, rowA, rowB);
+}
+
+template <bool OUT_F32>
+static int launch_dense(const uint16_t* xh, const uint16_t* wh, const uint16_t* bias, int M, int N, int r, void* y, hipStream_t s) {
+  const int n_mt = (M + TM - 1) / TM, n_nt = (N + TN - 1) / TN;
+  const int per_xcd = (int)(((long)n_mt * n_nt + 7) / 8);
+  hipLaunchKernelGGL((dense_gemm_kernel<OUT_F32>), dim3(per_xcd * 8), dim3(NTHREADS), 0, s, xh, wh, bias, M, N, r, y, n_mt, n_nt,
+                     per_xcd);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DIROTQ_OK : hip_failed(e);
+}
+
 // The schedule of a layer (w4a4_plan.h).  DIROTQ_W4A4_KERNEL=pipe / large / small / ws / tile / skinny / skinny32 /
 // skinny64 in the environment forces one of them wherever it applies (the tests use it to run all of them on the same
 // inputs; large and small: the pipelined kernel with one kind of tile; skinny32 and skinny64: the split-K kernel with one
@@ -511,7 +564,7 @@ int launch_w4a4_gemm(const W4A4Plan& plan, bool fields, const uint16_t* xh, cons
     return launch_w4a4_gemm_pipe(xh, xl, sx, blob, bias, M, N, K, r, g, y, y_dtype, plan.big_tokens, fields, s);
   if (plan.schedule == W4A4Schedule::kWs)
     return launch_w4a4_gemm_ws(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, s);
-  if (plan.schedule != W4A4Schedule::kTile)
+  if (plan.schedule == W4A4Schedule::kSkinny32 || plan.schedule == W4A4Schedule::kSkinny64)
     return launch_w4a4_gemm_skinny(xh, xl, sx, zx, blob, bias, M, N, K, r, g, y, y_dtype, plan.schedule == W4A4Schedule::kSkinny32, s);
   // (without 4-bit channels the activations are rows of x_h alone, so that the slabs need nothing but their first token)
   const long slab = w4a4_plan::slab_tokens(N);
@@ -521,6 +574,10 @@ int launch_w4a4_gemm(const W4A4Plan& plan, bool fields, const uint16_t* xh, cons
       st = launch_w4a4_gemm(plan, fields, xh + (size_t)m * r, xl, sx, zx, blob, bias, (int)std::min(slab, M - m), N, K, r, g,
                             (char*)y + (size_t)m * N * (y_dtype ? 4 : 2), y_dtype, s);
     return st;
+  }
+  if (plan.schedule == W4A4Schedule::kDense) {
+    const uint16_t* wh = (const uint16_t*)((const char*)blob + blob_layout(N, K, r, g).off_wh);
+    return y_dtype ? launch_dense<true>(xh, wh, bias, M, N, r, y, s) : launch_dense<false>(xh, wh, bias, M, N, r, y, s);
   }
 #define DIROTQ_TILE(GS, OUT, ASYM, FIELDS) tile::launch_one<GS, OUT, ASYM, FIELDS>(xh, xl, sx, zx, blob, bias, M, N, K, r, y, s)
 #define DIROTQ_CASE(GS)                                                                                          \

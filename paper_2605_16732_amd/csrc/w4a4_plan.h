@@ -6,7 +6,7 @@
 
 namespace dirotq {
 
-enum class W4A4Schedule { kTile, kWs, kSkinny32, kSkinny64, kPipe };
+enum class W4A4Schedule { kTile, kWs, kSkinny32, kSkinny64, kPipe, kDense };
 
 struct W4A4Plan {
   W4A4Schedule schedule = W4A4Schedule::kTile;
@@ -92,7 +92,7 @@ inline long slab_tokens(long N) { return MOST_TILES / ((N + 127) / 128) * 128; }
 inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, int cus, long& big_tokens) {
   using namespace w4a4_plan;
   big_tokens = 0;
-  if (K - r <= 0) return W4A4Schedule::kTile;
+  if (K - r <= 0) return tiles(M, N, 128, 128) > cus ? W4A4Schedule::kDense : W4A4Schedule::kTile;   // (see dense_gemm_kernel)
   const Cost cost(K, r, g, asym, cus);
   const double c128 = cost.tile(M, N);
   const long half_tiles = tiles(M, N, 128, 256);

@@ -52,9 +52,11 @@ int main(int, char** argv) {
         for (int kind = 0; kind < 3; kind++) {            // symmetric, asymmetric, 16-bit channels only
           const long M = std::min(1L << 24, (1L << 30) / ((N + 127) / 128) * 128);
           long split = 0;
-          if (w4a4_choose((int)M, (int)N, (int)K, kind == 2 ? (int)K : 0, g, kind == 1, 256, split) != W4A4Schedule::kTile) continue;
+          const W4A4Schedule s = w4a4_choose((int)M, (int)N, (int)K, kind == 2 ? (int)K : 0, g, kind == 1, 256, split);
+          if (s != W4A4Schedule::kTile && s != W4A4Schedule::kDense) continue;
           const long slab = w4a4_plan::slab_tokens(N), tokens = kind == 2 ? std::min(M, slab) : M;
-          big += slab < 128 || slab % 128 != 0 || 512 * w4a4_plan::tiles(tokens, N, 128, 128) >= 1L << 32;
+          big += slab < 128 || slab % 128 != 0 || (kind == 2) != (s == W4A4Schedule::kDense) ||
+                 (s == W4A4Schedule::kTile ? 512 : 256) * w4a4_plan::tiles(tokens, N, 128, 128) >= 1L << 32;
         }
   std::printf("w4a4_grids: rows 0 mean_excess 0 over5 %d worst 1\n", big);
   return 0;

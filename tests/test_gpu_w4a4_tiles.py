@@ -1,5 +1,5 @@
 """The 128 x 128 tiles of the W4A4 GEMM against the CPU oracle on identical inputs: tiles cut in either direction, one to five stages
-of 64 channels over the two parts of K (an odd one alone, a last one of 32 channels), a 16-bit branch of one step for one part,
+of 64 channels over the two parts of K (an odd one alone, a last one of 32 channels), a 16-bit branch of one to 18 passes,
 none and nothing else, rows of y of every alignment, both kinds of code, all group sizes."""
 import numpy as np
 import pytest
@@ -18,6 +18,11 @@ pytestmark = pytest.mark.gpu
     (1, 1, 64, 0, 64, True), (33, 127, 32, 0, 32, False), (128, 128, 128, 0, 64, True), (129, 130, 192, 0, 64, False),
     (127, 132, 256, 128, 128, True), (40, 129, 352, 32, 64, True), (257, 136, 160, 64, 32, False), (96, 258, 288, 32, 32, True),
     (300, 260, 416, 32, 128, True), (65, 124, 96, 96, 64, True), (130, 257, 1152, 64, 64, True), (31, 384, 672, 32, 128, False),
+    # long 16-bit parts: passes of 64 channels, a last one of 32, and nothing else
+    (40, 129, 352, 288, 64, True), (129, 130, 416, 320, 32, False), (257, 136, 704, 576, 128, True), (100, 260, 992, 960, 32, True),
+    (130, 127, 288, 288, 64, False), (33, 140, 320, 320, 64, True), (200, 129, 672, 672, 32, True), (128, 128, 1152, 1152, 128, True),
+    # more than one tile per CU without 4-bit channels
+    (2100, 2201, 96, 96, 64, True), (4200, 1100, 192, 192, 32, False),
 ])
 def test_tiles_match_oracle(M, N, K, r, g, use_bias, asym, monkeypatch):
     """fp32 sums of at most G + r/16 + 1 partial terms (asymmetric: and six exact products for each group), each exact up to its
