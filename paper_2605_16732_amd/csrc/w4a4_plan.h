@@ -26,12 +26,12 @@ inline double rounds(long work, long slots) { return (double)((work + slots - 1)
 
 // Costs in microseconds of the schedules: k = 1024 4-bit channels, q = 128 16-bit ones.  Fitted to what kernel B adds to
 // kernel A in whole layers (graph replay over three sets of weights and activations; K = 640 ... 12288, N = 320 ... 12288, all
-// group sizes, r up to 256): the split-K forms to 7250 layers, the 128 x 128 tiles to 1940 (5% off, the others up to 11%, root mean
-// square).  Symmetric layers became 3 to 5% faster in the tiles and the pipelined kernel with the field form; the persistent
-// kernels are fitted to 650 layers with it, up to 32768 tokens, times 1.05 (groups of 32: 1.03), which is what the tiles' cost
-// is above their present times: only the comparisons matter.  The numbers that depend on the kind of code stand as
-// {groups of 64, 128, 32 symmetric; the same asymmetric}; ragged: rows of y that do not begin at multiples of 8 (persistent
-// kernels: 8 or 16, tile: 16) bytes are stored in smaller pieces, down to single values.
+// group sizes): the split-K forms to 7250 layers of up to 9000 tokens with r up to 256, the 128 x 128 tiles to 1260 with the
+// field form and r up to 2048, the persistent kernels to 650 of those (3 to 6% off, root mean square).  The last two stand times
+// 1.03 and 1.02 (groups of 32, wave-specialised: 1.07), which is what the split-K forms' costs are above the
+// present times: only the comparisons matter.  The numbers that depend on the kind of code stand as {groups of 64, 128, 32
+// symmetric; the same asymmetric}; ragged: rows of y that do not begin at multiples of 8 (persistent kernels: 8 or 16, tile:
+// 16) bytes are stored in smaller pieces, down to single values.
 struct Cost {
   double k, q;
   int kind, cus;
@@ -54,24 +54,24 @@ struct Cost {
   }
   // 128 x 128 tiles, one per CU (LDS, registers)
   double tile(long M, long N) const {
-    static constexpr double K[6] = {5.28, 5.17, 8.43, 6.10, 5.99, 9.72};
+    static constexpr double K[6] = {4.81, 4.69, 8.13, 5.89, 5.95, 9.93};
     const long T = tiles(M, N, 128, 128);
-    const double ragged = N % 8 ? 1.55 : 0.0;
-    return 2.89 + rounds(T, cus) * (3.82 + ragged + 2.16 * q + K[kind] * k) + (double)T / cus * (1.89 + 0.49 * k);
+    const double ragged = N % 8 ? 1.39 : 0.0;
+    return 3.01 + rounds(T, cus) * (3.36 + ragged + 1.16 * q + K[kind] * k) + (double)T / cus * (1.41 + 0.92 * k);
   }
   // Large layers: outputs of a 256 x 256 tile for every CU, as a measure for rows that are stored value by value
   double outputs(long M, long N) const { return (double)M * (double)N / (65536.0 * cus); }
   // 256 x 128 tiles of the wave-specialised kernel
   double ws(long M, long N) const {
-    static constexpr double K[6] = {9.91, 9.70, 0.0, 12.90, 11.76, 27.29};
-    const double ragged = N % 4 ? 41.50 : N % 8 ? 8.70 : 0.0;
-    return 6.11 + rounds(tiles(M, N, 128, 256), cus) * (4.50 + 2.60 * q + K[kind] * k) + ragged * outputs(M, N);
+    static constexpr double K[6] = {9.85, 9.66, 0.0, 12.74, 11.89, 28.84};
+    const double ragged = N % 4 ? 40.26 : N % 8 ? 8.66 : 0.0;
+    return 5.77 + rounds(tiles(M, N, 128, 256), cus) * (4.44 + 2.61 * q + K[kind] * k) + ragged * outputs(M, N);
   }
   // the pipelined kernel, whose plan takes the time of `large` 256 x 256 tiles
   double pipe(double large, long M, long N) const {
-    static constexpr double K[3] = {17.40, 17.31, 27.92};
-    const double ragged = N % 4 ? 43.15 : N % 8 ? 7.65 : 0.0;
-    return 5.12 + large * (5.78 + 5.46 * q + K[kind] * k) + ragged * outputs(M, N);
+    static constexpr double K[3] = {17.33, 17.30, 28.00}, Q[3] = {5.39, 5.39, 7.85};
+    const double ragged = N % 4 ? 42.22 : N % 8 ? 7.77 : 0.0;
+    return 4.61 + large * (5.92 + Q[kind] * q + K[kind] * k) + ragged * outputs(M, N);
   }
 };
 
@@ -82,13 +82,13 @@ inline long slab_tokens(long N) { return MOST_TILES / ((N + 127) / 128) * 128; }
 
 // Large layers, from 128 tiles of 256 x 128 on: the cheapest of the pipelined kernel (symmetric; persistent workgroups, 256 x 256
 // and 256 x 128 tiles), the wave-specialised one (256 x 128; not symmetric groups of 32) and the 128 x 128 tiles.  What kernel B
-// takes, us, pipelined | wave-specialised | tiles: M = 4096, N = 3072, K = 1152 28 | 35 | 33; M = 4096, K = 3072, N = 1152 41 | 37 |
-// 43, N = 6144 (1.5 rounds of 256 x 256 tiles) 127 | 112 | 140; N = 4026, K = 1536, whose rows are stored value by value, 75 | 78
-// | 58; M = 10814, K = 3072, N = 2263, asymmetric - | 199 | 185.  500 layers that were not in the fit: on average 0.05% (symmetric,
-// at most 4%) and 0.18% (asymmetric, at most 8%) above the best of the three; 0.61% (at most 20%) and 0.25% with the rule from
-// before the field form.
+// takes, us, pipelined | wave-specialised | tiles: M = 4096, N = 3072, K = 1152 28 | 35 | 33; M = 4096, K = 3072, N = 1152 41 | 36 |
+// 41, N = 6144 (1.5 rounds of 256 x 256 tiles) 134 | 118 | 132; N = 4026, K = 1536, whose rows are stored value by value, 74 | 78
+// | 57; M = 10814, K = 3072, N = 2263, asymmetric - | 209 | 177.  500 layers that were not in the fit: on average 0.12% above the
+// best of the three (symmetric at most 4%, asymmetric 14%, next 4%).
 // Below: the cheapest of the split-K kernels (few tokens; 32 x 32 or 64 x 64 outputs per workgroup) and the 128 x 128 tiles:
-// 0.27% above the best of 1206 layers (mean).  big_tokens: see w4a4_pipe_plan.
+// 0.29% above the best of 1206 layers (mean).  150 layers of either kind with r = 320 to 2048: 0.17%.  big_tokens: see
+// w4a4_pipe_plan.
 inline W4A4Schedule w4a4_choose(int M, int N, int K, int r, int g, bool asym, int cus, long& big_tokens) {
   using namespace w4a4_plan;
   big_tokens = 0;
