@@ -23,7 +23,8 @@
 // Bound: instruction issue.  A tile of 32 x 32 and a group takes 64 cycles of MFMA, 40 of fma and about 26 integer
 // operations of 4.3 cycles, which add up (measured 200 cycles; three waves per SIMD with K in three parts: 190, lost
 // again in the exchange of their sums).  The 128 x 128 tiles before it had four waves that staged both operands through LDS
-// as fp8: M = 1000, K = N = 3072 34.3 -> 26.5 us (asymmetric 39.0 -> 28.4).
+// as fp8: M = 1000, K = N = 3072, r = 128 34.0 us, with the 16-bit branch in the order of the MFMA lanes 24.8, staged by rows 23.5
+// (asymmetric 39.1, 27.0, 25.7).
 #include <algorithm>
 #include <atomic>
 
